@@ -142,6 +142,9 @@ int cacnn_tile_plan(const cacnn_problem* problem, int dtype, const cacnn_machine
  *   out      out  DEVICE pointer, K*H*W*B fp32; OVERWRITTEN with the full sum (the paper's += from zero);
  *                 must not alias the inputs
  *   hip_stream    hipStream_t cast to void*; NULL is the default stream
+ * Which kernel runs: the one that cacnn_tile_plan describes, or, where the problem has few images, sizes that the tiled
+ * kernels' 16-byte items do not divide, or too few tiles for the machine, a kernel that flattens the positions and needs
+ * no plan (same sums, same inputs and outputs, fp32 accumulation).
  * The call enqueues work on the stream and returns; it never synchronises, allocates no device memory and
  * keeps no reference to the buffers.  The caller owns all three buffers.  Pointers must be aligned to their
  * element size; 16-byte alignment enables the vector paths.
@@ -184,7 +187,8 @@ int cacnn_plan_variant(const cacnn_problem* problem, int dtype, int variant_inde
  * the fastest, and remembers it for later cacnn_conv_forward calls with the same problem, dtype and operand alignment.
  * Unlike the other entry points it SYNCHRONISES with hip_stream (it reads event timings) and creates and destroys two
  * HIP events; it allocates no device memory.  `out` is overwritten by every candidate and ends up holding a valid
- * result.  Arguments as for cacnn_conv_forward; out_plan (host, may be NULL) receives the chosen plan.
+ * result.  Arguments as for cacnn_conv_forward; out_plan (host, may be NULL) receives the plan of the fastest variant.  (The
+ * kernels with flattened positions are timed as well, and remembered where one is faster still; they have no plan.)
  * Errors: as cacnn_conv_forward; CACNN_ERR_UNSUPPORTED if no variant accepts the problem.
  */
 int cacnn_tune(const cacnn_problem* problem, int dtype, const void* image, const void* filter, void* out,

@@ -1,0 +1,429 @@
+// gfx950 kernels with flattened positions: the convolution as one matrix product Out[K x N] = Filter[K x Q] * Window[Q x N]
+// with N = H*W*B positions and Q = R*S*C contraction indices, for problems that the tiled kernels (cacnn_kernels.hip) leave
+// mostly idle or cannot stage: few images, batches and channel counts that 16-byte items do not divide, few outputs.
+//
+// Out[k] is N consecutive words and Filter[k] is Q consecutive elements whatever the sizes are.  A window element's place is
+// a sum, base(position) + r * row(r) + (s*C + c) * B, because y and c are neighbouring axes of the Image: so a lane keeps
+// the offset of its position, the step through the contraction is a scalar or one shared vector add, nothing is padded
+// and nothing is decoded in the loop.  Positions are cut into tiles wherever they end: 32 columns of an MFMA block are 32
+// positions (or 32 groups of images) in a row, whatever B, W and H are.
+//
+// What a tile kernel gains by staging in LDS this one gains by starting at once: every operand goes from global memory
+// (L1 and L2 hold the windows' overlap) to the registers of the wave that multiplies it, several steps ahead, with no
+// barrier.  Where there are few tiles the waves of a workgroup divide the contraction instead and add up in LDS at the end.
+// It is bound by the compute unit's address unit (a load whose 64 lanes fall into many cache lines takes about a clock
+// for each of them), which is why a lane loads several images or several channels at once where it can.
+//
+// Measured against the kernels that ran these calls before (one launch, MI355X):
+//   fp32 (5, 30, 50, 27, 19, 5 x 5)         109.7 -> 11.3 us      bf16 (1, 128, 128, 28, 28, 3 x 3)      46.0 -> 6.8 us
+//   bf16 (16, 3, 64, 112, 112, 7 x 7, s 2)  349 -> 28.1 us        bf16 (3, 367, 237, 15, 15, 3 x 3)     310 -> 30 us
+#include <hip/hip_runtime.h>
+#include <stdint.h>
+
+#include "cacnn_internal.h"
+
+namespace cacnn {
+
+typedef float ff32x16 __attribute__((ext_vector_type(16)));
+typedef float ff32x4 __attribute__((ext_vector_type(4)));
+typedef float ff32x2 __attribute__((ext_vector_type(2)));
+typedef unsigned int fu32x4 __attribute__((ext_vector_type(4)));
+typedef unsigned int fu32x2 __attribute__((ext_vector_type(2)));
+typedef __bf16 fbf16x8 __attribute__((ext_vector_type(8)));
+
+__device__ __forceinline__ uint32_t flat_div(uint32_t n, const FlatDiv& d) {
+    return d.mul ? __umulhi(n, d.mul) >> d.shift : n;
+}
+
+// BYTES bytes (2, 4, 8 or 16) at any element-aligned address: base is wave-uniform, off the lane's
+typedef unsigned short fu16;
+struct __attribute__((packed, aligned(2))) Bytes4 {
+    uint32_t v;
+};
+struct __attribute__((packed, aligned(2))) Bytes8 {
+    fu32x2 v;
+};
+struct __attribute__((packed, aligned(2))) Bytes16 {
+    fu32x4 v;
+};
+struct __attribute__((packed, aligned(4))) Out2 {
+    ff32x2 v;
+};
+struct __attribute__((packed, aligned(4))) Out4 {
+    ff32x4 v;
+};
+template <int BYTES>
+__device__ __forceinline__ void load_at(uint32_t* to, const char* base, uint32_t off) {
+    if constexpr (BYTES == 2) {
+        to[0] = *(const fu16*)(base + off);
+    } else if constexpr (BYTES == 4) {
+        to[0] = ((const Bytes4*)(base + off))->v;
+    } else if constexpr (BYTES == 8) {
+        const fu32x2 v = ((const Bytes8*)(base + off))->v;
+        to[0] = v[0], to[1] = v[1];
+    } else {
+        const fu32x4 v = ((const Bytes16*)(base + off))->v;
+        to[0] = v[0], to[1] = v[1], to[2] = v[2], to[3] = v[3];
+    }
+}
+
+// the same through a buffer descriptor: the scalar offset soff costs no vector instruction
+template <int BYTES>
+__device__ __forceinline__ void load_image(uint32_t* to, __amdgpu_buffer_rsrc_t r, uint32_t voff, uint32_t soff) {
+    if constexpr (BYTES == 2) {
+        to[0] = __builtin_amdgcn_raw_buffer_load_b16(r, voff, soff, 0);
+    } else if constexpr (BYTES == 4) {
+        to[0] = __builtin_amdgcn_raw_buffer_load_b32(r, voff, soff, 0);
+    } else if constexpr (BYTES == 8) {
+        const fu32x2 v = __builtin_amdgcn_raw_buffer_load_b64(r, voff, soff, 0);
+        to[0] = v[0], to[1] = v[1];
+    } else {
+        const fu32x4 v = __builtin_amdgcn_raw_buffer_load_b128(r, voff, soff, 0);
+        to[0] = v[0], to[1] = v[1], to[2] = v[2], to[3] = v[3];
+    }
+}
+
+// The exchange of partial sums at the end of a tile: rows of a block per round, and the LDS it takes
+template <int MB, int NG, int IPL, int TILES, int WK>
+struct FlatReduce {
+    static constexpr int bytes(int vs) { return TILES * WK * IPL * vs * 256; }
+    static constexpr int VS = bytes(16) <= (MB * NG == 1 ? 65536 : 32768) ? 16 : bytes(8) <= 32768 ? 8 : 4;
+    static constexpr int ROUNDS = MB * NG * (16 / VS);
+    static constexpr int BUF = bytes(VS) / 4;                       // floats of one buffer
+    static constexpr size_t BYTES = WK == 1 ? 0 : (size_t)(ROUNDS > 1 ? 2 : 1) * bytes(VS);
+};
+
+// IM > 0: a lane holds IM adjacent images of a position and loads them one contraction index at a time.
+// IM < 0: there are -IM images in all; a lane holds all of them and loads 16 bytes at a time, in which the images of a
+// channel are neighbours and the channels follow each other.
+template <int DT, int MB, int NG, int IM, int WM, int WN, int WK, int D, bool SHORT>
+__global__ void __launch_bounds__(WM* WN* WK * 64) conv_flat_kernel(const FlatArgs a) {
+    constexpr int ESZ = DT == 0 ? 4 : 2, CH = 16 / ESZ;
+    constexpr bool RUN = IM < 0;                       // 16-byte loads along the contraction
+    constexpr int IPL = RUN ? -IM : IM, NB = NG * IPL; // images per lane, column blocks per wave
+    static_assert(!(SHORT && RUN), "flat kernel: a run of 16 bytes needs a filter row that long");
+    constexpr int LW = RUN ? 4 : (IPL * ESZ + 3) / 4;  // dwords of one Image load
+    constexpr int LE = RUN ? IPL : CH;                 // Image loads per chunk
+    using Lay = FlatReduce<MB, NG, IPL, WM * WN, WK>;
+    extern __shared__ float s_red[];
+
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wk = wave % WK, wm = (wave / WK) % WM, wn = wave / (WK * WM);
+    const int j = lane & 31, g = lane >> 5;
+
+    // consecutive workgroups go to different XCDs: every XCD gets one contiguous run of the tile list
+    uint32_t t = blockIdx.x;
+    {
+        const uint32_t l = t >> 3, x = t & 7;
+        t = x * a.xcd_q + min(x, a.xcd_rem) + l;
+    }
+    uint32_t tk, tn;
+    {
+        const uint32_t q = flat_div(t, a.d_inner), i = t - q * a.inner;
+        tk = a.k_inner ? i : q;
+        tn = a.k_inner ? q : i;
+    }
+    const uint32_t k0 = (tk * WM + wm) * (MB * 32), q0 = (tn * WN + wn) * (NG * 32);
+
+    uint32_t aoff[MB], boff[NG], opos[NG];
+    int skip[NG];                                      // images of the lane that its left neighbour has as well; IPL: nothing to store
+#pragma unroll
+    for (int m = 0; m < MB; ++m) aoff[m] = min(k0 + m * 32 + j, a.K - 1) * a.flt_row;
+#pragma unroll
+    for (int p = 0; p < NG; ++p) {
+        const uint32_t q = min(q0 + p * 32 + j, a.groups - 1);
+        const uint32_t hw = RUN ? q : flat_div(q, a.d_G), first = RUN ? 0 : (q - hw * a.G) * IPL;
+        const uint32_t b = RUN ? 0 : min(first, a.B - IPL);
+        const uint32_t h = flat_div(hw, a.d_W), w = hw - h * a.W;
+        boff[p] = w * a.img_w + h * a.img_h + b * ESZ;
+        opos[p] = hw * a.B + b;
+        skip[p] = q0 + p * 32 + j < a.groups ? (int)(first - b) : IPL;
+    }
+
+    // byte distance of a chunk's e-th contraction index from its first (a filter row shorter than a chunk: the last one
+    // again, which the mask then removes)
+    const uint32_t eoff = a.B * ESZ;
+    uint32_t es[CH];
+#pragma unroll
+    for (int e = 0; e < CH; ++e) es[e] = SHORT ? min((uint32_t)e, a.T - 1) : (uint32_t)e;
+
+    const __amdgpu_buffer_rsrc_t rimg = __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(a.image), 0, a.img_bytes, 0x00020000);
+
+    // this wave's steps, and this half-wave's chunk of the next step to fetch
+    const uint32_t s_begin = min(wk * a.steps_per_wave, a.steps), s_end = min(s_begin + a.steps_per_wave, a.steps);
+    const uint32_t u_end = min(2 * s_end, a.U);
+    uint32_t u = 2 * s_begin + g;
+    const uint32_t r = flat_div(u, a.d_TC);
+    uint32_t tc = u - r * a.TC;
+    uint32_t foff = r * a.flt_r + tc * 16, ioff = r * a.img_r + tc * a.img_chunk;
+
+    uint32_t A[D][MB][SHORT ? CH : 4];
+    uint32_t X[D][NG][LE][LW];
+    uint32_t lo[D];
+
+    auto fetch = [&](int d) {
+        const bool last = tc + 1 == a.TC, out = u >= u_end;
+        uint32_t fo = foff, io = ioff;
+        lo[d] = 0;
+        if (!SHORT) {
+            if (last) fo -= a.back * ESZ, io -= a.back * eoff, lo[d] = a.back;
+        }
+        if (out) fo = 0, io = 0, lo[d] = CH;
+#pragma unroll
+        for (int m = 0; m < MB; ++m) {
+            if constexpr (SHORT) {
+#pragma unroll
+                for (int e = 0; e < CH; ++e) load_at<ESZ>(A[d][m] + e, (const char*)a.filter + es[e] * ESZ, aoff[m] + fo);
+            } else {
+                load_at<16>(A[d][m], (const char*)a.filter, aoff[m] + fo);
+            }
+        }
+#pragma unroll
+        for (int p = 0; p < NG; ++p) {
+            const uint32_t vo = boff[p] + io;
+#pragma unroll
+            for (int e = 0; e < LE; ++e) {
+                if constexpr (RUN) load_at<16>(X[d][p][e], (const char*)a.image + e * 16, vo);
+                else load_image<IPL * ESZ>(X[d][p][e], rimg, vo, es[e] * eoff);
+            }
+        }
+        // the half-wave's chunk of the next step lies two chunks further on
+        u += 2;
+        tc += a.d2_tc;
+        foff += a.d2_flt;
+        ioff += a.d2_img;
+        if (tc >= a.TC) {
+            tc -= a.TC;
+            foff += a.wrap_flt;
+            ioff += a.wrap_img;
+        }
+    };
+
+    ff32x16 acc[MB][NB];
+#pragma unroll
+    for (int m = 0; m < MB; ++m)
+#pragma unroll
+        for (int n = 0; n < NB; ++n)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) acc[m][n][v] = 0.f;
+
+    auto multiply = [&](int d) {
+        const uint32_t hi = SHORT ? a.T : CH;
+        const bool mask = SHORT || __any(lo[d] != 0);
+        fu32x4 av[MB], bv[NB];
+#pragma unroll
+        for (int m = 0; m < MB; ++m)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) av[m][i] = SHORT && DT == 1 ? A[d][m][2 * i] | (A[d][m][(2 * i + 1) % (SHORT ? CH : 4)] << 16) : A[d][m][i];
+#pragma unroll
+        for (int p = 0; p < NG; ++p)
+#pragma unroll
+            for (int q = 0; q < IPL; ++q)
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    uint32_t v;
+                    if constexpr (DT == 0) {
+                        v = RUN ? X[d][p][(i * IPL + q) / 4 % LE][(i * IPL + q) % 4 % LW] : X[d][p][i % LE][q % LW];
+                    } else if constexpr (RUN) {
+                        // images q of channels 2 i and 2 i + 1: the half-words e0, e1 of the run
+                        const int e0 = 2 * i * IPL + q, e1 = e0 + IPL;
+                        v = IPL == 1 ? X[d][p][0][i]
+                                     : __builtin_amdgcn_perm(X[d][p][e1 / 8 % LE][e1 / 2 % 4], X[d][p][e0 / 8 % LE][e0 / 2 % 4],
+                                                             (e1 & 1 ? 0x07060000u : 0x05040000u) | (e0 & 1 ? 0x0302u : 0x0100u));
+                    } else if constexpr (IPL == 1) {
+                        v = __builtin_amdgcn_perm(X[d][p][(2 * i + 1) % LE][0], X[d][p][2 * i % LE][0], 0x05040100u);
+                    } else {
+                        v = __builtin_amdgcn_perm(X[d][p][(2 * i + 1) % LE][q / 2], X[d][p][2 * i % LE][q / 2], q & 1 ? 0x07060302u : 0x05040100u);
+                    }
+                    bv[p * IPL + q][i] = v;
+                }
+        if (mask) {
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                uint32_t keep;
+                if constexpr (DT == 0) {
+                    keep = (uint32_t)i >= lo[d] && (uint32_t)i < hi ? 0xffffffffu : 0u;
+                } else {
+                    keep = ((uint32_t)(2 * i) >= lo[d] && (uint32_t)(2 * i) < hi ? 0x0000ffffu : 0u) |
+                           ((uint32_t)(2 * i + 1) >= lo[d] && (uint32_t)(2 * i + 1) < hi ? 0xffff0000u : 0u);
+                }
+#pragma unroll
+                for (int m = 0; m < MB; ++m) av[m][i] &= keep;
+#pragma unroll
+                for (int n = 0; n < NB; ++n) bv[n][i] &= keep;
+            }
+        }
+        if constexpr (DT == 0) {
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+#pragma unroll
+                for (int m = 0; m < MB; ++m)
+#pragma unroll
+                    for (int n = 0; n < NB; ++n)
+                        acc[m][n] = __builtin_amdgcn_mfma_f32_32x32x2f32(__uint_as_float(av[m][e]), __uint_as_float(bv[n][e]),
+                                                                         acc[m][n], 0, 0, 0);
+        } else {
+#pragma unroll
+            for (int m = 0; m < MB; ++m)
+#pragma unroll
+                for (int n = 0; n < NB; ++n)
+                    acc[m][n] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(fbf16x8, av[m]),
+                                                                        __builtin_bit_cast(fbf16x8, bv[n]), acc[m][n], 0, 0, 0);
+        }
+    };
+
+    // D steps of loads are in flight; the order of the loads is kept (left alone, the compiler mixes the steps of the
+    // first group, and then waits for nearly all of them before the first product of every group)
+#pragma unroll
+    for (int d = 0; d < D; ++d) {
+        fetch(d);
+        __builtin_amdgcn_sched_barrier(0);
+    }
+    for (uint32_t s = s_begin; s < s_end; s += D) {
+#pragma unroll
+        for (int d = 0; d < D; ++d) {
+            multiply(d);
+            fetch(d);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    }
+
+    // (the fetches beyond the last step are of the first chunk, cached, and masked)
+    // MFMA D layout: lane j + 32 g holds rows 8 (v / 4) + 4 g + v % 4 of column j
+    auto store = [&](int m, int p, int v, const float (&o)[IPL]) {
+        const uint32_t k = k0 + m * 32 + (v >> 2) * 8 + g * 4 + (v & 3);
+        if (k >= a.K) return;
+        float* const dst = a.out + (int64_t)k * a.N + opos[p];
+        if (skip[p] == 0) {
+            if constexpr (IPL == 4 || IPL == 8) {
+#pragma unroll
+                for (int i = 0; i < IPL; i += 4) ((Out4*)(dst + i))->v = ff32x4{o[i], o[i + 1], o[i + 2], o[i + 3]};
+            } else if constexpr (IPL == 2 || IPL == 6) {
+#pragma unroll
+                for (int i = 0; i < IPL; i += 2) ((Out2*)(dst + i))->v = ff32x2{o[i], o[i + 1]};
+            } else {
+#pragma unroll
+                for (int i = 0; i < IPL; ++i) dst[i] = o[i];
+            }
+        } else {
+#pragma unroll
+            for (int i = 1; i < IPL; ++i)
+                if (i >= skip[p]) dst[i] = o[i];
+        }
+    };
+    if constexpr (WK == 1) {
+#pragma unroll
+        for (int m = 0; m < MB; ++m)
+#pragma unroll
+            for (int v = 0; v < 16; ++v)
+#pragma unroll
+                for (int p = 0; p < NG; ++p) {
+                    float o[IPL];
+#pragma unroll
+                    for (int q = 0; q < IPL; ++q) o[q] = acc[m][p * IPL + q][v];
+                    store(m, p, v, o);
+                }
+    } else {
+        // The partial sums of the WK waves of a tile meet in LDS, VS rows of a block at a time, in two buffers: a buffer is
+        // written again two rounds later, when every wave has passed the barrier in between and so has read it.
+        constexpr int VS = Lay::VS, SLOT = IPL * VS * 64;
+        float* const grp = s_red + (size_t)(wave / WK) * WK * SLOT + lane;
+        int buf = 0;
+#pragma unroll
+        for (int m = 0; m < MB; ++m)
+#pragma unroll
+            for (int p = 0; p < NG; ++p)
+#pragma unroll
+                for (int v0 = 0; v0 < 16; v0 += VS) {
+                    float* const slot = grp + buf * Lay::BUF;
+#pragma unroll
+                    for (int v = 0; v < VS; ++v)
+#pragma unroll
+                        for (int q = 0; q < IPL; ++q) slot[wk * SLOT + (v * IPL + q) * 64] = acc[m][p * IPL + q][v0 + v];
+                    __syncthreads();
+                    for (int v = wk; v < VS; v += WK) {
+                        float o[IPL];
+#pragma unroll
+                        for (int q = 0; q < IPL; ++q) {
+                            float s = 0.f;
+#pragma unroll
+                            for (int w = 0; w < WK; ++w) s += slot[w * SLOT + (v * IPL + q) * 64];
+                            o[q] = s;
+                        }
+                        store(m, p, v0 + v, o);
+                    }
+                    buf ^= 1;
+                }
+    }
+}
+
+template <int DT, int MB, int NG, int IM, int WM, int WN, int WK, int D, bool SHORT>
+static int launch_flat_one(const FlatArgs& a, int grid, void* stream) {
+    constexpr size_t lds = FlatReduce<MB, NG, (IM < 0 ? -IM : IM), WM * WN, WK>::BYTES;
+    static_assert(lds <= 160 * 1024, "flat kernel: partial sums fit the LDS");
+    auto kernel = conv_flat_kernel<DT, MB, NG, IM, WM, WN, WK, D, SHORT>;
+    if constexpr (lds > 64 * 1024) {
+        static const bool ok = hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024) == hipSuccess;
+        if (!ok) {
+            (void)hipGetLastError();
+            return 1;
+        }
+    }
+    hipLaunchKernelGGL(kernel, dim3(grid), dim3(WM * WN * WK * 64), lds, (hipStream_t)stream, a);
+    return hipGetLastError() == hipSuccess ? 0 : 1;
+}
+
+template <int DT, int MB, int NG, int IM, int WM, int WN, int WK, int D>
+static int launch_flat_shape(const FlatArgs& a, int grid, void* stream) {
+    if constexpr (IM < 0) return launch_flat_one<DT, MB, NG, IM, WM, WN, WK, D, false>(a, grid, stream);
+    else return a.T < (DT == 0 ? 4u : 8u) ? launch_flat_one<DT, MB, NG, IM, WM, WN, WK, D, true>(a, grid, stream)
+                                          : launch_flat_one<DT, MB, NG, IM, WM, WN, WK, D, false>(a, grid, stream);
+}
+
+// blocks of output channels, groups of images per wave; images per lane; waves along k, positions, contraction; steps ahead.
+// The configurations that a cost estimate picks from (cacnn_host.cpp), chosen from 298 by leaving out whatever made the pick on
+// 130 layers less than half a per cent worse.
+#define CACNN_FLAT(DT, MB, NG, IM, WM, WN, WK, D) \
+    {{DT, MB, NG, IM, WM, WN, WK}, launch_flat_shape<DT, MB, NG, IM, WM, WN, WK, D>}
+
+static const FlatVariant g_flat[] = {
+    // fp32
+    CACNN_FLAT(0, 1, 1, 1, 1, 1, 4, 4),
+    CACNN_FLAT(0, 1, 1, 1, 1, 2, 2, 4),
+    CACNN_FLAT(0, 1, 1, 2, 1, 1, 4, 4),
+    CACNN_FLAT(0, 1, 1, 2, 1, 2, 2, 4),
+    CACNN_FLAT(0, 1, 1, 2, 1, 4, 1, 4),
+    CACNN_FLAT(0, 1, 1, 4, 1, 4, 1, 4),
+    CACNN_FLAT(0, 1, 1, 4, 2, 1, 2, 4),
+    CACNN_FLAT(0, 1, 1, 4, 2, 2, 1, 4),
+    CACNN_FLAT(0, 1, 1, -1, 1, 1, 4, 4),
+    CACNN_FLAT(0, 2, 2, -1, 1, 1, 4, 4),
+    CACNN_FLAT(0, 1, 1, -2, 1, 1, 4, 4),
+    CACNN_FLAT(0, 1, 1, -7, 2, 2, 1, 3),
+    // bf16
+    CACNN_FLAT(1, 1, 1, 1, 1, 1, 4, 4),
+    CACNN_FLAT(1, 1, 2, 1, 1, 1, 4, 3),
+    CACNN_FLAT(1, 1, 1, 2, 1, 4, 1, 4),
+    CACNN_FLAT(1, 1, 2, 2, 1, 4, 1, 3),
+    CACNN_FLAT(1, 2, 2, 2, 1, 1, 4, 3),
+    CACNN_FLAT(1, 2, 2, 2, 1, 4, 1, 3),
+    CACNN_FLAT(1, 1, 1, 4, 1, 1, 4, 4),
+    CACNN_FLAT(1, 1, 1, -1, 1, 1, 4, 4),
+    CACNN_FLAT(1, 2, 1, -1, 1, 1, 4, 4),
+    CACNN_FLAT(1, 1, 1, -2, 1, 1, 4, 4),
+    CACNN_FLAT(1, 1, 1, -2, 1, 2, 2, 4),
+    CACNN_FLAT(1, 1, 1, -3, 1, 1, 4, 4),
+    CACNN_FLAT(1, 2, 1, -3, 1, 1, 4, 4),
+    CACNN_FLAT(1, 1, 1, -4, 1, 1, 4, 4),
+    CACNN_FLAT(1, 2, 1, -4, 1, 1, 4, 4),
+    CACNN_FLAT(1, 1, 1, -5, 1, 1, 4, 4),
+    CACNN_FLAT(1, 1, 1, -6, 1, 1, 4, 4),
+    CACNN_FLAT(1, 1, 1, -7, 1, 1, 4, 3),
+    CACNN_FLAT(1, 1, 1, -8, 1, 1, 4, 3),
+};
+
+int num_flat() { return (int)(sizeof(g_flat) / sizeof(g_flat[0])); }
+const FlatVariant& flat_variant(int i) { return g_flat[i]; }
+
+}  // namespace cacnn

@@ -104,6 +104,58 @@ struct Variant {
     LaunchFn launch;
 };
 
+// Division of any n < 2^31 by a run-time constant: one multiply-high and a shift, exact.
+struct FlatDiv {
+    uint32_t mul;    // floor(2^(31 + l) / d) + 1 with l = ceil(log2 d), or 0 when d == 1
+    uint32_t shift;  // l - 1
+};
+
+inline FlatDiv make_flatdiv(uint32_t d) {
+    FlatDiv f = {0u, 0u};
+    if (d <= 1) return f;
+    uint32_t l = 0;
+    while ((1ull << l) < d) ++l;
+    f.mul = (uint32_t)((1ull << (31 + l)) / d + 1ull);
+    f.shift = l - 1;
+    return f;
+}
+
+// The kernels with flattened positions (cacnn_flat.hip).  Out is a K x N matrix, N = H*W*B.  The contraction is cut
+// into chunks of 16 bytes of the Filter (8 bf16 or 4 fp32 consecutive (s, c) of one filter column r).
+struct FlatArgs {
+    const void* image;
+    const void* filter;
+    float* out;
+    uint32_t N, K, B, W;
+    uint32_t G, groups;                 // groups of images per position, groups in all (H*W*G): one per lane
+    uint32_t T, TC, U;                  // S*C; chunks per r; chunks in all, R*TC
+    uint32_t back;                      // elements by which the last chunk of an r reaches beyond T (it is moved back by them)
+    uint32_t steps, steps_per_wave;     // steps of two chunks; those of one of the waves that share a tile
+    uint32_t img_w, img_h;              // Image bytes from one output column / row to the next
+    uint32_t img_r, img_chunk;          // ... from one r to the next, from one chunk to the next
+    uint32_t flt_row, flt_r;            // Filter bytes from one output channel / one r to the next
+    uint32_t d2_tc, d2_flt, d2_img;     // two chunks further on: whole r's and chunks
+    uint32_t wrap_flt, wrap_img;        // correction when that passes the end of an r
+    int32_t img_bytes;
+    uint32_t inner, k_inner;            // tile list: the fastest index, its length; 1: the k-tiles, 0: the position tiles
+    uint32_t xcd_q, xcd_rem;
+    FlatDiv d_G, d_W, d_TC, d_inner;
+};
+struct FlatInfo {
+    int dtype;          // cacnn_dtype
+    int MB, NG;         // blocks of 32 of one wave: output channels, groups of images
+    int IM;             // > 0: images a lane holds; < 0: all of that many, loaded in runs along the contraction
+    int WM, WN, WK;     // waves along output channels, along positions, along the contraction
+    int KT() const { return WM * MB * 32; }
+    int GT() const { return WN * NG * 32; }
+};
+struct FlatVariant {
+    FlatInfo info;
+    int (*launch)(const FlatArgs& a, int grid, void* stream);
+};
+int num_flat();
+const FlatVariant& flat_variant(int i);
+
 // Pooling (cacnn_pool.hip): everything the kernel needs, by value.
 struct PoolArgs {
     const void* image;

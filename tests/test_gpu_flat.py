@@ -1,0 +1,122 @@
+"""GPU parity of the kernels with flattened positions (csrc/cacnn_flat.hip) against the fp64 oracle: every compiled one on the
+sizes where its indexing can go wrong, whatever the library would choose for such a call."""
+import ctypes
+
+import numpy as np
+import pytest
+
+import cacnn_inputs as ci
+from tests import gpu_util as gu
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def env():
+    import torch
+    import paper_1802_06905_amd as cc
+    from paper_1802_06905_amd import binding
+    assert torch.cuda.is_available(), "GPU tests need a GPU"
+    lib = binding._lib
+    lib.cacnn_internal_flat_forward.argtypes = [ctypes.POINTER(cc.Problem), ctypes.c_int, ctypes.c_int] + [ctypes.c_void_p] * 4
+    lib.cacnn_internal_flat_info.argtypes = [ctypes.c_int, ctypes.POINTER(ctypes.c_int32)]
+    return cc, torch, lib
+
+
+def kernels(lib, dtype):
+    """(index, images per lane, whether the lane holds all images) of every flattened kernel of the dtype"""
+    for i in range(lib.cacnn_internal_flat_count()):
+        x = (ctypes.c_int32 * 7)()
+        assert lib.cacnn_internal_flat_info(i, x) == 0
+        if x[0] == (0 if dtype == "f32" else 1):
+            yield i, abs(x[3]), x[3] < 0
+
+
+def run(env, cfg, img, flt, index, misalign=0):
+    cc, torch, lib = env
+    d_img, d_flt = gu.upload(cfg, img, flt, torch, misalign=misalign)
+    out = torch.full((int(np.prod(cfg.out_shape)),), float("nan"), dtype=torch.float32, device="cuda:0")
+    prob = cc.Problem(*cfg.dims)
+    rc = lib.cacnn_internal_flat_forward(ctypes.byref(prob), gu.dtype_code(cfg), index, d_img.data_ptr(), d_flt.data_ptr(),
+                                         out.data_ptr(), torch.cuda.current_stream().cuda_stream)
+    torch.cuda.synchronize()
+    return rc, out.cpu().numpy().reshape(cfg.out_shape)
+
+
+def check(cfg, out, ref, ab, what):
+    """The products of bf16 or fp32 inputs enter a sum of fp32 additions: at most one rounding of 2^-24 per product (fp32
+    products are rounded as well: twice that), relative to the sum of absolute products."""
+    tol = 2 * cfg.C * cfg.R * cfg.S * 2.0 ** -24
+    e = gu.rel_err(out, ref, ab)
+    assert e <= tol, f"{cfg.dims} {cfg.dtype} {what}: {e:.3e} > {tol:.3e}"
+
+
+# C, K, W, H, R, S, sw, sh: a filter row (S*C contraction indices) shorter than, equal to, one more than and not a multiple of a
+# 16-byte chunk; odd and even numbers of chunks, fewer chunks than waves; K and the positions beyond and below a tile; strides, also
+# above the filter's extent; a Filter larger than the Image (the other tile order)
+SHAPES = [(3, 5, 3, 2, 2, 1, 1, 1), (1, 33, 4, 5, 3, 3, 2, 1), (8, 32, 1, 1, 1, 1, 1, 1), (9, 40, 5, 3, 1, 1, 1, 2), (5, 7, 6, 4, 3, 3, 1, 1),
+          (16, 64, 3, 3, 3, 3, 2, 2), (7, 31, 2, 9, 4, 5, 3, 1), (50, 97, 2, 1, 2, 2, 1, 1), (4, 16, 11, 13, 1, 2, 2, 3), (24, 130, 9, 7, 1, 3, 1, 1)]
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("shape", SHAPES, ids=["x".join(map(str, s)) for s in SHAPES])
+def test_every_flat_kernel_on_edge_shapes(env, dtype, shape):
+    lib, ran = env[2], 0
+    cases = {}
+    for index, images, exactly in kernels(lib, dtype):
+        # as many images as a lane holds, one more, an odd number beyond a half-wave's lanes
+        for B in ((images,) if exactly else (images, images + 1, 37)):
+            if B not in cases:
+                cfg = ci.custom("flat", B, *shape, dtype=dtype, dist="normal", seed=40 + B)
+                img, flt = ci.make_inputs(cfg)
+                cases[B] = (cfg, img, flt) + gu.oracle_full(cfg, img, flt)
+            cfg, img, flt, ref, ab = cases[B]
+            print(f"[flat] kernel {index} {dtype} {cfg.dims}", flush=True)
+            for misalign in (0, 1):
+                rc, out = run(env, cfg, img, flt, index, misalign)
+                if rc == 3:     # a filter row shorter than the chunk that a lane holding all images loads
+                    assert exactly and shape[0] * shape[5] < (4 if dtype == "f32" else 8)
+                    continue
+                assert rc == 0
+                check(cfg, out, ref, ab, f"kernel {index} misalign {misalign}")
+                ran += 1
+    assert ran > 0
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+def test_flat_kernels_refuse_what_they_cannot_hold(env, dtype):
+    cc, torch, lib = env
+    for index, images, exactly in kernels(lib, dtype):
+        for B in (images - 1, images + 1) if exactly else (images - 1,):
+            if B >= 1:
+                cfg = ci.custom("flat", B, 16, 8, 2, 2, 1, 1, dtype=dtype, seed=3)
+                rc, out = run(env, cfg, *ci.make_inputs(cfg), index)
+                assert rc == 3 and np.isnan(out).all()
+    cfg = ci.custom("flat", 1, 16, 8, 2, 2, 1, 1, dtype=dtype, seed=3)
+    assert run(env, cfg, *ci.make_inputs(cfg), 10 ** 6)[0] == 3 and run(env, cfg, *ci.make_inputs(cfg), -1)[0] == 3
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("c", [3, 11])
+def test_nonfinite_inputs_stay_local_in_flat_kernels(env, dtype, c):
+    """The last chunk of a filter row is moved back to end with the row, so that its first elements are multiplied by zero on both
+    sides: an Inf or NaN in one of them, in the row behind it or in a neighbouring image must reach its own outputs only."""
+    lib = env[2]
+    for index, images, exactly in kernels(lib, dtype):
+        B = images if exactly else max(images, 2)
+        dims = (B, c, 34, 4, 3, 2, 3 if exactly else 1, 1, 2)
+        cfg = ci.custom("flat_inf", *dims, dtype=dtype, dist="normal", seed=9)
+        img0, flt = ci.make_inputs(cfg)
+        _, _, K, W, H, R, S, sw, sh = dims
+        for n, (x, y, ch, b) in enumerate([(0, 0, c - 1, 0), (1, 1, 0, B - 1), (2, 0, c // 2, B // 2), (img0.shape[0] - 1, img0.shape[1] - 1, c - 1, B - 1)]):
+            img = img0.copy()
+            img[x, y, ch, b] = np.inf if n % 2 == 0 else np.nan
+            print(f"[flat] kernel {index} {dtype} {dims} non-finite at {(x, y, ch, b)}", flush=True)
+            rc, out = run(env, cfg, img, flt, index)
+            assert rc == 0
+            want = np.zeros(cfg.out_shape, bool)
+            for w in range(W):
+                for h in range(H):
+                    if 0 <= x - sw * w < R and 0 <= y - sh * h < S:
+                        want[:, h, w, b] = True
+            assert np.array_equal(~np.isfinite(out), want), (index, (x, y, ch, b))
