@@ -8,15 +8,17 @@
 // and nothing is decoded in the loop.  Positions are cut into tiles wherever they end: 32 columns of an MFMA block are 32
 // positions (or 32 groups of images) in a row, whatever B, W and H are.
 //
-// What a tile kernel gains by staging in LDS this one gains by starting at once: every operand goes from global memory
-// (L1 and L2 hold the windows' overlap) to the registers of the wave that multiplies it, several steps ahead, with no
-// barrier.  Where there are few tiles the waves of a workgroup divide the contraction instead and add up in LDS at the end.
-// It is bound by the compute unit's address unit (a load whose 64 lanes fall into many cache lines takes about a clock
-// for each of them), which is why a lane loads several images or several channels at once where it can.
+// Two kernels.  The first takes every operand from global memory (L1 and L2 hold the windows' overlap) straight to the
+// registers of the wave that multiplies it, several steps ahead, with no barrier.  It is bound by the compute unit's
+// address unit: a load whose 64 lanes fall into many cache lines takes about a clock for each of them, which is why a lane
+// loads several images or several channels at once where it can.  The second stages both operands in LDS with loads that
+// run along memory, so that the address unit sees each byte of a tile once (it moves 64 bytes a clock then) instead of once
+// per wave in pieces of 32 bytes: 1.2 to 3 times faster for bf16, whose products are short, level for fp32.
+// Where there are few tiles the waves of a workgroup divide the contraction and add up in LDS at the end.
 //
-// Measured against the kernels that ran these calls before (one launch, MI355X):
-//   fp32 (5, 30, 50, 27, 19, 5 x 5)         109.7 -> 11.3 us      bf16 (1, 128, 128, 28, 28, 3 x 3)      46.0 -> 6.8 us
-//   bf16 (16, 3, 64, 112, 112, 7 x 7, s 2)  349 -> 28.1 us        bf16 (3, 367, 237, 15, 15, 3 x 3)     310 -> 30 us
+// Measured against the kernels that ran these calls before (one launch, MI355X; direct, then staged):
+//   fp32 (5, 30, 50, 27, 19, 5 x 5)         109.7 -> 11.3 / 10.0 us      bf16 (1, 128, 128, 28, 28, 3 x 3)    46.0 -> 6.8 / 5.0 us
+//   bf16 (16, 3, 64, 112, 112, 7 x 7, s 2)  349 -> 28.1 / 25.3 us        bf16 (3, 367, 237, 15, 15, 3 x 3)   310 -> 53 / 22.8 us
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -29,6 +31,8 @@ typedef float ff32x4 __attribute__((ext_vector_type(4)));
 typedef float ff32x2 __attribute__((ext_vector_type(2)));
 typedef unsigned int fu32x4 __attribute__((ext_vector_type(4)));
 typedef unsigned int fu32x2 __attribute__((ext_vector_type(2)));
+typedef short fs16x4 __attribute__((ext_vector_type(4)));
+#define FLAT_LDS(T) __attribute__((address_space(3))) T
 typedef __bf16 fbf16x8 __attribute__((ext_vector_type(8)));
 
 __device__ __forceinline__ uint32_t flat_div(uint32_t n, const FlatDiv& d) {
@@ -93,6 +97,56 @@ struct FlatReduce {
     static constexpr size_t BYTES = WK == 1 ? 0 : (size_t)(ROUNDS > 1 ? 2 : 1) * bytes(VS);
 };
 
+// Hands a wave's sums (NG groups of IPL column blocks) to store(m, group, row, IPL values); with WK > 1 the partial sums of the
+// WK waves of a tile first meet in LDS, VS rows of a block at a time, in two buffers: a buffer is written again two rounds later,
+// when every wave has passed the barrier in between and so has read it.
+template <int MB, int NG, int IPL, int TILES, int WK, class Store>
+__device__ __forceinline__ void flat_write_out(float* s_red, ff32x16 (&acc)[MB][NG * IPL], int wave, int wk, int lane, Store store) {
+    using Lay = FlatReduce<MB, NG, IPL, TILES, WK>;
+    if constexpr (WK == 1) {
+#pragma unroll
+        for (int m = 0; m < MB; ++m)
+#pragma unroll
+            for (int v = 0; v < 16; ++v)
+#pragma unroll
+                for (int p = 0; p < NG; ++p) {
+                    float o[IPL];
+#pragma unroll
+                    for (int q = 0; q < IPL; ++q) o[q] = acc[m][p * IPL + q][v];
+                    store(m, p, v, o);
+                }
+    } else {
+        constexpr int VS = Lay::VS, SLOT = IPL * VS * 64;
+        float* const grp = s_red + (size_t)(wave / WK) * WK * SLOT + lane;
+        int buf = 0;
+#pragma unroll
+        for (int m = 0; m < MB; ++m)
+#pragma unroll
+            for (int p = 0; p < NG; ++p)
+#pragma unroll
+                for (int v0 = 0; v0 < 16; v0 += VS) {
+                    float* const slot = grp + buf * Lay::BUF;
+#pragma unroll
+                    for (int v = 0; v < VS; ++v)
+#pragma unroll
+                        for (int q = 0; q < IPL; ++q) slot[wk * SLOT + (v * IPL + q) * 64] = acc[m][p * IPL + q][v0 + v];
+                    __syncthreads();
+                    for (int v = wk; v < VS; v += WK) {
+                        float o[IPL];
+#pragma unroll
+                        for (int q = 0; q < IPL; ++q) {
+                            float s = 0.f;
+#pragma unroll
+                            for (int w = 0; w < WK; ++w) s += slot[w * SLOT + (v * IPL + q) * 64];
+                            o[q] = s;
+                        }
+                        store(m, p, v0 + v, o);
+                    }
+                    buf ^= 1;
+                }
+    }
+}
+
 // IM > 0: a lane holds IM adjacent images of a position and loads them one contraction index at a time.
 // IM < 0: there are -IM images in all; a lane holds all of them and loads 16 bytes at a time, in which the images of a
 // channel are neighbours and the channels follow each other.
@@ -104,8 +158,7 @@ __global__ void __launch_bounds__(WM* WN* WK * 64) conv_flat_kernel(const FlatAr
     static_assert(!(SHORT && RUN), "flat kernel: a run of 16 bytes needs a filter row that long");
     constexpr int LW = RUN ? 4 : (IPL * ESZ + 3) / 4;  // dwords of one Image load
     constexpr int LE = RUN ? IPL : CH;                 // Image loads per chunk
-    using Lay = FlatReduce<MB, NG, IPL, WM * WN, WK>;
-    extern __shared__ float s_red[];
+    extern __shared__ __align__(16) float s_red[];
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -190,9 +243,9 @@ __global__ void __launch_bounds__(WM* WN* WK * 64) conv_flat_kernel(const FlatAr
         }
         // the half-wave's chunk of the next step lies two chunks further on
         u += 2;
-        tc += a.d2_tc;
-        foff += a.d2_flt;
-        ioff += a.d2_img;
+        tc += a.adv_tc;
+        foff += a.adv_flt;
+        ioff += a.adv_img;
         if (tc >= a.TC) {
             tc -= a.TC;
             foff += a.wrap_flt;
@@ -312,50 +365,7 @@ __global__ void __launch_bounds__(WM* WN* WK * 64) conv_flat_kernel(const FlatAr
                 if (i >= skip[p]) dst[i] = o[i];
         }
     };
-    if constexpr (WK == 1) {
-#pragma unroll
-        for (int m = 0; m < MB; ++m)
-#pragma unroll
-            for (int v = 0; v < 16; ++v)
-#pragma unroll
-                for (int p = 0; p < NG; ++p) {
-                    float o[IPL];
-#pragma unroll
-                    for (int q = 0; q < IPL; ++q) o[q] = acc[m][p * IPL + q][v];
-                    store(m, p, v, o);
-                }
-    } else {
-        // The partial sums of the WK waves of a tile meet in LDS, VS rows of a block at a time, in two buffers: a buffer is
-        // written again two rounds later, when every wave has passed the barrier in between and so has read it.
-        constexpr int VS = Lay::VS, SLOT = IPL * VS * 64;
-        float* const grp = s_red + (size_t)(wave / WK) * WK * SLOT + lane;
-        int buf = 0;
-#pragma unroll
-        for (int m = 0; m < MB; ++m)
-#pragma unroll
-            for (int p = 0; p < NG; ++p)
-#pragma unroll
-                for (int v0 = 0; v0 < 16; v0 += VS) {
-                    float* const slot = grp + buf * Lay::BUF;
-#pragma unroll
-                    for (int v = 0; v < VS; ++v)
-#pragma unroll
-                        for (int q = 0; q < IPL; ++q) slot[wk * SLOT + (v * IPL + q) * 64] = acc[m][p * IPL + q][v0 + v];
-                    __syncthreads();
-                    for (int v = wk; v < VS; v += WK) {
-                        float o[IPL];
-#pragma unroll
-                        for (int q = 0; q < IPL; ++q) {
-                            float s = 0.f;
-#pragma unroll
-                            for (int w = 0; w < WK; ++w) s += slot[w * SLOT + (v * IPL + q) * 64];
-                            o[q] = s;
-                        }
-                        store(m, p, v0 + v, o);
-                    }
-                    buf ^= 1;
-                }
-    }
+    flat_write_out<MB, NG, IPL, WM * WN, WK>(s_red, acc, wave, wk, lane, store);
 }
 
 template <int DT, int MB, int NG, int IM, int WM, int WN, int WK, int D, bool SHORT>
@@ -381,46 +391,409 @@ static int launch_flat_shape(const FlatArgs& a, int grid, void* stream) {
                                           : launch_flat_one<DT, MB, NG, IM, WM, WN, WK, D, false>(a, grid, stream);
 }
 
+// ---------------------------------------------------------------------------------------------------------------
+// The same product with both operands staged in LDS, NCH chunks of the contraction at a time.  Loads go through registers
+// (16-byte loads at any element alignment, zeroed where a chunk is shorter) two stages ahead.  The steps of a stage are not
+// written out a second time for the last, shorter stage: the larger code was 3 to 5 % slower on launches of 3 to 30 us.
+// IM > 0: the tile's columns are groups of IM adjacent images; LDS holds one row of columns per contraction index.
+// IM < 0: the columns are positions with all of their -IM images; LDS holds a position's chunks as they lie in memory.
+template <int DT, int MB, int NBW, int IM, int WM, int WN, int WK, int NCH>
+struct FlatLds {
+    static constexpr int ESZ = DT == 0 ? 4 : 2, CH = 16 / ESZ, THREADS = WM * WN * WK * 64;
+    static constexpr bool RUN = IM < 0;
+    static constexpr int IPL = RUN ? -IM : IM, NB = RUN ? NBW * IPL : NBW;
+    static constexpr int KT = WM * MB * 32, COLS = WN * NBW * 32;   // columns (RUN: positions) of the tile
+    static constexpr int GROUPS = RUN ? COLS : COLS / IPL;
+    static constexpr int FP = NCH + 1;                              // 16-byte units of a Filter row, odd: conflict-free reads
+    static constexpr int FLT_BYTES = KT * FP * 16;
+    // bytes of an Image row.  Positions: an odd number of 16-byte units.  bf16 columns: four rows' 64-byte pieces, which a
+    // transposing read takes at once, lie in different banks; fp32 columns: rows four apart differ by 32 banks.
+    static constexpr int ROW = RUN ? ((NCH * IPL) | 1) * 16 : DT == 0 ? COLS * 4 + 32 : COLS * 2 + (COLS == 32 ? 0 : 64);
+    static constexpr int IMG_BYTES = (RUN ? COLS : NCH * CH) * ROW;
+    static constexpr int BUF = FLT_BYTES + IMG_BYTES;
+    static constexpr int NF = KT * NCH / THREADS;                   // Filter items per thread and stage
+    static constexpr int RPP = RUN ? THREADS / NCH : THREADS / GROUPS;   // positions / contraction indices per pass
+    static constexpr int NI = RUN ? COLS / RPP : NCH * CH / RPP;    // Image items (RUN: of IPL loads each)
+    static constexpr int LW = RUN ? 4 : IPL * ESZ / 4;              // dwords of one Image load
+    static constexpr int STEPS = NCH / 2 / WK;                      // steps of two chunks per wave and stage
+    using Red = FlatReduce<MB, NBW, RUN ? IPL : 1, WM * WN, WK>;
+    static constexpr size_t LDS = 2 * BUF > (int)Red::BYTES ? (size_t)2 * BUF : Red::BYTES;
+    static_assert(NF * THREADS == KT * NCH && NF >= 1, "flat LDS kernel: whole Filter items per thread");
+    static_assert(RUN ? NI * RPP == COLS && NI >= 1 : (NI * RPP == NCH * CH && RPP % CH == 0 && NI >= 1), "flat LDS kernel: whole Image items per thread");
+    static_assert(STEPS >= 1 && STEPS * 2 * WK == NCH, "flat LDS kernel: whole steps per wave");
+    static_assert(LDS <= 160 * 1024, "flat LDS kernel: LDS size");
+};
+
+template <int DT, int MB, int NBW, int IM, int WM, int WN, int WK, int NCH>
+__global__ void __launch_bounds__(WM* WN* WK * 64) conv_flat_lds_kernel(const FlatArgs a) {
+    using GEO = FlatLds<DT, MB, NBW, IM, WM, WN, WK, NCH>;
+    constexpr int ESZ = GEO::ESZ, CH = GEO::CH, IPL = GEO::IPL, NB = GEO::NB, NF = GEO::NF, NI = GEO::NI, LW = GEO::LW;
+    constexpr int THREADS = GEO::THREADS, RPP = GEO::RPP;
+    constexpr bool RUN = GEO::RUN;
+    constexpr int LE = RUN ? IPL : 1;                  // loads per Image item
+    constexpr int NS = RUN ? 1 : NI;                   // chunks that a thread's Image items belong to
+    extern __shared__ __align__(16) char s_mem[];
+
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wk = wave % WK, wm = (wave / WK) % WM, wn = wave / (WK * WM);
+    const int j = lane & 31, g = lane >> 5;
+
+    uint32_t t = blockIdx.x;
+    {
+        const uint32_t l = t >> 3, x = t & 7;
+        t = x * a.xcd_q + min(x, a.xcd_rem) + l;
+    }
+    uint32_t tk, tn;
+    {
+        const uint32_t q = flat_div(t, a.d_inner), i = t - q * a.inner;
+        tk = a.k_inner ? i : q;
+        tn = a.k_inner ? q : i;
+    }
+    const uint32_t k0 = tk * GEO::KT, q0 = tn * GEO::GROUPS;
+    auto position = [&](uint32_t q, uint32_t& img, uint32_t& pos, int& skip) {
+        const uint32_t qc = min(q, a.groups - 1);
+        const uint32_t hw = RUN ? qc : flat_div(qc, a.d_G), first = RUN ? 0 : (qc - hw * a.G) * IPL;
+        const uint32_t b = RUN ? 0 : min(first, a.B - IPL);
+        const uint32_t h = flat_div(hw, a.d_W), w = hw - h * a.W;
+        img = w * a.img_w + h * a.img_h + b * ESZ;
+        pos = hw * a.B + b;
+        skip = q < a.groups ? (int)(first - b) : IPL;
+    };
+
+    // ---- staging: a thread's items, fixed but for the chunk that they move on to with every stage
+    struct Chunk {
+        uint32_t u, tc, flt, img;
+    };
+    auto chunk_at = [&](uint32_t u) {
+        const uint32_t r = flat_div(u, a.d_TC), tc = u - r * a.TC;
+        return Chunk{u, tc, r * a.flt_r + tc * 16, r * a.img_r + tc * a.img_chunk};
+    };
+    auto advance = [&](Chunk& c) {
+        c.u += NCH;
+        c.tc += a.adv_tc;
+        c.flt += a.adv_flt;
+        c.img += a.adv_img;
+        if (c.tc >= a.TC) {
+            c.tc -= a.TC;
+            c.flt += a.wrap_flt;
+            c.img += a.wrap_img;
+        }
+    };
+    const uint32_t eoff = a.B * ESZ;
+    const int fc = tid % NCH, fr = tid / NCH;
+    uint32_t aoff[NF];
+#pragma unroll
+    for (int i = 0; i < NF; ++i) aoff[i] = min(k0 + fr + i * (THREADS / NCH), a.K - 1) * a.flt_row;
+    Chunk fch = chunk_at(fc), ich[NS];
+    const int ig = RUN ? 0 : tid % GEO::GROUPS, ir = RUN ? fr : tid / GEO::GROUPS;
+    uint32_t boff[RUN ? NI : 1];
+    {
+        uint32_t pos;
+        int skip;
+        if constexpr (RUN) {
+#pragma unroll
+            for (int i = 0; i < NI; ++i) position(q0 + ir + i * RPP, boff[i], pos, skip);
+            ich[0] = fch;
+        } else {
+            position(q0 + ig, boff[0], pos, skip);
+#pragma unroll
+            for (int i = 0; i < NI; ++i) ich[i] = chunk_at(ir / CH + i * (RPP / CH));
+        }
+    }
+    const int ie = ir % CH;                            // (columns) the item's contraction index inside its chunk
+
+    uint32_t F[2][NF][4], X[2][NI][LE][LW], flo[2], ilo[2][NS];
+    auto fetch = [&](int set) {
+        {
+            const bool out = fch.u >= a.U, last = fch.tc + 1 == a.TC;
+            flo[set] = out ? CH : last ? a.back : 0;
+            const uint32_t fo = out ? 0 : last ? fch.flt - a.back * ESZ : fch.flt;
+#pragma unroll
+            for (int i = 0; i < NF; ++i) load_at<16>(F[set][i], (const char*)a.filter, aoff[i] + fo);
+            if constexpr (RUN) {
+                const uint32_t io = out ? 0 : last ? fch.img - a.back * eoff : fch.img;
+                ilo[set][0] = flo[set];
+#pragma unroll
+                for (int i = 0; i < NI; ++i)
+#pragma unroll
+                    for (int e = 0; e < LE; ++e) load_at<16>(X[set][i][e], (const char*)a.image + e * 16, boff[i] + io);
+            }
+            advance(fch);
+        }
+        if constexpr (!RUN) {
+#pragma unroll
+            for (int i = 0; i < NI; ++i) {
+                const bool out = ich[i].u >= a.U, last = ich[i].tc + 1 == a.TC;
+                ilo[set][i] = out ? CH : last ? a.back : 0;
+                const uint32_t io = out ? 0 : (last ? ich[i].img - a.back * eoff : ich[i].img) + ie * eoff;
+                load_at<LW * 4>(X[set][i][0], (const char*)a.image, boff[0] + io);
+                advance(ich[i]);
+            }
+        }
+    };
+    // elements [0, lo) of a chunk are zeros for both operands: a chunk beyond the last one, and the elements of the last chunk
+    // of a filter row that the chunk before it has as well
+    auto put = [&](int set, char* buf) {
+        uint32_t any = flo[set];
+#pragma unroll
+        for (int i = 0; i < NS; ++i) any |= ilo[set][i];
+        if (__any(any != 0)) {
+#pragma unroll
+            for (int d = 0; d < 4; ++d) {
+                const uint32_t lo = flo[set];
+                const uint32_t keep = DT == 0 ? ((uint32_t)d >= lo ? ~0u : 0u)
+                                              : ((uint32_t)(2 * d) >= lo ? 0xffffu : 0u) | ((uint32_t)(2 * d + 1) >= lo ? 0xffff0000u : 0u);
+#pragma unroll
+                for (int i = 0; i < NF; ++i) F[set][i][d] &= keep;
+            }
+            if constexpr (RUN) {
+                const uint32_t lo = flo[set] * IPL;
+#pragma unroll
+                for (int e = 0; e < LE; ++e)
+#pragma unroll
+                    for (int d = 0; d < 4; ++d) {
+                        const uint32_t f = DT == 0 ? e * 4 + d : e * 8 + 2 * d;
+                        const uint32_t keep = DT == 0 ? (f >= lo ? ~0u : 0u) : (f >= lo ? 0xffffu : 0u) | (f + 1 >= lo ? 0xffff0000u : 0u);
+#pragma unroll
+                        for (int i = 0; i < NI; ++i) X[set][i][e][d] &= keep;
+                    }
+            } else {
+#pragma unroll
+                for (int i = 0; i < NI; ++i) {
+                    const uint32_t keep = (uint32_t)ie >= ilo[set][i] ? ~0u : 0u;
+#pragma unroll
+                    for (int d = 0; d < LW; ++d) X[set][i][0][d] &= keep;
+                }
+            }
+        }
+#pragma unroll
+        for (int i = 0; i < NF; ++i)
+            *(fu32x4*)(buf + ((fr + i * (THREADS / NCH)) * GEO::FP + fc) * 16) = fu32x4{F[set][i][0], F[set][i][1], F[set][i][2], F[set][i][3]};
+        char* const img = buf + GEO::FLT_BYTES;
+#pragma unroll
+        for (int i = 0; i < NI; ++i) {
+            if constexpr (RUN) {
+#pragma unroll
+                for (int e = 0; e < LE; ++e)
+                    *(fu32x4*)(img + (ir + i * RPP) * GEO::ROW + (fc * IPL + e) * 16) = fu32x4{X[set][i][e][0], X[set][i][e][1], X[set][i][e][2], X[set][i][e][3]};
+            } else if constexpr (LW == 4) {
+                *(fu32x4*)(img + (ir + i * RPP) * GEO::ROW + ig * 16) = fu32x4{X[set][i][0][0], X[set][i][0][1 % LW], X[set][i][0][2 % LW], X[set][i][0][3 % LW]};
+            } else {
+                *(fu32x2*)(img + (ir + i * RPP) * GEO::ROW + ig * 8) = fu32x2{X[set][i][0][0], X[set][i][0][1 % LW]};
+            }
+        }
+    };
+
+    // ---- multiplication
+    ff32x16 acc[MB][NB];
+#pragma unroll
+    for (int m = 0; m < MB; ++m)
+#pragma unroll
+        for (int n = 0; n < NB; ++n)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) acc[m][n][v] = 0.f;
+    const int i16 = lane & 15, jhalf = (lane >> 4) & 1;
+    auto multiply = [&](const char* buf, uint32_t chunks) {
+        const char* const ap = buf + ((wm * MB * 32 + j) * GEO::FP + g) * 16;
+        const char* const img = buf + GEO::FLT_BYTES;
+#pragma unroll
+        for (int s = 0; s < GEO::STEPS; ++s) {
+            const int st = s * WK + wk;                // (steps dealt in turns: a last stage of few chunks keeps all waves busy)
+            if ((uint32_t)(2 * st) >= chunks) break;
+            fu32x4 av[MB], bv[NB];
+#pragma unroll
+            for (int m = 0; m < MB; ++m) av[m] = *(const fu32x4*)(ap + m * 32 * GEO::FP * 16 + st * 32);
+            if constexpr (RUN) {
+#pragma unroll
+                for (int p = 0; p < NBW; ++p) {
+                    const char* const xp = img + ((wn * NBW + p) * 32 + j) * GEO::ROW + (2 * st + g) * IPL * 16;
+                    fu32x4 x[IPL];
+#pragma unroll
+                    for (int e = 0; e < IPL; ++e) x[e] = *(const fu32x4*)(xp + e * 16);
+#pragma unroll
+                    for (int q = 0; q < IPL; ++q)
+#pragma unroll
+                        for (int i = 0; i < 4; ++i) {
+                            if constexpr (DT == 0) {
+                                bv[p * IPL + q][i] = x[(i * IPL + q) / 4][(i * IPL + q) % 4];
+                            } else {
+                                const int e0 = 2 * i * IPL + q, e1 = e0 + IPL;
+                                bv[p * IPL + q][i] = IPL == 1 ? x[0][i]
+                                                              : __builtin_amdgcn_perm(x[e1 / 8][e1 / 2 % 4], x[e0 / 8][e0 / 2 % 4],
+                                                                                      (e1 & 1 ? 0x07060000u : 0x05040000u) | (e0 & 1 ? 0x0302u : 0x0100u));
+                            }
+                        }
+                }
+            } else if constexpr (DT == 0) {
+                const char* const xp = img + (2 * st + g) * CH * GEO::ROW + (wn * NBW * 32 + j) * 4;
+#pragma unroll
+                for (int n = 0; n < NB; ++n)
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) bv[n][e] = *(const uint32_t*)(xp + e * GEO::ROW + n * 128);
+            } else {
+                // the transposing read: four rows (contraction indices) of 16 columns to a lane per column
+                const char* const xp = img + (16 * st + 8 * g + (i16 >> 2)) * GEO::ROW + wn * NBW * 64 + jhalf * 32 + (i16 & 3) * 8;
+#pragma unroll
+                for (int n = 0; n < NB; ++n) {
+                    const fs16x4 l = __builtin_amdgcn_ds_read_tr16_b64_v4i16((FLAT_LDS(fs16x4)*)(xp + n * 64));
+                    const fs16x4 h = __builtin_amdgcn_ds_read_tr16_b64_v4i16((FLAT_LDS(fs16x4)*)(xp + 4 * GEO::ROW + n * 64));
+                    bv[n] = __builtin_bit_cast(fu32x4, __builtin_shufflevector(l, h, 0, 1, 2, 3, 4, 5, 6, 7));
+                }
+            }
+            if constexpr (DT == 0) {
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+#pragma unroll
+                    for (int m = 0; m < MB; ++m)
+#pragma unroll
+                        for (int n = 0; n < NB; ++n)
+                            acc[m][n] = __builtin_amdgcn_mfma_f32_32x32x2f32(__uint_as_float(av[m][e]), __uint_as_float(bv[n][e]), acc[m][n], 0, 0, 0);
+            } else {
+#pragma unroll
+                for (int m = 0; m < MB; ++m)
+#pragma unroll
+                    for (int n = 0; n < NB; ++n)
+                        acc[m][n] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(fbf16x8, av[m]), __builtin_bit_cast(fbf16x8, bv[n]), acc[m][n], 0, 0, 0);
+            }
+        }
+    };
+
+    // Stage s is multiplied out of buffer s % 2 while the loads of stages s + 1 and s + 2 are in flight or in registers; a
+    // buffer is written again after the barrier that every wave reaches behind its reads of it.  All waves run the same
+    // number of stages.
+    char* const buf0 = s_mem;
+    char* const buf1 = s_mem + GEO::BUF;
+    const int stages = (int)((a.U + NCH - 1) / NCH);
+    fetch(0);
+    __builtin_amdgcn_sched_barrier(0);
+    fetch(1);
+    __builtin_amdgcn_sched_barrier(0);
+    put(0, buf0);
+    __builtin_amdgcn_sched_barrier(0);
+    fetch(0);
+    __syncthreads();
+    for (int s = 0;; s += 2) {
+        multiply(buf0, a.U - (uint32_t)s * NCH);
+        if (s + 1 >= stages) break;
+        put(1, buf1);
+        __builtin_amdgcn_sched_barrier(0);
+        fetch(1);
+        __syncthreads();
+        multiply(buf1, a.U - (uint32_t)(s + 1) * NCH);
+        if (s + 2 >= stages) break;
+        put(0, buf0);
+        __builtin_amdgcn_sched_barrier(0);
+        fetch(0);
+        __syncthreads();
+    }
+
+    // ---- Out
+    constexpr int SI = RUN ? IPL : 1;                  // images of a lane's column block group
+    uint32_t opos[NBW];
+    int skip[NBW];
+#pragma unroll
+    for (int p = 0; p < NBW; ++p) {
+        uint32_t img;
+        const uint32_t col = (wn * NBW + p) * 32 + j;
+        position(q0 + (RUN ? col : col / IPL), img, opos[p], skip[p]);
+        if (!RUN) {
+            opos[p] += col % IPL;
+            skip[p] = (int)(col % IPL) < skip[p];
+        }
+    }
+    auto store = [&](int m, int p, int v, const float (&o)[SI]) {
+        const uint32_t k = k0 + (wm * MB + m) * 32 + (v >> 2) * 8 + g * 4 + (v & 3);
+        if (k >= a.K || skip[p]) return;
+        float* const dst = a.out + (int64_t)k * a.N + opos[p];
+        if constexpr (SI == 4 || SI == 8) {
+#pragma unroll
+            for (int i = 0; i < SI; i += 4) ((Out4*)(dst + i))->v = ff32x4{o[i], o[i + 1], o[i + 2], o[i + 3]};
+        } else if constexpr (SI == 2 || SI == 6) {
+#pragma unroll
+            for (int i = 0; i < SI; i += 2) ((Out2*)(dst + i))->v = ff32x2{o[i], o[i + 1]};
+        } else {
+#pragma unroll
+            for (int i = 0; i < SI; ++i) dst[i] = o[i];
+        }
+    };
+    if constexpr (WK > 1) __syncthreads();             // the buffers become the exchange area of the partial sums
+    flat_write_out<MB, NBW, SI, WM * WN, WK>((float*)s_mem, acc, wave, wk, lane, store);
+}
+
+template <int DT, int MB, int NBW, int IM, int WM, int WN, int WK, int NCH>
+static int launch_flat_lds(const FlatArgs& a, int grid, void* stream) {
+    using GEO = FlatLds<DT, MB, NBW, IM, WM, WN, WK, NCH>;
+    auto kernel = conv_flat_lds_kernel<DT, MB, NBW, IM, WM, WN, WK, NCH>;
+    if constexpr (GEO::LDS > 64 * 1024) {
+        static const bool ok = hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024) == hipSuccess;
+        if (!ok) {
+            (void)hipGetLastError();
+            return 1;
+        }
+    }
+    hipLaunchKernelGGL(kernel, dim3(grid), dim3(GEO::THREADS), GEO::LDS, (hipStream_t)stream, a);
+    return hipGetLastError() == hipSuccess ? 0 : 1;
+}
+
 // blocks of output channels, groups of images per wave; images per lane; waves along k, positions, contraction; steps ahead.
-// The configurations that a cost estimate picks from (cacnn_host.cpp), chosen from 298 by leaving out whatever made the pick on
-// 130 layers less than half a per cent worse.
+// (The configurations that the cost estimate in cacnn_host.cpp picks from: chosen from 487 by leaving out, one after the
+// other, what made its picks on 390 layers of all sizes worse by least; the best of these is within 1.3 % of the best of all.)
 #define CACNN_FLAT(DT, MB, NG, IM, WM, WN, WK, D) \
-    {{DT, MB, NG, IM, WM, WN, WK}, launch_flat_shape<DT, MB, NG, IM, WM, WN, WK, D>}
+    {{DT, MB, NG, IM, WM, WN, WK, 0}, launch_flat_shape<DT, MB, NG, IM, WM, WN, WK, D>}
+
+#define CACNN_FLAT_LDS(DT, MB, NBW, IM, WM, WN, WK, NCH) \
+    {{DT, MB, NBW, IM, WM, WN, WK, NCH}, launch_flat_lds<DT, MB, NBW, IM, WM, WN, WK, NCH>}
 
 static const FlatVariant g_flat[] = {
     // fp32
     CACNN_FLAT(0, 1, 1, 1, 1, 1, 4, 4),
-    CACNN_FLAT(0, 1, 1, 1, 1, 2, 2, 4),
-    CACNN_FLAT(0, 1, 1, 2, 1, 1, 4, 4),
-    CACNN_FLAT(0, 1, 1, 2, 1, 2, 2, 4),
     CACNN_FLAT(0, 1, 1, 2, 1, 4, 1, 4),
     CACNN_FLAT(0, 1, 1, 4, 1, 4, 1, 4),
     CACNN_FLAT(0, 1, 1, 4, 2, 1, 2, 4),
     CACNN_FLAT(0, 1, 1, 4, 2, 2, 1, 4),
-    CACNN_FLAT(0, 1, 1, -1, 1, 1, 4, 4),
-    CACNN_FLAT(0, 2, 2, -1, 1, 1, 4, 4),
-    CACNN_FLAT(0, 1, 1, -2, 1, 1, 4, 4),
-    CACNN_FLAT(0, 1, 1, -7, 2, 2, 1, 3),
+    CACNN_FLAT_LDS(0, 1, 1, 2, 1, 1, 4, 8),
+    CACNN_FLAT_LDS(0, 1, 1, 2, 1, 1, 8, 32),
+    CACNN_FLAT_LDS(0, 1, 1, 4, 1, 1, 4, 8),
+    CACNN_FLAT_LDS(0, 1, 1, 4, 1, 1, 8, 32),
+    CACNN_FLAT_LDS(0, 1, 1, 4, 1, 2, 4, 16),
+    CACNN_FLAT_LDS(0, 1, 1, 4, 1, 4, 1, 8),
+    CACNN_FLAT_LDS(0, 1, 1, 4, 2, 2, 1, 8),
+    CACNN_FLAT_LDS(0, 1, 2, 4, 2, 2, 1, 8),
+    CACNN_FLAT_LDS(0, 1, 1, -1, 1, 1, 4, 16),
+    CACNN_FLAT_LDS(0, 1, 1, -1, 1, 1, 8, 32),
+    CACNN_FLAT_LDS(0, 1, 1, -1, 2, 2, 1, 8),
+    CACNN_FLAT_LDS(0, 1, 1, -2, 1, 1, 4, 8),
+    CACNN_FLAT_LDS(0, 1, 1, -3, 1, 1, 4, 8),
     // bf16
     CACNN_FLAT(1, 1, 1, 1, 1, 1, 4, 4),
     CACNN_FLAT(1, 1, 2, 1, 1, 1, 4, 3),
-    CACNN_FLAT(1, 1, 1, 2, 1, 4, 1, 4),
     CACNN_FLAT(1, 1, 2, 2, 1, 4, 1, 3),
-    CACNN_FLAT(1, 2, 2, 2, 1, 1, 4, 3),
     CACNN_FLAT(1, 2, 2, 2, 1, 4, 1, 3),
     CACNN_FLAT(1, 1, 1, 4, 1, 1, 4, 4),
-    CACNN_FLAT(1, 1, 1, -1, 1, 1, 4, 4),
-    CACNN_FLAT(1, 2, 1, -1, 1, 1, 4, 4),
-    CACNN_FLAT(1, 1, 1, -2, 1, 1, 4, 4),
-    CACNN_FLAT(1, 1, 1, -2, 1, 2, 2, 4),
-    CACNN_FLAT(1, 1, 1, -3, 1, 1, 4, 4),
-    CACNN_FLAT(1, 2, 1, -3, 1, 1, 4, 4),
-    CACNN_FLAT(1, 1, 1, -4, 1, 1, 4, 4),
-    CACNN_FLAT(1, 2, 1, -4, 1, 1, 4, 4),
-    CACNN_FLAT(1, 1, 1, -5, 1, 1, 4, 4),
-    CACNN_FLAT(1, 1, 1, -6, 1, 1, 4, 4),
-    CACNN_FLAT(1, 1, 1, -7, 1, 1, 4, 3),
-    CACNN_FLAT(1, 1, 1, -8, 1, 1, 4, 3),
+    CACNN_FLAT_LDS(1, 1, 1, 4, 1, 1, 4, 8),
+    CACNN_FLAT_LDS(1, 1, 1, 4, 1, 1, 8, 32),
+    CACNN_FLAT_LDS(1, 1, 1, 4, 2, 2, 1, 8),
+    CACNN_FLAT_LDS(1, 1, 1, 8, 1, 1, 4, 8),
+    CACNN_FLAT_LDS(1, 1, 1, 8, 1, 1, 8, 32),
+    CACNN_FLAT_LDS(1, 1, 1, 8, 1, 4, 1, 8),
+    CACNN_FLAT_LDS(1, 1, 1, 8, 2, 2, 1, 8),
+    CACNN_FLAT_LDS(1, 1, 2, 8, 4, 2, 1, 8),
+    CACNN_FLAT_LDS(1, 2, 2, 8, 2, 2, 1, 8),
+    CACNN_FLAT_LDS(1, 2, 2, 8, 2, 4, 1, 8),
+    CACNN_FLAT_LDS(1, 1, 1, -1, 1, 1, 4, 8),
+    CACNN_FLAT_LDS(1, 1, 1, -1, 1, 1, 8, 32),
+    CACNN_FLAT_LDS(1, 1, 1, -1, 2, 2, 1, 8),
+    CACNN_FLAT_LDS(1, 1, 1, -2, 1, 1, 4, 8),
+    CACNN_FLAT_LDS(1, 1, 1, -2, 1, 1, 8, 32),
+    CACNN_FLAT_LDS(1, 1, 1, -2, 4, 2, 1, 8),
+    CACNN_FLAT_LDS(1, 1, 1, -3, 1, 1, 4, 8),
+    CACNN_FLAT_LDS(1, 1, 1, -3, 4, 1, 1, 8),
+    CACNN_FLAT_LDS(1, 1, 1, -4, 1, 1, 8, 16),
+    CACNN_FLAT_LDS(1, 1, 1, -4, 4, 1, 1, 8),
+    CACNN_FLAT_LDS(1, 1, 1, -5, 1, 1, 8, 16),
+    CACNN_FLAT_LDS(1, 1, 1, -6, 1, 1, 8, 16),
+    CACNN_FLAT_LDS(1, 1, 1, -7, 1, 1, 4, 8),
 };
 
 int num_flat() { return (int)(sizeof(g_flat) / sizeof(g_flat[0])); }

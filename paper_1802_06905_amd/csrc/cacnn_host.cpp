@@ -1068,45 +1068,75 @@ double compulsory_us(const cacnn_problem& p, int dtype) {
     return (esz * ((double)p.B * p.C * IW * IH + (double)p.K * p.R * p.S * p.C) + 4.0 * (double)p.K * p.H * p.W * p.B) / 4.6e6;
 }
 
+// ... and what a kernel takes that would need `us` with all data at hand: the larger of the two, and a quarter of the smaller
+// that the other does not hide (fitted with the estimates below)
+double with_copy_time(double us, const cacnn_problem& p, int dtype) {
+    const double copy = compulsory_us(p, dtype);
+    return std::max(us, copy) + 0.25 * std::min(us, copy);
+}
+
 // Whether a kernel with flattened positions takes the problem: enough images for the group a lane holds (or exactly the
 // number it was compiled for, and a filter row of at least one 16-byte chunk), and Image and Filter within the 2 GiB
 // that its 32-bit byte offsets reach.
 bool flat_fits(const cacnn_problem& p, int dtype, const FlatInfo& v) {
     const int esz = dtype == CACNN_F32 ? 4 : 2;
     if (v.dtype != dtype) return false;
-    if (v.IM < 0 ? (p.B != -v.IM || p.S * p.C * esz < 16) : p.B < v.IM) return false;
+    if (v.IM < 0 ? p.B != -v.IM : p.B < v.IM) return false;
+    if ((v.IM < 0 || v.NCH) && p.S * p.C * esz < 16) return false;
     const double IW = (double)(p.sigma_w * (p.W - 1) + p.R), IH = (double)(p.sigma_h * (p.H - 1) + p.S);
     return IW * IH * (double)p.C * (double)p.B * esz < 2147483648.0 && (double)p.K * p.R * p.S * p.C * esz < 2147483648.0;
 }
 
-// Estimated launch time in microseconds, from what bounds these kernels on MI355X: the address unit of a compute unit
-// (every operand comes straight from global memory), the MFMA pipes, and the latency of a wave's chain of steps.
-// Clocks of one 64-lane load, measured out of L1: at least 8.5 for 2 and 4 bytes a lane and 17.4 for 8 and 16 (that is
-// the 64 bytes a clock L1 delivers), else about one for each separate run of bytes; lanes whose address is no multiple of
-// 4 bytes take 1.5 (4 and 8 bytes a lane) to 3 times (16 bytes) as long.  Over 130 layers of all sizes the configuration with
-// the smallest estimate was on average within 5 % of the fastest one, and the estimate within 35 % of the time.
+// Estimated launch time in microseconds, from what bounds these kernels on MI355X: the address unit of a compute unit, through
+// which every operand comes, the issue slots and MFMA pipes of its SIMDs, and the latency of a chain of steps or stages.
+// The clocks of one 64-lane load, measured out of L1: at least 8.5 for 2 and 4 bytes a lane and 17.4 for 8 and 16 (that is
+// the 64 bytes a clock L1 delivers), else about one for each separate run of bytes; runs that are not made of four
+// neighbouring lanes cost more, and lanes whose address is no multiple of 4 bytes take about twice (8 bytes and less) to
+// three and a half times (16 bytes) as long.  The other constants are a least-squares fit to the launch times of all
+// configurations on 390 layers drawn over all sizes: there the configuration with the smallest estimate takes 1.04 times as
+// long as the fastest one in the geometric mean, and the estimate is within 14 % of the time (one standard deviation).
+double load_clocks(int bytes, double run_bytes, bool aligned4, bool whole_quads) {
+    const double floor_clk = bytes <= 4 ? 8.5 : 17.4, run_lanes = std::max(run_bytes / bytes, 1.0);
+    const double odd = aligned4 || bytes == 2 ? 1.0 : bytes == 16 ? 3.4 : 1.9;
+    const double clk = std::max(floor_clk, std::min(64.0, 48.0 / run_lanes)) * odd;
+    return whole_quads || run_lanes >= 32.0 ? clk : std::max(clk, 40.0 - run_lanes);
+}
+
 double flat_us(const cacnn_problem& p, int dtype, const FlatInfo& v) {
     const bool f32 = dtype == CACNN_F32, run = v.IM < 0;
     const int esz = f32 ? 4 : 2, ch = 16 / esz, ipl = run ? -v.IM : v.IM;
-    auto load_clk = [](int bytes, double run_bytes, bool aligned4) {
-        const double floor_clk = bytes <= 4 ? 8.5 : 17.4, runs = 64.0 * bytes / std::max(run_bytes, (double)bytes);
-        const double odd = aligned4 || bytes == 2 ? 1.0 : bytes == 16 ? 3.0 : 1.5;
-        return std::max(floor_clk, std::min(64.0, 0.75 * runs)) * odd;
-    };
-    const int64_t T = p.S * p.C, chunks = p.R * ceil_div(T, ch), steps = (chunks + 1) / 2, mine = ceil_div(steps, v.WK) + 1;
+    const int64_t T = p.S * p.C, chunks = p.R * ceil_div(T, ch);
     const int64_t groups = p.H * p.W * (run ? 1 : ceil_div(p.B, ipl));
-    const double tiles = (double)ceil_div(p.K, v.KT()) * (double)ceil_div(groups, v.GT());
-    const double per_cu = std::ceil(tiles / 256.0), waves = v.WM * v.WN * v.WK;
-    const double a_clk = T < ch ? ch * 40.0 : load_clk(16, 32.0, f32 || T % 2 == 0);
-    const double b_clk = run ? ipl * load_clk(16, 32.0 * ipl, f32 || p.C * p.B % 2 == 0)
-                             : ch * load_clk(ipl * esz, (double)(std::min<int64_t>(p.B, 32 * ipl) * esz), f32 || p.B % 2 == 0);
-    const double load = per_cu * waves * mine * (v.MB * a_clk + v.NG * b_clk);
-    const double mfma = per_cu * std::ceil(waves / 4.0) * mine * (v.MB * v.NG * ipl * (f32 ? 256.0 : 32.0) + 40.0);
-    const double latency = (mine / 4.0 + 0.75) * 2000.0;
-    const double blocks = per_cu * v.MB * v.NG * ipl;           // of Out, per wave
-    const double clk = std::sqrt(load * load + mfma * mfma + latency * latency) + blocks * v.WM * v.WN * 256.0 +
-                       (v.WK > 1 ? blocks * waves * 32.0 : 0.0) + per_cu * 600.0;
-    return std::max(clk / 2200.0, compulsory_us(p, dtype)) + 2.6;
+    const double per_cu = std::ceil((double)ceil_div(p.K, v.KT()) * (double)ceil_div(groups, v.GT()) / 256.0);
+    const double waves = v.WM * v.WN * v.WK, simd_waves = std::ceil(waves / 4.0), mfma = f32 ? 256.0 : 32.0;   // of one block's step
+    const double blocks = v.MB * v.NG * (run || !v.NCH ? ipl : 1);                                            // of one wave
+    const bool flt_aligned = f32 || T % 2 == 0, img_aligned = f32 || (run ? p.C * p.B : p.B) % 2 == 0;
+    double clk;
+    if (!v.NCH) {
+        const double mine = (double)ceil_div((chunks + 1) / 2, v.WK) + 1.0;                                   // steps of a wave
+        const double a_clk = T < ch ? ch * 40.0 : load_clocks(16, 32.0, flt_aligned, true);
+        const double b_clk = run ? ipl * load_clocks(16, 32.0 * ipl, img_aligned, true)
+                                 : ch * load_clocks(ipl * esz, (double)(std::min<int64_t>(p.B, 32 * ipl) * esz), img_aligned,
+                                                    ipl == 4 || p.B % (4 * ipl) == 0);
+        const double load = per_cu * waves * mine * (v.MB * a_clk + v.NG * b_clk);
+        const double simd = per_cu * simd_waves * mine * (blocks * mfma + 112.0), latency = (mine / 4.0 + 0.75) * 923.0;
+        clk = std::sqrt(load * load + simd * simd + latency * latency);
+    } else {
+        const double stages = (double)ceil_div(chunks, v.NCH), cols = v.WN * v.NG * 32, kt = v.KT();
+        const double steps = std::max(1, v.NCH / 2 / v.WK);                                                   // of a wave per stage
+        const double flt_items = kt * v.NCH, img_items = run ? cols * v.NCH * ipl : (double)v.NCH * ch * v.GT();
+        const double load = flt_items / 64.0 * load_clocks(16, (double)std::min<int64_t>(v.NCH * 16, T * esz), flt_aligned, true) +
+                            img_items / 64.0 * (run ? load_clocks(16, (double)std::min<int64_t>(v.NCH * 16 * ipl, T * p.B * esz), img_aligned, true)
+                                                    : load_clocks(ipl * esz, std::min((double)p.B, cols) * esz, img_aligned, true));
+        const double simd = simd_waves * (steps * blocks * mfma + 80.6 * (flt_items + img_items) / (64.0 * waves));
+        const double lds = (flt_items + (run ? img_items : v.NCH * ch * cols * esz / 16.0)) / 4.0 + waves * steps * (v.MB + blocks / v.MB) * 10.24;
+        const double stage = std::sqrt(load * load + simd * simd + 0.048 * lds * lds);
+        const double together = std::min(per_cu, std::max(1.0, std::min(2.0, std::floor(8.0 / waves))));      // workgroups that overlap
+        const double busy = per_cu * stages * stage, latency = std::ceil(per_cu / together) * stages * 421.0;
+        clk = std::sqrt(busy * busy + latency * latency) + 1000.0;
+    }
+    clk += per_cu * blocks * (v.WM * v.WN * 203.0 + (v.WK > 1 ? waves * 100.0 : 0.0));                        // Out
+    return with_copy_time(clk / 2302.0, p, dtype) + 2.2;
 }
 
 // The flattened kernel with the smallest estimate, -1 if none takes the problem.
@@ -1157,9 +1187,10 @@ int launch_flat(const cacnn_problem& p, int dtype, int fi, const void* image, co
     a.img_chunk = (uint32_t)(ch * p.B * esz);
     a.flt_r = (uint32_t)(T * esz);
     a.flt_row = (uint32_t)p.R * a.flt_r;
-    a.d2_tc = 2 % a.TC;
-    a.d2_flt = 2 / a.TC * a.flt_r + a.d2_tc * 16u;
-    a.d2_img = 2 / a.TC * a.img_r + a.d2_tc * a.img_chunk;
+    const uint32_t adv = v.NCH ? v.NCH : 2;
+    a.adv_tc = adv % a.TC;
+    a.adv_flt = adv / a.TC * a.flt_r + a.adv_tc * 16u;
+    a.adv_img = adv / a.TC * a.img_r + a.adv_tc * a.img_chunk;
     a.wrap_flt = a.flt_r - a.TC * 16u;
     a.wrap_img = a.img_r - a.TC * a.img_chunk;
     a.img_bytes = (int32_t)img;
@@ -1193,10 +1224,10 @@ std::vector<PlanEntry> g_plans;
 
 // What cacnn_conv_forward launches: the planned variant or a kernel with flattened positions.  A generic variant always
 // gives way to a flattened kernel that takes the problem: on 104 layers of all sizes whose plan was a generic variant the
-// flattened kernel was 1.05 to 60 times faster, 4 times in the geometric mean.  A fixed-geometry variant, whose price is
-// a measurement, gives way where the flattened kernel is estimated to be faster (26 such layers: the fixed-geometry kernels
-// stay up to 2.7 times faster where a layer fills their tiles, the flattened ones up to 3.9 times where it leaves most
-// compute units idle).
+// flattened kernel was 1.05 to 60 times faster, 5 times in the geometric mean.  A fixed-geometry variant, whose price is
+// a measurement, gives way where the flattened kernel is estimated to take less than 0.7 of its time: on 60 such layers
+// the flattened kernel was 1.2 to 4 times faster below that line (layers that leave most compute units idle, taps of large
+// filters), and between it and the break-even both sides won, by up to 1.5 times (1.27 for the fixed-geometry ones).
 int plan_route(const cacnn_problem& p, int dtype, bool aligned, Route* out) {
     double tiled_us = 0.0, flat_est = 0.0;
     const int rc = plan_impl(&p, dtype, nullptr, &out->plan, aligned, &tiled_us);
@@ -1206,7 +1237,7 @@ int plan_route(const cacnn_problem& p, int dtype, bool aligned, Route* out) {
     // (a call whose plan cannot be launched is refused, as it would be without the flattened kernels)
     const VariantInfo& v = variant(out->plan.variant).info;
     if (fi >= 0 && tile_list_in_range(p, v, out->plan.xcd_walk, out->plan.xcd_split_k) &&
-        (v.fx_ct == 0 || flat_est < std::max(tiled_us, compulsory_us(p, dtype) + 2.6)))
+        (v.fx_ct == 0 || flat_est < 0.7 * (with_copy_time(tiled_us - 2.2, p, dtype) + 2.2)))
         out->flat = fi;
     return rc;
 }
@@ -1687,12 +1718,15 @@ int cacnn_closed_form_tiling(const cacnn_problem* p, double M, cacnn_closed_form
 }
 
 int cacnn_internal_flat_count(void) { return num_flat(); }
-int cacnn_internal_flat_info(int i, int32_t* seven) {
-    if (i < 0 || i >= num_flat() || !seven) return CACNN_ERR_INVALID_ARG;
+int cacnn_internal_flat_info(int i, int32_t* eight) {
+    if (i < 0 || i >= num_flat() || !eight) return CACNN_ERR_INVALID_ARG;
     const FlatInfo& v = flat_variant(i).info;
-    const int32_t x[7] = {v.dtype, v.MB, v.NG, v.IM, v.WM, v.WN, v.WK};
-    std::memcpy(seven, x, sizeof(x));
+    const int32_t x[8] = {v.dtype, v.MB, v.NG, v.IM, v.WM, v.WN, v.WK, v.NCH};
+    std::memcpy(eight, x, sizeof(x));
     return CACNN_OK;
+}
+double cacnn_internal_flat_us(const cacnn_problem* p, int dtype, int i) {
+    return p && i >= 0 && i < num_flat() && flat_fits(*p, dtype, flat_variant(i).info) ? flat_us(*p, dtype, flat_variant(i).info) : -1.0;
 }
 int cacnn_internal_flat_forward(const cacnn_problem* problem, int dtype, int index, const void* image, const void* filter, void* out,
                                 void* hip_stream) {

@@ -134,7 +134,7 @@ struct FlatArgs {
     uint32_t img_w, img_h;              // Image bytes from one output column / row to the next
     uint32_t img_r, img_chunk;          // ... from one r to the next, from one chunk to the next
     uint32_t flt_row, flt_r;            // Filter bytes from one output channel / one r to the next
-    uint32_t d2_tc, d2_flt, d2_img;     // two chunks further on: whole r's and chunks
+    uint32_t adv_tc, adv_flt, adv_img;  // from a chunk to the one that is fetched next in its place (2 or NCH further on)
     uint32_t wrap_flt, wrap_img;        // correction when that passes the end of an r
     int32_t img_bytes;
     uint32_t inner, k_inner;            // tile list: the fastest index, its length; 1: the k-tiles, 0: the position tiles
@@ -146,8 +146,9 @@ struct FlatInfo {
     int MB, NG;         // blocks of 32 of one wave: output channels, groups of images
     int IM;             // > 0: images a lane holds; < 0: all of that many, loaded in runs along the contraction
     int WM, WN, WK;     // waves along output channels, along positions, along the contraction
+    int NCH;            // 0: operands straight from global memory; else chunks per LDS stage, and NG counts blocks of columns
     int KT() const { return WM * MB * 32; }
-    int GT() const { return WN * NG * 32; }
+    int GT() const { return WN * NG * 32 / (NCH && IM > 0 ? IM : 1); }   // groups of images per tile
 };
 struct FlatVariant {
     FlatInfo info;

@@ -24,12 +24,12 @@ def env():
 
 
 def kernels(lib, dtype):
-    """(index, images per lane, whether the lane holds all images) of every flattened kernel of the dtype"""
+    """(index, images per group, whether that has to be all images, whether it stages in LDS) of every flattened kernel of the dtype"""
     for i in range(lib.cacnn_internal_flat_count()):
-        x = (ctypes.c_int32 * 7)()
+        x = (ctypes.c_int32 * 8)()
         assert lib.cacnn_internal_flat_info(i, x) == 0
         if x[0] == (0 if dtype == "f32" else 1):
-            yield i, abs(x[3]), x[3] < 0
+            yield i, abs(x[3]), x[3] < 0, x[7] > 0
 
 
 def run(env, cfg, img, flt, index, misalign=0):
@@ -53,9 +53,10 @@ def check(cfg, out, ref, ab, what):
 
 # C, K, W, H, R, S, sw, sh: a filter row (S*C contraction indices) shorter than, equal to, one more than and not a multiple of a
 # 16-byte chunk; odd and even numbers of chunks, fewer chunks than waves; K and the positions beyond and below a tile; strides, also
-# above the filter's extent; a Filter larger than the Image (the other tile order)
+# above the filter's extent; a Filter larger than the Image (the other tile order); one, two, several whole and partly filled LDS stages
 SHAPES = [(3, 5, 3, 2, 2, 1, 1, 1), (1, 33, 4, 5, 3, 3, 2, 1), (8, 32, 1, 1, 1, 1, 1, 1), (9, 40, 5, 3, 1, 1, 1, 2), (5, 7, 6, 4, 3, 3, 1, 1),
-          (16, 64, 3, 3, 3, 3, 2, 2), (7, 31, 2, 9, 4, 5, 3, 1), (50, 97, 2, 1, 2, 2, 1, 1), (4, 16, 11, 13, 1, 2, 2, 3), (24, 130, 9, 7, 1, 3, 1, 1)]
+          (16, 64, 3, 3, 3, 3, 2, 2), (7, 31, 2, 9, 4, 5, 3, 1), (50, 97, 2, 1, 2, 2, 1, 1), (4, 16, 11, 13, 1, 2, 2, 3), (24, 130, 9, 7, 1, 3, 1, 1),
+          (131, 20, 2, 3, 1, 3, 1, 1), (64, 72, 3, 2, 3, 3, 1, 1)]
 
 
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
@@ -63,8 +64,8 @@ SHAPES = [(3, 5, 3, 2, 2, 1, 1, 1), (1, 33, 4, 5, 3, 3, 2, 1), (8, 32, 1, 1, 1, 
 def test_every_flat_kernel_on_edge_shapes(env, dtype, shape):
     lib, ran = env[2], 0
     cases = {}
-    for index, images, exactly in kernels(lib, dtype):
-        # as many images as a lane holds, one more, an odd number beyond a half-wave's lanes
+    for index, images, exactly, lds in kernels(lib, dtype):
+        # as many images as a group holds, one more, an odd number beyond a half-wave's lanes
         for B in ((images,) if exactly else (images, images + 1, 37)):
             if B not in cases:
                 cfg = ci.custom("flat", B, *shape, dtype=dtype, dist="normal", seed=40 + B)
@@ -74,8 +75,8 @@ def test_every_flat_kernel_on_edge_shapes(env, dtype, shape):
             print(f"[flat] kernel {index} {dtype} {cfg.dims}", flush=True)
             for misalign in (0, 1):
                 rc, out = run(env, cfg, img, flt, index, misalign)
-                if rc == 3:     # a filter row shorter than the chunk that a lane holding all images loads
-                    assert exactly and shape[0] * shape[5] < (4 if dtype == "f32" else 8)
+                if rc == 3:     # a filter row shorter than a chunk
+                    assert (exactly or lds) and shape[0] * shape[5] < (4 if dtype == "f32" else 8)
                     continue
                 assert rc == 0
                 check(cfg, out, ref, ab, f"kernel {index} misalign {misalign}")
@@ -86,7 +87,7 @@ def test_every_flat_kernel_on_edge_shapes(env, dtype, shape):
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
 def test_flat_kernels_refuse_what_they_cannot_hold(env, dtype):
     cc, torch, lib = env
-    for index, images, exactly in kernels(lib, dtype):
+    for index, images, exactly, lds in kernels(lib, dtype):
         for B in (images - 1, images + 1) if exactly else (images - 1,):
             if B >= 1:
                 cfg = ci.custom("flat", B, 16, 8, 2, 2, 1, 1, dtype=dtype, seed=3)
@@ -102,9 +103,9 @@ def test_nonfinite_inputs_stay_local_in_flat_kernels(env, dtype, c):
     """The last chunk of a filter row is moved back to end with the row, so that its first elements are multiplied by zero on both
     sides: an Inf or NaN in one of them, in the row behind it or in a neighbouring image must reach its own outputs only."""
     lib = env[2]
-    for index, images, exactly in kernels(lib, dtype):
+    for index, images, exactly, lds in kernels(lib, dtype):
         B = images if exactly else max(images, 2)
-        dims = (B, c, 34, 4, 3, 2, 3 if exactly else 1, 1, 2)
+        dims = (B, c, 34, 4, 3, 2, 3 if exactly or lds else 1, 1, 2)
         cfg = ci.custom("flat_inf", *dims, dtype=dtype, dist="normal", seed=9)
         img0, flt = ci.make_inputs(cfg)
         _, _, K, W, H, R, S, sw, sh = dims
