@@ -154,6 +154,12 @@ _lib.cacnn_probe_mfma_and_fill_on.argtypes = [ctypes.c_int32, ctypes.c_int32, ct
                                               ctypes.c_size_t, ctypes.c_void_p, ctypes.c_int32, ctypes.c_int32, ctypes.c_void_p]
 _lib.cacnn_probe_copy.restype = ctypes.c_int
 _lib.cacnn_probe_copy.argtypes = [ctypes.c_void_p, ctypes.c_void_p, ctypes.c_size_t, ctypes.c_void_p]
+_lib.cacnn_internal_conv_forward_sized.restype = ctypes.c_int
+_lib.cacnn_internal_conv_forward_sized.argtypes = [ctypes.POINTER(Problem), ctypes.c_int] + [ctypes.c_void_p, ctypes.c_int64] * 3 + \
+    [ctypes.c_void_p]
+_lib.cacnn_internal_pool_forward_sized.restype = ctypes.c_int
+_lib.cacnn_internal_pool_forward_sized.argtypes = [ctypes.POINTER(Problem), ctypes.c_int, ctypes.c_int] + \
+    [ctypes.c_void_p, ctypes.c_int64] * 2 + [ctypes.c_void_p]
 _lib.cacnn_variant_count.restype = ctypes.c_int
 _lib.cacnn_variant_name.restype = ctypes.c_char_p
 _lib.cacnn_variant_name.argtypes = [ctypes.c_int]
@@ -199,6 +205,10 @@ def cacnn_tile_plan(problem, dtype: int, machine: Optional[Machine] = None) -> P
     return out
 
 
+_Tensor, _float32 = torch.Tensor, torch.float32
+_ESIZE = {CACNN_F32: 4, CACNN_BF16_F32ACC: 2}
+
+
 def _ptr(t) -> int:
     """Device address of a torch tensor (or a plain int address)."""
     if isinstance(t, int):
@@ -230,9 +240,15 @@ def _check_operands(where: str, problem: Problem, dtype: int, image, filt, out, 
             raise ValueError(f"{where}: {name} holds {t.numel()} elements, the problem needs {numel}")
 
 
+# torch.cuda.current_stream() makes a Python object of the handle, 3 us a call; this pair of calls asks for the handle alone (0.2 us)
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+_device = getattr(torch._C, "_cuda_getDevice", None)
+
+
 def _stream_handle(stream) -> int:
     if stream is None:
-        import torch
+        if _raw_stream is not None and _device is not None and torch.cuda.is_initialized():
+            return _raw_stream(_device())
         return int(torch.cuda.current_stream().cuda_stream)
     if isinstance(stream, int):
         return stream
@@ -242,6 +258,15 @@ def _stream_handle(stream) -> int:
 def cacnn_conv_forward(problem, dtype: int, image, filt, out, stream=None) -> None:
     """Enqueue Out = conv(Image, Filter) on `stream` (torch stream, raw handle, or None = torch's current stream).
     image/filt/out are device tensors laid out Image[IW,IH,C,B], Filter[K,R,S,C], Out[K,H,W,B] (fp32)."""
+    # The usual call: contiguous device tensors of the right element sizes.  Their lengths are checked by the library, which
+    # enqueues nothing if it finds fault with the call; then, and for every other kind of operand, the checks below
+    # tell what is wrong (17 comparisons and products in the interpreter took as long as the launch).
+    if type(problem) is Problem and type(image) is type(filt) is type(out) is _Tensor and image.is_cuda and filt.is_cuda and out.is_cuda \
+            and out.dtype is _float32 and image.element_size() == filt.element_size() == _ESIZE.get(dtype) \
+            and image.is_contiguous() and filt.is_contiguous() and out.is_contiguous():
+        if _lib.cacnn_internal_conv_forward_sized(ctypes.byref(problem), dtype, image.data_ptr(), image.numel(), filt.data_ptr(),
+                                                  filt.numel(), out.data_ptr(), out.numel(), _stream_handle(stream)) == 0:
+            return
     prob = _as_problem(problem)
     _check_operands("cacnn_conv_forward", prob, dtype, image, filt, out)
     rc = _lib.cacnn_conv_forward(ctypes.byref(prob), int(dtype), _ptr(image), _ptr(filt), _ptr(out),
@@ -326,6 +351,12 @@ def cacnn_pool_lower_bound(problem, M_words: float) -> PoolBound:
 
 def cacnn_pool_forward(problem, dtype: int, mode: int, image, out, stream=None) -> None:
     """Enqueue per-channel average (mode 0) or max (mode 1) pooling of Image[IW,IH,C,B] into Out[K=C,H,W,B] (fp32)."""
+    # (as in cacnn_conv_forward)
+    if type(problem) is Problem and type(image) is type(out) is _Tensor and image.is_cuda and out.is_cuda and out.dtype is _float32 \
+            and image.element_size() == _ESIZE.get(dtype) and image.is_contiguous() and out.is_contiguous():
+        if _lib.cacnn_internal_pool_forward_sized(ctypes.byref(problem), dtype, int(mode), image.data_ptr(), image.numel(),
+                                                  out.data_ptr(), out.numel(), _stream_handle(stream)) == 0:
+            return
     _check_operands("cacnn_pool_forward", _as_problem(problem), dtype, image, None, out, pooling=True)
     rc = _lib.cacnn_pool_forward(ctypes.byref(_as_problem(problem)), int(dtype), int(mode), _ptr(image), _ptr(out),
                                  _stream_handle(stream))

@@ -948,26 +948,53 @@ bool tile_list_in_range(const cacnn_problem& p, const VariantInfo& v, int walk, 
     return walk != 1 || split_k < 1 || n * (n / tk) < 4294967296.0;
 }
 
-int launch_with(const cacnn_problem& p, int dtype, int vi, int CT, int bR, int bS, int split_k, int walk, const void* image,
-                const void* filter, void* out, void* stream) {
+// A launch of one of the two kinds of kernels but for its three pointers: everything that depends on the problem, the
+// kernel and the operands' alignment alone.
+struct Launch {
+    const Variant* tiled = nullptr;
+    const FlatVariant* flat = nullptr;
+    KernelArgs a;
+    FlatArgs f;
+    int grid = 0;
+    size_t lds = 0;
+};
+
+bool pointers_legal(int dtype, const void* image, const void* filter, const void* out) {
+    const uintptr_t mask = dtype == CACNN_F32 ? 3 : 1;
+    return ((reinterpret_cast<uintptr_t>(image) | reinterpret_cast<uintptr_t>(filter)) & mask) == 0 && reinterpret_cast<uintptr_t>(out) % 4 == 0;
+}
+
+bool aligned16(const void* p) { return reinterpret_cast<uintptr_t>(p) % 16 == 0; }
+
+int fire(Launch& l, const void* image, const void* filter, void* out, void* stream) {
+    if (!have_device()) return CACNN_ERR_NO_DEVICE;
+    int rc;
+    if (l.flat) {
+        l.f.image = image;
+        l.f.filter = filter;
+        l.f.out = (float*)out;
+        rc = l.flat->launch(l.f, l.grid, stream);
+    } else {
+        l.a.image = image;
+        l.a.filter = filter;
+        l.a.out = (float*)out;
+        rc = l.tiled->launch(l.a, l.grid, l.lds, stream);
+    }
+    return rc == 0 ? CACNN_OK : CACNN_ERR_LAUNCH;
+}
+
+int prepare_tiled(const cacnn_problem& p, int dtype, int vi, int CT, int bR, int bS, int split_k, int walk, bool aligned_img,
+                  bool aligned_flt, Launch* out) {
     const Variant& var = variant(vi);
     const VariantInfo& v = var.info;
-    const bool aligned_img = (reinterpret_cast<uintptr_t>(image) % 16) == 0;
-    const bool aligned_flt = (reinterpret_cast<uintptr_t>(filter) % 16) == 0;
     const size_t esz = dtype == CACNN_F32 ? 4 : 2;
-    if (reinterpret_cast<uintptr_t>(image) % esz || reinterpret_cast<uintptr_t>(filter) % esz ||
-        reinterpret_cast<uintptr_t>(out) % 4)
-        return CACNN_ERR_INVALID_ARG;
     const bool vimg = vec_img_ok(v, p) && aligned_img;
     const Geometry g = make_geometry(v, p, CT, bR, bS, vimg);
     if (!g.legal || g.lds_bytes > 160 * 1024 || g.lds_bytes < 1) return CACNN_ERR_UNSUPPORTED;
     if (v.pipelined && !aligned_flt && !g.flt_resident) return CACNN_ERR_UNSUPPORTED;
 
-    KernelArgs a;
+    KernelArgs& a = out->a;
     std::memset(&a, 0, sizeof(a));
-    a.image = image;
-    a.filter = filter;
-    a.out = (float*)out;
     a.B = (int32_t)p.B;
     a.C = (int32_t)p.C;
     a.K = (int32_t)p.K;
@@ -1054,9 +1081,19 @@ int launch_with(const cacnn_problem& p, int dtype, int vi, int CT, int bR, int b
     a.flt_buf = g.flt_buf;
     a.flt_off = g.flt_off;
     a.flt_resident = g.flt_resident;
-    grid = launch_grid(v, g, grid, kDefaultMachine);
-    if (!have_device()) return CACNN_ERR_NO_DEVICE;
-    return var.launch(a, (int)grid, (size_t)g.lds_bytes, stream) == 0 ? CACNN_OK : CACNN_ERR_LAUNCH;
+    out->tiled = &var;
+    out->flat = nullptr;
+    out->grid = (int)launch_grid(v, g, grid, kDefaultMachine);
+    out->lds = (size_t)g.lds_bytes;
+    return CACNN_OK;
+}
+
+int launch_with(const cacnn_problem& p, int dtype, int vi, int CT, int bR, int bS, int split_k, int walk, const void* image,
+                const void* filter, void* out, void* stream) {
+    if (!pointers_legal(dtype, image, filter, out)) return CACNN_ERR_INVALID_ARG;
+    Launch l;
+    const int rc = prepare_tiled(p, dtype, vi, CT, bR, bS, split_k, walk, aligned16(image), aligned16(filter), &l);
+    return rc != CACNN_OK ? rc : fire(l, image, filter, out, stream);
 }
 
 // ------------------------------------------------------------------------------------------------------------
@@ -1154,21 +1191,16 @@ int choose_flat(const cacnn_problem& p, int dtype, double* us) {
     return best;
 }
 
-int launch_flat(const cacnn_problem& p, int dtype, int fi, const void* image, const void* filter, void* out, void* stream) {
+int prepare_flat(const cacnn_problem& p, int dtype, int fi, Launch* out) {
     const FlatVariant& var = flat_variant(fi);
     const FlatInfo& v = var.info;
     if (!flat_fits(p, dtype, v)) return CACNN_ERR_UNSUPPORTED;
     const int esz = dtype == CACNN_F32 ? 4 : 2, ch = 16 / esz;
-    if (reinterpret_cast<uintptr_t>(image) % esz || reinterpret_cast<uintptr_t>(filter) % esz || reinterpret_cast<uintptr_t>(out) % 4)
-        return CACNN_ERR_INVALID_ARG;
     const int64_t T = p.S * p.C;
     const int64_t IW = p.sigma_w * (p.W - 1) + p.R, IH = p.sigma_h * (p.H - 1) + p.S;
     const int64_t img = IW * IH * p.C * p.B * esz, flt = p.K * p.R * T * esz;
-    FlatArgs a;
+    FlatArgs& a = out->f;
     std::memset(&a, 0, sizeof(a));
-    a.image = image;
-    a.filter = filter;
-    a.out = (float*)out;
     a.N = (uint32_t)(p.H * p.W * p.B);
     a.K = (uint32_t)p.K;
     a.B = (uint32_t)p.B;
@@ -1205,22 +1237,31 @@ int launch_flat(const cacnn_problem& p, int dtype, int fi, const void* image, co
     a.d_W = make_flatdiv((uint32_t)p.W);
     a.d_TC = make_flatdiv(a.TC);
     a.d_inner = make_flatdiv(a.inner);
-    if (!have_device()) return CACNN_ERR_NO_DEVICE;
-    return var.launch(a, (int)grid, stream) == 0 ? CACNN_OK : CACNN_ERR_LAUNCH;
+    out->flat = &var;
+    out->tiled = nullptr;
+    out->grid = (int)grid;
+    return CACNN_OK;
 }
 
-// plan cache of cacnn_conv_forward, keyed by (problem, dtype | misaligned << 8); flat >= 0: that kernel with flattened
-// positions is launched instead of the plan's variant
-struct Route {
-    cacnn_plan plan;
-    int flat;
-};
+int launch_flat(const cacnn_problem& p, int dtype, int fi, const void* image, const void* filter, void* out, void* stream) {
+    if (!pointers_legal(dtype, image, filter, out)) return CACNN_ERR_INVALID_ARG;
+    Launch l;
+    const int rc = prepare_flat(p, dtype, fi, &l);
+    return rc != CACNN_OK ? rc : fire(l, image, filter, out, stream);
+}
+
+// Launch cache of cacnn_conv_forward, keyed by (problem, dtype, alignment of the two operands): planning costs tens of
+// microseconds and laying out a launch one, the launch itself two.  What is kept depends on the key alone, not on the buffers.
 struct PlanEntry {
     cacnn_problem p;
     int key;
-    Route route;
+    Launch launch;
 };
 std::vector<PlanEntry> g_plans;
+
+int launch_key(int dtype, const void* image, const void* filter) {
+    return dtype | (aligned16(image) ? 0 : 0x100) | (aligned16(filter) ? 0 : 0x200);
+}
 
 // What cacnn_conv_forward launches: the planned variant or a kernel with flattened positions.  A generic variant always
 // gives way to a flattened kernel that takes the problem: on 104 layers of all sizes whose plan was a generic variant the
@@ -1228,39 +1269,42 @@ std::vector<PlanEntry> g_plans;
 // a measurement, gives way where the flattened kernel is estimated to take less than 0.7 of its time: on 60 such layers
 // the flattened kernel was 1.2 to 4 times faster below that line (layers that leave most compute units idle, taps of large
 // filters), and between it and the break-even both sides won, by up to 1.5 times (1.27 for the fixed-geometry ones).
-int plan_route(const cacnn_problem& p, int dtype, bool aligned, Route* out) {
+int plan_route(const cacnn_problem& p, int dtype, bool aligned_img, bool aligned_flt, Launch* out) {
     double tiled_us = 0.0, flat_est = 0.0;
-    const int rc = plan_impl(&p, dtype, nullptr, &out->plan, aligned, &tiled_us);
-    out->flat = -1;
-    if (rc != CACNN_OK || planner_uses_lp()) return rc;
-    const int fi = choose_flat(p, dtype, &flat_est);
-    // (a call whose plan cannot be launched is refused, as it would be without the flattened kernels)
-    const VariantInfo& v = variant(out->plan.variant).info;
-    if (fi >= 0 && tile_list_in_range(p, v, out->plan.xcd_walk, out->plan.xcd_split_k) &&
-        (v.fx_ct == 0 || flat_est < 0.7 * (with_copy_time(tiled_us - 2.2, p, dtype) + 2.2)))
-        out->flat = fi;
-    return rc;
+    // the pipelined kernels need 16-byte aligned operands; a misaligned call is planned without them
+    cacnn_plan plan;
+    const int rc = plan_impl(&p, dtype, nullptr, &plan, aligned_img && aligned_flt, &tiled_us);
+    if (rc != CACNN_OK) return rc;
+    if (!planner_uses_lp()) {
+        const int fi = choose_flat(p, dtype, &flat_est);
+        // (a call whose plan cannot be launched is refused, as it would be without the flattened kernels)
+        const VariantInfo& v = variant(plan.variant).info;
+        if (fi >= 0 && tile_list_in_range(p, v, plan.xcd_walk, plan.xcd_split_k) &&
+            (v.fx_ct == 0 || flat_est < 0.7 * (with_copy_time(tiled_us - 2.2, p, dtype) + 2.2)))
+            return prepare_flat(p, dtype, fi, out);
+    }
+    return prepare_tiled(p, dtype, plan.variant, plan.b_c, plan.b_r, plan.b_s, plan.xcd_split_k, plan.xcd_walk, aligned_img, aligned_flt, out);
 }
 
-bool lookup_plan(const cacnn_problem& p, int key, Route* out) {
+bool lookup_plan(const cacnn_problem& p, int key, Launch* out) {
     std::lock_guard<std::mutex> lock(g_mutex);
     for (const PlanEntry& e : g_plans)
         if (e.key == key && std::memcmp(&e.p, &p, sizeof(cacnn_problem)) == 0) {
-            *out = e.route;
+            *out = e.launch;
             return true;
         }
     return false;
 }
 
-void store_plan(const cacnn_problem& p, int key, const Route& route) {
+void store_plan(const cacnn_problem& p, int key, const Launch& launch) {
     std::lock_guard<std::mutex> lock(g_mutex);
     for (PlanEntry& e : g_plans)
         if (e.key == key && std::memcmp(&e.p, &p, sizeof(cacnn_problem)) == 0) {
-            e.route = route;
+            e.launch = launch;
             return;
         }
     if (g_plans.size() >= 64) g_plans.erase(g_plans.begin());
-    g_plans.push_back(PlanEntry{p, key, route});
+    g_plans.push_back(PlanEntry{p, key, launch});
 }
 
 }  // namespace
@@ -1282,20 +1326,15 @@ int cacnn_conv_forward(const cacnn_problem* problem, int dtype, const void* imag
                        void* hip_stream) {
     if (!problem || !image || !filter || !out) return CACNN_ERR_NULL;
     if (dtype != CACNN_F32 && dtype != CACNN_BF16_F32ACC) return CACNN_ERR_UNSUPPORTED;
-    // plans are cached per (problem, dtype): planning costs tens of microseconds, a launch a few.
-    // The pipelined kernels need 16-byte aligned operands; a misaligned call is planned without them.
-    const bool aligned = reinterpret_cast<uintptr_t>(image) % 16 == 0 && reinterpret_cast<uintptr_t>(filter) % 16 == 0;
-    const int key = dtype | (aligned ? 0 : 0x100);
-    Route route;
-    if (!lookup_plan(*problem, key, &route)) {
-        const int rc = plan_route(*problem, dtype, aligned, &route);
+    const int key = launch_key(dtype, image, filter);
+    Launch launch;
+    if (!lookup_plan(*problem, key, &launch)) {
+        const int rc = plan_route(*problem, dtype, aligned16(image), aligned16(filter), &launch);
         if (rc != CACNN_OK) return rc;
-        store_plan(*problem, key, route);
+        store_plan(*problem, key, launch);
     }
-    if (route.flat >= 0) return launch_flat(*problem, dtype, route.flat, image, filter, out, hip_stream);
-    const cacnn_plan& plan = route.plan;
-    return launch_with(*problem, dtype, plan.variant, plan.b_c, plan.b_r, plan.b_s, plan.xcd_split_k, plan.xcd_walk, image, filter, out,
-                       hip_stream);
+    if (!pointers_legal(dtype, image, filter, out)) return CACNN_ERR_INVALID_ARG;
+    return fire(launch, image, filter, out, hip_stream);
 }
 
 int cacnn_conv_forward_with_plan(const cacnn_problem* problem, int dtype, const cacnn_plan* plan, const void* image,
@@ -1376,8 +1415,8 @@ int cacnn_tune(const cacnn_problem* problem, int dtype, const void* image, const
         if (vrc != CACNN_OK) return vrc;
     }
     if (!have_device()) return CACNN_ERR_NO_DEVICE;
-    const bool aligned = reinterpret_cast<uintptr_t>(image) % 16 == 0 && reinterpret_cast<uintptr_t>(filter) % 16 == 0;
-    const int key = dtype | (aligned ? 0 : 0x100);
+    const bool aligned = aligned16(image) && aligned16(filter);
+    const int key = launch_key(dtype, image, filter);
     hipStream_t stream = (hipStream_t)hip_stream;
     hipEvent_t e0, e1;
     if (hipEventCreate(&e0) != hipSuccess) return CACNN_ERR_LAUNCH;
@@ -1432,7 +1471,12 @@ int cacnn_tune(const cacnn_problem* problem, int dtype, const void* image, const
     cacnn_plan plan;
     const int rc = fill_plan(*problem, dtype, kDefaultMachine, best, &plan);
     if (rc != CACNN_OK) return rc;
-    store_plan(*problem, key, Route{plan, flat});
+    Launch launch;
+    const int lrc = flat >= 0 ? prepare_flat(*problem, dtype, flat, &launch)
+                              : prepare_tiled(*problem, dtype, plan.variant, plan.b_c, plan.b_r, plan.b_s, plan.xcd_split_k, plan.xcd_walk,
+                                              aligned16(image), aligned16(filter), &launch);
+    if (lrc != CACNN_OK) return lrc;
+    store_plan(*problem, key, launch);
     if (out_plan) *out_plan = plan;
     return CACNN_OK;
 }
@@ -1717,6 +1761,23 @@ int cacnn_closed_form_tiling(const cacnn_problem* p, double M, cacnn_closed_form
     return CACNN_OK;
 }
 
+// The two calls for the binding's tensors: element counts instead of a check in the interpreter.  CACNN_ERR_INVALID_ARG if a buffer
+// is shorter than the problem needs (nothing is enqueued).
+static bool holds(const cacnn_problem& p, int64_t image_elems, int64_t filter_elems, int64_t out_elems) {
+    if (!valid_problem(&p) || validate_dims(p) != CACNN_OK) return false;
+    return image_elems >= (p.sigma_w * (p.W - 1) + p.R) * (p.sigma_h * (p.H - 1) + p.S) * p.C * p.B &&
+           filter_elems >= p.K * p.R * p.S * p.C && out_elems >= p.K * p.H * p.W * p.B;
+}
+int cacnn_internal_conv_forward_sized(const cacnn_problem* problem, int dtype, const void* image, int64_t image_elems, const void* filter,
+                                      int64_t filter_elems, void* out, int64_t out_elems, void* hip_stream) {
+    if (!problem || !holds(*problem, image_elems, filter_elems, out_elems)) return CACNN_ERR_INVALID_ARG;
+    return cacnn_conv_forward(problem, dtype, image, filter, out, hip_stream);
+}
+int cacnn_internal_pool_forward_sized(const cacnn_problem* problem, int dtype, int mode, const void* image, int64_t image_elems, void* out,
+                                      int64_t out_elems, void* hip_stream) {
+    if (!problem || problem->K != problem->C || !holds(*problem, image_elems, INT64_MAX, out_elems)) return CACNN_ERR_INVALID_ARG;
+    return cacnn_pool_forward(problem, dtype, mode, image, out, hip_stream);
+}
 int cacnn_internal_flat_count(void) { return num_flat(); }
 int cacnn_internal_flat_info(int i, int32_t* eight) {
     if (i < 0 || i >= num_flat() || !eight) return CACNN_ERR_INVALID_ARG;

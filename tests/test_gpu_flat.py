@@ -121,3 +121,31 @@ def test_nonfinite_inputs_stay_local_in_flat_kernels(env, dtype, c):
                     if 0 <= x - sw * w < R and 0 <= y - sh * h < S:
                         want[:, h, w, b] = True
             assert np.array_equal(~np.isfinite(out), want), (index, (x, y, ch, b))
+
+
+def test_binding_refuses_short_device_tensors_and_uses_the_current_stream(env):
+    """The binding leaves the length check of ordinary device tensors to the library: a buffer one element short is refused with the
+    same error as before, before anything is enqueued, and a call without a stream goes to torch's current one."""
+    cc, torch, _ = env
+    cfg = ci.custom("binding", 4, 8, 8, 3, 3, 1, 1, dtype="f32", dist="normal", seed=5)
+    img, flt = ci.make_inputs(cfg)
+    d_img, d_flt = gu.upload(cfg, img, flt, torch)
+    n = int(np.prod(cfg.out_shape))
+    prob, out = cc.Problem(*cfg.dims), torch.full((n,), -7.0, device="cuda:0")
+    for args in ((d_img[:-1], d_flt, out), (d_img, d_flt[:-1], out), (d_img, d_flt, out[:-1]), (d_img.to(torch.float16), d_flt, out)):
+        with pytest.raises(ValueError):
+            cc.cacnn_conv_forward(prob, 0, *args)
+    pool = cc.Problem(4, 8, 8, 3, 3, 1, 1, 1, 1)
+    with pytest.raises(ValueError):
+        cc.cacnn_pool_forward(pool, 0, 1, d_img, out[:n - 1])
+    torch.cuda.synchronize()
+    assert bool((out == -7.0).all())
+    side, first = torch.cuda.Stream(), torch.full((n,), float("nan"), device="cuda:0")
+    torch.cuda.synchronize()
+    with torch.cuda.stream(side):
+        torch.cuda._sleep(2000000)                    # a millisecond of work that the call has to wait behind on its own stream
+        cc.cacnn_conv_forward(prob, 0, d_img, d_flt, first)
+        assert not side.query()
+    side.synchronize()
+    ref, ab = gu.oracle_full(cfg, img, flt)
+    check(cfg, first.cpu().numpy().reshape(cfg.out_shape), ref, ab, "side stream")
