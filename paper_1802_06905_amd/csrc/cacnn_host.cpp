@@ -1600,9 +1600,10 @@ int cacnn_pool_forward(const cacnn_problem* problem, int dtype, int mode, const 
     const size_t esz = dtype == CACNN_F32 ? 4 : 2;
     if (reinterpret_cast<uintptr_t>(image) % esz || reinterpret_cast<uintptr_t>(out) % 4) return CACNN_ERR_INVALID_ARG;
     const int full = dtype == CACNN_F32 ? 4 : 8;
-    const bool wide = p.B % full == 0 && reinterpret_cast<uintptr_t>(image) % 16 == 0 &&
-                      reinterpret_cast<uintptr_t>(out) % 16 == 0;
-    const int vec = wide ? full : 1;
+    // images per thread: as many as one load takes (16 bytes) or the largest power of two below that divides B
+    int vec = full;
+    while (vec > 1 && (p.B % vec || reinterpret_cast<uintptr_t>(image) % (vec * esz) || reinterpret_cast<uintptr_t>(out) % std::min(16, vec * 4)))
+        vec /= 2;
     PoolArgs a;
     std::memset(&a, 0, sizeof(a));
     a.image = image;
@@ -1621,14 +1622,18 @@ int cacnn_pool_forward(const cacnn_problem* problem, int dtype, int mode, const 
     a.TWC = (int32_t)ceil_div(p.W, a.n_xcd);              // one band of output columns per XCD
     const int64_t chunks = ceil_div(p.W, a.TWC);
     int64_t n = 0;
-    if (!mul_check(p.H, chunks * a.TWC, INT32_MAX, &n) || !mul_check(n, p.C, INT32_MAX, &n) ||
-        !mul_check(n, a.BV, INT32_MAX, &n))
+    // The reciprocal divisions in the kernel are exact while dividend * divisor < 2^32.  The limit is that of a thread per
+    // 16-byte load, or per image where those do not divide B, whatever the images per thread are.
+    const int64_t groups = vec == full ? p.B / full : p.B;
+    if (!mul_check(p.H, chunks * a.TWC, INT32_MAX, &n) || !mul_check(n, p.C, INT32_MAX, &n) || !mul_check(n, groups, INT32_MAX, &n) ||
+        (double)n * (double)std::max<int64_t>(std::max<int64_t>(groups, p.C), std::max<int64_t>(p.H, 64)) >= 4294967296.0)
         return CACNN_ERR_INVALID_ARG;
+    n = n / groups * a.BV;
     a.n_threads = (int32_t)n;
     a.n_wg = (int32_t)ceil_div(n, 256);
-    // the reciprocal divisions in the kernel are exact while dividend * divisor < 2^32
-    if ((double)n * (double)std::max<int64_t>(std::max<int64_t>(a.BV, p.C), std::max<int64_t>(p.H, 64)) >= 4294967296.0)
-        return CACNN_ERR_INVALID_ARG;
+    const double img_bytes = (double)(p.sigma_w * (p.W - 1) + p.R) * (double)(p.sigma_h * (p.H - 1) + p.S) * (double)p.C * (double)p.B * (double)esz;
+    a.img_bytes = img_bytes < 2147483648.0 ? (int32_t)img_bytes : 0;
+    a.stream = p.B % 32 == 0;
     a.xcd_q = a.n_wg / a.n_xcd;
     a.xcd_rem = a.n_wg % a.n_xcd;
     a.d_BV = make_fastdiv((uint32_t)a.BV);

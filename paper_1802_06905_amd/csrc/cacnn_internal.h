@@ -166,9 +166,11 @@ struct PoolArgs {
     int32_t TWC;              // output columns per chunk (the last chunk may overhang W)
     int32_t n_threads;        // chunks * H * TWC * C * BV
     int32_t n_wg, n_xcd, xcd_q, xcd_rem;   // workgroups, and the XCD remapping of their order
+    int32_t img_bytes;        // size of the Image; 0: 2 GiB or more
+    int32_t stream;           // 1: Out is stored past the caches
     FastDiv d_BV, d_C, d_TWC, d_H, d_nxcd;
 };
-// dtype: cacnn_dtype; mode: cacnn_pool_mode; vec: images per thread (1, or 4 for fp32 / 8 for bf16). 0 = launched.
+// dtype: cacnn_dtype; mode: cacnn_pool_mode; vec: images per thread (1, 2, 4, bf16 also 8). 0 = launched.
 int launch_pool(const PoolArgs& a, int dtype, int mode, int vec, void* stream);
 
 // Measurement kernels (cacnn_probe.hip).  0 = launched.
