@@ -393,8 +393,9 @@ static int launch_flat_shape(const FlatArgs& a, int grid, void* stream) {
 
 // ---------------------------------------------------------------------------------------------------------------
 // The same product with both operands staged in LDS, NCH chunks of the contraction at a time.  Loads go through registers
-// (16-byte loads at any element alignment, zeroed where a chunk is shorter) two stages ahead.  The steps of a stage are not
-// written out a second time for the last, shorter stage: the larger code was 3 to 5 % slower on launches of 3 to 30 us.
+// (16-byte loads at any element alignment, zeroed where a chunk is shorter) two stages ahead.  A stage always multiplies
+// all of its steps, the zeros of a last, shorter one included: a way out between the steps kept the compiler from reading
+// ahead (4 to 8 % of the time), and a second copy of the steps for whole stages cost as much in code as it gained.
 // IM > 0: the tile's columns are groups of IM adjacent images; LDS holds one row of columns per contraction index.
 // IM < 0: the columns are positions with all of their -IM images; LDS holds a position's chunks as they lie in memory.
 template <int DT, int MB, int NBW, int IM, int WM, int WN, int WK, int NCH>
@@ -594,68 +595,80 @@ __global__ void __launch_bounds__(WM* WN* WK * 64) conv_flat_lds_kernel(const Fl
 #pragma unroll
             for (int v = 0; v < 16; ++v) acc[m][n][v] = 0.f;
     const int i16 = lane & 15, jhalf = (lane >> 4) & 1;
-    auto multiply = [&](const char* buf, uint32_t chunks) {
+    auto read_step = [&](const char* buf, int st, fu32x4 (&av)[MB], fu32x4 (&bv)[NB]) {
         const char* const ap = buf + ((wm * MB * 32 + j) * GEO::FP + g) * 16;
         const char* const img = buf + GEO::FLT_BYTES;
 #pragma unroll
-        for (int s = 0; s < GEO::STEPS; ++s) {
-            const int st = s * WK + wk;                // (steps dealt in turns: a last stage of few chunks keeps all waves busy)
-            if ((uint32_t)(2 * st) >= chunks) break;
-            fu32x4 av[MB], bv[NB];
+                    for (int m = 0; m < MB; ++m) av[m] = *(const fu32x4*)(ap + m * 32 * GEO::FP * 16 + st * 32);
+                    if constexpr (RUN) {
 #pragma unroll
-            for (int m = 0; m < MB; ++m) av[m] = *(const fu32x4*)(ap + m * 32 * GEO::FP * 16 + st * 32);
-            if constexpr (RUN) {
+                        for (int p = 0; p < NBW; ++p) {
+                            const char* const xp = img + ((wn * NBW + p) * 32 + j) * GEO::ROW + (2 * st + g) * IPL * 16;
+                            fu32x4 x[IPL];
 #pragma unroll
-                for (int p = 0; p < NBW; ++p) {
-                    const char* const xp = img + ((wn * NBW + p) * 32 + j) * GEO::ROW + (2 * st + g) * IPL * 16;
-                    fu32x4 x[IPL];
+                            for (int e = 0; e < IPL; ++e) x[e] = *(const fu32x4*)(xp + e * 16);
 #pragma unroll
-                    for (int e = 0; e < IPL; ++e) x[e] = *(const fu32x4*)(xp + e * 16);
+                            for (int q = 0; q < IPL; ++q)
 #pragma unroll
-                    for (int q = 0; q < IPL; ++q)
-#pragma unroll
-                        for (int i = 0; i < 4; ++i) {
-                            if constexpr (DT == 0) {
-                                bv[p * IPL + q][i] = x[(i * IPL + q) / 4][(i * IPL + q) % 4];
-                            } else {
-                                const int e0 = 2 * i * IPL + q, e1 = e0 + IPL;
-                                bv[p * IPL + q][i] = IPL == 1 ? x[0][i]
-                                                              : __builtin_amdgcn_perm(x[e1 / 8][e1 / 2 % 4], x[e0 / 8][e0 / 2 % 4],
-                                                                                      (e1 & 1 ? 0x07060000u : 0x05040000u) | (e0 & 1 ? 0x0302u : 0x0100u));
-                            }
+                                for (int i = 0; i < 4; ++i) {
+                                    if constexpr (DT == 0) {
+                                        bv[p * IPL + q][i] = x[(i * IPL + q) / 4][(i * IPL + q) % 4];
+                                    } else {
+                                        const int e0 = 2 * i * IPL + q, e1 = e0 + IPL;
+                                        bv[p * IPL + q][i] = IPL == 1 ? x[0][i]
+                                                                      : __builtin_amdgcn_perm(x[e1 / 8][e1 / 2 % 4], x[e0 / 8][e0 / 2 % 4],
+                                                                                              (e1 & 1 ? 0x07060000u : 0x05040000u) | (e0 & 1 ? 0x0302u : 0x0100u));
+                                    }
+                                }
                         }
-                }
-            } else if constexpr (DT == 0) {
-                const char* const xp = img + (2 * st + g) * CH * GEO::ROW + (wn * NBW * 32 + j) * 4;
-#pragma unroll
-                for (int n = 0; n < NB; ++n)
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) bv[n][e] = *(const uint32_t*)(xp + e * GEO::ROW + n * 128);
-            } else {
-                // the transposing read: four rows (contraction indices) of 16 columns to a lane per column
-                const char* const xp = img + (16 * st + 8 * g + (i16 >> 2)) * GEO::ROW + wn * NBW * 64 + jhalf * 32 + (i16 & 3) * 8;
-#pragma unroll
-                for (int n = 0; n < NB; ++n) {
-                    const fs16x4 l = __builtin_amdgcn_ds_read_tr16_b64_v4i16((FLAT_LDS(fs16x4)*)(xp + n * 64));
-                    const fs16x4 h = __builtin_amdgcn_ds_read_tr16_b64_v4i16((FLAT_LDS(fs16x4)*)(xp + 4 * GEO::ROW + n * 64));
-                    bv[n] = __builtin_bit_cast(fu32x4, __builtin_shufflevector(l, h, 0, 1, 2, 3, 4, 5, 6, 7));
-                }
-            }
-            if constexpr (DT == 0) {
-#pragma unroll
-                for (int e = 0; e < 4; ++e)
-#pragma unroll
-                    for (int m = 0; m < MB; ++m)
+                    } else if constexpr (DT == 0) {
+                        const char* const xp = img + (2 * st + g) * CH * GEO::ROW + (wn * NBW * 32 + j) * 4;
 #pragma unroll
                         for (int n = 0; n < NB; ++n)
-                            acc[m][n] = __builtin_amdgcn_mfma_f32_32x32x2f32(__uint_as_float(av[m][e]), __uint_as_float(bv[n][e]), acc[m][n], 0, 0, 0);
-            } else {
 #pragma unroll
-                for (int m = 0; m < MB; ++m)
+                            for (int e = 0; e < 4; ++e) bv[n][e] = *(const uint32_t*)(xp + e * GEO::ROW + n * 128);
+                    } else {
+                        // the transposing read: four rows (contraction indices) of 16 columns to a lane per column
+                        const char* const xp = img + (16 * st + 8 * g + (i16 >> 2)) * GEO::ROW + wn * NBW * 64 + jhalf * 32 + (i16 & 3) * 8;
 #pragma unroll
-                    for (int n = 0; n < NB; ++n)
-                        acc[m][n] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(fbf16x8, av[m]), __builtin_bit_cast(fbf16x8, bv[n]), acc[m][n], 0, 0, 0);
-            }
+                        for (int n = 0; n < NB; ++n) {
+                            const fs16x4 l = __builtin_amdgcn_ds_read_tr16_b64_v4i16((FLAT_LDS(fs16x4)*)(xp + n * 64));
+                            const fs16x4 h = __builtin_amdgcn_ds_read_tr16_b64_v4i16((FLAT_LDS(fs16x4)*)(xp + 4 * GEO::ROW + n * 64));
+                            bv[n] = __builtin_bit_cast(fu32x4, __builtin_shufflevector(l, h, 0, 1, 2, 3, 4, 5, 6, 7));
+                        }
+                    }
+    };
+    auto mfma_step = [&](const fu32x4 (&av)[MB], const fu32x4 (&bv)[NB]) {
+                    if constexpr (DT == 0) {
+#pragma unroll
+                        for (int e = 0; e < 4; ++e)
+#pragma unroll
+                            for (int m = 0; m < MB; ++m)
+#pragma unroll
+                                for (int n = 0; n < NB; ++n)
+                                    acc[m][n] = __builtin_amdgcn_mfma_f32_32x32x2f32(__uint_as_float(av[m][e]), __uint_as_float(bv[n][e]), acc[m][n], 0, 0, 0);
+                    } else {
+#pragma unroll
+                        for (int m = 0; m < MB; ++m)
+#pragma unroll
+                            for (int n = 0; n < NB; ++n)
+                                acc[m][n] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(fbf16x8, av[m]), __builtin_bit_cast(fbf16x8, bv[n]), acc[m][n], 0, 0, 0);
+                    }
+    };
+    // The operands of AHEAD steps are read before the first of their products: left alone, the compiler reads a step's operands
+    // right in front of its products and waits for them every time.
+    constexpr int FIT = 32 / ((MB + NB) * 4), AHEAD = FIT < 1 ? 1 : FIT < GEO::STEPS ? FIT : GEO::STEPS;
+    auto multiply = [&](const char* buf) {
+#pragma unroll
+        for (int s0 = 0; s0 < GEO::STEPS; s0 += AHEAD) {
+            fu32x4 av[AHEAD][MB], bv[AHEAD][NB];
+#pragma unroll
+            for (int s = 0; s < AHEAD; ++s)
+                if (s0 + s < GEO::STEPS) read_step(buf, (s0 + s) * WK + wk, av[s], bv[s]);
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int s = 0; s < AHEAD; ++s)
+                if (s0 + s < GEO::STEPS) mfma_step(av[s], bv[s]);
         }
     };
 
@@ -665,27 +678,42 @@ __global__ void __launch_bounds__(WM* WN* WK * 64) conv_flat_lds_kernel(const Fl
     char* const buf0 = s_mem;
     char* const buf1 = s_mem + GEO::BUF;
     const int stages = (int)((a.U + NCH - 1) / NCH);
+    auto keep_order = [] {
+        // (neither the compiler's passes nor its scheduler may move loads past this point)
+        asm volatile("" ::: "memory");
+        __builtin_amdgcn_sched_barrier(0);
+    };
     fetch(0);
-    __builtin_amdgcn_sched_barrier(0);
+    keep_order();
     fetch(1);
-    __builtin_amdgcn_sched_barrier(0);
+    keep_order();
     put(0, buf0);
-    __builtin_amdgcn_sched_barrier(0);
+    keep_order();
     fetch(0);
+    keep_order();
     __syncthreads();
-    for (int s = 0;; s += 2) {
-        multiply(buf0, a.U - (uint32_t)s * NCH);
-        if (s + 1 >= stages) break;
+    // (no way out of the middle of the loop: the compiler would count loads as if the second half could be followed by the first
+    // half's wait, and wait for the younger of the two sets there as well)
+    int s = 0;
+    for (; s + 2 < stages; s += 2) {
+        multiply(buf0);
         put(1, buf1);
-        __builtin_amdgcn_sched_barrier(0);
+        keep_order();
         fetch(1);
+        keep_order();
         __syncthreads();
-        multiply(buf1, a.U - (uint32_t)(s + 1) * NCH);
-        if (s + 2 >= stages) break;
+        multiply(buf1);
         put(0, buf0);
-        __builtin_amdgcn_sched_barrier(0);
+        keep_order();
         fetch(0);
+        keep_order();
         __syncthreads();
+    }
+    multiply(buf0);
+    if (s + 1 < stages) {
+        put(1, buf1);
+        __syncthreads();
+        multiply(buf1);
     }
 
     // ---- Out
@@ -737,8 +765,9 @@ static int launch_flat_lds(const FlatArgs& a, int grid, void* stream) {
 }
 
 // blocks of output channels, groups of images per wave; images per lane; waves along k, positions, contraction; steps ahead.
-// (The configurations that the cost estimate in cacnn_host.cpp picks from: chosen from 487 by leaving out, one after the
-// other, what made its picks on 390 layers of all sizes worse by least; the best of these is within 1.3 % of the best of all.)
+// (The configurations that the cost estimate in cacnn_host.cpp picks from: chosen from 490 by leaving out, one after the
+// other, what made its picks on 390 layers of all sizes worse by least; on 330 others the best of these is within 0.3 % of the
+// best of all that were left then.)
 #define CACNN_FLAT(DT, MB, NG, IM, WM, WN, WK, D) \
     {{DT, MB, NG, IM, WM, WN, WK, 0}, launch_flat_shape<DT, MB, NG, IM, WM, WN, WK, D>}
 
@@ -758,12 +787,16 @@ static const FlatVariant g_flat[] = {
     CACNN_FLAT_LDS(0, 1, 1, 4, 1, 1, 8, 32),
     CACNN_FLAT_LDS(0, 1, 1, 4, 1, 2, 4, 16),
     CACNN_FLAT_LDS(0, 1, 1, 4, 1, 4, 1, 8),
+    CACNN_FLAT_LDS(0, 1, 1, 4, 2, 1, 4, 16),
     CACNN_FLAT_LDS(0, 1, 1, 4, 2, 2, 1, 8),
+    CACNN_FLAT_LDS(0, 1, 1, 4, 4, 2, 1, 8),
     CACNN_FLAT_LDS(0, 1, 2, 4, 2, 2, 1, 8),
+    CACNN_FLAT_LDS(0, 2, 2, 4, 2, 2, 1, 8),
     CACNN_FLAT_LDS(0, 1, 1, -1, 1, 1, 4, 16),
     CACNN_FLAT_LDS(0, 1, 1, -1, 1, 1, 8, 32),
     CACNN_FLAT_LDS(0, 1, 1, -1, 2, 2, 1, 8),
     CACNN_FLAT_LDS(0, 1, 1, -2, 1, 1, 4, 8),
+    CACNN_FLAT_LDS(0, 1, 1, -2, 1, 1, 8, 32),
     CACNN_FLAT_LDS(0, 1, 1, -3, 1, 1, 4, 8),
     // bf16
     CACNN_FLAT(1, 1, 1, 1, 1, 1, 4, 4),
@@ -773,11 +806,15 @@ static const FlatVariant g_flat[] = {
     CACNN_FLAT(1, 1, 1, 4, 1, 1, 4, 4),
     CACNN_FLAT_LDS(1, 1, 1, 4, 1, 1, 4, 8),
     CACNN_FLAT_LDS(1, 1, 1, 4, 1, 1, 8, 32),
+    CACNN_FLAT_LDS(1, 1, 1, 4, 2, 1, 4, 16),
     CACNN_FLAT_LDS(1, 1, 1, 4, 2, 2, 1, 8),
+    CACNN_FLAT_LDS(1, 1, 2, 4, 4, 2, 1, 8),
     CACNN_FLAT_LDS(1, 1, 1, 8, 1, 1, 4, 8),
     CACNN_FLAT_LDS(1, 1, 1, 8, 1, 1, 8, 32),
     CACNN_FLAT_LDS(1, 1, 1, 8, 1, 4, 1, 8),
     CACNN_FLAT_LDS(1, 1, 1, 8, 2, 2, 1, 8),
+    CACNN_FLAT_LDS(1, 1, 1, 8, 2, 4, 1, 8),
+    CACNN_FLAT_LDS(1, 1, 1, 8, 4, 2, 1, 8),
     CACNN_FLAT_LDS(1, 1, 2, 8, 4, 2, 1, 8),
     CACNN_FLAT_LDS(1, 2, 2, 8, 2, 2, 1, 8),
     CACNN_FLAT_LDS(1, 2, 2, 8, 2, 4, 1, 8),
@@ -788,6 +825,7 @@ static const FlatVariant g_flat[] = {
     CACNN_FLAT_LDS(1, 1, 1, -2, 1, 1, 8, 32),
     CACNN_FLAT_LDS(1, 1, 1, -2, 4, 2, 1, 8),
     CACNN_FLAT_LDS(1, 1, 1, -3, 1, 1, 4, 8),
+    CACNN_FLAT_LDS(1, 1, 1, -3, 1, 1, 8, 16),
     CACNN_FLAT_LDS(1, 1, 1, -3, 4, 1, 1, 8),
     CACNN_FLAT_LDS(1, 1, 1, -4, 1, 1, 8, 16),
     CACNN_FLAT_LDS(1, 1, 1, -4, 4, 1, 1, 8),

@@ -1129,12 +1129,12 @@ bool flat_fits(const cacnn_problem& p, int dtype, const FlatInfo& v) {
 // The clocks of one 64-lane load, measured out of L1: at least 8.5 for 2 and 4 bytes a lane and 17.4 for 8 and 16 (that is
 // the 64 bytes a clock L1 delivers), else about one for each separate run of bytes; runs that are not made of four
 // neighbouring lanes cost more, and lanes whose address is no multiple of 4 bytes take about twice (8 bytes and less) to
-// three and a half times (16 bytes) as long.  The other constants are a least-squares fit to the launch times of all
-// configurations on 390 layers drawn over all sizes: there the configuration with the smallest estimate takes 1.04 times as
+// three times (16 bytes) as long.  The other constants are a least-squares fit to the launch times of all
+// configurations on 330 layers drawn over all sizes: there the configuration with the smallest estimate takes 1.04 times as
 // long as the fastest one in the geometric mean, and the estimate is within 14 % of the time (one standard deviation).
 double load_clocks(int bytes, double run_bytes, bool aligned4, bool whole_quads) {
     const double floor_clk = bytes <= 4 ? 8.5 : 17.4, run_lanes = std::max(run_bytes / bytes, 1.0);
-    const double odd = aligned4 || bytes == 2 ? 1.0 : bytes == 16 ? 3.4 : 1.9;
+    const double odd = aligned4 || bytes == 2 ? 1.0 : bytes == 16 ? 3.0 : 1.8;
     const double clk = std::max(floor_clk, std::min(64.0, 48.0 / run_lanes)) * odd;
     return whole_quads || run_lanes >= 32.0 ? clk : std::max(clk, 40.0 - run_lanes);
 }
@@ -1156,7 +1156,7 @@ double flat_us(const cacnn_problem& p, int dtype, const FlatInfo& v) {
                                  : ch * load_clocks(ipl * esz, (double)(std::min<int64_t>(p.B, 32 * ipl) * esz), img_aligned,
                                                     ipl == 4 || p.B % (4 * ipl) == 0);
         const double load = per_cu * waves * mine * (v.MB * a_clk + v.NG * b_clk);
-        const double simd = per_cu * simd_waves * mine * (blocks * mfma + 112.0), latency = (mine / 4.0 + 0.75) * 923.0;
+        const double simd = per_cu * simd_waves * mine * (blocks * mfma + 62.0), latency = (mine / 4.0 + 0.75) * 1020.0;
         clk = std::sqrt(load * load + simd * simd + latency * latency);
     } else {
         const double stages = (double)ceil_div(chunks, v.NCH), cols = v.WN * v.NG * 32, kt = v.KT();
@@ -1165,15 +1165,15 @@ double flat_us(const cacnn_problem& p, int dtype, const FlatInfo& v) {
         const double load = flt_items / 64.0 * load_clocks(16, (double)std::min<int64_t>(v.NCH * 16, T * esz), flt_aligned, true) +
                             img_items / 64.0 * (run ? load_clocks(16, (double)std::min<int64_t>(v.NCH * 16 * ipl, T * p.B * esz), img_aligned, true)
                                                     : load_clocks(ipl * esz, std::min((double)p.B, cols) * esz, img_aligned, true));
-        const double simd = simd_waves * (steps * blocks * mfma + 80.6 * (flt_items + img_items) / (64.0 * waves));
+        const double simd = simd_waves * (steps * blocks * mfma + 66.0 * (flt_items + img_items) / (64.0 * waves));
         const double lds = (flt_items + (run ? img_items : v.NCH * ch * cols * esz / 16.0)) / 4.0 + waves * steps * (v.MB + blocks / v.MB) * 10.24;
-        const double stage = std::sqrt(load * load + simd * simd + 0.048 * lds * lds);
+        const double stage = std::sqrt(load * load + simd * simd + 0.063 * lds * lds);
         const double together = std::min(per_cu, std::max(1.0, std::min(2.0, std::floor(8.0 / waves))));      // workgroups that overlap
-        const double busy = per_cu * stages * stage, latency = std::ceil(per_cu / together) * stages * 421.0;
+        const double busy = per_cu * stages * stage, latency = std::ceil(per_cu / together) * stages * 357.0;
         clk = std::sqrt(busy * busy + latency * latency) + 1000.0;
     }
-    clk += per_cu * blocks * (v.WM * v.WN * 203.0 + (v.WK > 1 ? waves * 100.0 : 0.0));                        // Out
-    return with_copy_time(clk / 2302.0, p, dtype) + 2.2;
+    clk += per_cu * blocks * (v.WM * v.WN * 200.0 + (v.WK > 1 ? waves * 110.0 : 0.0));                        // Out
+    return with_copy_time(clk / 2272.0, p, dtype) + 2.1;
 }
 
 // The flattened kernel with the smallest estimate, -1 if none takes the problem.
@@ -1280,7 +1280,7 @@ int plan_route(const cacnn_problem& p, int dtype, bool aligned_img, bool aligned
         // (a call whose plan cannot be launched is refused, as it would be without the flattened kernels)
         const VariantInfo& v = variant(plan.variant).info;
         if (fi >= 0 && tile_list_in_range(p, v, plan.xcd_walk, plan.xcd_split_k) &&
-            (v.fx_ct == 0 || flat_est < 0.7 * (with_copy_time(tiled_us - 2.2, p, dtype) + 2.2)))
+            (v.fx_ct == 0 || flat_est < 0.7 * (with_copy_time(tiled_us - 2.1, p, dtype) + 2.1)))
             return prepare_flat(p, dtype, fi, out);
     }
     return prepare_tiled(p, dtype, plan.variant, plan.b_c, plan.b_r, plan.b_s, plan.xcd_split_k, plan.xcd_walk, aligned_img, aligned_flt, out);
