@@ -79,9 +79,14 @@ __device__ __forceinline__ void pool_take(float (&acc)[VEC], const PoolWords<VEC
 // BIG: the Image is larger than the 2 GiB of a buffer descriptor; 64-bit addresses.
 // WR x WS: the window the kernel is compiled for, all of whose loads are in flight at once (0: any window, eight loads
 // at a time).  One load takes the address unit as long whether a lane asks for 2 bytes or 4, and twice as long for 8
-// or 16, so VEC is the largest of 8, 4, 2 (fp32: 4, 2) that divides B.  Offsets are 32 bits wide and the window's part of them is
+// or 16, so VEC is the largest of 8, 4, 2 (fp32: 4, 2) that divides B (4 where Out is streamed).  Offsets are 32 bits wide and the window's part of them is
 // scalar: with 64-bit products per element the vector unit, not memory, set the pace of calls with a small VEC.
-template <int DT, int MODE, int VEC, int WR, int WS, bool BIG>
+// STREAM: Out past the L2, where a row of images is whole cache lines (B a multiple of 32); elsewhere the pieces of a line
+// come from several instructions and the L2 has to put them together (bf16 (20, 192, 27, 27, 3 x 3, s 2) 7.4 us through it, 8.4
+// past it; fp32 (8, 80, 111, 111, 3 x 3) 17.6 and 30.9).  A template parameter because the compiler makes one store of the two
+// sides of a branch and drops the hint: fp32 max (128, 496, 43, 2, 2 x 2, s 2) 20.5 us without the hint, 18.1 with it;
+// (32, 64, 56, 56, 3 x 3, s 2) 29.1 and 24.8; bf16 (32, 100, 50, 75, 2 x 2, s 2) 29.7 and 27.2.
+template <int DT, int MODE, int VEC, int WR, int WS, bool BIG, bool STREAM>
 __global__ void __launch_bounds__(256) pool_kernel(const PoolArgs a) {
     constexpr int ESZ = DT == 0 ? 4 : 2;
     // consecutive workgroups go to different XCDs: give every XCD one contiguous run of the output instead, so the
@@ -153,14 +158,11 @@ __global__ void __launch_bounds__(256) pool_kernel(const PoolArgs a) {
     }
     float* const dst = a.out + (((c * (uint32_t)a.H + h) * (uint32_t)a.W + w) * (uint32_t)a.B + bv * VEC);
     if constexpr (VEC >= 4) {
-        // (streamed only where a row of images is whole cache lines: the pieces of a line come from several instructions
-        // otherwise, and the L2 has to put them together)
-        if (a.stream) {
 #pragma unroll
-            for (int i = 0; i < VEC; i += 4) __builtin_nontemporal_store(pf32x4{acc[i], acc[i + 1], acc[i + 2], acc[i + 3]}, (pf32x4*)(dst + i));
-        } else {
-#pragma unroll
-            for (int i = 0; i < VEC; i += 4) *(pf32x4*)(dst + i) = pf32x4{acc[i], acc[i + 1], acc[i + 2], acc[i + 3]};
+        for (int i = 0; i < VEC; i += 4) {
+            const pf32x4 v = {acc[i], acc[i + 1], acc[i + 2], acc[i + 3]};
+            if constexpr (STREAM) __builtin_nontemporal_store(v, (pf32x4*)(dst + i));
+            else *(pf32x4*)(dst + i) = v;
         }
     } else if constexpr (VEC == 2) {
         *(pf32x2*)dst = pf32x2{acc[0], acc[1]};
@@ -169,22 +171,31 @@ __global__ void __launch_bounds__(256) pool_kernel(const PoolArgs a) {
     }
 }
 
-template <int DT, int MODE, int VEC>
+template <int DT, int MODE, int VEC, bool STREAM>
 static int launch_one(const PoolArgs& a, void* stream) {
-    if (a.img_bytes == 0) hipLaunchKernelGGL((pool_kernel<DT, MODE, VEC, 0, 0, true>), dim3(a.n_wg), dim3(256), 0, (hipStream_t)stream, a);
-    else if (a.R == 3 && a.S == 3) hipLaunchKernelGGL((pool_kernel<DT, MODE, VEC, 3, 3, false>), dim3(a.n_wg), dim3(256), 0, (hipStream_t)stream, a);
-    else if (a.R == 2 && a.S == 2) hipLaunchKernelGGL((pool_kernel<DT, MODE, VEC, 2, 2, false>), dim3(a.n_wg), dim3(256), 0, (hipStream_t)stream, a);
-    else hipLaunchKernelGGL((pool_kernel<DT, MODE, VEC, 0, 0, false>), dim3(a.n_wg), dim3(256), 0, (hipStream_t)stream, a);
+    const dim3 grid(a.n_wg), block(256);
+    const hipStream_t st = (hipStream_t)stream;
+    if (a.img_bytes == 0) hipLaunchKernelGGL((pool_kernel<DT, MODE, VEC, 0, 0, true, STREAM>), grid, block, 0, st, a);
+    else if (a.R == 3 && a.S == 3) hipLaunchKernelGGL((pool_kernel<DT, MODE, VEC, 3, 3, false, STREAM>), grid, block, 0, st, a);
+    else if (a.R == 2 && a.S == 2) hipLaunchKernelGGL((pool_kernel<DT, MODE, VEC, 2, 2, false, STREAM>), grid, block, 0, st, a);
+    else hipLaunchKernelGGL((pool_kernel<DT, MODE, VEC, 0, 0, false, STREAM>), grid, block, 0, st, a);
     return hipGetLastError() == hipSuccess ? 0 : 1;
+}
+
+template <int DT, int MODE, int VEC>
+static int launch_stream(const PoolArgs& a, void* stream) {
+    if constexpr (VEC >= 4)
+        if (a.stream) return launch_one<DT, MODE, VEC, true>(a, stream);
+    return launch_one<DT, MODE, VEC, false>(a, stream);
 }
 
 template <int DT, int MODE>
 static int launch_vec(const PoolArgs& a, int vec, void* stream) {
     if constexpr (DT == 1)
-        if (vec == 8) return launch_one<DT, MODE, 8>(a, stream);
-    if (vec == 4) return launch_one<DT, MODE, 4>(a, stream);
-    if (vec == 2) return launch_one<DT, MODE, 2>(a, stream);
-    return launch_one<DT, MODE, 1>(a, stream);
+        if (vec == 8) return launch_stream<DT, MODE, 8>(a, stream);
+    if (vec == 4) return launch_stream<DT, MODE, 4>(a, stream);
+    if (vec == 2) return launch_stream<DT, MODE, 2>(a, stream);
+    return launch_stream<DT, MODE, 1>(a, stream);
 }
 
 int launch_pool(const PoolArgs& a, int dtype, int mode, int vec, void* stream) {

@@ -44,6 +44,20 @@ def test_images_per_thread_and_windows(env, dtype, B):
                     assert np.max(np.abs(got - ref)) <= (R * S + 1) * 2.0 ** -24
 
 
+# rows of whole cache lines: 4 images per thread, and 8 where the thread count at 4 would pass the limit of the kernel's divisions
+@pytest.mark.parametrize("C", [7000, 30000])
+def test_streamed_output_at_the_thread_limit(env, C):
+    cc, torch = env
+    dims = (32, C, C, 1, 1, 2, 2, 1, 1)
+    img = torch.empty(2, 2, C, 32, device="cuda:0", dtype=torch.bfloat16).uniform_(-1, 1)
+    out = torch.full((C, 1, 1, 32), float("nan"), device="cuda:0")
+    print(f"[pool] thread limit {dims}", flush=True)
+    cc.cacnn_pool_forward(dims, 1, 1, img, out)
+    ref = img.amax(dim=(0, 1)).float().view(C, 1, 1, 32)
+    torch.cuda.synchronize()
+    assert torch.equal(out, ref)
+
+
 def test_image_beyond_two_gib(env):
     """Windows that do not overlap, so that the reference is a reshape: 2.2 GB of fp32 and of bf16."""
     cc, torch = env
