@@ -425,7 +425,12 @@ struct FlatLds {
     static_assert(LDS <= 160 * 1024, "flat LDS kernel: LDS size");
 };
 
-template <int DT, int MB, int NBW, int IM, int WM, int WN, int WK, int NCH>
+// STREAM: Out past the L2, only where every store instruction writes whole cache lines; elsewhere the L2 has to put the pieces of a
+// line together.  One launch, buffers in rotation, through the L2 and past it: bf16 (16, 3, 64, 112, 112, 7 x 7, s 2) 21.4 and 20.6
+// us, 32 images 48.2 and 36.8, (32, 3, 64, 112, 112, 3 x 3, s 2) 37.2 and 24.1, fp32 (12, 3, 16, 112, 112, 3 x 3, s 2) 12.5 and 11.9; of
+// pieces of lines, bf16 (20, 3, 64, 111, 111, 3 x 3, s 2) 21.7 and 33.0, (12, 64, 256, 57, 55, 1 x 1) 14.9 and 19.0.  A template
+// parameter because the compiler makes one ordinary store of the two sides of a branch.
+template <int DT, int MB, int NBW, int IM, int WM, int WN, int WK, int NCH, bool STREAM>
 __global__ void __launch_bounds__(WM* WN* WK * 64) conv_flat_lds_kernel(const FlatArgs a) {
     using GEO = FlatLds<DT, MB, NBW, IM, WM, WN, WK, NCH>;
     constexpr int ESZ = GEO::ESZ, CH = GEO::CH, IPL = GEO::IPL, NB = GEO::NB, NF = GEO::NF, NI = GEO::NI, LW = GEO::LW;
@@ -734,7 +739,9 @@ __global__ void __launch_bounds__(WM* WN* WK * 64) conv_flat_lds_kernel(const Fl
         const uint32_t k = k0 + (wm * MB + m) * 32 + (v >> 2) * 8 + g * 4 + (v & 3);
         if (k >= a.K || skip[p]) return;
         float* const dst = a.out + (int64_t)k * a.N + opos[p];
-        if constexpr (SI == 4 || SI == 8) {
+        if constexpr (STREAM) {
+            __builtin_nontemporal_store(o[0], dst);
+        } else if constexpr (SI == 4 || SI == 8) {
 #pragma unroll
             for (int i = 0; i < SI; i += 4) ((Out4*)(dst + i))->v = ff32x4{o[i], o[i + 1], o[i + 2], o[i + 3]};
         } else if constexpr (SI == 2 || SI == 6) {
@@ -749,10 +756,10 @@ __global__ void __launch_bounds__(WM* WN* WK * 64) conv_flat_lds_kernel(const Fl
     flat_write_out<MB, NBW, SI, WM * WN, WK>((float*)s_mem, acc, wave, wk, lane, store);
 }
 
-template <int DT, int MB, int NBW, int IM, int WM, int WN, int WK, int NCH>
-static int launch_flat_lds(const FlatArgs& a, int grid, void* stream) {
+template <int DT, int MB, int NBW, int IM, int WM, int WN, int WK, int NCH, bool STREAM>
+static int launch_flat_lds_as(const FlatArgs& a, int grid, void* stream) {
     using GEO = FlatLds<DT, MB, NBW, IM, WM, WN, WK, NCH>;
-    auto kernel = conv_flat_lds_kernel<DT, MB, NBW, IM, WM, WN, WK, NCH>;
+    auto kernel = conv_flat_lds_kernel<DT, MB, NBW, IM, WM, WN, WK, NCH, STREAM>;
     if constexpr (GEO::LDS > 64 * 1024) {
         static const bool ok = hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024) == hipSuccess;
         if (!ok) {
@@ -762,6 +769,15 @@ static int launch_flat_lds(const FlatArgs& a, int grid, void* stream) {
     }
     hipLaunchKernelGGL(kernel, dim3(grid), dim3(GEO::THREADS), GEO::LDS, (hipStream_t)stream, a);
     return hipGetLastError() == hipSuccess ? 0 : 1;
+}
+
+// Out is streamed where the 32 columns of a block are one cache line: a lane stores one image and none that another has (B a
+// multiple of IM), and the rows of Out are whole lines.
+template <int DT, int MB, int NBW, int IM, int WM, int WN, int WK, int NCH>
+static int launch_flat_lds(const FlatArgs& a, int grid, void* stream) {
+    if constexpr (IM >= -1)
+        if (a.B % (IM > 0 ? IM : 1) == 0 && a.N % 32 == 0) return launch_flat_lds_as<DT, MB, NBW, IM, WM, WN, WK, NCH, true>(a, grid, stream);
+    return launch_flat_lds_as<DT, MB, NBW, IM, WM, WN, WK, NCH, false>(a, grid, stream);
 }
 
 // blocks of output channels, groups of images per wave; images per lane; waves along k, positions, contraction; steps ahead.

@@ -84,6 +84,26 @@ def test_every_flat_kernel_on_edge_shapes(env, dtype, shape):
     assert ran > 0
 
 
+# rows of Out that are whole cache lines, which the kernels that stage in LDS store past the L2: one line in all, K beyond a tile,
+# several tiles of positions with the last one partly filled
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("shape", [(8, 5, 8, 4, 1, 1, 1, 1), (9, 65, 16, 10, 3, 3, 1, 1), (3, 33, 32, 33, 7, 7, 2, 2)], ids=lambda s: "x".join(map(str, s)))
+def test_streamed_output_of_staged_kernels(env, dtype, shape):
+    lib, ran = env[2], 0
+    for index, images, exactly, lds in kernels(lib, dtype):
+        if not lds or (exactly and images > 1):
+            continue
+        cfg = ci.custom("flat", images, *shape, dtype=dtype, dist="normal", seed=50 + images)
+        img, flt = ci.make_inputs(cfg)
+        ref, ab = gu.oracle_full(cfg, img, flt)
+        print(f"[flat] kernel {index} {dtype} {cfg.dims}", flush=True)
+        rc, out = run(env, cfg, img, flt, index)
+        assert rc == 0
+        check(cfg, out, ref, ab, f"kernel {index}")
+        ran += 1
+    assert ran > 0
+
+
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
 def test_flat_kernels_refuse_what_they_cannot_hold(env, dtype):
     cc, torch, lib = env
