@@ -17,8 +17,8 @@
 // Where there are few tiles the waves of a workgroup divide the contraction and add up in LDS at the end.
 //
 // Measured against the kernels that ran these calls before (one launch, MI355X; direct, then staged):
-//   fp32 (5, 30, 50, 27, 19, 5 x 5)         109.7 -> 11.3 / 10.0 us      bf16 (1, 128, 128, 28, 28, 3 x 3)    46.0 -> 6.8 / 5.0 us
-//   bf16 (16, 3, 64, 112, 112, 7 x 7, s 2)  349 -> 28.1 / 25.3 us        bf16 (3, 367, 237, 15, 15, 3 x 3)   310 -> 53 / 22.8 us
+//   fp32 (5, 30, 50, 27, 19, 5 x 5)         109.7 -> 11.3 / 9.3 us       bf16 (1, 128, 128, 28, 28, 3 x 3)    46.0 -> 6.8 / 5.0 us
+//   bf16 (16, 3, 64, 112, 112, 7 x 7, s 2)  349 -> 28.1 / 20.4 us        bf16 (3, 367, 237, 15, 15, 3 x 3)   310 -> 53 / 22.8 us
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
