@@ -160,6 +160,10 @@ _lib.cacnn_internal_conv_forward_sized.argtypes = [ctypes.POINTER(Problem), ctyp
 _lib.cacnn_internal_pool_forward_sized.restype = ctypes.c_int
 _lib.cacnn_internal_pool_forward_sized.argtypes = [ctypes.POINTER(Problem), ctypes.c_int, ctypes.c_int] + \
     [ctypes.c_void_p, ctypes.c_int64] * 2 + [ctypes.c_void_p]
+_lib.cacnn_internal_route.restype = ctypes.c_int
+_lib.cacnn_internal_route.argtypes = [ctypes.POINTER(Problem), ctypes.c_int, ctypes.c_void_p, ctypes.c_void_p, ctypes.POINTER(ctypes.c_int32)]
+_lib.cacnn_internal_flat_info.restype = ctypes.c_int
+_lib.cacnn_internal_flat_info.argtypes = [ctypes.c_int, ctypes.POINTER(ctypes.c_int32)]
 _lib.cacnn_variant_count.restype = ctypes.c_int
 _lib.cacnn_variant_name.restype = ctypes.c_char_p
 _lib.cacnn_variant_name.argtypes = [ctypes.c_int]
@@ -273,6 +277,22 @@ def cacnn_conv_forward(problem, dtype: int, image, filt, out, stream=None) -> No
                                  _stream_handle(stream))
     if rc != 0:
         raise CacnnError(rc, "cacnn_conv_forward")
+
+
+def routed_kernel(problem, dtype: int, image: int = 0, filt: int = 0):
+    """(name, workgroups, threads of one) of the kernel that cacnn_conv_forward launches for a problem and operands at these addresses,
+    whose alignment is all that matters (host only).  A variant's name is that of cacnn_variant_name; a flattened kernel's is "bf16 flat
+    m<blocks of output channels> n<blocks of columns> i<images per lane, < 0: all of the batch> w<waves along k, columns, contraction>
+    c<chunks per LDS stage, 0: straight from global memory>"."""
+    four, eight = (ctypes.c_int32 * 4)(), (ctypes.c_int32 * 8)()
+    rc = _lib.cacnn_internal_route(ctypes.byref(_as_problem(problem)), int(dtype), int(image), int(filt), four)
+    if rc != 0:
+        raise CacnnError(rc, "cacnn_internal_route")
+    if not four[0]:
+        return cacnn_variant_name(four[1]), four[2], four[3]
+    _lib.cacnn_internal_flat_info(four[1], eight)
+    dt, mb, ng, im, wm, wn, wk, nch = eight
+    return f"{'bf16' if dt else 'f32'} flat m{mb} n{ng} i{im} w{wm}x{wn}x{wk} c{nch}", four[2], four[3]
 
 
 def cacnn_tune(problem, dtype: int, image, filt, out, stream=None) -> Plan:

@@ -1307,6 +1307,15 @@ void store_plan(const cacnn_problem& p, int key, const Launch& launch) {
     g_plans.push_back(PlanEntry{p, key, launch});
 }
 
+// the launch of a call with these operands, remembered or planned now
+int route(const cacnn_problem& p, int dtype, const void* image, const void* filter, Launch* out) {
+    const int key = launch_key(dtype, image, filter);
+    if (lookup_plan(p, key, out)) return CACNN_OK;
+    const int rc = plan_route(p, dtype, aligned16(image), aligned16(filter), out);
+    if (rc == CACNN_OK) store_plan(p, key, *out);
+    return rc;
+}
+
 }  // namespace
 
 extern "C" {
@@ -1326,13 +1335,9 @@ int cacnn_conv_forward(const cacnn_problem* problem, int dtype, const void* imag
                        void* hip_stream) {
     if (!problem || !image || !filter || !out) return CACNN_ERR_NULL;
     if (dtype != CACNN_F32 && dtype != CACNN_BF16_F32ACC) return CACNN_ERR_UNSUPPORTED;
-    const int key = launch_key(dtype, image, filter);
     Launch launch;
-    if (!lookup_plan(*problem, key, &launch)) {
-        const int rc = plan_route(*problem, dtype, aligned16(image), aligned16(filter), &launch);
-        if (rc != CACNN_OK) return rc;
-        store_plan(*problem, key, launch);
-    }
+    const int rc = route(*problem, dtype, image, filter, &launch);
+    if (rc != CACNN_OK) return rc;
     if (!pointers_legal(dtype, image, filter, out)) return CACNN_ERR_INVALID_ARG;
     return fire(launch, image, filter, out, hip_stream);
 }
@@ -1790,6 +1795,20 @@ int cacnn_internal_pool_forward_sized(const cacnn_problem* problem, int dtype, i
                                       int64_t out_elems, void* hip_stream) {
     if (!problem || problem->K != problem->C || !holds(*problem, image_elems, INT64_MAX, out_elems)) return CACNN_ERR_INVALID_ARG;
     return cacnn_pool_forward(problem, dtype, mode, image, out, hip_stream);
+}
+// Which kernel cacnn_conv_forward launches for a problem and operands at these addresses (of which the alignment alone matters):
+// {0: a variant with box tiles, 1: a flattened kernel; its index; workgroups; threads of one}.  Nothing is enqueued.
+int cacnn_internal_route(const cacnn_problem* problem, int dtype, const void* image, const void* filter, int32_t* four) {
+    if (!problem || !four) return CACNN_ERR_NULL;
+    if (dtype != CACNN_F32 && dtype != CACNN_BF16_F32ACC) return CACNN_ERR_UNSUPPORTED;
+    Launch l;
+    const int rc = route(*problem, dtype, image, filter, &l);
+    if (rc != CACNN_OK) return rc;
+    four[0] = l.flat ? 1 : 0;
+    four[1] = l.flat ? (int32_t)(l.flat - &flat_variant(0)) : (int32_t)(l.tiled - &variant(0));
+    four[2] = l.grid;
+    four[3] = l.flat ? l.flat->info.threads() : l.tiled->info.threads();
+    return CACNN_OK;
 }
 int cacnn_internal_flat_count(void) { return num_flat(); }
 int cacnn_internal_flat_info(int i, int32_t* eight) {

@@ -1,0 +1,56 @@
+"""Which kernel cacnn_conv_forward launches (host only: nothing is enqueued): the layers that stay on the variants with box tiles, those that
+go to the kernels with flattened positions, and that a call that cannot be planned is still refused."""
+import pytest
+
+import cacnn_inputs as ci
+import paper_1802_06905_amd as cc
+from paper_1802_06905_amd import binding
+
+F32, BF16 = cc.CACNN_F32, cc.CACNN_BF16_F32ACC
+
+
+def routed(dims, dtype, image=0, filt=0):
+    name, workgroups, threads = binding.routed_kernel(dims, dtype, image, filt)
+    assert workgroups >= 1 and workgroups * threads < 2 ** 32       # what a launch can hold
+    return name
+
+
+@pytest.mark.parametrize("name", ["c2", "c3", "c4", "c5"])
+def test_fixed_geometry_layers_run_their_planned_variant(name):
+    cfg = ci.CONFIGS[name]
+    dtype = F32 if cfg.dtype == "f32" else BF16
+    assert routed(cfg.dims, dtype) == cc.cacnn_variant_name(cc.cacnn_tile_plan(cfg.dims, dtype).variant)
+    # operands that are not 16-byte aligned rule out the kernels that need it, whichever of the two it is
+    for image, filt in ((4, 0), (0, 8), (4, 4)):
+        assert " flat " in routed(cfg.dims, dtype, image, filt)
+    assert " flat " not in routed(cfg.dims, dtype)                  # (and nothing of that is remembered for aligned ones)
+
+
+# one image, images that 16-byte items do not divide, channels that they do not divide, few tiles
+@pytest.mark.parametrize("dtype,dims", [(F32, (1, 3, 8, 16, 16, 3, 3, 1, 1)), (F32, (5, 30, 50, 27, 19, 5, 5, 1, 1)),
+                                        (BF16, (1, 128, 128, 28, 28, 3, 3, 1, 1)), (BF16, (16, 3, 64, 112, 112, 7, 7, 2, 2)),
+                                        (BF16, (3, 367, 237, 15, 15, 3, 3, 1, 1)), (BF16, (64, 30, 64, 14, 14, 3, 3, 1, 1)),
+                                        (F32, (64, 1, 48, 28, 28, 3, 3, 1, 1)), (BF16, (8, 512, 512, 7, 7, 1, 1, 1, 1))])
+def test_small_and_ragged_layers_run_flattened(dtype, dims):
+    assert " flat " in routed(dims, dtype)
+
+
+@pytest.mark.parametrize("dtype,dims", [(F32, (128, 9, 8, 700, 700, 3, 3, 1, 1)), (BF16, (250, 9, 8, 700, 700, 3, 3, 1, 1))])
+def test_an_image_of_two_gib_stays_on_box_tiles(dtype, dims):
+    problem = cc.Problem(*dims)
+    assert problem.IW * problem.IH * problem.C * problem.B * (4 if dtype == F32 else 2) >= 2 ** 31
+    assert routed(dims, dtype) == cc.cacnn_variant_name(cc.cacnn_tile_plan(dims, dtype).variant)
+    below = (dims[0] // 2,) + dims[1:]
+    assert " flat " in routed(below, dtype)
+
+
+@pytest.mark.parametrize("dtype,dims", [(BF16, (1, 1, 1, 30000, 30000, 1, 1, 1, 1)), (BF16, (1, 1, 1, 16384, 2 ** 15, 1, 8, 1, 1))])
+def test_a_tile_list_beyond_the_index_range_is_refused(dtype, dims):
+    with pytest.raises(cc.CacnnError):
+        binding.routed_kernel(dims, dtype)
+
+
+def test_arguments_out_of_range_are_refused():
+    for dims, dtype in (((1, 3, 8, 16, 16, 3, 3, 1, 1), 2), ((1, 0, 8, 16, 16, 3, 3, 1, 1), F32), ((2 ** 31, 3, 8, 16, 16, 3, 3, 1, 1), F32)):
+        with pytest.raises(cc.CacnnError):
+            binding.routed_kernel(dims, dtype)
