@@ -150,14 +150,22 @@ __device__ __forceinline__ void flat_write_out(float* s_red, ff32x16 (&acc)[MB][
 // IM > 0: a lane holds IM adjacent images of a position and loads them one contraction index at a time.
 // IM < 0: there are -IM images in all; a lane holds all of them and loads 16 bytes at a time, in which the images of a
 // channel are neighbours and the channels follow each other.
-template <int DT, int MB, int NG, int IM, int WM, int WN, int WK, int D, bool SHORT>
+// SHORT: a filter row (T = S*C indices) is shorter than a chunk, which is one r then; only the T elements that exist are loaded, the
+// others stay zero.
+// AHEAD: steps whose loads are in flight.  0, for short rows and for waves of one step at most: every load is of a step that is
+// multiplied.  The loop of the longer contractions fetches up to 2 AHEAD - 1 steps beyond the last one, and with those and a short row's
+// last element repeated up to the end of the chunk, a 1 x 1 layer of one channel took up to 64 times the loads it needs: fp32
+// (1, 2, 2, 1059, 1059, 7 x 1) 415 -> 44 us, bf16 (1, 3, 81, 821, 821, 1 x 1) 664 -> 102, (4, 2, 192, 37, 37, 1 x 1) 10.8 -> 4.1, and with
+// whole chunks fp32 (7, 4, 136, 90, 39, 1 x 1) 10.8 -> 7.2, bf16 (3, 8, 176, 8, 8, 1 x 1) 5.3 -> 2.6.
+template <int DT, int MB, int NG, int IM, int WM, int WN, int WK, int AHEAD, bool SHORT>
 __global__ void __launch_bounds__(WM* WN* WK * 64) conv_flat_kernel(const FlatArgs a) {
     constexpr int ESZ = DT == 0 ? 4 : 2, CH = 16 / ESZ;
     constexpr bool RUN = IM < 0;                       // 16-byte loads along the contraction
     constexpr int IPL = RUN ? -IM : IM, NB = NG * IPL; // images per lane, column blocks per wave
-    static_assert(!(SHORT && RUN), "flat kernel: a run of 16 bytes needs a filter row that long");
+    static_assert(!SHORT || (!RUN && AHEAD == 0), "flat kernel: a run of 16 bytes needs a filter row that long");
     constexpr int LW = RUN ? 4 : (IPL * ESZ + 3) / 4;  // dwords of one Image load
     constexpr int LE = RUN ? IPL : CH;                 // Image loads per chunk
+    constexpr int D = AHEAD ? AHEAD : 1;               // steps of operands in registers
     extern __shared__ __align__(16) float s_red[];
 
     const int tid = threadIdx.x, lane = tid & 63;
@@ -194,13 +202,7 @@ __global__ void __launch_bounds__(WM* WN* WK * 64) conv_flat_kernel(const FlatAr
         skip[p] = q0 + p * 32 + j < a.groups ? (int)(first - b) : IPL;
     }
 
-    // byte distance of a chunk's e-th contraction index from its first (a filter row shorter than a chunk: the last one
-    // again, which the mask then removes)
-    const uint32_t eoff = a.B * ESZ;
-    uint32_t es[CH];
-#pragma unroll
-    for (int e = 0; e < CH; ++e) es[e] = SHORT ? min((uint32_t)e, a.T - 1) : (uint32_t)e;
-
+    const uint32_t eoff = a.B * ESZ;                   // bytes from one contraction index to the next
     const __amdgpu_buffer_rsrc_t rimg = __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(a.image), 0, a.img_bytes, 0x00020000);
 
     // this wave's steps, and this half-wave's chunk of the next step to fetch
@@ -227,7 +229,8 @@ __global__ void __launch_bounds__(WM* WN* WK * 64) conv_flat_kernel(const FlatAr
         for (int m = 0; m < MB; ++m) {
             if constexpr (SHORT) {
 #pragma unroll
-                for (int e = 0; e < CH; ++e) load_at<ESZ>(A[d][m] + e, (const char*)a.filter + es[e] * ESZ, aoff[m] + fo);
+                for (int e = 0; e < CH; ++e)
+                    if ((uint32_t)e < a.T) load_at<ESZ>(A[d][m] + e, (const char*)a.filter + e * ESZ, aoff[m] + fo);
             } else {
                 load_at<16>(A[d][m], (const char*)a.filter, aoff[m] + fo);
             }
@@ -238,7 +241,7 @@ __global__ void __launch_bounds__(WM* WN* WK * 64) conv_flat_kernel(const FlatAr
 #pragma unroll
             for (int e = 0; e < LE; ++e) {
                 if constexpr (RUN) load_at<16>(X[d][p][e], (const char*)a.image + e * 16, vo);
-                else load_image<IPL * ESZ>(X[d][p][e], rimg, vo, es[e] * eoff);
+                else if (!SHORT || (uint32_t)e < a.T) load_image<IPL * ESZ>(X[d][p][e], rimg, vo, e * eoff);
             }
         }
         // the half-wave's chunk of the next step lies two chunks further on
@@ -262,8 +265,7 @@ __global__ void __launch_bounds__(WM* WN* WK * 64) conv_flat_kernel(const FlatAr
             for (int v = 0; v < 16; ++v) acc[m][n][v] = 0.f;
 
     auto multiply = [&](int d) {
-        const uint32_t hi = SHORT ? a.T : CH;
-        const bool mask = SHORT || __any(lo[d] != 0);
+        const bool mask = __any(lo[d] != 0);
         fu32x4 av[MB], bv[NB];
 #pragma unroll
         for (int m = 0; m < MB; ++m)
@@ -296,10 +298,10 @@ __global__ void __launch_bounds__(WM* WN* WK * 64) conv_flat_kernel(const FlatAr
             for (int i = 0; i < 4; ++i) {
                 uint32_t keep;
                 if constexpr (DT == 0) {
-                    keep = (uint32_t)i >= lo[d] && (uint32_t)i < hi ? 0xffffffffu : 0u;
+                    keep = (uint32_t)i >= lo[d] ? 0xffffffffu : 0u;
                 } else {
-                    keep = ((uint32_t)(2 * i) >= lo[d] && (uint32_t)(2 * i) < hi ? 0x0000ffffu : 0u) |
-                           ((uint32_t)(2 * i + 1) >= lo[d] && (uint32_t)(2 * i + 1) < hi ? 0xffff0000u : 0u);
+                    keep = ((uint32_t)(2 * i) >= lo[d] ? 0x0000ffffu : 0u) |
+                           ((uint32_t)(2 * i + 1) >= lo[d] ? 0xffff0000u : 0u);
                 }
 #pragma unroll
                 for (int m = 0; m < MB; ++m) av[m][i] &= keep;
@@ -326,19 +328,37 @@ __global__ void __launch_bounds__(WM* WN* WK * 64) conv_flat_kernel(const FlatAr
         }
     };
 
-    // D steps of loads are in flight; the order of the loads is kept (left alone, the compiler mixes the steps of the
-    // first group, and then waits for nearly all of them before the first product of every group)
+    if constexpr (SHORT) {
 #pragma unroll
-    for (int d = 0; d < D; ++d) {
-        fetch(d);
-        __builtin_amdgcn_sched_barrier(0);
+        for (int e = 0; e < CH; ++e) {
+#pragma unroll
+            for (int m = 0; m < MB; ++m) A[0][m][e] = 0;
+#pragma unroll
+            for (int p = 0; p < NG; ++p)
+#pragma unroll
+                for (int i = 0; i < LW; ++i) X[0][p][e][i] = 0;
+        }
     }
-    for (uint32_t s = s_begin; s < s_end; s += D) {
+    if constexpr (AHEAD == 0) {
+        for (uint32_t s = s_begin; s < s_end; ++s) {
+            fetch(0);
+            multiply(0);
+        }
+    } else {
+        // D steps of loads are in flight; the order of the loads is kept (left alone, the compiler mixes the steps of the
+        // first group, and then waits for nearly all of them before the first product of every group)
 #pragma unroll
         for (int d = 0; d < D; ++d) {
-            multiply(d);
             fetch(d);
             __builtin_amdgcn_sched_barrier(0);
+        }
+        for (uint32_t s = s_begin; s < s_end; s += D) {
+#pragma unroll
+            for (int d = 0; d < D; ++d) {
+                multiply(d);
+                fetch(d);
+                __builtin_amdgcn_sched_barrier(0);
+            }
         }
     }
 
@@ -386,9 +406,13 @@ static int launch_flat_one(const FlatArgs& a, int grid, void* stream) {
 
 template <int DT, int MB, int NG, int IM, int WM, int WN, int WK, int D>
 static int launch_flat_shape(const FlatArgs& a, int grid, void* stream) {
-    if constexpr (IM < 0) return launch_flat_one<DT, MB, NG, IM, WM, WN, WK, D, false>(a, grid, stream);
-    else return a.T < (DT == 0 ? 4u : 8u) ? launch_flat_one<DT, MB, NG, IM, WM, WN, WK, D, true>(a, grid, stream)
-                                          : launch_flat_one<DT, MB, NG, IM, WM, WN, WK, D, false>(a, grid, stream);
+    if constexpr (IM < 0) {
+        return launch_flat_one<DT, MB, NG, IM, WM, WN, WK, D, false>(a, grid, stream);
+    } else {
+        if (a.T < (DT == 0 ? 4u : 8u)) return launch_flat_one<DT, MB, NG, IM, WM, WN, WK, 0, true>(a, grid, stream);
+        if (a.steps_per_wave <= 1) return launch_flat_one<DT, MB, NG, IM, WM, WN, WK, 0, false>(a, grid, stream);
+        return launch_flat_one<DT, MB, NG, IM, WM, WN, WK, D, false>(a, grid, stream);
+    }
 }
 
 // ---------------------------------------------------------------------------------------------------------------

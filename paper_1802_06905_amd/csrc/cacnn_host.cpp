@@ -1149,9 +1149,21 @@ double flat_us(const cacnn_problem& p, int dtype, const FlatInfo& v) {
     const double blocks = v.MB * v.NG * (run || !v.NCH ? ipl : 1);                                            // of one wave
     const bool flt_aligned = f32 || T % 2 == 0, img_aligned = f32 || (run ? p.C * p.B : p.B) % 2 == 0;
     double clk;
+    if (T < ch) {
+        // Filter rows shorter than a chunk: T loads for each operand and step, of which the waves share R / 2, nothing fetched ahead.  Fitted
+        // on 1350 such layers: 18 % (one standard deviation), the pick is within 1.02 of the fastest.
+        const int64_t steps = (chunks + 1) / 2, mine = ceil_div(steps, v.WK);
+        const double busy = (double)(v.WM * v.WN * ceil_div(steps, mine));                                    // waves that have a step
+        const double b_clk = load_clocks(ipl * esz, (double)(std::min<int64_t>(p.B, 32 * ipl) * esz), img_aligned, ipl == 4 || p.B % (4 * ipl) == 0);
+        const double load = per_cu * busy * mine * T * (v.MB * 12.7 + v.NG * b_clk * 0.79);
+        const double simd = per_cu * std::ceil(busy / 4.0) * mine * blocks * mfma, latency = mine * 1244.0;
+        clk = std::sqrt(load * load + simd * simd + latency * latency);
+        clk += per_cu * blocks * (v.WM * v.WN * 105.0 + (v.WK > 1 ? waves * 82.0 : 0.0));                     // Out
+        return with_copy_time(clk / 2272.0, p, dtype) + 2.1;
+    }
     if (!v.NCH) {
         const double mine = (double)ceil_div((chunks + 1) / 2, v.WK) + 1.0;                                   // steps of a wave
-        const double a_clk = T < ch ? ch * 40.0 : load_clocks(16, 32.0, flt_aligned, true);
+        const double a_clk = load_clocks(16, 32.0, flt_aligned, true);
         const double b_clk = run ? ipl * load_clocks(16, 32.0 * ipl, img_aligned, true)
                                  : ch * load_clocks(ipl * esz, (double)(std::min<int64_t>(p.B, 32 * ipl) * esz), img_aligned,
                                                     ipl == 4 || p.B % (4 * ipl) == 0);
@@ -1263,9 +1275,19 @@ int launch_key(int dtype, const void* image, const void* filter) {
     return dtype | (aligned16(image) ? 0 : 0x100) | (aligned16(filter) ? 0 : 0x200);
 }
 
-// What cacnn_conv_forward launches: the planned variant or a kernel with flattened positions.  A generic variant always
-// gives way to a flattened kernel that takes the problem: on 104 layers of all sizes whose plan was a generic variant the
-// flattened kernel was 1.05 to 60 times faster, 5 times in the geometric mean.  A fixed-geometry variant, whose price is
+// One large fp32 image whose filter rows are shorter than a chunk (fewer than 4 channels of a 1 x 1 filter, a 3 x 3 one on a single
+// channel): each lane's load takes 4 bytes from a place of its own, which the box tiles of 16 x 16 positions of one image do
+// better where there are many positions.  (1, 1, 40, W, W, 1 x 1), box tiles and flattened: W = 180 6.1 and 4.6 us, 280 7.9 and
+// 7.8, 340 9.3 and 10.2, 528 18.1 and 21.2; over 320 layers the flattened kernel takes 0.3 to 1.0 times as long up to 80 000 positions
+// and 0.7 to 1.5 times, mostly more than 1.0, from 117 000 on.  Images that do not fill a
+// box tile in one direction, a second image, and bf16: the flattened one is faster at every size measured.
+bool boxes_for_short_rows(const cacnn_problem& p, int dtype) {
+    return dtype == CACNN_F32 && p.B == 1 && p.S * p.C < 4 && p.W * p.H >= 100000 && std::min(p.W, p.H) >= 16;
+}
+
+// What cacnn_conv_forward launches: the planned variant or a kernel with flattened positions.  A generic variant
+// gives way to a flattened kernel that takes the problem, but for the case above: on 1500 layers whose plan was a generic variant, large and
+// small ones and all those where the two estimates are near each other, the flattened kernel took 0.02 to 1.0 times as long.  A fixed-geometry variant, whose price is
 // a measurement, gives way where the flattened kernel is estimated to take less than 0.7 of its time: on 60 such layers
 // the flattened kernel was 1.2 to 4 times faster below that line (layers that leave most compute units idle, taps of large
 // filters), and between it and the break-even both sides won, by up to 1.5 times (1.27 for the fixed-geometry ones).
@@ -1280,7 +1302,7 @@ int plan_route(const cacnn_problem& p, int dtype, bool aligned_img, bool aligned
         // (a call whose plan cannot be launched is refused, as it would be without the flattened kernels)
         const VariantInfo& v = variant(plan.variant).info;
         if (fi >= 0 && tile_list_in_range(p, v, plan.xcd_walk, plan.xcd_split_k) &&
-            (v.fx_ct == 0 || flat_est < 0.7 * (with_copy_time(tiled_us - 2.1, p, dtype) + 2.1)))
+            (v.fx_ct == 0 ? !boxes_for_short_rows(p, dtype) : flat_est < 0.7 * (with_copy_time(tiled_us - 2.1, p, dtype) + 2.1)))
             return prepare_flat(p, dtype, fi, out);
     }
     return prepare_tiled(p, dtype, plan.variant, plan.b_c, plan.b_r, plan.b_s, plan.xcd_split_k, plan.xcd_walk, aligned_img, aligned_flt, out);

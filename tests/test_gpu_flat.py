@@ -84,6 +84,28 @@ def test_every_flat_kernel_on_edge_shapes(env, dtype, shape):
     assert ran > 0
 
 
+# filter rows of 1 to 7 contraction indices, and of one whole chunk: the waves that share a tile have no step, one, two or several,
+# the last of an odd number of columns fills half of one
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("c,r,s", [(1, 1, 1), (1, 2, 2), (3, 1, 1), (1, 8, 3), (2, 11, 1), (5, 9, 1), (7, 17, 1), (1, 5, 7), (8, 1, 1), (4, 2, 2)])
+def test_short_rows_and_single_steps(env, dtype, c, r, s):
+    lib, ran = env[2], 0
+    for index, images, exactly, lds in kernels(lib, dtype):
+        if exactly or lds:
+            continue
+        for B in (images, 13):
+            cfg = ci.custom("flat", B, c, 35, 7, 6, r, s, 2, 1, dtype=dtype, dist="normal", seed=70 + c)
+            img, flt = ci.make_inputs(cfg)
+            ref, ab = gu.oracle_full(cfg, img, flt)
+            print(f"[flat] kernel {index} {dtype} {cfg.dims}", flush=True)
+            for misalign in (0, 1):
+                rc, out = run(env, cfg, img, flt, index, misalign)
+                assert rc == 0
+                check(cfg, out, ref, ab, f"kernel {index} misalign {misalign}")
+                ran += 1
+    assert ran > 0
+
+
 # rows of Out that are whole cache lines, which the kernels that stage in LDS store past the L2: one line in all, K beyond a tile,
 # several tiles of positions with the last one partly filled
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])

@@ -35,6 +35,19 @@ def test_small_and_ragged_layers_run_flattened(dtype, dims):
     assert " flat " in routed(dims, dtype)
 
 
+# filter rows shorter than 16 bytes: one large fp32 image is the case where box tiles are faster (up to 1.5 times)
+@pytest.mark.parametrize("C,R,S", [(1, 1, 1), (3, 1, 1), (1, 3, 3), (2, 7, 1)])
+def test_one_large_image_with_short_filter_rows(C, R, S):
+    for K in (1, 40):
+        assert " flat " not in routed((1, C, K, 1000, 1000, R, S, 1, 1), F32)
+        assert " flat " not in routed((1, C, K, 250, 400, R, S, 1, 1), F32)
+        assert " flat " in routed((1, C, K, 250, 399, R, S, 1, 1), F32)
+        assert " flat " in routed((2, C, K, 1000, 1000, R, S, 1, 1), F32)
+        assert " flat " in routed((1, C, K, 12, 10000, R, S, 1, 1), F32) and " flat " in routed((1, C, K, 10000, 12, R, S, 1, 1), F32)
+        assert " flat " in routed((1, C, K, 1000, 1000, R, S, 1, 1), BF16)
+    assert " flat " in routed((1, 4, 40, 1000, 1000, 1, 1, 1, 1), F32)
+
+
 @pytest.mark.parametrize("dtype,dims", [(F32, (128, 9, 8, 700, 700, 3, 3, 1, 1)), (BF16, (250, 9, 8, 700, 700, 3, 3, 1, 1))])
 def test_an_image_of_two_gib_stays_on_box_tiles(dtype, dims):
     problem = cc.Problem(*dims)
