@@ -1285,12 +1285,25 @@ bool boxes_for_short_rows(const cacnn_problem& p, int dtype) {
     return dtype == CACNN_F32 && p.B == 1 && p.S * p.C < 4 && p.W * p.H >= 100000 && std::min(p.W, p.H) >= 16;
 }
 
+// A flattened kernel takes the place of a fixed-geometry one where its estimate is below this share of the other's time: on 60 layers the
+// flattened kernel was 1.2 to 4 times faster below 0.7 (layers that leave most compute units idle, taps of large
+// filters), and between it and the break-even both sides won, by up to 1.5 times (1.27 for the fixed-geometry ones).
+// The estimate knows nothing of windows read again from beyond the L2.  For bf16, whose products do not hide that, on Images of more than
+// 100 MB it is too low by up to 2.2 times, the more the windows overlap and the larger the Image is than the last-level
+// cache of 256 MB: (16, 888, 24, 126, 126, 3 x 3) 435 us and 571 flattened, (16, 1360, 3, 127, 127, 3 x 3) 562 and 978, (32, 152, 1, 151, 107,
+// 1 x 7) 109 and 134.  The line there is fitted on 173 such layers: with 0.7 28 of them take up to 1.74 times as long as on
+// their fixed-geometry kernel, with this one none more than 1.04; on 150 others 18 up to 1.45, and one, 1.14.  fp32 layers of these sizes: 0.24 to 0.87 times as long with 0.7.
+double flat_margin(const cacnn_problem& p, int dtype) {
+    const double image = 2.0 * (double)(p.sigma_w * (p.W - 1) + p.R) * (double)(p.sigma_h * (p.H - 1) + p.S) * (double)p.C * (double)p.B;
+    if (dtype == CACNN_F32 || image < 100e6) return 0.7;
+    const double overlap = std::max(1.0, (double)p.R / (double)p.sigma_w) * std::max(1.0, (double)p.S / (double)p.sigma_h);
+    return std::min(0.7, 0.85 * std::pow(overlap * std::max(1.0, image / 256e6), -0.2));
+}
+
 // What cacnn_conv_forward launches: the planned variant or a kernel with flattened positions.  A generic variant
 // gives way to a flattened kernel that takes the problem, but for the case above: on 1500 layers whose plan was a generic variant, large and
-// small ones and all those where the two estimates are near each other, the flattened kernel took 0.02 to 1.0 times as long.  A fixed-geometry variant, whose price is
-// a measurement, gives way where the flattened kernel is estimated to take less than 0.7 of its time: on 60 such layers
-// the flattened kernel was 1.2 to 4 times faster below that line (layers that leave most compute units idle, taps of large
-// filters), and between it and the break-even both sides won, by up to 1.5 times (1.27 for the fixed-geometry ones).
+// small ones and all those where the two estimates are near each other, the flattened kernel took 0.02 to 1.0 times as long.  A fixed-geometry
+// variant, whose price is a measurement, gives way below flat_margin.
 int plan_route(const cacnn_problem& p, int dtype, bool aligned_img, bool aligned_flt, Launch* out) {
     double tiled_us = 0.0, flat_est = 0.0;
     // the pipelined kernels need 16-byte aligned operands; a misaligned call is planned without them
@@ -1302,7 +1315,7 @@ int plan_route(const cacnn_problem& p, int dtype, bool aligned_img, bool aligned
         // (a call whose plan cannot be launched is refused, as it would be without the flattened kernels)
         const VariantInfo& v = variant(plan.variant).info;
         if (fi >= 0 && tile_list_in_range(p, v, plan.xcd_walk, plan.xcd_split_k) &&
-            (v.fx_ct == 0 ? !boxes_for_short_rows(p, dtype) : flat_est < 0.7 * (with_copy_time(tiled_us - 2.1, p, dtype) + 2.1)))
+            (v.fx_ct == 0 ? !boxes_for_short_rows(p, dtype) : flat_est < flat_margin(p, dtype) * (with_copy_time(tiled_us - 2.1, p, dtype) + 2.1)))
             return prepare_flat(p, dtype, fi, out);
     }
     return prepare_tiled(p, dtype, plan.variant, plan.b_c, plan.b_r, plan.b_s, plan.xcd_split_k, plan.xcd_walk, aligned_img, aligned_flt, out);
