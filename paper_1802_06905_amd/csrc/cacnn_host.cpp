@@ -1114,13 +1114,15 @@ double with_copy_time(double us, const cacnn_problem& p, int dtype) {
 
 // Whether a kernel with flattened positions takes the problem: enough images for the group a lane holds (or exactly the
 // number it was compiled for, and a filter row of at least one 16-byte chunk), and Image and Filter within the 2 GiB
-// that its 32-bit byte offsets reach.
+// that its 32-bit byte offsets reach, and a launch of fewer than 2^32 threads (its workgroups walk no list of tiles, there is one for each).
 bool flat_fits(const cacnn_problem& p, int dtype, const FlatInfo& v) {
     const int esz = dtype == CACNN_F32 ? 4 : 2;
     if (v.dtype != dtype) return false;
     if (v.IM < 0 ? p.B != -v.IM : p.B < v.IM) return false;
     if ((v.IM < 0 || v.NCH) && p.S * p.C * esz < 16) return false;
     const double IW = (double)(p.sigma_w * (p.W - 1) + p.R), IH = (double)(p.sigma_h * (p.H - 1) + p.S);
+    const double groups = (double)p.H * (double)p.W * (double)(v.IM < 0 ? 1 : ceil_div(p.B, v.IM));
+    if ((double)ceil_div(p.K, v.KT()) * std::ceil(groups / v.GT()) * v.threads() >= 4294967296.0) return false;
     return IW * IH * (double)p.C * (double)p.B * esz < 2147483648.0 && (double)p.K * p.R * p.S * p.C * esz < 2147483648.0;
 }
 
@@ -1239,8 +1241,7 @@ int prepare_flat(const cacnn_problem& p, int dtype, int fi, Launch* out) {
     a.wrap_img = a.img_r - a.TC * a.img_chunk;
     a.img_bytes = (int32_t)img;
     const int64_t tiles_k = ceil_div(p.K, v.KT()), tiles_n = ceil_div(a.groups, v.GT());
-    int64_t grid = 0;
-    if (!mul_check(tiles_k, tiles_n, INT32_MAX, &grid)) return CACNN_ERR_UNSUPPORTED;
+    const int64_t grid = tiles_k * tiles_n;
     a.k_inner = img >= flt ? 1u : 0u;
     a.inner = (uint32_t)(a.k_inner ? tiles_k : tiles_n);
     a.xcd_q = (uint32_t)grid / 8;

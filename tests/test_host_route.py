@@ -1,5 +1,7 @@
 """Which kernel cacnn_conv_forward launches (host only: nothing is enqueued): the layers that stay on the variants with box tiles, those that
 go to the kernels with flattened positions, and that a call that cannot be planned is still refused."""
+import ctypes
+
 import pytest
 
 import cacnn_inputs as ci
@@ -64,6 +66,27 @@ def test_an_image_of_two_gib_stays_on_box_tiles(dtype, dims):
     assert routed(dims, dtype) == cc.cacnn_variant_name(cc.cacnn_tile_plan(dims, dtype).variant)
     below = (dims[0] // 2,) + dims[1:]
     assert " flat " in routed(below, dtype)
+
+
+@pytest.mark.parametrize("dims", [(1, 1, 1, 24000, 24000, 1, 1, 1, 1), (1, 1, 1, 20000, 20000, 1, 8, 1, 1)])
+def test_flattened_kernels_decline_launches_of_2_32_threads(dims):
+    """They have one workgroup per tile: with small tiles and an Out of 2^28 words and more the threads of a launch would not fit 32 bits."""
+    lib = binding._lib
+    lib.cacnn_internal_flat_us.restype = ctypes.c_double
+    lib.cacnn_internal_flat_us.argtypes = [ctypes.POINTER(cc.Problem), ctypes.c_int, ctypes.c_int]
+    problem, taken, declined = cc.Problem(*dims), 0, 0
+    for i in range(lib.cacnn_internal_flat_count()):
+        x = (ctypes.c_int32 * 8)()
+        assert lib.cacnn_internal_flat_info(i, x) == 0
+        dtype, mb, ng, im, wm, wn, wk, nch = x
+        if dtype != BF16 or im not in (1, -1) or (nch and dims[1] * dims[6] < 8):
+            continue
+        tiles = -(-dims[3] * dims[4] // (32 * ng * wn))                # (one output channel, one image)
+        fits = tiles * 64 * wm * wn * wk < 2 ** 32
+        assert (lib.cacnn_internal_flat_us(ctypes.byref(problem), BF16, i) > 0) == fits
+        taken, declined = taken + fits, declined + (not fits)
+    assert taken and declined
+    routed(dims, BF16)
 
 
 @pytest.mark.parametrize("dtype,dims", [(BF16, (1, 1, 1, 30000, 30000, 1, 1, 1, 1)), (BF16, (1, 1, 1, 16384, 2 ** 15, 1, 8, 1, 1))])
