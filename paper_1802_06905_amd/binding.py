@@ -265,6 +265,8 @@ def cacnn_conv_forward(problem, dtype: int, image, filt, out, stream=None) -> No
     # The usual call: contiguous device tensors of the right element sizes.  Their lengths are checked by the library, which
     # enqueues nothing if it finds fault with the call; then, and for every other kind of operand, the checks below
     # tell what is wrong (17 comparisons and products in the interpreter took as long as the launch).
+    if type(dtype) is not int:
+        dtype = int(dtype)
     if type(problem) is Problem and type(image) is type(filt) is type(out) is _Tensor and image.is_cuda and filt.is_cuda and out.is_cuda \
             and out.dtype is _float32 and image.element_size() == filt.element_size() == _ESIZE.get(dtype) \
             and image.is_contiguous() and filt.is_contiguous() and out.is_contiguous():
@@ -372,6 +374,8 @@ def cacnn_pool_lower_bound(problem, M_words: float) -> PoolBound:
 def cacnn_pool_forward(problem, dtype: int, mode: int, image, out, stream=None) -> None:
     """Enqueue per-channel average (mode 0) or max (mode 1) pooling of Image[IW,IH,C,B] into Out[K=C,H,W,B] (fp32)."""
     # (as in cacnn_conv_forward)
+    if type(dtype) is not int:
+        dtype = int(dtype)
     if type(problem) is Problem and type(image) is type(out) is _Tensor and image.is_cuda and out.is_cuda and out.dtype is _float32 \
             and image.element_size() == _ESIZE.get(dtype) and image.is_contiguous() and out.is_contiguous():
         if _lib.cacnn_internal_pool_forward_sized(ctypes.byref(problem), dtype, int(mode), image.data_ptr(), image.numel(),
