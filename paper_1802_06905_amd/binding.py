@@ -211,6 +211,7 @@ def cacnn_tile_plan(problem, dtype: int, machine: Optional[Machine] = None) -> P
 
 _Tensor, _float32 = torch.Tensor, torch.float32
 _ESIZE = {CACNN_F32: 4, CACNN_BF16_F32ACC: 2}
+_ARGUMENT_ERRORS = (1, 2, 3)            # CACNN_ERR_NULL, CACNN_ERR_INVALID_ARG, CACNN_ERR_UNSUPPORTED
 
 
 def _ptr(t) -> int:
@@ -263,16 +264,20 @@ def cacnn_conv_forward(problem, dtype: int, image, filt, out, stream=None) -> No
     """Enqueue Out = conv(Image, Filter) on `stream` (torch stream, raw handle, or None = torch's current stream).
     image/filt/out are device tensors laid out Image[IW,IH,C,B], Filter[K,R,S,C], Out[K,H,W,B] (fp32)."""
     # The usual call: contiguous device tensors of the right element sizes.  Their lengths are checked by the library, which
-    # enqueues nothing if it finds fault with the call; then, and for every other kind of operand, the checks below
-    # tell what is wrong (17 comparisons and products in the interpreter took as long as the launch).
+    # enqueues nothing if it finds fault with an argument; then, and for every other kind of operand, the checks below
+    # tell what is wrong (17 comparisons and products in the interpreter took as long as the launch).  An error of the runtime or a
+    # missing device is final: the work may have been enqueued.
     if type(dtype) is not int:
         dtype = int(dtype)
     if type(problem) is Problem and type(image) is type(filt) is type(out) is _Tensor and image.is_cuda and filt.is_cuda and out.is_cuda \
             and out.dtype is _float32 and image.element_size() == filt.element_size() == _ESIZE.get(dtype) \
             and image.is_contiguous() and filt.is_contiguous() and out.is_contiguous():
-        if _lib.cacnn_internal_conv_forward_sized(ctypes.byref(problem), dtype, image.data_ptr(), image.numel(), filt.data_ptr(),
-                                                  filt.numel(), out.data_ptr(), out.numel(), _stream_handle(stream)) == 0:
+        rc = _lib.cacnn_internal_conv_forward_sized(ctypes.byref(problem), dtype, image.data_ptr(), image.numel(), filt.data_ptr(),
+                                                    filt.numel(), out.data_ptr(), out.numel(), _stream_handle(stream))
+        if rc == 0:
             return
+        if rc not in _ARGUMENT_ERRORS:
+            raise CacnnError(rc, "cacnn_conv_forward")
     prob = _as_problem(problem)
     _check_operands("cacnn_conv_forward", prob, dtype, image, filt, out)
     rc = _lib.cacnn_conv_forward(ctypes.byref(prob), int(dtype), _ptr(image), _ptr(filt), _ptr(out),
@@ -378,9 +383,12 @@ def cacnn_pool_forward(problem, dtype: int, mode: int, image, out, stream=None) 
         dtype = int(dtype)
     if type(problem) is Problem and type(image) is type(out) is _Tensor and image.is_cuda and out.is_cuda and out.dtype is _float32 \
             and image.element_size() == _ESIZE.get(dtype) and image.is_contiguous() and out.is_contiguous():
-        if _lib.cacnn_internal_pool_forward_sized(ctypes.byref(problem), dtype, int(mode), image.data_ptr(), image.numel(),
-                                                  out.data_ptr(), out.numel(), _stream_handle(stream)) == 0:
+        rc = _lib.cacnn_internal_pool_forward_sized(ctypes.byref(problem), dtype, int(mode), image.data_ptr(), image.numel(),
+                                                    out.data_ptr(), out.numel(), _stream_handle(stream))
+        if rc == 0:
             return
+        if rc not in _ARGUMENT_ERRORS:
+            raise CacnnError(rc, "cacnn_pool_forward")
     _check_operands("cacnn_pool_forward", _as_problem(problem), dtype, image, None, out, pooling=True)
     rc = _lib.cacnn_pool_forward(ctypes.byref(_as_problem(problem)), int(dtype), int(mode), _ptr(image), _ptr(out),
                                  _stream_handle(stream))

@@ -72,3 +72,21 @@ def test_dtype_may_be_whatever_int_accepts(library, call, dtype):
     lib = library()
     call(dtype, torch.bfloat16)
     assert len(lib.calls) == 1 and int(lib.calls[0][1][1]) == 1
+
+
+@pytest.mark.parametrize("call", [conv, pool])
+@pytest.mark.parametrize("status", [4, 5])
+def test_an_error_of_the_runtime_is_raised_and_nothing_is_enqueued_twice(library, call, status):
+    lib = library(status)
+    with pytest.raises(cc.CacnnError) as error:
+        call(0)
+    assert error.value.status == status and len(lib.calls) == 1
+
+
+@pytest.mark.parametrize("call", [conv, pool])
+@pytest.mark.parametrize("status", [2, 3])
+def test_an_argument_that_the_library_refuses_is_its_error(library, call, status):
+    library(status, status)
+    with pytest.raises(cc.CacnnError) as error:
+        call(0)
+    assert error.value.status == status
