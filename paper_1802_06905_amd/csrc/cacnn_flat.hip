@@ -391,15 +391,8 @@ __global__ void __launch_bounds__(WM* WN* WK * 64) conv_flat_kernel(const FlatAr
 template <int DT, int MB, int NG, int IM, int WM, int WN, int WK, int D, bool SHORT>
 static int launch_flat_one(const FlatArgs& a, int grid, void* stream) {
     constexpr size_t lds = FlatReduce<MB, NG, (IM < 0 ? -IM : IM), WM * WN, WK>::BYTES;
-    static_assert(lds <= 160 * 1024, "flat kernel: partial sums fit the LDS");
+    static_assert(lds <= 64 * 1024, "flat kernel: partial sums fit the LDS that a launch gets without asking");
     auto kernel = conv_flat_kernel<DT, MB, NG, IM, WM, WN, WK, D, SHORT>;
-    if constexpr (lds > 64 * 1024) {
-        static const bool ok = hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024) == hipSuccess;
-        if (!ok) {
-            (void)hipGetLastError();
-            return 1;
-        }
-    }
     hipLaunchKernelGGL(kernel, dim3(grid), dim3(WM * WN * WK * 64), lds, (hipStream_t)stream, a);
     return hipGetLastError() == hipSuccess ? 0 : 1;
 }
@@ -785,8 +778,11 @@ static int launch_flat_lds_as(const FlatArgs& a, int grid, void* stream) {
     using GEO = FlatLds<DT, MB, NBW, IM, WM, WN, WK, NCH>;
     auto kernel = conv_flat_lds_kernel<DT, MB, NBW, IM, WM, WN, WK, NCH, STREAM>;
     if constexpr (GEO::LDS > 64 * 1024) {
-        static const bool ok = hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024) == hipSuccess;
-        if (!ok) {
+        static OncePerDevice once;
+        int device = -1;
+        if (hipGetDevice(&device) != hipSuccess || !once(device, [&] {
+                return hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024) == hipSuccess;
+            })) {
             (void)hipGetLastError();
             return 1;
         }

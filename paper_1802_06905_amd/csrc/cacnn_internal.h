@@ -6,7 +6,23 @@
 #include <stddef.h>
 #include <stdint.h>
 
+#include <atomic>
+
 namespace cacnn {
+
+// Set-up that a process needs once for each device: done(device, set_up) calls set_up() until it has succeeded there.  A failure is not
+// remembered; threads that come at the same time may both set up.
+struct OncePerDevice {
+    std::atomic<uint64_t> devices{0};
+    template <class SetUp>
+    bool operator()(int device, SetUp set_up) {
+        const uint64_t bit = device >= 0 && device < 64 ? 1ull << device : 0;
+        if (devices.load(std::memory_order_acquire) & bit) return true;
+        if (!set_up()) return false;
+        devices.fetch_or(bit, std::memory_order_release);
+        return true;
+    }
+};
 
 // Division of small unsigned numbers by a run-time constant with one multiply-high.
 // Exact for n * d < 2^32 (the staged-tile indices it is used on are bounded by the LDS size).

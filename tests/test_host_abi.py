@@ -45,6 +45,35 @@ def test_struct_sizes_match_the_header():
                      ctypes.sizeof(cc.MachineL2), ctypes.sizeof(cc.L2Plan)]
 
 
+def run_cpp(src):
+    """Compile a program against the internal header and return what it prints."""
+    with tempfile.TemporaryDirectory() as d:
+        open(os.path.join(d, "t.cpp"), "w").write(src)
+        subprocess.run(["g++", "-std=c++17", "-O2", "-I", os.path.join(ROOT, "paper_1802_06905_amd", "csrc"),
+                        "-o", os.path.join(d, "t"), os.path.join(d, "t.cpp")], check=True)
+        return subprocess.run([os.path.join(d, "t")], capture_output=True, text=True, check=True).stdout
+
+
+def test_set_up_per_device_is_tried_again_after_a_failure():
+    """The dynamic-LDS limit of a kernel is raised once for each device; a failure must not stay for the life of the process."""
+    out = run_cpp(r'''
+    #include <cstdio>
+    #include "cacnn_internal.h"
+    int main() {
+      cacnn::OncePerDevice once;
+      int calls = 0;
+      auto with = [&](int device, bool result) {
+        const bool done = once(device, [&] { ++calls; return result; });
+        printf("%d%d ", done, calls);
+      };
+      with(0, false), with(0, true), with(0, false);       // done with the second attempt
+      with(3, false), with(3, true), with(3, false);       // another device has its own
+      with(64, true), with(64, false);                     // beyond the mask nothing is kept
+    }
+    ''')
+    assert out.split() == "01 12 12 03 14 14 15 06".split()
+
+
 def test_fastdiv_is_exact_over_its_domain():
     """The kernels divide staged-tile indices by run-time constants with one multiply-high; check the host-made
     magic numbers against plain division for every divisor up to 4096 over the index range an LDS tile can have."""
