@@ -442,8 +442,8 @@ struct FlatLds {
     static_assert(LDS <= 160 * 1024, "flat LDS kernel: LDS size");
 };
 
-// STREAM: Out past the L2, only where every store instruction writes whole cache lines; elsewhere the L2 has to put the pieces of a
-// line together.  One launch, buffers in rotation, through the L2 and past it: bf16 (16, 3, 64, 112, 112, 7 x 7, s 2) 21.4 and 20.6
+// STREAM: Out past the L2, only where every store instruction writes whole halves of cache lines; elsewhere the L2 has to put the pieces
+// together.  One launch, buffers in rotation, through the L2 and past it: bf16 (16, 3, 64, 112, 112, 7 x 7, s 2) 21.4 and 20.6
 // us, 32 images 48.2 and 36.8, (32, 3, 64, 112, 112, 3 x 3, s 2) 37.2 and 24.1, fp32 (12, 3, 16, 112, 112, 3 x 3, s 2) 12.5 and 11.9; of
 // pieces of lines, bf16 (20, 3, 64, 111, 111, 3 x 3, s 2) 21.7 and 33.0, (12, 64, 256, 57, 55, 1 x 1) 14.9 and 19.0.  A template
 // parameter because the compiler makes one ordinary store of the two sides of a branch.
@@ -791,12 +791,14 @@ static int launch_flat_lds_as(const FlatArgs& a, int grid, void* stream) {
     return hipGetLastError() == hipSuccess ? 0 : 1;
 }
 
-// Out is streamed where the 32 columns of a block are one cache line: a lane stores one image and none that another has (B a
-// multiple of IM), and the rows of Out are whole lines.
+// Out is streamed where the 32 columns of a block are one run of 128 bytes: a lane stores one image and none that another has (B a
+// multiple of IM), the rows of Out are whole lines, and Out starts at a multiple of 64 bytes, half a line.  At other addresses,
+// past the L2 and through it: bf16 (32, 3, 64, 112, 112, 7 x 7, s 2) 54.4 and 49.5 us, (32, 3, 64, 112, 112, 3 x 3, s 2) 51.3 and 39.2,
+// (64, 30, 64, 56, 56, 3 x 3) 28.3 and 30.6; 64 bytes beyond a line 40.3 and 49.9, 31.8 and 39.1, 26.4 and 30.3.
 template <int DT, int MB, int NBW, int IM, int WM, int WN, int WK, int NCH>
 static int launch_flat_lds(const FlatArgs& a, int grid, void* stream) {
     if constexpr (IM >= -1)
-        if (a.B % (IM > 0 ? IM : 1) == 0 && a.N % 32 == 0) return launch_flat_lds_as<DT, MB, NBW, IM, WM, WN, WK, NCH, true>(a, grid, stream);
+        if (a.B % (IM > 0 ? IM : 1) == 0 && a.N % 32 == 0 && reinterpret_cast<uintptr_t>(a.out) % 64 == 0) return launch_flat_lds_as<DT, MB, NBW, IM, WM, WN, WK, NCH, true>(a, grid, stream);
     return launch_flat_lds_as<DT, MB, NBW, IM, WM, WN, WK, NCH, false>(a, grid, stream);
 }
 

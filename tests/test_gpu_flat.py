@@ -32,14 +32,21 @@ def kernels(lib, dtype):
             yield i, abs(x[3]), x[3] < 0, x[7] > 0
 
 
-def run(env, cfg, img, flt, index, misalign=0):
+GUARD = 96      # words before and behind Out that a call must leave alone
+
+
+def run(env, cfg, img, flt, index, misalign=0, out_offset=0):
     cc, torch, lib = env
     d_img, d_flt = gu.upload(cfg, img, flt, torch, misalign=misalign)
-    out = torch.full((int(np.prod(cfg.out_shape)),), float("nan"), dtype=torch.float32, device="cuda:0")
+    n, first = int(np.prod(cfg.out_shape)), GUARD + out_offset
+    words = torch.full((first + n + GUARD,), -7.0, dtype=torch.float32, device="cuda:0")
+    out = words[first:first + n]
+    out.fill_(float("nan"))
     prob = cc.Problem(*cfg.dims)
     rc = lib.cacnn_internal_flat_forward(ctypes.byref(prob), gu.dtype_code(cfg), index, d_img.data_ptr(), d_flt.data_ptr(),
                                          out.data_ptr(), torch.cuda.current_stream().cuda_stream)
     torch.cuda.synchronize()
+    assert bool((words[:first] == -7.0).all()) and bool((words[first + n:] == -7.0).all()), (cfg.dims, index)
     return rc, out.cpu().numpy().reshape(cfg.out_shape)
 
 
@@ -106,8 +113,8 @@ def test_short_rows_and_single_steps(env, dtype, c, r, s):
     assert ran > 0
 
 
-# rows of Out that are whole cache lines, which the kernels that stage in LDS store past the L2: one line in all, K beyond a tile,
-# several tiles of positions with the last one partly filled
+# rows of Out that are whole cache lines, which the kernels that stage in LDS store past the L2 (where Out starts at a multiple of 64
+# bytes: words 0 and 16 behind a line, not 1): one line in all, K beyond a tile, several tiles of positions with the last one partly filled
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
 @pytest.mark.parametrize("shape", [(8, 5, 8, 4, 1, 1, 1, 1), (9, 65, 16, 10, 3, 3, 1, 1), (3, 33, 32, 33, 7, 7, 2, 2)], ids=lambda s: "x".join(map(str, s)))
 def test_streamed_output_of_staged_kernels(env, dtype, shape):
@@ -119,9 +126,10 @@ def test_streamed_output_of_staged_kernels(env, dtype, shape):
         img, flt = ci.make_inputs(cfg)
         ref, ab = gu.oracle_full(cfg, img, flt)
         print(f"[flat] kernel {index} {dtype} {cfg.dims}", flush=True)
-        rc, out = run(env, cfg, img, flt, index)
-        assert rc == 0
-        check(cfg, out, ref, ab, f"kernel {index}")
+        for out_offset in (0, 16, 1):
+            rc, out = run(env, cfg, img, flt, index, out_offset=out_offset)
+            assert rc == 0
+            check(cfg, out, ref, ab, f"kernel {index} out {out_offset}")
         ran += 1
     assert ran > 0
 
