@@ -35,10 +35,6 @@ typedef short fs16x4 __attribute__((ext_vector_type(4)));
 #define FLAT_LDS(T) __attribute__((address_space(3))) T
 typedef __bf16 fbf16x8 __attribute__((ext_vector_type(8)));
 
-__device__ __forceinline__ uint32_t flat_div(uint32_t n, const FlatDiv& d) {
-    return d.mul ? __umulhi(n, d.mul) >> d.shift : n;
-}
-
 // BYTES bytes (2, 4, 8 or 16) at any element-aligned address: base is wave-uniform, off the lane's
 typedef unsigned short fu16;
 struct __attribute__((packed, aligned(2))) Bytes4 {
@@ -173,12 +169,7 @@ __global__ void __launch_bounds__(WM* WN* WK * 64) conv_flat_kernel(const FlatAr
     const int wk = wave % WK, wm = (wave / WK) % WM, wn = wave / (WK * WM);
     const int j = lane & 31, g = lane >> 5;
 
-    // consecutive workgroups go to different XCDs: every XCD gets one contiguous run of the tile list
-    uint32_t t = blockIdx.x;
-    {
-        const uint32_t l = t >> 3, x = t & 7;
-        t = x * a.xcd_q + min(x, a.xcd_rem) + l;
-    }
+    const uint32_t t = xcd_order(blockIdx.x, a.xcd_shift, a.xcd_q, a.xcd_rem);
     uint32_t tk, tn;
     {
         const uint32_t q = flat_div(t, a.d_inner), i = t - q * a.inner;
@@ -462,11 +453,7 @@ __global__ void __launch_bounds__(WM* WN* WK * 64) conv_flat_lds_kernel(const Fl
     const int wk = wave % WK, wm = (wave / WK) % WM, wn = wave / (WK * WM);
     const int j = lane & 31, g = lane >> 5;
 
-    uint32_t t = blockIdx.x;
-    {
-        const uint32_t l = t >> 3, x = t & 7;
-        t = x * a.xcd_q + min(x, a.xcd_rem) + l;
-    }
+    const uint32_t t = xcd_order(blockIdx.x, a.xcd_shift, a.xcd_q, a.xcd_rem);
     uint32_t tk, tn;
     {
         const uint32_t q = flat_div(t, a.d_inner), i = t - q * a.inner;

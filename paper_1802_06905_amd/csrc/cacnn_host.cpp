@@ -1146,7 +1146,7 @@ double flat_us(const cacnn_problem& p, int dtype, const FlatInfo& v) {
     const int esz = f32 ? 4 : 2, ch = 16 / esz, ipl = run ? -v.IM : v.IM;
     const int64_t T = p.S * p.C, chunks = p.R * ceil_div(T, ch);
     const int64_t groups = p.H * p.W * (run ? 1 : ceil_div(p.B, ipl));
-    const double per_cu = std::ceil((double)ceil_div(p.K, v.KT()) * (double)ceil_div(groups, v.GT()) / 256.0);
+    const double per_cu = std::ceil((double)ceil_div(p.K, v.KT()) * (double)ceil_div(groups, v.GT()) / (double)kDefaultMachine.num_cu);
     const double waves = v.WM * v.WN * v.WK, simd_waves = std::ceil(waves / 4.0), mfma = f32 ? 256.0 : 32.0;   // of one block's step
     const double blocks = v.MB * v.NG * (run || !v.NCH ? ipl : 1);                                            // of one wave
     const bool flt_aligned = f32 || T % 2 == 0, img_aligned = f32 || (run ? p.C * p.B : p.B) % 2 == 0;
@@ -1244,8 +1244,9 @@ int prepare_flat(const cacnn_problem& p, int dtype, int fi, Launch* out) {
     const int64_t grid = tiles_k * tiles_n;
     a.k_inner = img >= flt ? 1u : 0u;
     a.inner = (uint32_t)(a.k_inner ? tiles_k : tiles_n);
-    a.xcd_q = (uint32_t)grid / 8;
-    a.xcd_rem = (uint32_t)grid % 8;
+    while (2 << a.xcd_shift <= xcd_count()) ++a.xcd_shift;      // (a power of two XCDs at most that many)
+    a.xcd_q = (uint32_t)grid >> a.xcd_shift;
+    a.xcd_rem = (uint32_t)grid & ((1u << a.xcd_shift) - 1);
     a.d_G = make_flatdiv(a.G);
     a.d_W = make_flatdiv((uint32_t)p.W);
     a.d_TC = make_flatdiv(a.TC);

@@ -74,6 +74,41 @@ def test_set_up_per_device_is_tried_again_after_a_failure():
     assert out.split() == "01 12 12 03 14 14 15 06".split()
 
 
+def test_flattened_kernels_division_and_tile_order():
+    """The division that the flattened kernels decode positions with, for any dividend below 2^31, and the order of the tiles: whatever the
+    number of XCDs and of tiles, every tile is taken once and the workgroups of an XCD take consecutive ones."""
+    out = run_cpp(r'''
+    #include <cstdio>
+    #include <vector>
+    #include "cacnn_internal.h"
+    using namespace cacnn;
+    int main() {
+      uint64_t state = 1;
+      for (uint32_t i = 0; i < 40000; ++i) {
+        state = state * 6364136223846793005ull + 1442695040888963407ull;
+        const uint32_t d = i < 5000 ? i + 1 : (uint32_t)(state >> 33) >> (i % 31) | 1;
+        const FlatDiv f = make_flatdiv(d);
+        const uint32_t top = 2147483647u, near = top / d * d;
+        for (uint32_t n : {0u, 1u, d - 1, d, d + 1, 2 * (uint64_t)d < top ? 2 * d - 1 : d, near, near - 1, top, top - 1, (uint32_t)(state >> 34)})
+          if (n <= top && flat_div(n, f) != n / d) { printf("bad %u / %u\n", n, d); return 0; }
+      }
+      for (uint32_t shift = 0; shift <= 6; ++shift)
+        for (uint32_t grid : {1u, 2u, 7u, 8u, 9u, 63u, 64u, 65u, 1000u}) {
+          const uint32_t xcds = 1u << shift;
+          std::vector<int> seen(grid, 0);
+          for (uint32_t wg = 0; wg < grid; ++wg) {
+            const uint32_t t = xcd_order(wg, shift, grid / xcds, grid % xcds);
+            if (t >= grid || seen[t]++ || (wg >= xcds && t != xcd_order(wg - xcds, shift, grid / xcds, grid % xcds) + 1)) {
+              printf("bad order %u %u %u\n", xcds, grid, wg); return 0;
+            }
+          }
+        }
+      printf("fine\n");
+    }
+    ''')
+    assert out.strip() == "fine"
+
+
 def test_fastdiv_is_exact_over_its_domain():
     """The kernels divide staged-tile indices by run-time constants with one multiply-high; check the host-made
     magic numbers against plain division for every divisor up to 4096 over the index range an LDS tile can have."""
