@@ -26,6 +26,24 @@ def say(msg):
     sys.stdout.flush()
 
 
+def family(name):
+    """Kernel family of a name as cacnn_variant_name and routed_kernel give it: fxd, ws, pipe, ..., flat, or one-tile."""
+    tag = name.split()[1]
+    return "one-tile" if tag.startswith("k") else tag
+
+
+def run_planned_and_routed(cc, torch, cfg, img, flt, ref, ab):
+    """The planned variant, and what cacnn_conv_forward launches where that is another kernel, each against the oracle; the names of both."""
+    from paper_1802_06905_amd import binding
+    dt = gu.dtype_code(cfg)
+    plan = cc.cacnn_tile_plan(cfg.dims, dt)
+    planned, routed = cc.cacnn_variant_name(plan.variant), binding.routed_kernel(cfg.dims, dt)[0]
+    say(f"[parity] {cfg.name} {cfg.dtype} {cfg.dims} planned {planned} [{plan.b_c} {plan.b_r} {plan.b_s}], routed {routed}")
+    gu.assert_parity(cfg, gu.run_gpu(cc, torch, cfg, img, flt, plan=plan), ref, ab, planned)
+    gu.assert_parity(cfg, gu.run_gpu(cc, torch, cfg, img, flt), ref, ab, routed)
+    return planned, routed
+
+
 @pytest.mark.parametrize("name", ["c1", "c2", "c3", "c4", "c5"])
 def test_benchmark_shape_full_array(env, name):
     """The five benchmark shapes at full size, in the launch configuration the benchmark times (planner's choice),
@@ -52,19 +70,15 @@ LAYERS = [("bf16", 128, 256, 384, 13, 13, 3, 3, 1, 1), ("bf16", 64, 256, 512, 14
 
 @pytest.mark.parametrize("layer", LAYERS, ids=["x".join(str(v) for v in l) for l in LAYERS])
 def test_whole_layers_on_the_fixed_geometry_kernels(env, layer):
-    """Whole layers at ordinary sizes through cacnn_conv_forward: the planner gives them a fixed-geometry kernel, and every
-    output element agrees with the oracle (tiles that overhang Out in w, h, k or b; strided staging)."""
+    """Whole layers at ordinary sizes on the planned variant and through cacnn_conv_forward: the planner gives them a fixed-geometry kernel, and
+    every output element agrees with the oracle (tiles that overhang Out in w, h, k or b; strided staging)."""
     cc, torch = env
     dtype, dims = layer[0], layer[1:]
     cfg = ci.custom("layer", *dims, dtype=dtype, dist="normal", seed=61)
-    plan = cc.cacnn_tile_plan(cfg.dims, gu.dtype_code(cfg))
-    name = cc.cacnn_variant_name(plan.variant)
-    say(f"[parity] layer {layer} planner's kernel '{name}' grid {plan.grid[0]}")
-    assert " fx" in name, name
     img, flt = ci.make_inputs(cfg)
-    out = gu.run_gpu(cc, torch, cfg, img, flt)
     ref, ab = gu.oracle_full(cfg, img, flt)
-    gu.assert_parity(cfg, out, ref, ab, f"layer {layer}")
+    planned, _ = run_planned_and_routed(cc, torch, cfg, img, flt, ref, ab)
+    assert " fx" in planned, planned
 
 
 # shapes that span several tiles with ragged tails in every dimension, strides, asymmetric filters
@@ -296,6 +310,17 @@ def test_unaligned_pointers_take_the_scalar_paths(env, dtype):
     say(f"[parity] unaligned {dtype}")
     out = gu.run_gpu(cc, torch, cfg, img, flt, misalign=1)
     gu.assert_parity(cfg, out, ref, ab, "misaligned by one element")
+    # cacnn_conv_forward runs a flattened kernel; the scalar paths are those of the one-tile variants
+    ran = 0
+    for vi in range(cc.cacnn_variant_count()):
+        name = cc.cacnn_variant_name(vi)
+        if not name.startswith(dtype) or family(name) != "one-tile":
+            continue
+        plan, _ = cc.cacnn_plan_variant(cfg.dims, gu.dtype_code(cfg), vi)
+        say(f"[parity] unaligned {name}")
+        gu.assert_parity(cfg, gu.run_gpu(cc, torch, cfg, img, flt, plan=plan, misalign=1), ref, ab, name)
+        ran += 1
+    assert ran >= 2
 
 
 def test_runs_on_a_side_stream_and_overwrites_out(env):
@@ -320,15 +345,15 @@ def test_nonfinite_inputs_stay_local(env):
         cfg = ci.custom("inf", 2, 3, 5, 6, 5, 3, 3, 1, 1, dtype=dtype, dist="normal", seed=13)
         img, flt = ci.make_inputs(cfg)
         img[4, 3, 1, 0] = np.inf
-        say(f"[parity] inf {dtype}")
-        out = gu.run_gpu(cc, torch, cfg, img, flt)
-        bad = ~np.isfinite(out)
         want = np.zeros(cfg.out_shape, bool)
         for w in range(cfg.W):
             for h in range(cfg.H):
                 if 0 <= 4 - w < cfg.R and 0 <= 3 - h < cfg.S:
                     want[:, h, w, 0] = True
-        assert np.array_equal(bad, want)
+        for plan in (None, cc.cacnn_tile_plan(cfg.dims, gu.dtype_code(cfg))):
+            say(f"[parity] inf {dtype} {'routed' if plan is None else 'planned'}")
+            out = gu.run_gpu(cc, torch, cfg, img, flt, plan=plan)
+            assert np.array_equal(~np.isfinite(out), want)
 
 
 def fixed_geometry_case(name):
@@ -505,6 +530,14 @@ def test_tuned_plan_is_correct(env, dtype):
     gu.assert_parity(cfg, d_out.cpu().numpy().reshape(cfg.out_shape), ref, ab, "out after cacnn_tune")
     say(f"[tune] {dtype}: planned '{cc.cacnn_variant_name(planned.variant)}' {t_planned * 1e3:.1f} us, "
         f"tuned '{cc.cacnn_variant_name(tuned.variant)}' b_c={tuned.b_c} b_r={tuned.b_r} b_s={tuned.b_s}")
+    # what is remembered is the returned variant, or a flattened kernel that was faster still
+    from paper_1802_06905_amd import binding
+    remembered = binding.routed_kernel(cfg.dims, dt, d_img.data_ptr(), d_flt.data_ptr())[0]
+    assert remembered == cc.cacnn_variant_name(tuned.variant) or family(remembered) == "flat", remembered
+    d_out.fill_(float("nan"))
+    cc.cacnn_conv_forward_with_plan(cfg.dims, dt, tuned, d_img, d_flt, d_out)
+    torch.cuda.synchronize()
+    gu.assert_parity(cfg, d_out.cpu().numpy().reshape(cfg.out_shape), ref, ab, "the tuned plan")
     d_out.fill_(float("nan"))
     t_tuned = timed()
     gu.assert_parity(cfg, d_out.cpu().numpy().reshape(cfg.out_shape), ref, ab, "cacnn_conv_forward after cacnn_tune")
@@ -523,16 +556,22 @@ def test_launches_can_be_captured_in_a_graph_and_replayed(env):
     n_out = int(np.prod(cfg.out_shape))
     eager = torch.full((n_out,), float("nan"), dtype=torch.float32, device="cuda:0")
     cc.cacnn_conv_forward(cfg.dims, 0, d_img, d_flt, eager)          # also plans and sets the kernel up outside the capture
+    plan, planned = cc.cacnn_tile_plan(cfg.dims, 0), torch.full_like(eager, float("nan"))    # (the planned variant is another kernel)
+    cc.cacnn_conv_forward_with_plan(cfg.dims, 0, plan, d_img, d_flt, planned)
     torch.cuda.synchronize()
     gu.assert_parity(cfg, eager.cpu().numpy().reshape(cfg.out_shape), ref, ab, "eager")
+    gu.assert_parity(cfg, planned.cpu().numpy().reshape(cfg.out_shape), ref, ab, "eager, planned variant")
     outs = [torch.full((n_out,), float("nan"), dtype=torch.float32, device="cuda:0") for _ in range(4)]
     side = torch.cuda.Stream()
     side.wait_stream(torch.cuda.current_stream())
     graph = torch.cuda.CUDAGraph()
     with torch.cuda.stream(side):
         with torch.cuda.graph(graph, stream=side):
-            for o in outs:
-                cc.cacnn_conv_forward(cfg.dims, 0, d_img, d_flt, o)
+            for i, o in enumerate(outs):
+                if i % 2 == 0:
+                    cc.cacnn_conv_forward(cfg.dims, 0, d_img, d_flt, o)
+                else:
+                    cc.cacnn_conv_forward_with_plan(cfg.dims, 0, plan, d_img, d_flt, o)
     torch.cuda.synchronize()
     for rep in range(3):
         for o in outs:
@@ -541,37 +580,35 @@ def test_launches_can_be_captured_in_a_graph_and_replayed(env):
         graph.replay()
         torch.cuda.synchronize()
         for i, o in enumerate(outs):
-            assert torch.equal(o, eager), f"replay {rep}, launch {i}"
+            assert torch.equal(o, planned if i % 2 else eager), f"replay {rep}, launch {i}"
 
 
 def test_planner_picks_on_mid_size_layers(env):
-    """cacnn_conv_forward with the planner's own choice on the mid-size and ragged layers the cost model is fitted on
-    and judged by (bench.py's two lists): whatever generic kernel and contraction tile the fitted model picks, the
+    """The planner's own choice and what cacnn_conv_forward makes of it on the mid-size and ragged layers the cost model is fitted on
+    and judged by (bench.py's two lists): whatever kernel and contraction tile the fitted model picks, the
     result is the oracle's."""
     import bench
     cc, torch = env
-    picked = set()
+    planned, routed = set(), set()
     for sh in bench.PLANNER_SHAPES + bench.CALIBRATION_SHAPES:
         dtype, dims = sh[0], sh[1:]
         cfg = ci.custom("mid", *dims, dtype=dtype, dist="normal", seed=21)
-        plan = cc.cacnn_tile_plan(dims, 0 if dtype == "f32" else 1)
-        vname = cc.cacnn_variant_name(plan.variant)
-        say(f"[parity] mid-size {dtype} {dims} -> {vname} [{plan.b_c} {plan.b_r} {plan.b_s}]")
         img, flt = ci.make_inputs(cfg)
-        out = gu.run_gpu(cc, torch, cfg, img, flt)
         ref, ab = gu.oracle_full(cfg, img, flt)
-        gu.assert_parity(cfg, out, ref, ab, vname)
-        picked.add(vname.split()[1] if not vname.split()[1].startswith("k") else "one-tile")
-    assert len(picked) >= 3, picked          # the layers exercise several kernel families
+        names = run_planned_and_routed(cc, torch, cfg, img, flt, ref, ab)
+        planned.add(family(names[0]))
+        routed.add(family(names[1]))
+    assert len(planned) >= 3, planned          # the layers exercise several kernel families
+    assert "flat" in routed and len(routed) >= 2, routed
 
 
 def test_planner_path_on_random_shapes(env):
     """Seeded random problems (both dtypes; batch, channel, image and filter sizes from lists that include 1, primes and
-    the kernels' tile sizes; strides up to 3) through cacnn_conv_forward with the planner's own choice, against the oracle."""
+    the kernels' tile sizes; strides up to 3) with the planner's own choice and through cacnn_conv_forward, against the oracle."""
     import random
     cc, torch = env
     rng = random.Random(20260)
-    done, families = 0, set()
+    done, planned, routed = 0, set(), set()
     while done < 60:
         dtype = rng.choice(["f32", "bf16"])
         dims = (rng.choice([1, 2, 3, 5, 8, 16, 24, 32, 40, 64, 96, 128]), rng.choice([1, 3, 4, 8, 16, 24, 32, 48, 64, 96, 128, 200, 256]),
@@ -582,13 +619,11 @@ def test_planner_path_on_random_shapes(env):
         if macs > 6e9 or (done % 2 == 1 and macs < 1e8):      # every other one is a mid-size problem
             continue
         cfg = ci.custom("rnd", *dims, dtype=dtype, dist="normal", seed=3000 + done)
-        plan = cc.cacnn_tile_plan(dims, 0 if dtype == "f32" else 1)
-        vname = cc.cacnn_variant_name(plan.variant)
-        say(f"[parity] random {done} {dtype} {dims} -> {vname} [{plan.b_c} {plan.b_r} {plan.b_s}]")
         img, flt = ci.make_inputs(cfg)
-        out = gu.run_gpu(cc, torch, cfg, img, flt)
         ref, ab = gu.oracle_full(cfg, img, flt)
-        gu.assert_parity(cfg, out, ref, ab, vname)
-        families.add(vname.split()[1] if not vname.split()[1].startswith("k") else "one-tile")
+        names = run_planned_and_routed(cc, torch, cfg, img, flt, ref, ab)
+        planned.add(family(names[0]))
+        routed.add(family(names[1]))
         done += 1
-    assert len(families) >= 3, families
+    assert len(planned) >= 3, planned
+    assert "flat" in routed and len(routed) >= 3, routed
