@@ -244,17 +244,19 @@ def shape_report(cc, cfg, sec):
         b = cc.cacnn_lower_bound(cfg.dims, fast_bytes / esz)
         return max(4 * b.term[0], esz * max(b.term[1:]))
     lb_bytes = bound_bytes(LDS_BYTES)
-    vname = cc.cacnn_variant_name(plan.variant)
-    hbm = committed_traffic(cfg.name, vname, plan.xcd_split_k)
+    # what was timed: the planned variant, or a kernel with flattened positions, which no plan describes
+    vname, grid, _ = cc.binding.routed_kernel(cfg.dims, dt)
+    planned = vname == cc.cacnn_variant_name(plan.variant)
+    hbm = committed_traffic(cfg.name, vname, plan.xcd_split_k if planned else 0)
     F = float(cfg.macs)
     M_lds = LDS_BYTES / esz
-    staged = esz * (plan.predicted_words - n_out) + 4 * n_out
+    staged = esz * (plan.predicted_words - n_out) + 4 * n_out if planned else None
 
     def xcd_level_bound_bytes():
         # Two levels: an LDS tile inside an XCD's share.  The HBM-side bytes are the misses of eight 4 MiB L2s, so the
         # bound that applies to them is Section 7's (eight processors, M = one L2) for the division the launch uses:
         # a_K groups of output channels x 8 / a_K ranges of positions (only the product a_B a_W a_H enters the bound)
-        ak = max(1, plan.xcd_split_k)
+        ak = max(1, plan.xcd_split_k) if planned else 1
         rest, a = 8 // ak, [1, ak, 1, 1]
         for i, extent in ((0, cfg.B), (3, cfg.H), (2, cfg.W)):
             f = 1
@@ -277,13 +279,14 @@ def shape_report(cc, cfg, sec):
         "xcd_division_a_B_a_K_a_W_a_H": xcd_div, "paper_parallel_bound_bytes_8_xcds_M_l2": xcd_bound,
         "hbm_bytes_over_parallel_bound": (hbm / xcd_bound) if hbm else None,
         # global -> LDS bytes of the launched schedule plus Out once (cacnn_plan.predicted_words, in bytes): the traffic
-        # the paper's model counts at M = LDS, against Theorem 1 and against matmul-style reuse F / sqrt(M) (Section 1)
+        # the paper's model counts at M = LDS, against Theorem 1 and against matmul-style reuse F / sqrt(M) (Section 1); none for a
+        # kernel with flattened positions
         "planned_staged_bytes": staged,
-        "staged_bytes_over_bound_at_M_lds": staged / lb_bytes,
+        "staged_bytes_over_bound_at_M_lds": staged / lb_bytes if planned else None,
         "matmul_reuse_bytes_at_M_lds": esz * F / M_lds ** 0.5,
-        "staged_bytes_over_matmul_reuse": staged / (esz * F / M_lds ** 0.5),
-        "variant": vname, "grid": plan.grid[0], "lds_bytes": plan.lds_bytes_used,
-        "b_c": plan.b_c, "hbm_bytes_recorded": hbm,
+        "staged_bytes_over_matmul_reuse": staged / (esz * F / M_lds ** 0.5) if planned else None,
+        "variant": vname, "grid": grid, "lds_bytes": plan.lds_bytes_used if planned else None,
+        "b_c": plan.b_c if planned else None, "hbm_bytes_recorded": hbm,
     }
 
 
@@ -360,7 +363,7 @@ def cpu_baseline(cfg, img, flt, np):
 def traffic_probe(cc, torch, ci, np, cfg, xcd_split_k=0, xcd_walk=0):
     """Dispatch sequence for the HBM-traffic counters (FETCH_SIZE / WRITE_SIZE, KiB per dispatch):
     a plain copy of known size to scale the counters by, then the workload cold (caches evicted) and warm.
-    xcd_split_k > 0 forces that division of the XCDs over the output channels (0: the planner's)."""
+    xcd_split_k > 0 forces that division of the XCDs over the output channels on the planned variant (0: what cacnn_conv_forward runs)."""
     n = 512 * 1024 * 1024
     src = torch.empty(n, dtype=torch.uint8, device="cuda:0").fill_(1)
     dst = torch.empty(n, dtype=torch.uint8, device="cuda:0")
@@ -379,15 +382,20 @@ def traffic_probe(cc, torch, ci, np, cfg, xcd_split_k=0, xcd_walk=0):
     evict = torch.empty(1024 * 1024 * 1024, dtype=torch.uint8, device="cuda:0").fill_(3)   # push everything out
     torch.cuda.synchronize()
     plan = cc.cacnn_tile_plan(cfg.dims, dt)
+    variant = cc.cacnn_variant_name(plan.variant)
     if xcd_split_k:
         plan.xcd_split_k, plan.xcd_walk = xcd_split_k, xcd_walk
-    cc.cacnn_conv_forward_with_plan(cfg.dims, dt, plan, d_img, d_flt, d_out)      # cold
-    torch.cuda.synchronize()
-    cc.cacnn_conv_forward_with_plan(cfg.dims, dt, plan, d_img, d_flt, d_out)      # warm
-    torch.cuda.synchronize()
+    elif cc.binding.routed_kernel(cfg.dims, dt)[0] != variant:
+        variant, plan.xcd_split_k, plan.xcd_walk = cc.binding.routed_kernel(cfg.dims, dt)[0], 0, 0
+    for _ in ("cold", "warm"):
+        if plan.xcd_split_k:
+            cc.cacnn_conv_forward_with_plan(cfg.dims, dt, plan, d_img, d_flt, d_out)
+        else:
+            cc.cacnn_conv_forward(cfg.dims, dt, d_img, d_flt, d_out)
+        torch.cuda.synchronize()
     del evict
     print(json.dumps({"traffic_probe": cfg.name, "copy_bytes_each_way": n, "xcd_split_k": plan.xcd_split_k,
-                      "xcd_walk": plan.xcd_walk, "variant": cc.cacnn_variant_name(plan.variant)}))
+                      "xcd_walk": plan.xcd_walk, "variant": variant}))
 
 
 def division_report(cc, torch, ci, np, cfg, steps, warmup):
@@ -464,22 +472,24 @@ def pool_traffic_probe(cc, torch, ci, np, cfg):
 
 def pooling_report(cc, torch, ci, np, steps, warmup, with_cpu):
     """The pooling path (Section 6 of the paper) on its workload p1, max and average: HBM-bound, so the figure is
-    compulsory bytes (Image once + Out once) over time against the published HBM peak, with the oracle timed beside it."""
+    compulsory bytes (Image once + Out once) over time against the published HBM peak, with the oracle timed beside it.
+    Five sets of buffers in rotation, 650 MB: one set alone would stay in the 256 MB last-level cache from one launch to the next."""
     cfg = ci.POOL_CONFIGS["p1"]
     img, _ = ci.make_inputs(cfg)
-    d_img = torch.from_numpy(img.reshape(-1)).cuda()
-    d_out = torch.empty(int(np.prod(cfg.out_shape)), dtype=torch.float32, device="cuda:0")
+    d_imgs = [torch.from_numpy(img.reshape(-1)).cuda() for _ in range(5)]
+    d_outs = [torch.empty(int(np.prod(cfg.out_shape)), dtype=torch.float32, device="cuda:0") for _ in d_imgs]
+    d_out = d_outs[0]
     nbytes = 4 * (int(np.prod(cfg.image_shape)) + int(np.prod(cfg.out_shape)))
     rep = {"workload": f"p1: B={cfg.B} C=K={cfg.C} W=H={cfg.W} R=S={cfg.R} sigma={cfg.sigma_w} f32",
            "compulsory_bytes": nbytes, "bound": "hbm", "peak_GBps": HBM_PEAK_GBS}
     for mode, code in (("max", 1), ("avg", 0)):
-        for _ in range(warmup):
-            cc.cacnn_pool_forward(cfg.dims, 0, code, d_img, d_out)
+        for i in range(max(warmup, 5)):
+            cc.cacnn_pool_forward(cfg.dims, 0, code, d_imgs[i % 5], d_outs[i % 5])
         torch.cuda.synchronize()
         e0, e1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
         e0.record()
-        for _ in range(steps):
-            cc.cacnn_pool_forward(cfg.dims, 0, code, d_img, d_out)
+        for i in range(steps):
+            cc.cacnn_pool_forward(cfg.dims, 0, code, d_imgs[i % 5], d_outs[i % 5])
         e1.record()
         torch.cuda.synchronize()
         sec = e0.elapsed_time(e1) / steps * 1e-3
