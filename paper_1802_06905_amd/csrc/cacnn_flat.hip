@@ -11,7 +11,7 @@
 // Two kernels.  The first takes every operand from global memory (L1 and L2 hold the windows' overlap) straight to the
 // registers of the wave that multiplies it, several steps ahead, with no barrier.  It is bound by the compute unit's
 // address unit: a load whose 64 lanes fall into many cache lines takes about a clock for each of them, which is why a lane
-// loads several images or several channels at once where it can.  The second stages both operands in LDS with loads that
+// loads several images at once where it can.  The second stages both operands in LDS with loads that
 // run along memory, so that the address unit sees each byte of a tile once (it moves 64 bytes a clock then) instead of once
 // per wave in pieces of 32 bytes: 1.2 to 3 times faster for bf16, whose products are short, level for fp32.
 // Where there are few tiles the waves of a workgroup divide the contraction and add up in LDS at the end.
@@ -143,9 +143,7 @@ __device__ __forceinline__ void flat_write_out(float* s_red, ff32x16 (&acc)[MB][
     }
 }
 
-// IM > 0: a lane holds IM adjacent images of a position and loads them one contraction index at a time.
-// IM < 0: there are -IM images in all; a lane holds all of them and loads 16 bytes at a time, in which the images of a
-// channel are neighbours and the channels follow each other.
+// A lane holds IM adjacent images of a position and loads them one contraction index at a time.
 // SHORT: a filter row (T = S*C indices) is shorter than a chunk, which is one r then; only the T elements that exist are loaded, the
 // others stay zero.
 // AHEAD: steps whose loads are in flight.  0, for short rows and for waves of one step at most: every load is of a step that is
@@ -156,11 +154,10 @@ __device__ __forceinline__ void flat_write_out(float* s_red, ff32x16 (&acc)[MB][
 template <int DT, int MB, int NG, int IM, int WM, int WN, int WK, int AHEAD, bool SHORT>
 __global__ void __launch_bounds__(WM* WN* WK * 64) conv_flat_kernel(const FlatArgs a) {
     constexpr int ESZ = DT == 0 ? 4 : 2, CH = 16 / ESZ;
-    constexpr bool RUN = IM < 0;                       // 16-byte loads along the contraction
-    constexpr int IPL = RUN ? -IM : IM, NB = NG * IPL; // images per lane, column blocks per wave
-    static_assert(!SHORT || (!RUN && AHEAD == 0), "flat kernel: a run of 16 bytes needs a filter row that long");
-    constexpr int LW = RUN ? 4 : (IPL * ESZ + 3) / 4;  // dwords of one Image load
-    constexpr int LE = RUN ? IPL : CH;                 // Image loads per chunk
+    static_assert(IM == 1 || IM == 2 || IM == 4, "flat kernel: images per lane that one load and one store take");
+    static_assert(!SHORT || AHEAD == 0, "flat kernel: short rows have no steps ahead");
+    constexpr int NB = NG * IM;                        // column blocks per wave
+    constexpr int LW = (IM * ESZ + 3) / 4;             // dwords of one Image load
     constexpr int D = AHEAD ? AHEAD : 1;               // steps of operands in registers
     extern __shared__ __align__(16) float s_red[];
 
@@ -179,18 +176,18 @@ __global__ void __launch_bounds__(WM* WN* WK * 64) conv_flat_kernel(const FlatAr
     const uint32_t k0 = (tk * WM + wm) * (MB * 32), q0 = (tn * WN + wn) * (NG * 32);
 
     uint32_t aoff[MB], boff[NG], opos[NG];
-    int skip[NG];                                      // images of the lane that its left neighbour has as well; IPL: nothing to store
+    int skip[NG];                                      // images of the lane that its left neighbour has as well; IM: nothing to store
 #pragma unroll
     for (int m = 0; m < MB; ++m) aoff[m] = min(k0 + m * 32 + j, a.K - 1) * a.flt_row;
 #pragma unroll
     for (int p = 0; p < NG; ++p) {
         const uint32_t q = min(q0 + p * 32 + j, a.groups - 1);
-        const uint32_t hw = RUN ? q : flat_div(q, a.d_G), first = RUN ? 0 : (q - hw * a.G) * IPL;
-        const uint32_t b = RUN ? 0 : min(first, a.B - IPL);
+        const uint32_t hw = flat_div(q, a.d_G), first = (q - hw * a.G) * IM;
+        const uint32_t b = min(first, a.B - IM);
         const uint32_t h = flat_div(hw, a.d_W), w = hw - h * a.W;
         boff[p] = w * a.img_w + h * a.img_h + b * ESZ;
         opos[p] = hw * a.B + b;
-        skip[p] = q0 + p * 32 + j < a.groups ? (int)(first - b) : IPL;
+        skip[p] = q0 + p * 32 + j < a.groups ? (int)(first - b) : IM;
     }
 
     const uint32_t eoff = a.B * ESZ;                   // bytes from one contraction index to the next
@@ -205,7 +202,7 @@ __global__ void __launch_bounds__(WM* WN* WK * 64) conv_flat_kernel(const FlatAr
     uint32_t foff = r * a.flt_r + tc * 16, ioff = r * a.img_r + tc * a.img_chunk;
 
     uint32_t A[D][MB][SHORT ? CH : 4];
-    uint32_t X[D][NG][LE][LW];
+    uint32_t X[D][NG][CH][LW];
     uint32_t lo[D];
 
     auto fetch = [&](int d) {
@@ -230,10 +227,8 @@ __global__ void __launch_bounds__(WM* WN* WK * 64) conv_flat_kernel(const FlatAr
         for (int p = 0; p < NG; ++p) {
             const uint32_t vo = boff[p] + io;
 #pragma unroll
-            for (int e = 0; e < LE; ++e) {
-                if constexpr (RUN) load_at<16>(X[d][p][e], (const char*)a.image + e * 16, vo);
-                else if (!SHORT || (uint32_t)e < a.T) load_image<IPL * ESZ>(X[d][p][e], rimg, vo, e * eoff);
-            }
+            for (int e = 0; e < CH; ++e)
+                if (!SHORT || (uint32_t)e < a.T) load_image<IM * ESZ>(X[d][p][e], rimg, vo, e * eoff);
         }
         // the half-wave's chunk of the next step lies two chunks further on
         u += 2;
@@ -265,24 +260,13 @@ __global__ void __launch_bounds__(WM* WN* WK * 64) conv_flat_kernel(const FlatAr
 #pragma unroll
         for (int p = 0; p < NG; ++p)
 #pragma unroll
-            for (int q = 0; q < IPL; ++q)
+            for (int q = 0; q < IM; ++q)
 #pragma unroll
                 for (int i = 0; i < 4; ++i) {
                     uint32_t v;
-                    if constexpr (DT == 0) {
-                        v = RUN ? X[d][p][(i * IPL + q) / 4 % LE][(i * IPL + q) % 4 % LW] : X[d][p][i % LE][q % LW];
-                    } else if constexpr (RUN) {
-                        // images q of channels 2 i and 2 i + 1: the half-words e0, e1 of the run
-                        const int e0 = 2 * i * IPL + q, e1 = e0 + IPL;
-                        v = IPL == 1 ? X[d][p][0][i]
-                                     : __builtin_amdgcn_perm(X[d][p][e1 / 8 % LE][e1 / 2 % 4], X[d][p][e0 / 8 % LE][e0 / 2 % 4],
-                                                             (e1 & 1 ? 0x07060000u : 0x05040000u) | (e0 & 1 ? 0x0302u : 0x0100u));
-                    } else if constexpr (IPL == 1) {
-                        v = __builtin_amdgcn_perm(X[d][p][(2 * i + 1) % LE][0], X[d][p][2 * i % LE][0], 0x05040100u);
-                    } else {
-                        v = __builtin_amdgcn_perm(X[d][p][(2 * i + 1) % LE][q / 2], X[d][p][2 * i % LE][q / 2], q & 1 ? 0x07060302u : 0x05040100u);
-                    }
-                    bv[p * IPL + q][i] = v;
+                    if constexpr (DT == 0) v = X[d][p][i % CH][q % LW];
+                    else v = __builtin_amdgcn_perm(X[d][p][(2 * i + 1) % CH][q / 2 % LW], X[d][p][2 * i % CH][q / 2 % LW], q & 1 ? 0x07060302u : 0x05040100u);
+                    bv[p * IM + q][i] = v;
                 }
         if (mask) {
 #pragma unroll
@@ -355,33 +339,26 @@ __global__ void __launch_bounds__(WM* WN* WK * 64) conv_flat_kernel(const FlatAr
 
     // (the fetches beyond the last step are of the first chunk, cached, and masked)
     // MFMA D layout: lane j + 32 g holds rows 8 (v / 4) + 4 g + v % 4 of column j
-    auto store = [&](int m, int p, int v, const float (&o)[IPL]) {
+    auto store = [&](int m, int p, int v, const float (&o)[IM]) {
         const uint32_t k = k0 + m * 32 + (v >> 2) * 8 + g * 4 + (v & 3);
         if (k >= a.K) return;
         float* const dst = a.out + (int64_t)k * a.N + opos[p];
         if (skip[p] == 0) {
-            if constexpr (IPL == 4 || IPL == 8) {
-#pragma unroll
-                for (int i = 0; i < IPL; i += 4) ((Out4*)(dst + i))->v = ff32x4{o[i], o[i + 1], o[i + 2], o[i + 3]};
-            } else if constexpr (IPL == 2 || IPL == 6) {
-#pragma unroll
-                for (int i = 0; i < IPL; i += 2) ((Out2*)(dst + i))->v = ff32x2{o[i], o[i + 1]};
-            } else {
-#pragma unroll
-                for (int i = 0; i < IPL; ++i) dst[i] = o[i];
-            }
+            if constexpr (IM == 4) ((Out4*)dst)->v = ff32x4{o[0], o[1], o[2], o[3]};
+            else if constexpr (IM == 2) ((Out2*)dst)->v = ff32x2{o[0], o[1]};
+            else dst[0] = o[0];
         } else {
 #pragma unroll
-            for (int i = 1; i < IPL; ++i)
+            for (int i = 1; i < IM; ++i)
                 if (i >= skip[p]) dst[i] = o[i];
         }
     };
-    flat_write_out<MB, NG, IPL, WM * WN, WK>(s_red, acc, wave, wk, lane, store);
+    flat_write_out<MB, NG, IM, WM * WN, WK>(s_red, acc, wave, wk, lane, store);
 }
 
 template <int DT, int MB, int NG, int IM, int WM, int WN, int WK, int D, bool SHORT>
 static int launch_flat_one(const FlatArgs& a, int grid, void* stream) {
-    constexpr size_t lds = FlatReduce<MB, NG, (IM < 0 ? -IM : IM), WM * WN, WK>::BYTES;
+    constexpr size_t lds = FlatReduce<MB, NG, IM, WM * WN, WK>::BYTES;
     static_assert(lds <= 64 * 1024, "flat kernel: partial sums fit the LDS that a launch gets without asking");
     auto kernel = conv_flat_kernel<DT, MB, NG, IM, WM, WN, WK, D, SHORT>;
     hipLaunchKernelGGL(kernel, dim3(grid), dim3(WM * WN * WK * 64), lds, (hipStream_t)stream, a);
@@ -390,13 +367,9 @@ static int launch_flat_one(const FlatArgs& a, int grid, void* stream) {
 
 template <int DT, int MB, int NG, int IM, int WM, int WN, int WK, int D>
 static int launch_flat_shape(const FlatArgs& a, int grid, void* stream) {
-    if constexpr (IM < 0) {
-        return launch_flat_one<DT, MB, NG, IM, WM, WN, WK, D, false>(a, grid, stream);
-    } else {
-        if (a.T < (DT == 0 ? 4u : 8u)) return launch_flat_one<DT, MB, NG, IM, WM, WN, WK, 0, true>(a, grid, stream);
-        if (a.steps_per_wave <= 1) return launch_flat_one<DT, MB, NG, IM, WM, WN, WK, 0, false>(a, grid, stream);
-        return launch_flat_one<DT, MB, NG, IM, WM, WN, WK, D, false>(a, grid, stream);
-    }
+    if (a.T < (DT == 0 ? 4u : 8u)) return launch_flat_one<DT, MB, NG, IM, WM, WN, WK, 0, true>(a, grid, stream);
+    if (a.steps_per_wave <= 1) return launch_flat_one<DT, MB, NG, IM, WM, WN, WK, 0, false>(a, grid, stream);
+    return launch_flat_one<DT, MB, NG, IM, WM, WN, WK, D, false>(a, grid, stream);
 }
 
 // ---------------------------------------------------------------------------------------------------------------
@@ -608,61 +581,61 @@ __global__ void __launch_bounds__(WM* WN* WK * 64) conv_flat_lds_kernel(const Fl
         const char* const ap = buf + ((wm * MB * 32 + j) * GEO::FP + g) * 16;
         const char* const img = buf + GEO::FLT_BYTES;
 #pragma unroll
-                    for (int m = 0; m < MB; ++m) av[m] = *(const fu32x4*)(ap + m * 32 * GEO::FP * 16 + st * 32);
-                    if constexpr (RUN) {
+        for (int m = 0; m < MB; ++m) av[m] = *(const fu32x4*)(ap + m * 32 * GEO::FP * 16 + st * 32);
+        if constexpr (RUN) {
 #pragma unroll
-                        for (int p = 0; p < NBW; ++p) {
-                            const char* const xp = img + ((wn * NBW + p) * 32 + j) * GEO::ROW + (2 * st + g) * IPL * 16;
-                            fu32x4 x[IPL];
+            for (int p = 0; p < NBW; ++p) {
+                const char* const xp = img + ((wn * NBW + p) * 32 + j) * GEO::ROW + (2 * st + g) * IPL * 16;
+                fu32x4 x[IPL];
 #pragma unroll
-                            for (int e = 0; e < IPL; ++e) x[e] = *(const fu32x4*)(xp + e * 16);
+                for (int e = 0; e < IPL; ++e) x[e] = *(const fu32x4*)(xp + e * 16);
 #pragma unroll
-                            for (int q = 0; q < IPL; ++q)
+                for (int q = 0; q < IPL; ++q)
 #pragma unroll
-                                for (int i = 0; i < 4; ++i) {
-                                    if constexpr (DT == 0) {
-                                        bv[p * IPL + q][i] = x[(i * IPL + q) / 4][(i * IPL + q) % 4];
-                                    } else {
-                                        const int e0 = 2 * i * IPL + q, e1 = e0 + IPL;
-                                        bv[p * IPL + q][i] = IPL == 1 ? x[0][i]
-                                                                      : __builtin_amdgcn_perm(x[e1 / 8][e1 / 2 % 4], x[e0 / 8][e0 / 2 % 4],
-                                                                                              (e1 & 1 ? 0x07060000u : 0x05040000u) | (e0 & 1 ? 0x0302u : 0x0100u));
-                                    }
-                                }
-                        }
-                    } else if constexpr (DT == 0) {
-                        const char* const xp = img + (2 * st + g) * CH * GEO::ROW + (wn * NBW * 32 + j) * 4;
-#pragma unroll
-                        for (int n = 0; n < NB; ++n)
-#pragma unroll
-                            for (int e = 0; e < 4; ++e) bv[n][e] = *(const uint32_t*)(xp + e * GEO::ROW + n * 128);
-                    } else {
-                        // the transposing read: four rows (contraction indices) of 16 columns to a lane per column
-                        const char* const xp = img + (16 * st + 8 * g + (i16 >> 2)) * GEO::ROW + wn * NBW * 64 + jhalf * 32 + (i16 & 3) * 8;
-#pragma unroll
-                        for (int n = 0; n < NB; ++n) {
-                            const fs16x4 l = __builtin_amdgcn_ds_read_tr16_b64_v4i16((FLAT_LDS(fs16x4)*)(xp + n * 64));
-                            const fs16x4 h = __builtin_amdgcn_ds_read_tr16_b64_v4i16((FLAT_LDS(fs16x4)*)(xp + 4 * GEO::ROW + n * 64));
-                            bv[n] = __builtin_bit_cast(fu32x4, __builtin_shufflevector(l, h, 0, 1, 2, 3, 4, 5, 6, 7));
+                    for (int i = 0; i < 4; ++i) {
+                        if constexpr (DT == 0) {
+                            bv[p * IPL + q][i] = x[(i * IPL + q) / 4][(i * IPL + q) % 4];
+                        } else {
+                            const int e0 = 2 * i * IPL + q, e1 = e0 + IPL;
+                            bv[p * IPL + q][i] = IPL == 1 ? x[0][i]
+                                                          : __builtin_amdgcn_perm(x[e1 / 8][e1 / 2 % 4], x[e0 / 8][e0 / 2 % 4],
+                                                                                  (e1 & 1 ? 0x07060000u : 0x05040000u) | (e0 & 1 ? 0x0302u : 0x0100u));
                         }
                     }
+            }
+        } else if constexpr (DT == 0) {
+            const char* const xp = img + (2 * st + g) * CH * GEO::ROW + (wn * NBW * 32 + j) * 4;
+#pragma unroll
+            for (int n = 0; n < NB; ++n)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) bv[n][e] = *(const uint32_t*)(xp + e * GEO::ROW + n * 128);
+        } else {
+            // the transposing read: four rows (contraction indices) of 16 columns to a lane per column
+            const char* const xp = img + (16 * st + 8 * g + (i16 >> 2)) * GEO::ROW + wn * NBW * 64 + jhalf * 32 + (i16 & 3) * 8;
+#pragma unroll
+            for (int n = 0; n < NB; ++n) {
+                const fs16x4 l = __builtin_amdgcn_ds_read_tr16_b64_v4i16((FLAT_LDS(fs16x4)*)(xp + n * 64));
+                const fs16x4 h = __builtin_amdgcn_ds_read_tr16_b64_v4i16((FLAT_LDS(fs16x4)*)(xp + 4 * GEO::ROW + n * 64));
+                bv[n] = __builtin_bit_cast(fu32x4, __builtin_shufflevector(l, h, 0, 1, 2, 3, 4, 5, 6, 7));
+            }
+        }
     };
     auto mfma_step = [&](const fu32x4 (&av)[MB], const fu32x4 (&bv)[NB]) {
-                    if constexpr (DT == 0) {
+        if constexpr (DT == 0) {
 #pragma unroll
-                        for (int e = 0; e < 4; ++e)
+            for (int e = 0; e < 4; ++e)
 #pragma unroll
-                            for (int m = 0; m < MB; ++m)
+                for (int m = 0; m < MB; ++m)
 #pragma unroll
-                                for (int n = 0; n < NB; ++n)
-                                    acc[m][n] = __builtin_amdgcn_mfma_f32_32x32x2f32(__uint_as_float(av[m][e]), __uint_as_float(bv[n][e]), acc[m][n], 0, 0, 0);
-                    } else {
+                    for (int n = 0; n < NB; ++n)
+                        acc[m][n] = __builtin_amdgcn_mfma_f32_32x32x2f32(__uint_as_float(av[m][e]), __uint_as_float(bv[n][e]), acc[m][n], 0, 0, 0);
+        } else {
 #pragma unroll
-                        for (int m = 0; m < MB; ++m)
+            for (int m = 0; m < MB; ++m)
 #pragma unroll
-                            for (int n = 0; n < NB; ++n)
-                                acc[m][n] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(fbf16x8, av[m]), __builtin_bit_cast(fbf16x8, bv[n]), acc[m][n], 0, 0, 0);
-                    }
+                for (int n = 0; n < NB; ++n)
+                    acc[m][n] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(fbf16x8, av[m]), __builtin_bit_cast(fbf16x8, bv[n]), acc[m][n], 0, 0, 0);
+        }
     };
     // The operands of AHEAD steps are read before the first of their products: left alone, the compiler reads a step's operands
     // right in front of its products and waits for them every time.
@@ -745,9 +718,8 @@ __global__ void __launch_bounds__(WM* WN* WK * 64) conv_flat_lds_kernel(const Fl
         float* const dst = a.out + (int64_t)k * a.N + opos[p];
         if constexpr (STREAM) {
             __builtin_nontemporal_store(o[0], dst);
-        } else if constexpr (SI == 4 || SI == 8) {
-#pragma unroll
-            for (int i = 0; i < SI; i += 4) ((Out4*)(dst + i))->v = ff32x4{o[i], o[i + 1], o[i + 2], o[i + 3]};
+        } else if constexpr (SI == 4) {
+            ((Out4*)dst)->v = ff32x4{o[0], o[1], o[2], o[3]};
         } else if constexpr (SI == 2 || SI == 6) {
 #pragma unroll
             for (int i = 0; i < SI; i += 2) ((Out2*)(dst + i))->v = ff32x2{o[i], o[i + 1]};
@@ -785,7 +757,8 @@ static int launch_flat_lds_as(const FlatArgs& a, int grid, void* stream) {
 template <int DT, int MB, int NBW, int IM, int WM, int WN, int WK, int NCH>
 static int launch_flat_lds(const FlatArgs& a, int grid, void* stream) {
     if constexpr (IM >= -1)
-        if (a.B % (IM > 0 ? IM : 1) == 0 && a.N % 32 == 0 && reinterpret_cast<uintptr_t>(a.out) % 64 == 0) return launch_flat_lds_as<DT, MB, NBW, IM, WM, WN, WK, NCH, true>(a, grid, stream);
+        if (a.B % (IM > 0 ? IM : 1) == 0 && a.N % 32 == 0 && reinterpret_cast<uintptr_t>(a.out) % 64 == 0)
+            return launch_flat_lds_as<DT, MB, NBW, IM, WM, WN, WK, NCH, true>(a, grid, stream);
     return launch_flat_lds_as<DT, MB, NBW, IM, WM, WN, WK, NCH, false>(a, grid, stream);
 }
 

@@ -1051,7 +1051,7 @@ int prepare_tiled(const cacnn_problem& p, int dtype, int vi, int CT, int bR, int
             if (a.tiles_b % d == 0) g_b = d;
         a.b_group = g_b;
     }
-    if (!tile_list_in_range(p, v, walk, split_k)) return CACNN_ERR_INVALID_ARG;
+    if (!tile_list_in_range(p, v, walk, split_k)) return CACNN_ERR_INVALID_ARG;    // (before the layout is chosen, which walks the tiles)
     a.xcd_q = a.n_tiles / a.n_xcd;
     a.xcd_rem = a.n_tiles % a.n_xcd;
     a.d_nxcd = make_fastdiv((uint32_t)a.n_xcd);
@@ -1068,7 +1068,7 @@ int prepare_tiled(const cacnn_problem& p, int dtype, int vi, int CT, int bR, int
     a.kpg = a.tiles_k / split_k;
     a.grp = a.n_tiles / split_k;
     a.npos = a.grp / a.kpg;
-    if (!tile_list_in_range(p, v, walk, split_k)) return CACNN_ERR_INVALID_ARG;
+    if (!tile_list_in_range(p, v, walk, split_k)) return CACNN_ERR_INVALID_ARG;    // (with the layout's walk)
     a.pos_fastest = walk;
     a.d_npos = make_fastdiv((uint32_t)a.npos);
     a.d_tk = make_fastdiv((uint32_t)a.kpg);
@@ -1119,7 +1119,7 @@ bool flat_fits(const cacnn_problem& p, int dtype, const FlatInfo& v) {
     const int esz = dtype == CACNN_F32 ? 4 : 2;
     if (v.dtype != dtype) return false;
     if (v.IM < 0 ? p.B != -v.IM : p.B < v.IM) return false;
-    if ((v.IM < 0 || v.NCH) && p.S * p.C * esz < 16) return false;
+    if (v.NCH && p.S * p.C * esz < 16) return false;
     const double IW = (double)(p.sigma_w * (p.W - 1) + p.R), IH = (double)(p.sigma_h * (p.H - 1) + p.S);
     const double groups = (double)p.H * (double)p.W * (double)(v.IM < 0 ? 1 : ceil_div(p.B, v.IM));
     if ((double)ceil_div(p.K, v.KT()) * std::ceil(groups / v.GT()) * v.threads() >= 4294967296.0) return false;
@@ -1166,9 +1166,8 @@ double flat_us(const cacnn_problem& p, int dtype, const FlatInfo& v) {
     if (!v.NCH) {
         const double mine = (double)ceil_div((chunks + 1) / 2, v.WK) + 1.0;                                   // steps of a wave
         const double a_clk = load_clocks(16, 32.0, flt_aligned, true);
-        const double b_clk = run ? ipl * load_clocks(16, 32.0 * ipl, img_aligned, true)
-                                 : ch * load_clocks(ipl * esz, (double)(std::min<int64_t>(p.B, 32 * ipl) * esz), img_aligned,
-                                                    ipl == 4 || p.B % (4 * ipl) == 0);
+        const double b_clk = ch * load_clocks(ipl * esz, (double)(std::min<int64_t>(p.B, 32 * ipl) * esz), img_aligned,
+                                              ipl == 4 || p.B % (4 * ipl) == 0);
         const double load = per_cu * waves * mine * (v.MB * a_clk + v.NG * b_clk);
         const double simd = per_cu * simd_waves * mine * (blocks * mfma + 62.0), latency = (mine / 4.0 + 0.75) * 1020.0;
         clk = std::sqrt(load * load + simd * simd + latency * latency);
@@ -1294,7 +1293,8 @@ bool boxes_for_short_rows(const cacnn_problem& p, int dtype) {
 // 100 MB it is too low by up to 2.2 times, the more the windows overlap and the larger the Image is than the last-level
 // cache of 256 MB: (16, 888, 24, 126, 126, 3 x 3) 435 us and 571 flattened, (16, 1360, 3, 127, 127, 3 x 3) 562 and 978, (32, 152, 1, 151, 107,
 // 1 x 7) 109 and 134.  The line there is fitted on 173 such layers: with 0.7 28 of them take up to 1.74 times as long as on
-// their fixed-geometry kernel, with this one none more than 1.04; on 150 others 18 up to 1.45, and one, 1.14.  fp32 layers of these sizes: 0.24 to 0.87 times as long with 0.7.
+// their fixed-geometry kernel, with this one none more than 1.04; on 150 others 18 up to 1.45, and one, 1.14.  fp32 layers of these
+// sizes: 0.24 to 0.87 times as long with 0.7.
 double flat_margin(const cacnn_problem& p, int dtype) {
     const double image = 2.0 * (double)(p.sigma_w * (p.W - 1) + p.R) * (double)(p.sigma_h * (p.H - 1) + p.S) * (double)p.C * (double)p.B;
     if (dtype == CACNN_F32 || image < 100e6) return 0.7;

@@ -174,7 +174,7 @@ struct FlatInfo {
     int MB, NG;         // blocks of 32 of one wave: output channels, groups of images
     int IM;             // > 0: images a lane holds; < 0: all of that many, loaded in runs along the contraction
     int WM, WN, WK;     // waves along output channels, along positions, along the contraction
-    int NCH;            // 0: operands straight from global memory; else chunks per LDS stage, and NG counts blocks of columns
+    int NCH;            // 0: operands straight from global memory (IM > 0); else chunks per LDS stage, and NG counts blocks of columns
     int threads() const { return WM * WN * WK * 64; }
     int KT() const { return WM * MB * 32; }
     int GT() const { return WN * NG * 32 / (NCH && IM > 0 ? IM : 1); }   // groups of images per tile
