@@ -199,3 +199,44 @@ def test_binding_refuses_short_device_tensors_and_uses_the_current_stream(env):
     side.synchronize()
     ref, ab = gu.oracle_full(cfg, img, flt)
     check(cfg, first.cpu().numpy().reshape(cfg.out_shape), ref, ab, "side stream")
+
+
+# Image or Filter just below the 2 GiB that the 32-bit offsets reach: many images, one image, a long contraction
+@pytest.mark.parametrize("dtype,dims", [("bf16", (32, 16, 5, 1446, 1446, 3, 3, 1, 1)), ("bf16", (1, 16, 3, 8188, 8190, 3, 1, 1, 1)),
+                                        ("bf16", (2, 131071, 8191, 1, 1, 1, 1, 1, 1)), ("f32", (32, 16, 5, 1022, 1021, 3, 3, 1, 1)),
+                                        ("f32", (1, 16, 3, 5790, 5790, 2, 2, 1, 1)), ("f32", (4, 65535, 8191, 1, 1, 1, 1, 1, 1))])
+def test_operands_just_below_two_gib(env, dtype, dims):
+    """Inputs of -1, 0 and 1, whose sums are exact: every output is written, and those at the corners and at drawn positions are right."""
+    cc, torch, lib = env
+    B, C, K, W, H, R, S, sw, sh = dims
+    kind, esz = (torch.float32, 4) if dtype == "f32" else (torch.bfloat16, 2)
+    img_shape, flt_shape = (sw * (W - 1) + R, sh * (H - 1) + S, C, B), (K, R, S, C)
+    size = max(int(np.prod(img_shape, dtype=np.int64)), int(np.prod(flt_shape, dtype=np.int64))) * esz
+    assert 0.99 * 2 ** 31 < size < 2 ** 31
+    gen = torch.Generator(device="cuda:0")
+    gen.manual_seed(12)
+    img = torch.randint(-1, 2, img_shape, device="cuda:0", dtype=torch.int8, generator=gen).to(kind)
+    flt = torch.randint(-1, 2, flt_shape, device="cuda:0", dtype=torch.int8, generator=gen).to(kind)
+    words = torch.empty(K * H * W * B + 2 * GUARD, device="cuda:0")
+    out = words[GUARD:-GUARD].view(K, H, W, B)
+    rng = np.random.default_rng(3)
+    at = sorted({(w, h) for w in (0, W // 2, W - 1) for h in (0, H // 2, H - 1)} | {(int(rng.integers(W)), int(rng.integers(H))) for _ in range(40)})
+    windows = torch.stack([img[sw * w:sw * w + R, sh * h:sh * h + S].reshape(R * S * C, B) for w, h in at]).cpu().float()
+    want = torch.matmul(flt.view(K, -1).cpu().float(), windows)                   # position, k, image; integers below 2^24
+    prob, ran = cc.Problem(*dims), 0
+    for index, images, exactly, lds in kernels(lib, dtype):
+        if B < images or (exactly and B != images):
+            continue
+        words.fill_(-7.0)
+        out.fill_(float("nan"))
+        print(f"[flat] kernel {index} {dtype} {dims}", flush=True)
+        rc = lib.cacnn_internal_flat_forward(ctypes.byref(prob), 0 if dtype == "f32" else 1, index, img.data_ptr(), flt.data_ptr(),
+                                             out.data_ptr(), torch.cuda.current_stream().cuda_stream)
+        torch.cuda.synchronize()
+        assert rc == 0
+        assert bool((words[:GUARD] == -7.0).all()) and bool((words[-GUARD:] == -7.0).all())
+        assert not bool(torch.isnan(out).any())
+        got = torch.stack([out[:, h, w] for w, h in at]).cpu()
+        assert torch.equal(got, want), (index, dims)
+        ran += 1
+    assert ran >= 4

@@ -99,3 +99,25 @@ def test_arguments_out_of_range_are_refused():
     for dims, dtype in (((1, 3, 8, 16, 16, 3, 3, 1, 1), 2), ((1, 0, 8, 16, 16, 3, 3, 1, 1), F32), ((2 ** 31, 3, 8, 16, 16, 3, 3, 1, 1), F32)):
         with pytest.raises(cc.CacnnError):
             binding.routed_kernel(dims, dtype)
+
+
+def test_the_launch_cache_is_safe_with_several_threads():
+    """More problems than the cache holds, from eight threads at once (ctypes lets go of the interpreter's lock in a call): every answer is the
+    one that a single thread gets."""
+    import threading
+    problems = [((b, c, 24, 9, 7, 3, 3, 1, 1), dtype) for b in (1, 3, 8, 32, 64) for c in (1, 3, 8, 16, 24, 32, 48, 64, 65, 100) for dtype in (F32, BF16)]
+    want = [binding.routed_kernel(*p) for p in problems]
+    wrong = []
+
+    def work(first):
+        for i in range(2 * len(problems)):
+            n = (first * 13 + i * 7) % len(problems)
+            if binding.routed_kernel(*problems[n]) != want[n]:
+                wrong.append(problems[n])
+
+    threads = [threading.Thread(target=work, args=(t,)) for t in range(8)]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    assert len(set(want)) > 5 and not wrong
