@@ -1621,13 +1621,8 @@ int cacnn_pool_lower_bound(const cacnn_problem* problem, double M_words, cacnn_p
     return CACNN_OK;
 }
 
-int cacnn_pool_forward(const cacnn_problem* problem, int dtype, int mode, const void* image, void* out,
-                       void* hip_stream) {
-    if (!problem || !image || !out) return CACNN_ERR_NULL;
-    if (dtype != CACNN_F32 && dtype != CACNN_BF16_F32ACC) return CACNN_ERR_UNSUPPORTED;
-    if (mode != CACNN_POOL_AVG && mode != CACNN_POOL_MAX) return CACNN_ERR_UNSUPPORTED;
-    if (!valid_problem(problem) || problem->K != problem->C) return CACNN_ERR_INVALID_ARG;
-    const cacnn_problem& p = *problem;
+// What a pooling call launches; CACNN_OK, or why it is refused.
+static int prepare_pool(const cacnn_problem& p, int dtype, const void* image, const void* out, PoolArgs* args, int* images) {
     {
         // element counts of Image and Out within the kernel's 32-bit indexing
         const int64_t lim = INT32_MAX;
@@ -1646,10 +1641,10 @@ int cacnn_pool_forward(const cacnn_problem* problem, int dtype, int mode, const 
     int vec = full;
     while (vec > 1 && (p.B % vec || reinterpret_cast<uintptr_t>(image) % (vec * esz) || reinterpret_cast<uintptr_t>(out) % std::min(16, vec * 4)))
         vec /= 2;
-    PoolArgs a;
+    PoolArgs& a = *args;
     std::memset(&a, 0, sizeof(a));
     a.image = image;
-    a.out = (float*)out;
+    a.out = (float*)const_cast<void*>(out);
     a.B = (int32_t)p.B;
     a.C = (int32_t)p.C;
     a.W = (int32_t)p.W;
@@ -1672,10 +1667,16 @@ int cacnn_pool_forward(const cacnn_problem* problem, int dtype, int mode, const 
         return CACNN_ERR_INVALID_ARG;
     // Where a row of images is whole cache lines the kernel stores past the L2, and a thread's 8 floats would reach memory in two
     // instructions of half lines each: 4 images per thread then, whose stores are contiguous (bf16 (32, 100, 50, 75, 2 x 2, s 2)
-    // 27.6 us with 8, 24.7 with 4; (128, 64, 56, 56, 3 x 3, s 2) 75.2 and 74.0), where the thread count still fits the limit.  Where Out
-    // itself does not start on half a line both ways win, by up to 1.16 times: it is stored past the L2 there too.
+    // 27.6 us with 8, 24.7 with 4; (128, 64, 56, 56, 3 x 3, s 2) 75.2 and 74.0), where the thread count still fits the limit.  With 4 there are
+    // twice the loads, though, and where windows overlap and are read from the caches these set the pace: so windows of at most five
+    // elements, or with at most 9/4 reads of an element.  With 8 and with 4: (64, 13, 98, 98, 7 x 7) 33.9 and 49.0 us, (256, 399, 2, 50, 7 x 8, s 1 2)
+    // 150 and 164, (32, 291, 18, 18, 7 x 7) 19.7 and 21.3, (32, 118, 70, 70, 3 x 3) 23.5 and 25.0; (64, 138, 20, 20, 2 x 1) 5.3 and 4.6; over
+    // 500 calls the choice loses 1.012 to the better of both in the geometric mean (always 4: 1.06).  Where Out itself does not start on half a line
+    // ordinary stores and these win in turn, by up to 1.16 times: it is stored past the L2 there too.
     a.stream = p.B % 32 == 0;
-    if (a.stream && vec == 8 && n * 2 <= INT32_MAX &&
+    const double overlap = std::max(1.0, (double)p.R / (double)p.sigma_w) * std::max(1.0, (double)p.S / (double)p.sigma_h);
+    const bool few_loads = p.R * p.S <= 5 || overlap <= 2.25;
+    if (a.stream && few_loads && vec == 8 && n * 2 <= INT32_MAX &&
         (double)n * 2.0 * (double)std::max<int64_t>(std::max<int64_t>(groups * 2, p.C), std::max<int64_t>(p.H, 64)) < 4294967296.0) {
         vec = 4;
         a.BV = (int32_t)(p.B / vec);
@@ -1692,8 +1693,22 @@ int cacnn_pool_forward(const cacnn_problem* problem, int dtype, int mode, const 
     a.d_TWC = make_fastdiv((uint32_t)a.TWC);
     a.d_H = make_fastdiv((uint32_t)a.H);
     a.d_nxcd = make_fastdiv((uint32_t)a.n_xcd);
+    *images = vec;
+    return CACNN_OK;
+}
+
+int cacnn_pool_forward(const cacnn_problem* problem, int dtype, int mode, const void* image, void* out,
+                       void* hip_stream) {
+    if (!problem || !image || !out) return CACNN_ERR_NULL;
+    if (dtype != CACNN_F32 && dtype != CACNN_BF16_F32ACC) return CACNN_ERR_UNSUPPORTED;
+    if (mode != CACNN_POOL_AVG && mode != CACNN_POOL_MAX) return CACNN_ERR_UNSUPPORTED;
+    if (!valid_problem(problem) || problem->K != problem->C) return CACNN_ERR_INVALID_ARG;
+    PoolArgs a;
+    int images = 0;
+    const int rc = prepare_pool(*problem, dtype, image, out, &a, &images);
+    if (rc != CACNN_OK) return rc;
     if (!have_device()) return CACNN_ERR_NO_DEVICE;
-    return launch_pool(a, dtype, mode, vec, hip_stream) == 0 ? CACNN_OK : CACNN_ERR_LAUNCH;
+    return launch_pool(a, dtype, mode, images, hip_stream) == 0 ? CACNN_OK : CACNN_ERR_LAUNCH;
 }
 
 int cacnn_probe_mfma(int dtype, const void* operands, float* sink, int32_t iters, int64_t* mfma_issued, void* hip_stream) {
@@ -1847,6 +1862,13 @@ int cacnn_internal_route(const cacnn_problem* problem, int dtype, const void* im
     four[2] = l.grid;
     four[3] = l.flat ? l.flat->info.threads() : l.tiled->info.threads();
     return CACNN_OK;
+}
+// Images per thread of a pooling call with operands at these addresses, 0 if it is refused
+int cacnn_internal_pool_images(const cacnn_problem* problem, int dtype, const void* image, const void* out) {
+    PoolArgs a;
+    int images = 0;
+    if (!problem || !valid_problem(problem) || problem->K != problem->C || (dtype != CACNN_F32 && dtype != CACNN_BF16_F32ACC)) return 0;
+    return prepare_pool(*problem, dtype, image, out, &a, &images) == CACNN_OK ? images : 0;
 }
 int cacnn_internal_flat_count(void) { return num_flat(); }
 int cacnn_internal_flat_info(int i, int32_t* eight) {

@@ -79,7 +79,7 @@ __device__ __forceinline__ void pool_take(float (&acc)[VEC], const PoolWords<VEC
 // BIG: the Image is larger than the 2 GiB of a buffer descriptor; 64-bit addresses.
 // WR x WS: the window the kernel is compiled for, all of whose loads are in flight at once (0: any window, eight loads
 // at a time).  One load takes the address unit as long whether a lane asks for 2 bytes or 4, and twice as long for 8
-// or 16, so VEC is the largest of 8, 4, 2 (fp32: 4, 2) that divides B (4 where Out is streamed).  Offsets are 32 bits wide and the window's part of them is
+// or 16, so VEC is the largest of 8, 4, 2 (fp32: 4, 2) that divides B (bf16 with Out past the L2: 4 where few loads go to an output).  Offsets are 32 bits wide and the window's part of them is
 // scalar: with 64-bit products per element the vector unit, not memory, set the pace of calls with a small VEC.
 // STREAM: Out past the L2, where a row of images is whole cache lines (B a multiple of 32); elsewhere the pieces of a line
 // come from several instructions and the L2 has to put them together (bf16 (20, 192, 27, 27, 3 x 3, s 2) 7.4 us through it, 8.4

@@ -121,3 +121,26 @@ def test_the_launch_cache_is_safe_with_several_threads():
     for t in threads:
         t.join()
     assert len(set(want)) > 5 and not wrong
+
+
+def pool_images(dims, dtype, image=0, out=0):
+    lib = binding._lib
+    lib.cacnn_internal_pool_images.argtypes = [ctypes.POINTER(cc.Problem), ctypes.c_int, ctypes.c_void_p, ctypes.c_void_p]
+    return lib.cacnn_internal_pool_images(ctypes.byref(cc.Problem(*dims)), dtype, image, out)
+
+
+def test_images_per_thread_of_a_pooling_call():
+    """One 16-byte load's images, fewer where B or an address asks for it; bf16 rows of whole cache lines: half as many, but for windows whose
+    overlap has the loads set the pace."""
+    def at(B, R, S, sw, sh, dtype, image=0, out=0):
+        return pool_images((B, 40, 40, 20, 20, R, S, sw, sh), dtype, image, out)
+    for B, bf16, f32 in ((1, 1, 1), (3, 1, 1), (6, 2, 2), (20, 4, 4), (8, 8, 4)):
+        assert (at(B, 3, 3, 1, 1, BF16), at(B, 3, 3, 1, 1, F32)) == (bf16, f32)
+    assert [at(8, 3, 3, 1, 1, BF16, image) for image in (2, 4, 8, 16)] == [1, 2, 4, 8] and at(8, 3, 3, 1, 1, BF16, 0, 4) == 1
+    for R, S, sw, sh in ((2, 2, 2, 2), (2, 2, 1, 1), (3, 3, 2, 2), (7, 7, 7, 7), (1, 1, 1, 1), (3, 1, 1, 1)):
+        assert at(64, R, S, sw, sh, BF16) == 4 and at(64, R, S, sw, sh, F32) == 4
+    for R, S, sw, sh in ((3, 3, 1, 1), (7, 7, 1, 1), (7, 8, 1, 2), (7, 7, 2, 2), (7, 1, 1, 1), (5, 5, 1, 1)):
+        assert at(64, R, S, sw, sh, BF16) == 8 and at(64, R, S, sw, sh, F32) == 4
+    # (4 images per thread only where the kernel's divisions hold as many threads)
+    assert pool_images((32, 7000, 7000, 1, 1, 2, 2, 1, 1), BF16) == 4 and pool_images((32, 30000, 30000, 1, 1, 2, 2, 1, 1), BF16) == 8
+    assert pool_images((64, 40, 39, 20, 20, 2, 2, 2, 2), BF16) == 0
