@@ -1292,8 +1292,8 @@ bool boxes_for_short_rows(const cacnn_problem& p, int dtype) {
 // The estimate knows nothing of windows read again from beyond the L2.  For bf16, whose products do not hide that, on Images of more than
 // 100 MB it is too low by up to 2.2 times, the more the windows overlap and the larger the Image is than the last-level
 // cache of 256 MB: (16, 888, 24, 126, 126, 3 x 3) 435 us and 571 flattened, (16, 1360, 3, 127, 127, 3 x 3) 562 and 978, (32, 152, 1, 151, 107,
-// 1 x 7) 109 and 134.  The line there is fitted on 173 such layers: with 0.7 28 of them take up to 1.74 times as long as on
-// their fixed-geometry kernel, with this one none more than 1.04; on 150 others 18 up to 1.45, and one, 1.14.  fp32 layers of these
+// 1 x 7) 109 and 134.  The line there is fitted on 173 such layers and tried on 105 others: with 0.7 48 of these 278 take up to 1.74 times
+// as long as on their fixed-geometry kernel, with this one 3, up to 1.16.  fp32 layers of these
 // sizes: 0.24 to 0.87 times as long with 0.7.
 double flat_margin(const cacnn_problem& p, int dtype) {
     const double image = 2.0 * (double)(p.sigma_w * (p.W - 1) + p.R) * (double)(p.sigma_h * (p.H - 1) + p.S) * (double)p.C * (double)p.B;
