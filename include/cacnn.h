@@ -142,9 +142,9 @@ int cacnn_tile_plan(const cacnn_problem* problem, int dtype, const cacnn_machine
  *   out      out  DEVICE pointer, K*H*W*B fp32; OVERWRITTEN with the full sum (the paper's += from zero);
  *                 must not alias the inputs
  *   hip_stream    hipStream_t cast to void*; NULL is the default stream
- * Which kernel runs: the one that cacnn_tile_plan describes, or, where the problem has few images, sizes that the tiled
- * kernels' 16-byte items do not divide, or too few tiles for the machine, a kernel that flattens the positions and needs
- * no plan (same sums, same inputs and outputs, fp32 accumulation).
+ * Which kernel runs: the one that cacnn_tile_plan describes, or, where that is a generic one (few images, sizes or
+ * addresses that 16-byte items do not divide) or has too few tiles for the machine, mostly a kernel that flattens the
+ * positions and needs no plan (same sums, same inputs and outputs, fp32 accumulation).
  * The call enqueues work on the stream and returns; it never synchronises, allocates no device memory and
  * keeps no reference to the buffers.  The caller owns all three buffers.  Pointers must be aligned to their
  * element size; 16-byte alignment enables the vector paths.
