@@ -166,7 +166,7 @@ __global__ void __launch_bounds__(WM* WN* WK * 64) conv_flat_kernel(const FlatAr
     const int wk = wave % WK, wm = (wave / WK) % WM, wn = wave / (WK * WM);
     const int j = lane & 31, g = lane >> 5;
 
-    const uint32_t t = xcd_order(blockIdx.x, a.xcd_shift, a.xcd_q, a.xcd_rem);
+    const uint32_t t = xcd_order(blockIdx.x, a.xcd_q, a.xcd_rem);
     uint32_t tk, tn;
     {
         const uint32_t q = flat_div(t, a.d_inner), i = t - q * a.inner;
@@ -426,7 +426,7 @@ __global__ void __launch_bounds__(WM* WN* WK * 64) conv_flat_lds_kernel(const Fl
     const int wk = wave % WK, wm = (wave / WK) % WM, wn = wave / (WK * WM);
     const int j = lane & 31, g = lane >> 5;
 
-    const uint32_t t = xcd_order(blockIdx.x, a.xcd_shift, a.xcd_q, a.xcd_rem);
+    const uint32_t t = xcd_order(blockIdx.x, a.xcd_q, a.xcd_rem);
     uint32_t tk, tn;
     {
         const uint32_t q = flat_div(t, a.d_inner), i = t - q * a.inner;

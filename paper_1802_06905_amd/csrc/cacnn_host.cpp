@@ -605,7 +605,7 @@ int64_t launch_grid(const VariantInfo& v, const Geometry& g, int64_t n_tiles, co
     return std::min<int64_t>(n_tiles, mach.num_cu * resident);
 }
 
-// XCD count used for the tile remapping; CACNN_XCDS=1 switches the remapping off (debugging aid)
+// XCD count used for the tile remapping of the box tiles and of pooling; CACNN_XCDS=1 switches the remapping off (debugging aid)
 int xcd_count() {
     static int n = [] {
         const char* e = std::getenv("CACNN_XCDS");
@@ -1243,9 +1243,8 @@ int prepare_flat(const cacnn_problem& p, int dtype, int fi, Launch* out) {
     const int64_t grid = tiles_k * tiles_n;
     a.k_inner = img >= flt ? 1u : 0u;
     a.inner = (uint32_t)(a.k_inner ? tiles_k : tiles_n);
-    while (2 << a.xcd_shift <= xcd_count()) ++a.xcd_shift;      // (a power of two XCDs at most that many)
-    a.xcd_q = (uint32_t)grid >> a.xcd_shift;
-    a.xcd_rem = (uint32_t)grid & ((1u << a.xcd_shift) - 1);
+    a.xcd_q = (uint32_t)grid / kFlatXcds;
+    a.xcd_rem = (uint32_t)grid % kFlatXcds;
     a.d_G = make_flatdiv(a.G);
     a.d_W = make_flatdiv((uint32_t)p.W);
     a.d_TC = make_flatdiv(a.TC);

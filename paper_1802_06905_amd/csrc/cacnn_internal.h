@@ -140,11 +140,14 @@ constexpr uint32_t flat_div(uint32_t n, FlatDiv d) {
     return d.mul ? (uint32_t)(((uint64_t)n * d.mul) >> 32) >> d.shift : n;
 }
 
-// The tile of a workgroup: the dispatcher deals workgroups to 2^shift XCDs in turn, and every XCD gets one contiguous run of the
-// tile list, q tiles and one more for the first rem of them.  (A shift and a mask: the division by any number of XCDs took 0.08 us of the
-// 2.6 us of the smallest launches.)
-constexpr uint32_t xcd_order(uint32_t workgroup, uint32_t shift, uint32_t q, uint32_t rem) {
-    const uint32_t l = workgroup >> shift, x = workgroup & ((1u << shift) - 1);
+// The tile of a workgroup of these kernels: the dispatcher deals workgroups to the 8 XCDs in turn, and every XCD gets one contiguous run
+// of the tile list, q tiles and one more for the first rem of them.  The count is fixed, unlike that of the box tiles' order: on a
+// device with fewer XCDs every tile is still taken once, in another order.  With the count as an argument (a division: 0.08 us of the
+// 2.6 us of the smallest launches; a shift and a mask: two instructions more) one staged configuration, bf16 with 8 images per lane
+// on 64 x 128 tiles, took 1.02 times as long, in one layer 1.10, over three builds.
+constexpr uint32_t kFlatXcds = 8;
+constexpr uint32_t xcd_order(uint32_t workgroup, uint32_t q, uint32_t rem) {
+    const uint32_t l = workgroup / kFlatXcds, x = workgroup % kFlatXcds;
     return x * q + (x < rem ? x : rem) + l;
 }
 
@@ -166,7 +169,7 @@ struct FlatArgs {
     uint32_t wrap_flt, wrap_img;        // correction when that passes the end of an r
     int32_t img_bytes;
     uint32_t inner, k_inner;            // tile list: the fastest index, its length; 1: the k-tiles, 0: the position tiles
-    uint32_t xcd_shift, xcd_q, xcd_rem;
+    uint32_t xcd_q, xcd_rem;
     FlatDiv d_G, d_W, d_TC, d_inner;
 };
 struct FlatInfo {
