@@ -143,8 +143,8 @@ constexpr uint32_t flat_div(uint32_t n, FlatDiv d) {
 // The tile of a workgroup of these kernels: the dispatcher deals workgroups to the 8 XCDs in turn, and every XCD gets one contiguous run
 // of the tile list, q tiles and one more for the first rem of them.  The count is fixed, unlike that of the box tiles' order: on a
 // device with fewer XCDs every tile is still taken once, in another order.  With the count as an argument (a division: 0.08 us of the
-// 2.6 us of the smallest launches; a shift and a mask: two instructions more) one staged configuration, bf16 with 8 images per lane
-// on 64 x 128 tiles, took 1.02 times as long, in one layer 1.10, over three builds.
+// 2.6 us of the smallest launches; a shift and a mask: two instructions more) two staged configurations, bf16 with 8 images per lane
+// on 64 x 128 tiles and fp32 with 4 on 32 x 64, took 1.01 to 1.02 times as long in most of four builds.
 constexpr uint32_t kFlatXcds = 8;
 constexpr uint32_t xcd_order(uint32_t workgroup, uint32_t q, uint32_t rem) {
     const uint32_t l = workgroup / kFlatXcds, x = workgroup % kFlatXcds;
