@@ -144,7 +144,10 @@ int cacnn_tile_plan(const cacnn_problem* problem, int dtype, const cacnn_machine
  *   hip_stream    hipStream_t cast to void*; NULL is the default stream
  * Which kernel runs: the one that cacnn_tile_plan describes, or, where that is a generic one (few images, sizes or
  * addresses that 16-byte items do not divide) or has too few tiles for the machine, mostly a kernel that flattens the
- * positions and needs no plan (same sums, same inputs and outputs, fp32 accumulation).
+ * positions and needs no plan (same sums, same inputs and outputs, fp32 accumulation).  On the default stream (hip_stream NULL), where
+ * launches follow one another, few tiles with a long contraction are shared by several workgroups each, which exchange partial sums in
+ * 8 MiB of device memory that the library's code object holds; on every other stream, and so in a graph, the same call runs a kernel that needs
+ * none.  Either adds up in a fixed order, the two in different ones: the last bits of a call's result may depend on the stream, on nothing else.
  * The call enqueues work on the stream and returns; it never synchronises, allocates no device memory and
  * keeps no reference to the buffers.  The caller owns all three buffers.  Pointers must be aligned to their
  * element size; 16-byte alignment enables the vector paths.

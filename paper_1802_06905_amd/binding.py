@@ -162,6 +162,8 @@ _lib.cacnn_internal_pool_forward_sized.argtypes = [ctypes.POINTER(Problem), ctyp
     [ctypes.c_void_p, ctypes.c_int64] * 2 + [ctypes.c_void_p]
 _lib.cacnn_internal_route.restype = ctypes.c_int
 _lib.cacnn_internal_route.argtypes = [ctypes.POINTER(Problem), ctypes.c_int, ctypes.c_void_p, ctypes.c_void_p, ctypes.POINTER(ctypes.c_int32)]
+_lib.cacnn_internal_route_split.restype = ctypes.c_int
+_lib.cacnn_internal_route_split.argtypes = [ctypes.POINTER(Problem), ctypes.c_int, ctypes.c_void_p, ctypes.c_void_p, ctypes.POINTER(ctypes.c_int32)]
 _lib.cacnn_internal_flat_info.restype = ctypes.c_int
 _lib.cacnn_internal_flat_info.argtypes = [ctypes.c_int, ctypes.POINTER(ctypes.c_int32)]
 _lib.cacnn_variant_count.restype = ctypes.c_int
@@ -298,8 +300,25 @@ def routed_kernel(problem, dtype: int, image: int = 0, filt: int = 0):
     if not four[0]:
         return cacnn_variant_name(four[1]), four[2], four[3]
     _lib.cacnn_internal_flat_info(four[1], eight)
+    return _flat_name(eight), four[2], four[3]
+
+
+def _flat_name(eight) -> str:
     dt, mb, ng, im, wm, wn, wk, nch = eight
-    return f"{'bf16' if dt else 'f32'} flat m{mb} n{ng} i{im} w{wm}x{wn}x{wk} c{nch}", four[2], four[3]
+    return f"{'bf16' if dt else 'f32'} flat m{mb} n{ng} i{im} w{wm}x{wn}x{wk} c{nch}"
+
+
+def routed_split(problem, dtype: int, image: int = 0, filt: int = 0):
+    """(name, parts, workgroups) of the flattened kernel that runs instead on the null stream, each tile's contraction shared by `parts`
+    workgroups, or None where the call is the same on every stream (host only)."""
+    three, eight = (ctypes.c_int32 * 3)(), (ctypes.c_int32 * 8)()
+    rc = _lib.cacnn_internal_route_split(ctypes.byref(_as_problem(problem)), int(dtype), int(image), int(filt), three)
+    if rc != 0:
+        raise CacnnError(rc, "cacnn_internal_route_split")
+    if not three[1]:
+        return None
+    _lib.cacnn_internal_flat_info(three[0], eight)
+    return _flat_name(eight), three[1], three[2]
 
 
 def cacnn_tune(problem, dtype: int, image, filt, out, stream=None) -> Plan:

@@ -411,8 +411,17 @@ struct FlatLds {
 // us, 32 images 48.2 and 36.8, (32, 3, 64, 112, 112, 3 x 3, s 2) 37.2 and 24.1, fp32 (12, 3, 16, 112, 112, 3 x 3, s 2) 12.5 and 11.9; of
 // pieces of lines, bf16 (20, 3, 64, 111, 111, 3 x 3, s 2) 21.7 and 33.0, (12, 64, 256, 57, 55, 1 x 1) 14.9 and 19.0.  A template
 // parameter because the compiler makes one ordinary store of the two sides of a branch.
-template <int DT, int MB, int NBW, int IM, int WM, int WN, int WK, int NCH, bool STREAM>
-__global__ void __launch_bounds__(WM* WN* WK * 64) conv_flat_lds_kernel(const FlatArgs a) {
+constexpr int OUT_CACHED = 0, OUT_STREAMED = 1, OUT_SPLIT = 2;
+
+// OUT_SPLIT: the contraction of a tile is divided over a.parts workgroups, for calls whose tiles leave most compute units idle while each of
+// the few at work walks a long contraction.  Every workgroup leaves its sums in the device's scratch memory and counts itself; the one
+// that comes last adds all of them, in the order of the parts (the result does not depend on which one that is), and writes Out.  No
+// workgroup waits for another.  The scratch belongs to one launch at a time: the host makes such launches on the null stream alone.
+__device__ float g_split_sums[kSplitWords];
+__device__ unsigned int g_split_arrived[kSplitTiles];      // zero between launches: the workgroup that comes last clears its tile's
+
+template <int DT, int MB, int NBW, int IM, int WM, int WN, int WK, int NCH, int OUT, class Args>
+__global__ void __launch_bounds__(WM* WN* WK * 64) conv_flat_lds_kernel(const Args a) {
     using GEO = FlatLds<DT, MB, NBW, IM, WM, WN, WK, NCH>;
     constexpr int ESZ = GEO::ESZ, CH = GEO::CH, IPL = GEO::IPL, NB = GEO::NB, NF = GEO::NF, NI = GEO::NI, LW = GEO::LW;
     constexpr int THREADS = GEO::THREADS, RPP = GEO::RPP;
@@ -426,7 +435,11 @@ __global__ void __launch_bounds__(WM* WN* WK * 64) conv_flat_lds_kernel(const Fl
     const int wk = wave % WK, wm = (wave / WK) % WM, wn = wave / (WK * WM);
     const int j = lane & 31, g = lane >> 5;
 
-    const uint32_t t = xcd_order(blockIdx.x, a.xcd_q, a.xcd_rem);
+    uint32_t t = xcd_order(blockIdx.x, a.xcd_q, a.xcd_rem), part = 0;
+    if constexpr (OUT == OUT_SPLIT) {
+        part = flat_div(t, a.d_tiles);
+        t -= part * a.tiles;
+    }
     uint32_t tk, tn;
     {
         const uint32_t q = flat_div(t, a.d_inner), i = t - q * a.inner;
@@ -463,12 +476,20 @@ __global__ void __launch_bounds__(WM* WN* WK * 64) conv_flat_lds_kernel(const Fl
             c.img += a.wrap_img;
         }
     };
+    // this workgroup's stages, and the chunk behind its last one
+    int stages = (int)((a.U + NCH - 1) / NCH);
+    uint32_t u_first = 0, u_end = a.U;
+    if constexpr (OUT == OUT_SPLIT) {
+        u_first = part * a.part_stages * NCH;
+        stages = min((int)a.part_stages, stages - (int)(part * a.part_stages));
+        u_end = min(a.U, u_first + stages * NCH);
+    }
     const uint32_t eoff = a.B * ESZ;
     const int fc = tid % NCH, fr = tid / NCH;
     uint32_t aoff[NF];
 #pragma unroll
     for (int i = 0; i < NF; ++i) aoff[i] = min(k0 + fr + i * (THREADS / NCH), a.K - 1) * a.flt_row;
-    Chunk fch = chunk_at(fc), ich[NS];
+    Chunk fch = chunk_at(u_first + fc), ich[NS];
     const int ig = RUN ? 0 : tid % GEO::GROUPS, ir = RUN ? fr : tid / GEO::GROUPS;
     uint32_t boff[RUN ? NI : 1];
     {
@@ -481,7 +502,7 @@ __global__ void __launch_bounds__(WM* WN* WK * 64) conv_flat_lds_kernel(const Fl
         } else {
             position(q0 + ig, boff[0], pos, skip);
 #pragma unroll
-            for (int i = 0; i < NI; ++i) ich[i] = chunk_at(ir / CH + i * (RPP / CH));
+            for (int i = 0; i < NI; ++i) ich[i] = chunk_at(u_first + ir / CH + i * (RPP / CH));
         }
     }
     const int ie = ir % CH;                            // (columns) the item's contraction index inside its chunk
@@ -489,7 +510,7 @@ __global__ void __launch_bounds__(WM* WN* WK * 64) conv_flat_lds_kernel(const Fl
     uint32_t F[2][NF][4], X[2][NI][LE][LW], flo[2], ilo[2][NS];
     auto fetch = [&](int set) {
         {
-            const bool out = fch.u >= a.U, last = fch.tc + 1 == a.TC;
+            const bool out = fch.u >= u_end, last = fch.tc + 1 == a.TC;
             flo[set] = out ? CH : last ? a.back : 0;
             const uint32_t fo = out ? 0 : last ? fch.flt - a.back * ESZ : fch.flt;
 #pragma unroll
@@ -507,7 +528,7 @@ __global__ void __launch_bounds__(WM* WN* WK * 64) conv_flat_lds_kernel(const Fl
         if constexpr (!RUN) {
 #pragma unroll
             for (int i = 0; i < NI; ++i) {
-                const bool out = ich[i].u >= a.U, last = ich[i].tc + 1 == a.TC;
+                const bool out = ich[i].u >= u_end, last = ich[i].tc + 1 == a.TC;
                 ilo[set][i] = out ? CH : last ? a.back : 0;
                 const uint32_t io = out ? 0 : (last ? ich[i].img - a.back * eoff : ich[i].img) + ie * eoff;
                 load_at<LW * 4>(X[set][i][0], (const char*)a.image, boff[0] + io);
@@ -659,7 +680,6 @@ __global__ void __launch_bounds__(WM* WN* WK * 64) conv_flat_lds_kernel(const Fl
     // number of stages.
     char* const buf0 = s_mem;
     char* const buf1 = s_mem + GEO::BUF;
-    const int stages = (int)((a.U + NCH - 1) / NCH);
     auto keep_order = [] {
         // (neither the compiler's passes nor its scheduler may move loads past this point)
         asm volatile("" ::: "memory");
@@ -716,7 +736,7 @@ __global__ void __launch_bounds__(WM* WN* WK * 64) conv_flat_lds_kernel(const Fl
         const uint32_t k = k0 + (wm * MB + m) * 32 + (v >> 2) * 8 + g * 4 + (v & 3);
         if (k >= a.K || skip[p]) return;
         float* const dst = a.out + (int64_t)k * a.N + opos[p];
-        if constexpr (STREAM) {
+        if constexpr (OUT == OUT_STREAMED) {
             __builtin_nontemporal_store(o[0], dst);
         } else if constexpr (SI == 4) {
             ((Out4*)dst)->v = ff32x4{o[0], o[1], o[2], o[3]};
@@ -729,13 +749,57 @@ __global__ void __launch_bounds__(WM* WN* WK * 64) conv_flat_lds_kernel(const Fl
         }
     };
     if constexpr (WK > 1) __syncthreads();             // the buffers become the exchange area of the partial sums
-    flat_write_out<MB, NBW, SI, WM * WN, WK>((float*)s_mem, acc, wave, wk, lane, store);
+    if constexpr (OUT == OUT_SPLIT) {
+        constexpr uint32_t ROWS = WM * MB * WN * NBW * 16, TILE = ROWS * SI * 64;     // rows of 64 lanes' sums, words of a part
+        float* const mine = g_split_sums + (size_t)(t * a.parts + part) * TILE;
+        auto row_of = [&](int m, int p, int v) { return (((wm * MB + m) * (WN * NBW) + wn * NBW + p) * 16 + v) * (SI * 64) + lane; };
+        flat_write_out<MB, NBW, SI, WM * WN, WK>((float*)s_mem, acc, wave, wk, lane, [&](int m, int p, int v, const float (&o)[SI]) {
+#pragma unroll
+            for (int i = 0; i < SI; ++i) __hip_atomic_store(mine + row_of(m, p, v) + i * 64, o[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        });
+        // The sums pass through stores and loads of the device's scope, which the L2s of the XCDs do not keep; a wave's stores have arrived
+        // when it has waited for them.  (A device-scope fence would write back and invalidate an L2: 10 to 60 us in such a launch.)
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        __syncthreads();
+        unsigned int* const last = (unsigned int*)s_mem;
+        if (tid == 0) {
+            *last = __hip_atomic_fetch_add(&g_split_arrived[t], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + 1 == a.parts;
+            if (*last) __hip_atomic_store(&g_split_arrived[t], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
+        __syncthreads();
+        if (!*last) return;
+        float* const sums = g_split_sums + (size_t)t * a.parts * TILE;
+        // rows divided over the waves of a column of them as above; the loads of a part are in flight together
+        float o[MB][NBW][16 / WK][SI];
+        auto each_row = [&](auto f) {
+#pragma unroll
+            for (int m = 0; m < MB; ++m)
+#pragma unroll
+                for (int p = 0; p < NBW; ++p)
+#pragma unroll
+                    for (int v = 0; v < 16 / WK; ++v) f(m, p, v);
+        };
+        each_row([&](int m, int p, int v) {
+#pragma unroll
+            for (int i = 0; i < SI; ++i) o[m][p][v][i] = 0.f;
+        });
+#pragma unroll 4
+        for (uint32_t q = 0; q < a.parts; ++q)
+            each_row([&](int m, int p, int v) {
+#pragma unroll
+                for (int i = 0; i < SI; ++i) 
+                    o[m][p][v][i] += __hip_atomic_load(sums + (size_t)q * TILE + row_of(m, p, v * WK + wk) + i * 64, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            });
+        each_row([&](int m, int p, int v) { store(m, p, v * WK + wk, o[m][p][v]); });
+    } else {
+        flat_write_out<MB, NBW, SI, WM * WN, WK>((float*)s_mem, acc, wave, wk, lane, store);
+    }
 }
 
-template <int DT, int MB, int NBW, int IM, int WM, int WN, int WK, int NCH, bool STREAM>
-static int launch_flat_lds_as(const FlatArgs& a, int grid, void* stream) {
+template <int DT, int MB, int NBW, int IM, int WM, int WN, int WK, int NCH, int OUT, class Args>
+static int launch_flat_lds_as(const Args& a, int grid, void* stream) {
     using GEO = FlatLds<DT, MB, NBW, IM, WM, WN, WK, NCH>;
-    auto kernel = conv_flat_lds_kernel<DT, MB, NBW, IM, WM, WN, WK, NCH, STREAM>;
+    auto kernel = conv_flat_lds_kernel<DT, MB, NBW, IM, WM, WN, WK, NCH, OUT, Args>;
     if constexpr (GEO::LDS > 64 * 1024) {
         static OncePerDevice once;
         int device = -1;
@@ -758,8 +822,13 @@ template <int DT, int MB, int NBW, int IM, int WM, int WN, int WK, int NCH>
 static int launch_flat_lds(const FlatArgs& a, int grid, void* stream) {
     if constexpr (IM >= -1)
         if (a.B % (IM > 0 ? IM : 1) == 0 && a.N % 32 == 0 && reinterpret_cast<uintptr_t>(a.out) % 64 == 0)
-            return launch_flat_lds_as<DT, MB, NBW, IM, WM, WN, WK, NCH, true>(a, grid, stream);
-    return launch_flat_lds_as<DT, MB, NBW, IM, WM, WN, WK, NCH, false>(a, grid, stream);
+            return launch_flat_lds_as<DT, MB, NBW, IM, WM, WN, WK, NCH, OUT_STREAMED>(a, grid, stream);
+    return launch_flat_lds_as<DT, MB, NBW, IM, WM, WN, WK, NCH, OUT_CACHED>(a, grid, stream);
+}
+
+template <int DT, int MB, int NBW, int IM, int WM, int WN, int WK, int NCH>
+static int launch_flat_split(const FlatSplitArgs& a, int grid, void* stream) {
+    return launch_flat_lds_as<DT, MB, NBW, IM, WM, WN, WK, NCH, OUT_SPLIT>(a, grid, stream);
 }
 
 // blocks of output channels, groups of images per wave; images per lane; waves along k, positions, contraction; steps ahead.
@@ -767,10 +836,10 @@ static int launch_flat_lds(const FlatArgs& a, int grid, void* stream) {
 // other, what made its picks on 390 layers of all sizes worse by least; on 330 others the best of these is within 0.3 % of the
 // best of all that were left then.)
 #define CACNN_FLAT(DT, MB, NG, IM, WM, WN, WK, D) \
-    {{DT, MB, NG, IM, WM, WN, WK, 0}, launch_flat_shape<DT, MB, NG, IM, WM, WN, WK, D>}
+    {{DT, MB, NG, IM, WM, WN, WK, 0}, launch_flat_shape<DT, MB, NG, IM, WM, WN, WK, D>, nullptr}
 
 #define CACNN_FLAT_LDS(DT, MB, NBW, IM, WM, WN, WK, NCH) \
-    {{DT, MB, NBW, IM, WM, WN, WK, NCH}, launch_flat_lds<DT, MB, NBW, IM, WM, WN, WK, NCH>}
+    {{DT, MB, NBW, IM, WM, WN, WK, NCH}, launch_flat_lds<DT, MB, NBW, IM, WM, WN, WK, NCH>, launch_flat_split<DT, MB, NBW, IM, WM, WN, WK, NCH>}
 
 static const FlatVariant g_flat[] = {
     // fp32

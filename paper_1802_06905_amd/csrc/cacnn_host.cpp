@@ -953,9 +953,11 @@ bool tile_list_in_range(const cacnn_problem& p, const VariantInfo& v, int walk, 
 struct Launch {
     const Variant* tiled = nullptr;
     const FlatVariant* flat = nullptr;
+    const FlatVariant* split = nullptr;     // what runs instead on the null stream: workgroups that share a tile's contraction
     KernelArgs a;
     FlatArgs f;
-    int grid = 0;
+    FlatSplitArgs fs;
+    int grid = 0, split_grid = 0;
     size_t lds = 0;
 };
 
@@ -969,7 +971,12 @@ bool aligned16(const void* p) { return reinterpret_cast<uintptr_t>(p) % 16 == 0;
 int fire(Launch& l, const void* image, const void* filter, void* out, void* stream) {
     if (!have_device()) return CACNN_ERR_NO_DEVICE;
     int rc;
-    if (l.flat) {
+    if (l.split && !stream) {
+        l.fs.image = image;
+        l.fs.filter = filter;
+        l.fs.out = (float*)out;
+        rc = l.split->launch_split(l.fs, l.split_grid, stream);
+    } else if (l.flat) {
         l.f.image = image;
         l.f.filter = filter;
         l.f.out = (float*)out;
@@ -1082,7 +1089,7 @@ int prepare_tiled(const cacnn_problem& p, int dtype, int vi, int CT, int bR, int
     a.flt_off = g.flt_off;
     a.flt_resident = g.flt_resident;
     out->tiled = &var;
-    out->flat = nullptr;
+    out->flat = out->split = nullptr;
     out->grid = (int)launch_grid(v, g, grid, kDefaultMachine);
     out->lds = (size_t)g.lds_bytes;
     return CACNN_OK;
@@ -1141,12 +1148,17 @@ double load_clocks(int bytes, double run_bytes, bool aligned4, bool whole_quads)
     return whole_quads || run_lanes >= 32.0 ? clk : std::max(clk, 40.0 - run_lanes);
 }
 
-double flat_us(const cacnn_problem& p, int dtype, const FlatInfo& v) {
+// part_stages > 0: a tile's contraction is divided into parts of so many stages.  Sums leave in parallel and meet at the memory behind the L2s:
+// 1.67 us, 0.245 us for every part that the last workgroup reads 16 rows a wave of, and the sums at 2.7 TB/s (fitted to 14000
+// launches of 400 layers: 10 % (one standard deviation) where the time is within 1.5 of the layer's best).
+double flat_us(const cacnn_problem& p, int dtype, const FlatInfo& v, int64_t part_stages = 0) {
     const bool f32 = dtype == CACNN_F32, run = v.IM < 0;
     const int esz = f32 ? 4 : 2, ch = 16 / esz, ipl = run ? -v.IM : v.IM;
     const int64_t T = p.S * p.C, chunks = p.R * ceil_div(T, ch);
     const int64_t groups = p.H * p.W * (run ? 1 : ceil_div(p.B, ipl));
-    const double per_cu = std::ceil((double)ceil_div(p.K, v.KT()) * (double)ceil_div(groups, v.GT()) / (double)kDefaultMachine.num_cu);
+    const int64_t stages_in_all = v.NCH ? ceil_div(chunks, v.NCH) : 0, parts = part_stages ? ceil_div(stages_in_all, part_stages) : 1;
+    const double tiles = (double)ceil_div(p.K, v.KT()) * (double)ceil_div(groups, v.GT());
+    const double per_cu = std::ceil(tiles * (double)parts / (double)kDefaultMachine.num_cu);
     const double waves = v.WM * v.WN * v.WK, simd_waves = std::ceil(waves / 4.0), mfma = f32 ? 256.0 : 32.0;   // of one block's step
     const double blocks = v.MB * v.NG * (run || !v.NCH ? ipl : 1);                                            // of one wave
     const bool flt_aligned = f32 || T % 2 == 0, img_aligned = f32 || (run ? p.C * p.B : p.B) % 2 == 0;
@@ -1172,7 +1184,7 @@ double flat_us(const cacnn_problem& p, int dtype, const FlatInfo& v) {
         const double simd = per_cu * simd_waves * mine * (blocks * mfma + 62.0), latency = (mine / 4.0 + 0.75) * 1020.0;
         clk = std::sqrt(load * load + simd * simd + latency * latency);
     } else {
-        const double stages = (double)ceil_div(chunks, v.NCH), cols = v.WN * v.NG * 32, kt = v.KT();
+        const double stages = (double)(part_stages ? part_stages : stages_in_all), cols = v.WN * v.NG * 32, kt = v.KT();
         const double steps = std::max(1, v.NCH / 2 / v.WK);                                                   // of a wave per stage
         const double flt_items = kt * v.NCH, img_items = run ? cols * v.NCH * ipl : (double)v.NCH * ch * v.GT();
         const double load = flt_items / 64.0 * load_clocks(16, (double)std::min<int64_t>(v.NCH * 16, T * esz), flt_aligned, true) +
@@ -1186,7 +1198,9 @@ double flat_us(const cacnn_problem& p, int dtype, const FlatInfo& v) {
         clk = std::sqrt(busy * busy + latency * latency) + 1000.0;
     }
     clk += per_cu * blocks * (v.WM * v.WN * 200.0 + (v.WK > 1 ? waves * 110.0 : 0.0));                        // Out
-    return with_copy_time(clk / 2272.0, p, dtype) + 2.1;
+    double us = with_copy_time(clk / 2272.0, p, dtype) + 2.1;
+    if (parts > 1) us += 1.67 + 0.245 * (double)parts * v.words() / (waves * 1024.0) + 1.5e-6 * tiles * (double)parts * v.words();
+    return us;
 }
 
 // The flattened kernel with the smallest estimate, -1 if none takes the problem.
@@ -1199,6 +1213,40 @@ int choose_flat(const cacnn_problem& p, int dtype, double* us) {
         if (best < 0 || t < *us) {
             best = i;
             *us = t;
+        }
+    }
+    return best;
+}
+
+// The stages of a part and the number of parts when a tile's contraction is divided into `want` of them, as evenly as whole stages
+// allow; 0 if it cannot be (the kernel stages nothing, there are too few stages or too many sums).
+int split_parts(const cacnn_problem& p, int dtype, const FlatInfo& v, int64_t want, int64_t* part_stages) {
+    if (!v.NCH || want < 2) return 0;
+    const int64_t groups = p.H * p.W * (v.IM < 0 ? 1 : ceil_div(p.B, v.IM));
+    const int64_t tiles = ceil_div(p.K, v.KT()) * ceil_div(groups, v.GT());
+    const int64_t stages = ceil_div(p.R * ceil_div(p.S * p.C, dtype == CACNN_F32 ? 4 : 8), v.NCH);
+    *part_stages = ceil_div(stages, want);
+    const int64_t parts = ceil_div(stages, *part_stages);
+    return parts >= 2 && tiles <= kSplitTiles && parts * tiles <= kSplitWords / v.words() ? (int)parts : 0;
+}
+
+// The kernel and the number of parts with the smallest estimate among launches whose workgroups share a tile's contraction, -1 if there is none
+int choose_split(const cacnn_problem& p, int dtype, int only, int* best_parts, double* us) {
+    static const int kParts[] = {2, 3, 4, 6, 8, 12, 16, 24, 32, 48};
+    int best = -1;
+    for (int i = only < 0 ? 0 : only; i < (only < 0 ? num_flat() : only + 1); ++i) {
+        const FlatInfo& v = flat_variant(i).info;
+        if (!v.NCH || !flat_fits(p, dtype, v)) continue;
+        for (int want : kParts) {
+            int64_t part_stages = 0;
+            const int parts = split_parts(p, dtype, v, want, &part_stages);
+            if (!parts) continue;
+            const double t = flat_us(p, dtype, v, part_stages);
+            if (best < 0 || t < *us) {
+                best = i;
+                *best_parts = parts;
+                *us = t;
+            }
         }
     }
     return best;
@@ -1250,8 +1298,28 @@ int prepare_flat(const cacnn_problem& p, int dtype, int fi, Launch* out) {
     a.d_TC = make_flatdiv(a.TC);
     a.d_inner = make_flatdiv(a.inner);
     out->flat = &var;
+    out->split = nullptr;
     out->tiled = nullptr;
     out->grid = (int)grid;
+    return CACNN_OK;
+}
+
+int prepare_split(const cacnn_problem& p, int dtype, int fi, int want, Launch* out) {
+    int64_t part_stages = 0;
+    Launch l;
+    if (prepare_flat(p, dtype, fi, &l) != CACNN_OK) return CACNN_ERR_UNSUPPORTED;
+    const int parts = split_parts(p, dtype, l.flat->info, want, &part_stages);
+    if (!parts) return CACNN_ERR_UNSUPPORTED;
+    FlatSplitArgs& a = out->fs;
+    static_cast<FlatArgs&>(a) = l.f;
+    a.parts = (uint32_t)parts;
+    a.part_stages = (uint32_t)part_stages;
+    a.tiles = (uint32_t)l.grid;
+    a.d_tiles = make_flatdiv(a.tiles);
+    out->split = l.flat;
+    out->split_grid = l.grid * parts;
+    a.xcd_q = (uint32_t)out->split_grid / kFlatXcds;
+    a.xcd_rem = (uint32_t)out->split_grid % kFlatXcds;
     return CACNN_OK;
 }
 
@@ -1301,6 +1369,12 @@ double flat_margin(const cacnn_problem& p, int dtype) {
     return std::min(0.7, 0.85 * std::pow(overlap * std::max(1.0, image / 256e6), -0.2));
 }
 
+// Workgroups share a tile's contraction where the estimate of that is below the other kernel's by this factor: with 1.0 15 of 400 layers
+// take up to 1.22 times as long as undivided, with 1.2 one (1.05 times), and the time over all 400 is 0.888 of the undivided one, against 0.882.
+// fp32 (1, 784, 64, 3, 12, 3 x 3) 42.2 -> 8.8 us, (4, 464, 156, 10, 7, 3 x 3) 30.6 -> 12.6, bf16 (3, 859, 480, 42, 5, 3 x 3, s 2) 41.5 ->
+// 28.5, (72, 976, 16, 5, 5, 3 x 3, s 2) 27.8 -> 11.7
+constexpr double kSplitMargin = 1.2;
+
 // What cacnn_conv_forward launches: the planned variant or a kernel with flattened positions.  A generic variant
 // gives way to a flattened kernel that takes the problem, but for the case above: on 1500 layers whose plan was a generic variant, large and
 // small ones and all those where the two estimates are near each other, the flattened kernel took 0.02 to 1.0 times as long.  A fixed-geometry
@@ -1316,8 +1390,14 @@ int plan_route(const cacnn_problem& p, int dtype, bool aligned_img, bool aligned
         // (a call whose plan cannot be launched is refused, as it would be without the flattened kernels)
         const VariantInfo& v = variant(plan.variant).info;
         if (fi >= 0 && tile_list_in_range(p, v, plan.xcd_walk, plan.xcd_split_k) &&
-            (v.fx_ct == 0 ? !boxes_for_short_rows(p, dtype) : flat_est < flat_margin(p, dtype) * (with_copy_time(tiled_us - 2.1, p, dtype) + 2.1)))
-            return prepare_flat(p, dtype, fi, out);
+            (v.fx_ct == 0 ? !boxes_for_short_rows(p, dtype) : flat_est < flat_margin(p, dtype) * (with_copy_time(tiled_us - 2.1, p, dtype) + 2.1))) {
+            const int frc = prepare_flat(p, dtype, fi, out);
+            int parts = 0;
+            double split_est = 0.0;
+            const int si = frc == CACNN_OK ? choose_split(p, dtype, -1, &parts, &split_est) : -1;
+            if (si >= 0 && split_est * kSplitMargin < flat_est) (void)prepare_split(p, dtype, si, parts, out);
+            return frc;
+        }
     }
     return prepare_tiled(p, dtype, plan.variant, plan.b_c, plan.b_r, plan.b_s, plan.xcd_split_k, plan.xcd_walk, aligned_img, aligned_flt, out);
 }
@@ -1506,6 +1586,20 @@ int cacnn_tune(const cacnn_problem* problem, int dtype, const void* image, const
             best_ms = ms;
         }
     }
+    // ... and those whose workgroups share the contraction, each with the number of parts that the estimate likes best
+    int split = -1, split_parts = 0;
+    for (int i = 0; i < num_flat() && best.variant >= 0 && !hip_stream; ++i) {
+        int parts = 0;
+        double us = 0.0;
+        Launch l;
+        if (choose_split(*problem, dtype, i, &parts, &us) < 0 || prepare_split(*problem, dtype, i, parts, &l) != CACNN_OK) continue;
+        const float ms = time_ms([&] { return fire(l, image, filter, out, nullptr); });
+        if (ms >= 0.f && ms < best_ms) {
+            split = i;
+            split_parts = parts;
+            best_ms = ms;
+        }
+    }
     (void)hipEventDestroy(e0);
     (void)hipEventDestroy(e1);
     if (best.variant < 0) return status;
@@ -1517,6 +1611,7 @@ int cacnn_tune(const cacnn_problem* problem, int dtype, const void* image, const
                               : prepare_tiled(*problem, dtype, plan.variant, plan.b_c, plan.b_r, plan.b_s, plan.xcd_split_k, plan.xcd_walk,
                                               aligned16(image), aligned16(filter), &launch);
     if (lrc != CACNN_OK) return lrc;
+    if (split >= 0) (void)prepare_split(*problem, dtype, split, split_parts, &launch);
     store_plan(*problem, key, launch);
     if (out_plan) *out_plan = plan;
     return CACNN_OK;
@@ -1862,6 +1957,18 @@ int cacnn_internal_route(const cacnn_problem* problem, int dtype, const void* im
     four[3] = l.flat ? l.flat->info.threads() : l.tiled->info.threads();
     return CACNN_OK;
 }
+// {kernel; parts; workgroups} where cacnn_conv_forward launches, on the null stream, workgroups that share a tile's contraction; else zeros
+int cacnn_internal_route_split(const cacnn_problem* problem, int dtype, const void* image, const void* filter, int32_t* three) {
+    if (!problem || !three) return CACNN_ERR_NULL;
+    if (dtype != CACNN_F32 && dtype != CACNN_BF16_F32ACC) return CACNN_ERR_UNSUPPORTED;
+    Launch l;
+    const int rc = route(*problem, dtype, image, filter, &l);
+    if (rc != CACNN_OK) return rc;
+    three[0] = l.split ? (int32_t)(l.split - &flat_variant(0)) : 0;
+    three[1] = l.split ? (int32_t)l.fs.parts : 0;
+    three[2] = l.split ? l.split_grid : 0;
+    return CACNN_OK;
+}
 // Images per thread of a pooling call with operands at these addresses, 0 if it is refused
 int cacnn_internal_pool_images(const cacnn_problem* problem, int dtype, const void* image, const void* out) {
     PoolArgs a;
@@ -1889,6 +1996,17 @@ int cacnn_internal_flat_forward(const cacnn_problem* problem, int dtype, int ind
     if (rc != CACNN_OK) return rc;
     if (index < 0 || index >= num_flat()) return CACNN_ERR_UNSUPPORTED;
     return launch_flat(*problem, dtype, index, image, filter, out, hip_stream);
+}
+// The same kernel with the contraction of a tile divided into about `parts` parts, on the null stream
+int cacnn_internal_split_forward(const cacnn_problem* problem, int dtype, int index, int parts, const void* image, const void* filter, void* out) {
+    if (!problem || !image || !filter || !out) return CACNN_ERR_NULL;
+    if (dtype != CACNN_F32 && dtype != CACNN_BF16_F32ACC) return CACNN_ERR_UNSUPPORTED;
+    if (!valid_problem(problem) || validate_dims(*problem) != CACNN_OK) return CACNN_ERR_INVALID_ARG;
+    if (index < 0 || index >= num_flat()) return CACNN_ERR_UNSUPPORTED;
+    if (!pointers_legal(dtype, image, filter, out)) return CACNN_ERR_INVALID_ARG;
+    Launch l;
+    const int rc = prepare_split(*problem, dtype, index, parts, &l);
+    return rc != CACNN_OK ? rc : fire(l, image, filter, out, nullptr);
 }
 
 int cacnn_variant_count(void) { return num_variants(); }

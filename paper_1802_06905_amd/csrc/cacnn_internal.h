@@ -172,6 +172,13 @@ struct FlatArgs {
     uint32_t xcd_q, xcd_rem;
     FlatDiv d_G, d_W, d_TC, d_inner;
 };
+// A launch whose workgroups share a tile's contraction: parts of part_stages LDS stages each (the last may be shorter).
+struct FlatSplitArgs : FlatArgs {
+    uint32_t parts, part_stages, tiles;
+    FlatDiv d_tiles;
+};
+// What the device's scratch memory for them holds: tiles, and words of partial sums.
+constexpr uint32_t kSplitTiles = 4096, kSplitWords = 2u << 20;
 struct FlatInfo {
     int dtype;          // cacnn_dtype
     int MB, NG;         // blocks of 32 of one wave: output channels, groups of images
@@ -181,10 +188,12 @@ struct FlatInfo {
     int threads() const { return WM * WN * WK * 64; }
     int KT() const { return WM * MB * 32; }
     int GT() const { return WN * NG * 32 / (NCH && IM > 0 ? IM : 1); }   // groups of images per tile
+    int words() const { return KT() * WN * NG * 32 * (NCH && IM > 0 ? 1 : IM < 0 ? -IM : IM); }   // outputs of a tile
 };
 struct FlatVariant {
     FlatInfo info;
     int (*launch)(const FlatArgs& a, int grid, void* stream);
+    int (*launch_split)(const FlatSplitArgs& a, int grid, void* stream);   // null: operands straight from global memory
 };
 int num_flat();
 const FlatVariant& flat_variant(int i);

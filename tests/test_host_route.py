@@ -144,3 +144,18 @@ def test_images_per_thread_of_a_pooling_call():
     # (4 images per thread only where the kernel's divisions hold as many threads)
     assert pool_images((32, 7000, 7000, 1, 1, 2, 2, 1, 1), BF16) == 4 and pool_images((32, 30000, 30000, 1, 1, 2, 2, 1, 1), BF16) == 8
     assert pool_images((64, 40, 39, 20, 20, 2, 2, 2, 2), BF16) == 0
+
+
+# Workgroups share a tile's contraction where few tiles have a long one; their sums and tiles fit the scratch memory, and where the tiles
+# fill the device or the contraction is short nothing is divided.
+def test_long_contractions_of_few_tiles_are_divided():
+    for dtype, dims in ((F32, (1, 784, 64, 3, 12, 3, 3, 1, 1)), (BF16, (72, 976, 16, 5, 5, 3, 3, 2, 2)), (BF16, (3, 859, 480, 42, 5, 3, 3, 2, 2))):
+        name, parts, workgroups = binding.routed_split(dims, dtype)
+        assert " flat " in name and not name.endswith(" c0") and parts >= 2 and workgroups % parts == 0
+        m, n, i, w, _ = name.split()[2:]
+        wm, wn, _ = (int(x) for x in w[1:].split("x"))
+        words = wm * int(m[1:]) * 32 * wn * int(n[1:]) * 32 * max(1, -int(i[1:]))
+        assert workgroups * words <= 2 ** 21 and workgroups // parts <= 4096
+    for dtype, dims in ((F32, (1, 3, 8, 16, 16, 3, 3, 1, 1)), (BF16, (1, 128, 128, 28, 28, 3, 3, 1, 1)), (BF16, (16, 3, 64, 112, 112, 7, 7, 2, 2)),
+                        (F32, (64, 64, 64, 56, 56, 1, 1, 1, 1)), (F32, (7, 1, 8, 5, 5, 1, 1, 1, 1))):
+        assert binding.routed_split(dims, dtype) is None
