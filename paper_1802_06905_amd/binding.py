@@ -292,13 +292,18 @@ def routed_kernel(problem, dtype: int, image: int = 0, filt: int = 0):
     """(name, workgroups, threads of one) of the kernel that cacnn_conv_forward launches for a problem and operands at these addresses,
     whose alignment is all that matters (host only).  A variant's name is that of cacnn_variant_name; a flattened kernel's is "bf16 flat
     m<blocks of output channels> n<blocks of columns> i<images per lane, < 0: all of the batch> w<waves along k, columns, contraction>
-    c<chunks per LDS stage, 0: straight from global memory>"."""
+    c<chunks per LDS stage, 0: straight from global memory>", that of one which keeps a tile's window in LDS "bf16 flat window m<blocks of output
+    channels> n<blocks of columns> w<waves along k, columns> b<images of a tile>"."""
     four, eight = (ctypes.c_int32 * 4)(), (ctypes.c_int32 * 8)()
     rc = _lib.cacnn_internal_route(ctypes.byref(_as_problem(problem)), int(dtype), int(image), int(filt), four)
     if rc != 0:
         raise CacnnError(rc, "cacnn_internal_route")
     if not four[0]:
         return cacnn_variant_name(four[1]), four[2], four[3]
+    if four[0] == 2:
+        _lib.cacnn_internal_window_info(four[1], eight)
+        mb, nb, wm, wn, tb = eight[:5]
+        return f"bf16 flat window m{mb} n{nb} w{wm}x{wn} b{tb}", four[2], four[3]
     _lib.cacnn_internal_flat_info(four[1], eight)
     return _flat_name(eight), four[2], four[3]
 

@@ -953,10 +953,12 @@ bool tile_list_in_range(const cacnn_problem& p, const VariantInfo& v, int walk, 
 struct Launch {
     const Variant* tiled = nullptr;
     const FlatVariant* flat = nullptr;
+    const WindowVariant* window = nullptr;
     const FlatVariant* split = nullptr;     // what runs instead on the null stream: workgroups that share a tile's contraction
     KernelArgs a;
     FlatArgs f;
     FlatSplitArgs fs;
+    WindowArgs w;
     int grid = 0, split_grid = 0;
     size_t lds = 0;
 };
@@ -981,6 +983,11 @@ int fire(Launch& l, const void* image, const void* filter, void* out, void* stre
         l.f.filter = filter;
         l.f.out = (float*)out;
         rc = l.flat->launch(l.f, l.grid, stream);
+    } else if (l.window) {
+        l.w.image = image;
+        l.w.filter = filter;
+        l.w.out = (float*)out;
+        rc = l.window->launch(l.w, l.grid, l.lds, stream);
     } else {
         l.a.image = image;
         l.a.filter = filter;
@@ -1090,6 +1097,7 @@ int prepare_tiled(const cacnn_problem& p, int dtype, int vi, int CT, int bR, int
     a.flt_resident = g.flt_resident;
     out->tiled = &var;
     out->flat = out->split = nullptr;
+    out->window = nullptr;
     out->grid = (int)launch_grid(v, g, grid, kDefaultMachine);
     out->lds = (size_t)g.lds_bytes;
     return CACNN_OK;
@@ -1299,6 +1307,7 @@ int prepare_flat(const cacnn_problem& p, int dtype, int fi, Launch* out) {
     a.d_inner = make_flatdiv(a.inner);
     out->flat = &var;
     out->split = nullptr;
+    out->window = nullptr;
     out->tiled = nullptr;
     out->grid = (int)grid;
     return CACNN_OK;
@@ -1328,6 +1337,133 @@ int launch_flat(const cacnn_problem& p, int dtype, int fi, const void* image, co
     Launch l;
     const int rc = prepare_flat(p, dtype, fi, &l);
     return rc != CACNN_OK ? rc : fire(l, image, filter, out, stream);
+}
+
+// ------------------------------------------------------------------------------------------------------------
+// The bf16 kernels that keep a tile's window in LDS (cacnn_window.hip).
+
+struct WindowTile {
+    int TW = 0, TH = 0;     // output columns and rows
+    int bufs = 0;           // boxes in LDS: 2, workgroups walk position tiles, or 1, they take one each
+};
+
+// The launch of a window kernel with these tiles; CACNN_ERR_UNSUPPORTED where it does not take them.  Whole 16-byte items along b, filter
+// columns of at least one chunk, Image, Filter and a row of Out within the 2 GiB of 32-bit offsets, the Filter tile and the boxes in LDS.
+int prepare_window(const cacnn_problem& p, int wi, const WindowTile& t, Launch* out) {
+    const WindowVariant& var = window_variant(wi);
+    const WindowInfo& v = var.info;
+    const int64_t IW = p.sigma_w * (p.W - 1) + p.R, IH = p.sigma_h * (p.H - 1) + p.S;
+    const double img = 2.0 * (double)IW * (double)IH * (double)p.C * (double)p.B, flt = 2.0 * (double)p.K * p.R * p.S * p.C;
+    if (p.B % 8 != 0 || p.S * p.C < 8 || img >= 2147483648.0 || flt >= 2147483648.0) return CACNN_ERR_UNSUPPORTED;
+    if (20.0 * (double)p.H * (double)p.W * (double)p.B >= 2147483648.0) return CACNN_ERR_UNSUPPORTED;
+    if (t.TW < 1 || t.TH < 1 || (t.TW & (t.TW - 1)) || (t.TH & (t.TH - 1)) || t.TW * t.TH * v.TB != v.cols()) return CACNN_ERR_UNSUPPORTED;
+    const int64_t nx = p.sigma_w * (t.TW - 1) + p.R, ny = p.sigma_h * (t.TH - 1) + p.S, waves = v.threads() / 64;
+    const double box = (double)nx * (double)ny * p.C * v.TB * 2.0, chunks = (double)p.R * (double)ceil_div(p.S * p.C, 8);
+    if (box > 131072.0 || chunks * v.KT() * 16.0 > 131072.0) return CACNN_ERR_UNSUPPORTED;
+    WindowArgs& a = out->w;
+    std::memset(&a, 0, sizeof(a));
+    a.N = (uint32_t)(p.H * p.W * p.B);
+    a.K = (uint32_t)p.K;
+    a.B = (uint32_t)p.B;
+    a.C = (uint32_t)p.C;
+    a.W = (uint32_t)p.W;
+    a.H = (uint32_t)p.H;
+    a.sw = (uint32_t)p.sigma_w;
+    a.sh = (uint32_t)p.sigma_h;
+    a.img_bytes = (uint32_t)img;
+    a.img_x = (uint32_t)(IH * p.C * p.B * 2);
+    a.img_w = (uint32_t)p.sigma_w * a.img_x;
+    a.img_h = (uint32_t)(p.sigma_h * p.C * p.B * 2);
+    a.flt_tap = (uint32_t)(p.S * p.C * 2);
+    a.flt_k = (uint32_t)p.R * a.flt_tap;
+    while ((1 << a.tw_shift) < t.TW) ++a.tw_shift;
+    while ((1 << a.th_shift) < t.TH) ++a.th_shift;
+    a.tiles_h = (uint32_t)ceil_div(p.H, t.TH);
+    a.tiles_b = (uint32_t)ceil_div(p.B, v.TB);
+    a.tiles_n = (uint32_t)ceil_div(p.W, t.TW) * a.tiles_h * a.tiles_b;
+    a.plane = (uint32_t)(ny * p.C);
+    a.rows = (uint32_t)nx * a.plane;
+    a.TC = (uint32_t)ceil_div(p.S * p.C, 8);
+    a.back = 8 * a.TC - (uint32_t)(p.S * p.C);
+    a.U = (uint32_t)p.R * a.TC;
+    a.steps = ((a.U + 1) / 2 + 1) & ~1u;
+    a.UP = 2 * a.steps + 1;                     // odd: the rows that a read takes at once lie in different banks
+    const uint32_t row = (uint32_t)v.TB * 2;
+    a.off_r = a.plane * row;
+    a.adv_i = 2 % a.TC;
+    a.adv_off = 2 / a.TC * a.off_r + a.adv_i * 8 * row;
+    a.wrap_off = a.off_r - a.TC * 8 * row;
+    a.img_items = (uint32_t)ceil_div(ceil_div(a.rows * row, 1024), waves);
+    a.img_lds = a.img_items * (uint32_t)waves * 1024;
+    a.flt_lds = (uint32_t)ceil_div((int64_t)v.KT() * a.UP * 16, 1024) * 1024;
+    a.zeros = a.flt_lds + (uint32_t)t.bufs * a.img_lds;
+    out->lds = (size_t)a.zeros + 8 * row;
+    if (a.img_items > kWindowItems || out->lds > 160 * 1024) return CACNN_ERR_UNSUPPORTED;
+    const int64_t tiles_k = ceil_div(p.K, v.KT());
+    int64_t walkers = a.tiles_n;                // workgroups of a tile of output channels
+    if (t.bufs == 2) {
+        const int64_t per_cu = std::max<int64_t>(1, std::min<int64_t>(160 * 1024 / (int64_t)out->lds, 16 / waves));
+        walkers = std::max<int64_t>(1, std::min<int64_t>(walkers, kDefaultMachine.num_cu * per_cu / tiles_k));
+    }
+    if ((double)tiles_k * (double)a.tiles_n * v.threads() >= 4294967296.0) return CACNN_ERR_UNSUPPORTED;
+    a.t_step = (uint32_t)walkers;
+    a.k_inner = img >= flt ? 1u : 0u;
+    a.inner = (uint32_t)(a.k_inner ? tiles_k : walkers);
+    out->grid = (int)(tiles_k * walkers);
+    a.xcd_q = (uint32_t)out->grid / kFlatXcds;
+    a.xcd_rem = (uint32_t)out->grid % kFlatXcds;
+    a.d_inner = make_flatdiv(a.inner);
+    a.d_tb = make_flatdiv(a.tiles_b);
+    a.d_th = make_flatdiv(a.tiles_h);
+    a.d_plane = make_flatdiv(a.plane);
+    a.d_UP = make_flatdiv(a.UP);
+    a.d_TC = make_flatdiv(a.TC);
+    out->window = &var;
+    out->tiled = nullptr;
+    out->flat = out->split = nullptr;
+    return CACNN_OK;
+}
+
+// The window kernel of a first layer: few channels, and a batch of which every tile is whole rows of images (others, whose stores are pieces of
+// cache lines, took up to 1.36 times as long as the flattened kernels).  The box with the fewest staged words that leaves room for
+// a second workgroup on the compute unit; one box per workgroup or two, whichever fills its last round of tiles better.  -1 where the
+// flattened kernel's estimate is below 10 us (1.7 us are spent before the first product: 5.6 -> 7.3 us at (8, 3, 64, 56, 56, 7 x 7, s 2)), and, up to 22
+// us, where less than 0.64 of the last round and of the tiles along k is filled ((128, 3, 48, 56, 24, 3 x 3) 10.6 -> 12.3 us).  Over 113 first layers of
+// 8 us and more the time is 0.89 of the flattened kernels' in the geometric mean, 0.51 at best and 1.03 at worst.
+int choose_window(const cacnn_problem& p, double flat_est, WindowTile* tile) {
+    if (flat_est < 10.0 || p.C > 4 || (p.B % 32 != 0 && p.B != 16 && p.B != 8)) return -1;
+    const int TB = (int)std::min<int64_t>(p.B, 32);
+    int best = -1;
+    double best_fill = 0.0;
+    for (int i = 0; i < num_window(); ++i) {
+        const WindowInfo& v = window_variant(i).info;
+        if (v.TB != TB) continue;
+        for (int bufs = 2; bufs >= 1; --bufs) {
+            Launch l;
+            WindowTile t, pick;
+            double words = 0.0;
+            t.bufs = bufs;
+            for (t.TW = v.cols() / TB; t.TW >= 1; t.TW /= 2) {
+                t.TH = v.cols() / TB / t.TW;
+                if (prepare_window(p, i, t, &l) != CACNN_OK || l.lds > 80 * 1024) continue;
+                const double w = (double)l.w.tiles_n * (double)l.w.rows;
+                if (!pick.TW || w < words) pick = t, words = w;
+            }
+            if (!pick.TW || prepare_window(p, i, pick, &l) != CACNN_OK) continue;
+            // tiles per round of the workgroups that are resident together (launch_bounds: four waves a SIMD)
+            const double resident = (double)kDefaultMachine.num_cu * (double)std::min<int64_t>(160 * 1024 / (int64_t)l.lds, 16 / (v.threads() / 64));
+            const double rounds = bufs == 2 ? (double)l.w.tiles_n / l.w.t_step : (double)l.grid / resident;
+            const double fill = rounds / std::ceil(rounds);
+            if (best < 0 || fill > best_fill + 0.1) {       // (nearly level, two boxes are faster: (16, 3, 64, 112, 112, 7 x 7, s 2) 16.4 us with fills of 0.68, 17.9 with 0.77)
+                best = i;
+                best_fill = fill;
+                *tile = pick;
+            }
+        }
+    }
+    if (best < 0) return -1;
+    best_fill *= (double)p.K / (double)round_up(p.K, window_variant(best).info.KT());
+    return best_fill < 0.64 && flat_est < 22.0 ? -1 : best;
 }
 
 // Launch cache of cacnn_conv_forward, keyed by (problem, dtype, alignment of the two operands): planning costs tens of
@@ -1391,6 +1527,9 @@ int plan_route(const cacnn_problem& p, int dtype, bool aligned_img, bool aligned
         const VariantInfo& v = variant(plan.variant).info;
         if (fi >= 0 && tile_list_in_range(p, v, plan.xcd_walk, plan.xcd_split_k) &&
             (v.fx_ct == 0 ? !boxes_for_short_rows(p, dtype) : flat_est < flat_margin(p, dtype) * (with_copy_time(tiled_us - 2.1, p, dtype) + 2.1))) {
+            WindowTile tile;
+            const int wi = dtype != CACNN_F32 && aligned_img ? choose_window(p, flat_est, &tile) : -1;
+            if (wi >= 0 && prepare_window(p, wi, tile, out) == CACNN_OK) return CACNN_OK;
             const int frc = prepare_flat(p, dtype, fi, out);
             int parts = 0;
             double split_est = 0.0;
@@ -1944,17 +2083,17 @@ int cacnn_internal_pool_forward_sized(const cacnn_problem* problem, int dtype, i
     return cacnn_pool_forward(problem, dtype, mode, image, out, hip_stream);
 }
 // Which kernel cacnn_conv_forward launches for a problem and operands at these addresses (of which the alignment alone matters):
-// {0: a variant with box tiles, 1: a flattened kernel; its index; workgroups; threads of one}.  Nothing is enqueued.
+// {0: a variant with box tiles, 1: a flattened kernel, 2: a window kernel; its index; workgroups; threads of one}.  Nothing is enqueued.
 int cacnn_internal_route(const cacnn_problem* problem, int dtype, const void* image, const void* filter, int32_t* four) {
     if (!problem || !four) return CACNN_ERR_NULL;
     if (dtype != CACNN_F32 && dtype != CACNN_BF16_F32ACC) return CACNN_ERR_UNSUPPORTED;
     Launch l;
     const int rc = route(*problem, dtype, image, filter, &l);
     if (rc != CACNN_OK) return rc;
-    four[0] = l.flat ? 1 : 0;
-    four[1] = l.flat ? (int32_t)(l.flat - &flat_variant(0)) : (int32_t)(l.tiled - &variant(0));
+    four[0] = l.window ? 2 : l.flat ? 1 : 0;
+    four[1] = l.window ? (int32_t)(l.window - &window_variant(0)) : l.flat ? (int32_t)(l.flat - &flat_variant(0)) : (int32_t)(l.tiled - &variant(0));
     four[2] = l.grid;
-    four[3] = l.flat ? l.flat->info.threads() : l.tiled->info.threads();
+    four[3] = l.window ? l.window->info.threads() : l.flat ? l.flat->info.threads() : l.tiled->info.threads();
     return CACNN_OK;
 }
 // {kernel; parts; workgroups} where cacnn_conv_forward launches, on the null stream, workgroups that share a tile's contraction; else zeros
@@ -2007,6 +2146,33 @@ int cacnn_internal_split_forward(const cacnn_problem* problem, int dtype, int in
     Launch l;
     const int rc = prepare_split(*problem, dtype, index, parts, &l);
     return rc != CACNN_OK ? rc : fire(l, image, filter, out, nullptr);
+}
+
+int cacnn_internal_window_count(void) { return num_window(); }
+// {blocks of 32 output channels and of 32 columns of a wave; waves along either; images of a tile}
+int cacnn_internal_window_info(int i, int32_t* five) {
+    if (i < 0 || i >= num_window() || !five) return CACNN_ERR_INVALID_ARG;
+    const WindowInfo& v = window_variant(i).info;
+    const int32_t x[5] = {v.MB, v.NB, v.WM, v.WN, v.TB};
+    std::memcpy(five, x, sizeof(x));
+    return CACNN_OK;
+}
+// A window kernel with tiles of TW columns and `bufs` boxes, bf16
+int cacnn_internal_window_forward(const cacnn_problem* problem, int index, int TW, int bufs, const void* image, const void* filter, void* out,
+                                  void* hip_stream) {
+    if (!problem || !image || !filter || !out) return CACNN_ERR_NULL;
+    if (!valid_problem(problem) || validate_dims(*problem) != CACNN_OK) return CACNN_ERR_INVALID_ARG;
+    if (index < 0 || index >= num_window() || TW < 1 || bufs < 1 || bufs > 2) return CACNN_ERR_UNSUPPORTED;
+    const WindowInfo& v = window_variant(index).info;
+    if (!pointers_legal(CACNN_BF16_F32ACC, image, filter, out)) return CACNN_ERR_INVALID_ARG;
+    if (!aligned16(image)) return CACNN_ERR_UNSUPPORTED;
+    WindowTile t;
+    t.TW = TW;
+    t.TH = v.cols() / v.TB / TW;
+    t.bufs = bufs;
+    Launch l;
+    const int rc = prepare_window(*problem, index, t, &l);
+    return rc != CACNN_OK ? rc : fire(l, image, filter, out, hip_stream);
 }
 
 int cacnn_variant_count(void) { return num_variants(); }

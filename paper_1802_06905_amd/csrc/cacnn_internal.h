@@ -198,6 +198,40 @@ struct FlatVariant {
 int num_flat();
 const FlatVariant& flat_variant(int i);
 
+// The bf16 kernels that keep a tile's window in LDS (cacnn_window.hip).  Offsets and strides in bytes.
+struct WindowArgs {
+    const void* image;
+    const void* filter;
+    float* out;
+    uint32_t N, K, B, C, W, H, sw, sh;
+    uint32_t img_bytes;
+    uint32_t img_x, img_w, img_h;                 // Image: one x, output column, output row further on
+    uint32_t flt_k, flt_tap;                      // Filter: one output channel, one r further on
+    uint32_t tw_shift, th_shift;                  // log2 of a tile's output columns / rows
+    uint32_t tiles_b, tiles_h, tiles_n;           // position tiles along b and h, and in all
+    uint32_t inner, k_inner, xcd_q, xcd_rem;      // tile list, as in FlatArgs
+    uint32_t t_step;                              // position tiles from one of a workgroup's to the next
+    uint32_t plane, rows;                         // rows of TB images in the box: of one x, in all
+    uint32_t TC, U, UP, steps, back;              // chunks of one r, in all; those of a Filter row in LDS; steps; rows by which the last chunk of an r is moved back
+    uint32_t off_r, adv_i, adv_off, wrap_off;     // LDS bytes from one r to the next; from a chunk to the one two further on
+    uint32_t img_items;                           // 1 KiB pieces of the box that every wave loads
+    uint32_t img_lds, flt_lds, zeros;             // LDS bytes of a box and of the Filter tile; where the zeros are
+    FlatDiv d_inner, d_tb, d_th, d_plane, d_UP, d_TC;
+};
+constexpr int kWindowItems = 8;                   // 1 KiB pieces of the box that one wave loads, at most
+struct WindowInfo {
+    int MB, NB, WM, WN, TB;
+    int threads() const { return WM * WN * 64; }
+    int KT() const { return WM * MB * 32; }
+    int cols() const { return WN * NB * 32; }
+};
+struct WindowVariant {
+    WindowInfo info;
+    int (*launch)(const WindowArgs& a, int grid, size_t lds, void* stream);
+};
+int num_window();
+const WindowVariant& window_variant(int i);
+
 // Pooling (cacnn_pool.hip): everything the kernel needs, by value.
 struct PoolArgs {
     const void* image;

@@ -159,3 +159,15 @@ def test_long_contractions_of_few_tiles_are_divided():
     for dtype, dims in ((F32, (1, 3, 8, 16, 16, 3, 3, 1, 1)), (BF16, (1, 128, 128, 28, 28, 3, 3, 1, 1)), (BF16, (16, 3, 64, 112, 112, 7, 7, 2, 2)),
                         (F32, (64, 64, 64, 56, 56, 1, 1, 1, 1)), (F32, (7, 1, 8, 5, 5, 1, 1, 1, 1))):
         assert binding.routed_split(dims, dtype) is None
+
+
+# A tile's window in LDS: first layers of few channels with whole rows of images, where the time before the first product is small beside the
+# rest; not for other batches, Images that 16-byte loads cannot read, or a last round of tiles that is mostly empty.
+def test_first_layers_keep_their_window_in_lds():
+    for dims in ((16, 3, 64, 112, 112, 7, 7, 2, 2), (32, 3, 64, 112, 112, 7, 7, 2, 2), (256, 3, 16, 98, 98, 5, 5, 1, 1)):
+        assert " flat window " in routed(dims, BF16)
+        assert " flat window " not in routed(dims, BF16, image=8) and " flat " in routed(dims, BF16, image=8)
+        assert " flat window " in routed(dims, BF16, filt=2)
+        assert " flat window " not in routed(dims, F32)
+    for dims in ((8, 3, 64, 56, 56, 7, 7, 2, 2), (40, 3, 64, 112, 112, 7, 7, 2, 2), (16, 2, 64, 112, 112, 7, 3, 2, 2), (64, 3, 59, 33, 72, 5, 5, 1, 1)):
+        assert " flat window " not in routed(dims, BF16) and " flat " in routed(dims, BF16)
