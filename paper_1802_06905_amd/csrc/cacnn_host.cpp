@@ -9,6 +9,7 @@
 #include <cstring>
 #include <limits>
 #include <list>
+#include <memory>
 #include <mutex>
 #include <unordered_map>
 #include <vector>
@@ -970,30 +971,22 @@ bool pointers_legal(int dtype, const void* image, const void* filter, const void
 
 bool aligned16(const void* p) { return reinterpret_cast<uintptr_t>(p) % 16 == 0; }
 
-int fire(Launch& l, const void* image, const void* filter, void* out, void* stream) {
+template <class Args>
+Args with_buffers(const Args& args, const void* image, const void* filter, void* out) {
+    Args a = args;
+    a.image = image;
+    a.filter = filter;
+    a.out = (float*)out;
+    return a;
+}
+
+int fire(const Launch& l, const void* image, const void* filter, void* out, void* stream) {
     if (!have_device()) return CACNN_ERR_NO_DEVICE;
     int rc;
-    if (l.split && !stream) {
-        l.fs.image = image;
-        l.fs.filter = filter;
-        l.fs.out = (float*)out;
-        rc = l.split->launch_split(l.fs, l.split_grid, stream);
-    } else if (l.flat) {
-        l.f.image = image;
-        l.f.filter = filter;
-        l.f.out = (float*)out;
-        rc = l.flat->launch(l.f, l.grid, stream);
-    } else if (l.window) {
-        l.w.image = image;
-        l.w.filter = filter;
-        l.w.out = (float*)out;
-        rc = l.window->launch(l.w, l.grid, l.lds, stream);
-    } else {
-        l.a.image = image;
-        l.a.filter = filter;
-        l.a.out = (float*)out;
-        rc = l.tiled->launch(l.a, l.grid, l.lds, stream);
-    }
+    if (l.split && !stream) rc = l.split->launch_split(with_buffers(l.fs, image, filter, out), l.split_grid, stream);
+    else if (l.flat) rc = l.flat->launch(with_buffers(l.f, image, filter, out), l.grid, stream);
+    else if (l.window) rc = l.window->launch(with_buffers(l.w, image, filter, out), l.grid, l.lds, stream);
+    else rc = l.tiled->launch(with_buffers(l.a, image, filter, out), l.grid, l.lds, stream);
     return rc == 0 ? CACNN_OK : CACNN_ERR_LAUNCH;
 }
 
@@ -1468,10 +1461,12 @@ int choose_window(const cacnn_problem& p, double flat_est, WindowTile* tile) {
 
 // Launch cache of cacnn_conv_forward, keyed by (problem, dtype, alignment of the two operands): planning costs tens of
 // microseconds and laying out a launch one, the launch itself two.  What is kept depends on the key alone, not on the buffers.
+// An entry is never changed: a call holds on to its launch (a kilobyte, which it need not copy) while others come and go.
+using LaunchPtr = std::shared_ptr<const Launch>;
 struct PlanEntry {
     cacnn_problem p;
     int key;
-    Launch launch;
+    LaunchPtr launch;
 };
 std::vector<PlanEntry> g_plans;
 
@@ -1541,33 +1536,31 @@ int plan_route(const cacnn_problem& p, int dtype, bool aligned_img, bool aligned
     return prepare_tiled(p, dtype, plan.variant, plan.b_c, plan.b_r, plan.b_s, plan.xcd_split_k, plan.xcd_walk, aligned_img, aligned_flt, out);
 }
 
-bool lookup_plan(const cacnn_problem& p, int key, Launch* out) {
+LaunchPtr lookup_plan(const cacnn_problem& p, int key) {
     std::lock_guard<std::mutex> lock(g_mutex);
     for (const PlanEntry& e : g_plans)
-        if (e.key == key && std::memcmp(&e.p, &p, sizeof(cacnn_problem)) == 0) {
-            *out = e.launch;
-            return true;
-        }
-    return false;
+        if (e.key == key && std::memcmp(&e.p, &p, sizeof(cacnn_problem)) == 0) return e.launch;
+    return nullptr;
 }
 
-void store_plan(const cacnn_problem& p, int key, const Launch& launch) {
+LaunchPtr store_plan(const cacnn_problem& p, int key, const Launch& launch) {
+    LaunchPtr kept = std::make_shared<const Launch>(launch);
     std::lock_guard<std::mutex> lock(g_mutex);
     for (PlanEntry& e : g_plans)
-        if (e.key == key && std::memcmp(&e.p, &p, sizeof(cacnn_problem)) == 0) {
-            e.launch = launch;
-            return;
-        }
+        if (e.key == key && std::memcmp(&e.p, &p, sizeof(cacnn_problem)) == 0) return e.launch = kept;
     if (g_plans.size() >= 64) g_plans.erase(g_plans.begin());
-    g_plans.push_back(PlanEntry{p, key, launch});
+    g_plans.push_back(PlanEntry{p, key, kept});
+    return kept;
 }
 
 // the launch of a call with these operands, remembered or planned now
-int route(const cacnn_problem& p, int dtype, const void* image, const void* filter, Launch* out) {
+int route(const cacnn_problem& p, int dtype, const void* image, const void* filter, LaunchPtr* out) {
     const int key = launch_key(dtype, image, filter);
-    if (lookup_plan(p, key, out)) return CACNN_OK;
-    const int rc = plan_route(p, dtype, aligned16(image), aligned16(filter), out);
-    if (rc == CACNN_OK) store_plan(p, key, *out);
+    *out = lookup_plan(p, key);
+    if (*out) return CACNN_OK;
+    Launch launch;
+    const int rc = plan_route(p, dtype, aligned16(image), aligned16(filter), &launch);
+    if (rc == CACNN_OK) *out = store_plan(p, key, launch);
     return rc;
 }
 
@@ -1590,11 +1583,11 @@ int cacnn_conv_forward(const cacnn_problem* problem, int dtype, const void* imag
                        void* hip_stream) {
     if (!problem || !image || !filter || !out) return CACNN_ERR_NULL;
     if (dtype != CACNN_F32 && dtype != CACNN_BF16_F32ACC) return CACNN_ERR_UNSUPPORTED;
-    Launch launch;
+    LaunchPtr launch;
     const int rc = route(*problem, dtype, image, filter, &launch);
     if (rc != CACNN_OK) return rc;
     if (!pointers_legal(dtype, image, filter, out)) return CACNN_ERR_INVALID_ARG;
-    return fire(launch, image, filter, out, hip_stream);
+    return fire(*launch, image, filter, out, hip_stream);
 }
 
 int cacnn_conv_forward_with_plan(const cacnn_problem* problem, int dtype, const cacnn_plan* plan, const void* image,
@@ -2087,9 +2080,10 @@ int cacnn_internal_pool_forward_sized(const cacnn_problem* problem, int dtype, i
 int cacnn_internal_route(const cacnn_problem* problem, int dtype, const void* image, const void* filter, int32_t* four) {
     if (!problem || !four) return CACNN_ERR_NULL;
     if (dtype != CACNN_F32 && dtype != CACNN_BF16_F32ACC) return CACNN_ERR_UNSUPPORTED;
-    Launch l;
-    const int rc = route(*problem, dtype, image, filter, &l);
+    LaunchPtr launch;
+    const int rc = route(*problem, dtype, image, filter, &launch);
     if (rc != CACNN_OK) return rc;
+    const Launch& l = *launch;
     four[0] = l.window ? 2 : l.flat ? 1 : 0;
     four[1] = l.window ? (int32_t)(l.window - &window_variant(0)) : l.flat ? (int32_t)(l.flat - &flat_variant(0)) : (int32_t)(l.tiled - &variant(0));
     four[2] = l.grid;
@@ -2100,9 +2094,10 @@ int cacnn_internal_route(const cacnn_problem* problem, int dtype, const void* im
 int cacnn_internal_route_split(const cacnn_problem* problem, int dtype, const void* image, const void* filter, int32_t* three) {
     if (!problem || !three) return CACNN_ERR_NULL;
     if (dtype != CACNN_F32 && dtype != CACNN_BF16_F32ACC) return CACNN_ERR_UNSUPPORTED;
-    Launch l;
-    const int rc = route(*problem, dtype, image, filter, &l);
+    LaunchPtr launch;
+    const int rc = route(*problem, dtype, image, filter, &launch);
     if (rc != CACNN_OK) return rc;
+    const Launch& l = *launch;
     three[0] = l.split ? (int32_t)(l.split - &flat_variant(0)) : 0;
     three[1] = l.split ? (int32_t)l.fs.parts : 0;
     three[2] = l.split ? l.split_grid : 0;
