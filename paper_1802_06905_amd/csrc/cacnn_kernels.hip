@@ -3098,6 +3098,177 @@ __global__ void __launch_bounds__(512) conv_f32_stem_direct_kernel(const KernelA
     }
 }
 
+// The same layer with one k-tile (K <= 64), where the Filter tile never changes: eight multiplying waves, two sets of four that work on two
+// tiles half a tile apart.  At the end of a tile its 32 KiB of Out take about as long to leave the compute unit as a quarter of the tile's
+// products take, and with one wave per SIMD nothing else is done meanwhile; here a set's stores come first in the half-step in
+// which the other set has its second half of products.  A half-step is 7 of the 14 groups of products for either set, and
+// there is one barrier at its end: half-step k is the first half of tile k for set k % 2 and the second half of tile k - 1 for the other, which
+// also fetches tile k + 1, as nobody reads the third buffer then.
+// No staging waves, so the loads to LDS are issued by waves that read LDS: as assembly, because the compiler makes every LDS access it
+// knows of wait for all outstanding loads into LDS.  A set waits for its loads at the end of a half-step in which it stores nothing.
+// Measured, four multiplying waves and four staging ones before (us): (32, 3, 64, 112, 112) 74.3 -> 70.2, (128, 3, 64, 54, 21) 34.9 -> 31.6, (256, 3, 37, 22,
+// 22) 32.6 -> 29.3.  The products alone are 54 us of the first: 13 rounds of 154 MFMAs of 64 cycles on tiles for 12.25.
+typedef int i32x4 __attribute__((ext_vector_type(4)));
+#pragma clang diagnostic push
+#pragma clang diagnostic ignored "-Winline-asm"
+// 64 lanes x 16 bytes, lane L's from byte off of the descriptor to LDS byte dst + 16 L (m0 belongs to no one for longer than the instruction it is set for)
+__device__ __forceinline__ void load_to_lds_unseen(i32x4 d, uint32_t off, uint32_t dst) {
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds" ::"s"(dst), "v"(off), "s"(d) : "memory", "m0");
+}
+#pragma clang diagnostic pop
+
+template <int TW, int TH, bool RAGGED>
+__global__ void __launch_bounds__(512) conv_f32_stem_pair_kernel(const KernelArgs a) {
+    using GEO = F32StemDirect<TW, TH>;
+    constexpr int R = GEO::R, S = GEO::S, C = GEO::C, SW = GEO::SW, SH = GEO::SH;
+    constexpr int TB = GEO::TB, KT = GEO::KT, WM = GEO::WM, NBLK = GEO::NBLK, XPB = GEO::XPB, ROWB = GEO::ROWB;
+    constexpr int QH = GEO::QH, QP = GEO::QP, FPW = GEO::FPW, IBUF = GEO::IMG_BYTES;
+    static_assert(GEO::WM * GEO::WN == 4 && NBLK == TW, "stem pair geometry: four waves a set, a wave owns one tile row");
+    extern __shared__ __align__(16) float smem_f[];
+    CACNN_LDS(char)* const lds = (CACNN_LDS(char)*)smem_f;
+    const int tid = threadIdx.x;
+    const int wave_id = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int lane = tid & 63;
+    const int set = wave_id >> 2, w4 = wave_id & 3, wm = w4 % WM, wn = w4 / WM;
+    const int total = ((int)a.n_tiles - (int)blockIdx.x + (int)gridDim.x - 1) / (int)gridDim.x;    // tiles of this workgroup
+    if (total <= 0) return;
+
+    // Image: lane L of wave p of a set fetches piece 64 p + L of a plane: row piece / 8 (rows are B words apart in global memory), 16
+    // bytes (piece % 8) of its 128; lanes beyond the last piece fetch the last one again
+    const int piece = min(w4 * 64 + lane, GEO::PIECES - 1);
+    const uint32_t ivoff = (uint32_t)(piece >> 3) * (uint32_t)a.B * 4u + (uint32_t)(piece & 7) * 16u;
+    const uint32_t plane_bytes = (uint32_t)a.IH * a.C * a.B * 4u;
+    const int64_t img_bytes = (int64_t)a.IW * a.IH * a.C * a.B * 4;
+    auto tile_at = [&](int u) { return decode_tile_index(a, blockIdx.x + u * gridDim.x, KT, TB, TW, TH); };
+    auto buffer_of = [&](int u) { return (uint32_t)(u % GEO::NBUF) * IBUF; };
+    auto fetch = [&](int u) {
+        const TileCoord tc = tile_at(u);
+        const int64_t org = ((((int64_t)SW * tc.w0 * a.IH + (int64_t)SH * tc.h0) * C) * a.B + tc.b0) * 4;
+        const uint64_t at = (uint64_t)a.image + (uint64_t)org;
+        i32x4 d;
+        d[0] = __builtin_amdgcn_readfirstlane((int)(uint32_t)at);
+        d[1] = __builtin_amdgcn_readfirstlane((int)((uint32_t)(at >> 32) & 0xffffu));
+        d[2] = __builtin_amdgcn_readfirstlane((int)min(img_bytes - org, (int64_t)0x7fffffff));
+        d[3] = 0x00020000;
+        const uint32_t dst = (uint32_t)(uintptr_t)lds + buffer_of(u) + w4 * 1024;
+#pragma unroll
+        for (int x = 0; x < GEO::XS; ++x) load_to_lds_unseen(d, ivoff + (uint32_t)x * plane_bytes, dst + x * XPB);
+    };
+    auto fetched = [] { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); };
+
+    const int j = lane & 31, g = lane >> 5;
+    f32x16 acc[1][NBLK];
+    // per-lane LDS offsets: Filter row of output channel wm*32 + j, slots 11 g ..; Image: image j, rows 11 g ..
+    const uint32_t al = (uint32_t)(GEO::FLT_OFF + ((wm * 32 + j) * FPW + g * QH) * 4);
+    const uint32_t xl = (uint32_t)(j * 4 + g * QH * ROWB + wn * SH * C * ROWB);
+    float A[2][GEO::G0], X[2][NBLK][GEO::G0];
+    // group gi = 2 r + half: slots q0 .. q0 + n - 1 of filter column r
+    auto load_group = [&](uint32_t xb, int gi, int set) {
+        const int r = gi >> 1, q0 = (gi & 1) ? GEO::G0 : 0, n = (gi & 1) ? GEO::G1 : GEO::G0;
+#pragma unroll
+        for (int t = 0; t < n; ++t) A[set][t] = *(const CACNN_LDS(float)*)(lds + al + (r * QP + q0 + t) * 4);
+#pragma unroll
+        for (int nb = 0; nb < NBLK; ++nb)       // column block nb of this wave: output column nb of tile row wn
+#pragma unroll
+            for (int t = 0; t < n; ++t)
+                X[set][nb][t] = *(const CACNN_LDS(float)*)(lds + xb + (r + nb * SW) * XPB + (q0 + t) * ROWB);
+    };
+    auto mfma_group = [&](int gi, int set) {
+        const int n = (gi & 1) ? GEO::G1 : GEO::G0;
+#pragma unroll
+        for (int t = 0; t < n; ++t)
+#pragma unroll
+            for (int nb = 0; nb < NBLK; ++nb) {
+                float x = X[set][nb][t];
+                // slot 21 (q = 10 in the upper half-wave) does not exist
+                if ((gi & 1) && t == n - 1) x = g ? 0.f : x;
+                acc[0][nb] = __builtin_amdgcn_mfma_f32_32x32x2f32(A[set][t], x, acc[0][nb], 0, 0, 0);
+            }
+    };
+    // groups FIRST .. FIRST + R - 1 of a tile; the first of a tile is read here, that of the second half at the end of the first
+    auto half = [&](uint32_t xb, auto first) {
+        constexpr int FIRST = decltype(first)::value;
+        if constexpr (FIRST == 0) load_group(xb, 0, 0);
+#pragma unroll
+        for (int gi = FIRST; gi < FIRST + R; ++gi) {
+            if (gi + 1 < 2 * R) load_group(xb, gi + 1, (gi + 1) & 1);
+            mfma_group(gi, gi & 1);
+            if (gi + 1 < 2 * R) interleave_hint<GEO::G0 * NBLK, GEO::G0 * (NBLK + 1)>();
+        }
+        asm volatile("" ::: "memory");          // keep the reads above where they are
+    };
+    const int64_t out_kstride = (int64_t)a.H * a.W * a.B;                    // floats between output channels
+    const uint32_t out_lane = (uint32_t)(g * 4) * (uint32_t)out_kstride + j;  // < 2^31: checked by the host
+    // Out tile: block n is output column w_l, row h_l; a lane owns image j
+    auto store = [&](const TileCoord& tc) {
+        if (!RAGGED || (tc.k0 + KT <= a.K && tc.w0 + TW <= a.W && tc.h0 + TH <= a.H && tc.b0 + TB <= a.B && a.B % 32 == 0)) {
+#pragma unroll
+            for (int nb = 0; nb < NBLK; ++nb) {
+                float* const blk = a.out + ((((int64_t)(tc.k0 + wm * 32) * a.H + tc.h0 + wn) * a.W + tc.w0 + nb) * a.B + tc.b0);
+                store_block_exact<true>(blk, out_kstride, out_lane, acc[0][nb]);
+            }
+        } else {
+            // a tile that overhangs Out: the blocks of positions inside, this lane's image if it is inside, the rows of output
+            // channels inside
+            const int rows = (tc.b0 + j < a.B && tc.h0 + wn < a.H) ? a.K - (tc.k0 + wm * 32 + g * 4) : 0;
+#pragma unroll
+            for (int nb = 0; nb < NBLK; ++nb) {
+                float* const blk = a.out + ((((int64_t)(tc.k0 + wm * 32) * a.H + tc.h0 + wn) * a.W + tc.w0 + nb) * a.B + tc.b0);
+                store_block_rows(blk, out_kstride, out_lane, acc[0][nb], tc.w0 + nb < a.W ? rows : 0);
+            }
+        }
+    };
+
+    if (set == 0) fetch(0);
+    {
+        // Filter [K][R][S][C] -> LDS [k][r][22], slot 21 zero, rows beyond K zeros.  The rows are one contiguous run in global memory:
+        // read in order, all loads of a batch in flight together, scattered into LDS.
+        float* const s_flt = smem_f + GEO::FLT_OFF / 4;
+        constexpr int ROW = R * S * C, TOTAL = KT * ROW, BATCH = 8, PT = 512;
+        const float* const src = (const float*)a.filter;
+        const int have = min(KT, a.K) * ROW;
+        for (int e0 = 0; e0 < TOTAL; e0 += BATCH * PT) {
+            float v[BATCH];
+#pragma unroll
+            for (int u = 0; u < BATCH; ++u) {
+                const int e = e0 + u * PT + tid;
+                v[u] = e < have ? src[e] : 0.f;
+            }
+#pragma unroll
+            for (int u = 0; u < BATCH; ++u) {
+                const int e = e0 + u * PT + tid;
+                if (e < TOTAL) {
+                    const int kl = e / ROW, q = e % ROW;
+                    s_flt[kl * FPW + (q / (S * C)) * QP + q % (S * C)] = v[u];
+                }
+            }
+        }
+        for (int e = tid; e < KT * R; e += PT) s_flt[(e / R) * FPW + (e % R) * QP + QP - 1] = 0.f;
+    }
+    fetched();
+    lds_done_then_barrier();
+    zero_acc(acc);
+    if (set == 1) {
+        // (half-step 0)
+        if (total > 1) fetch(1);
+        fetched();
+        lds_done_then_barrier();
+    }
+    TileCoord done = {};
+    for (int u = set; u < total; u += 2) {
+        const uint32_t xb = xl + buffer_of(u);
+        if (u != set) store(done);
+        half(xb, std::integral_constant<int, 0>{});
+        lds_done_then_barrier();
+        if (u + 2 < total) fetch(u + 2);
+        half(xb, std::integral_constant<int, R>{});
+        fetched();
+        if (u + 1 < total) lds_done_then_barrier();
+        done = tile_at(u);
+    }
+    if (set < total) store(done);
+}
+
 // ---------------------------------------------------------------------------------------------------------------
 // launch table
 
@@ -3384,7 +3555,13 @@ static const Variant g_variants[] = {
      [](const KernelArgs& a, int grid, size_t lds, void* stream) -> int {
          static bool attr_done = false;
          if (!F32StemDirect<2, 2>::matches_host(a) || lds != (size_t)F32StemDirect<2, 2>::LDS_BYTES) return 1;
-         static bool attr_done_ragged = false;
+         static bool attr_done_ragged = false, pair_done = false, pair_done_ragged = false;
+         // (the offsets of a box's nine planes have to fit 31 bits)
+         if (a.tiles_k == 1 && (int64_t)a.IH * a.C * a.B * 4 * (F32StemDirect<2, 2>::XS + 1) < (int64_t)1 << 31) {
+             if (a.B % 32 == 0 && a.W % 2 == 0 && a.H % 2 == 0 && a.K % 64 == 0)
+                 return launch_kernel(conv_f32_stem_pair_kernel<2, 2, false>, pair_done, 512, a, grid, lds, stream);
+             return launch_kernel(conv_f32_stem_pair_kernel<2, 2, true>, pair_done_ragged, 512, a, grid, lds, stream);
+         }
          if (a.B % 32 == 0 && a.W % 2 == 0 && a.H % 2 == 0 && a.K % 64 == 0)
              return launch_kernel(conv_f32_stem_direct_kernel<2, 2, false>, attr_done, 512, a, grid, lds, stream);
          return launch_kernel(conv_f32_stem_direct_kernel<2, 2, true>, attr_done_ragged, 512, a, grid, lds, stream);
