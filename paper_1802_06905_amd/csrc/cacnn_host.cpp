@@ -1107,10 +1107,20 @@ int launch_with(const cacnn_problem& p, int dtype, int vi, int CT, int bR, int b
 // ------------------------------------------------------------------------------------------------------------
 // The kernels with flattened positions (cacnn_flat.hip): which of them takes a problem, what it costs, its launch.
 
-// the time that reading Image and Filter and writing Out once takes at the rate of a large copy
+// bytes of the Image that some output reads (strides beyond the filter's extent leave some out), of Filter and of Out
+struct Bytes {
+    double image, filter, out;
+};
+Bytes compulsory_bytes(const cacnn_problem& p, int dtype) {
+    const double esz = dtype == CACNN_F32 ? 4.0 : 2.0;
+    const double cols = (double)std::min(p.sigma_w * (p.W - 1) + p.R, p.W * p.R), rows = (double)std::min(p.sigma_h * (p.H - 1) + p.S, p.H * p.S);
+    return {esz * (double)p.B * p.C * cols * rows, esz * (double)p.K * p.R * p.S * p.C, 4.0 * (double)p.K * p.H * p.W * p.B};
+}
+
+// the time that reading and writing them once takes at the rate of a large copy
 double compulsory_us(const cacnn_problem& p, int dtype) {
-    const double IW = (double)(p.sigma_w * (p.W - 1) + p.R), IH = (double)(p.sigma_h * (p.H - 1) + p.S), esz = dtype == CACNN_F32 ? 4.0 : 2.0;
-    return (esz * ((double)p.B * p.C * IW * IH + (double)p.K * p.R * p.S * p.C) + 4.0 * (double)p.K * p.H * p.W * p.B) / 4.6e6;
+    const Bytes b = compulsory_bytes(p, dtype);
+    return (b.image + b.filter + b.out) / 4.6e6;
 }
 
 // ... and what a kernel takes that would need `us` with all data at hand: the larger of the two, and a quarter of the smaller
@@ -1500,6 +1510,35 @@ double flat_margin(const cacnn_problem& p, int dtype) {
     return std::min(0.7, 0.85 * std::pow(overlap * std::max(1.0, image / 256e6), -0.2));
 }
 
+// The two estimates compared as measurements correct them: whether the flattened kernel is expected to take less than a share of the
+// fixed-geometry one's time.  The factors on either estimate are least-squares fits of the logarithm of time over estimate, on 1850
+// layers whose plan is a fixed-geometry variant and whose flattened estimate is not below the margin above, drawn over sizes up to 250 MB and
+// 60 (fp32 7.6) GFLOP, all run on both: the planner's price is low by up to half where a launch is short, and by the more the larger
+// Out's part of the words is; the flattened kernel's is low for large Images with overlapping windows.  At these shares (fp32 0.8, bf16 0.75) the
+// time over all of them is 0.867 and 0.863 of the fixed-geometry kernels' in the geometric mean (the faster of the two each time:
+// 0.829 and 0.795), and three take longer, by up to 1.19; at 0.83 and 0.8 it is 0.854 and 0.836, nine take up to 1.2 times as long and
+// one of 4 us 1.45, at 0.9 44 do, up to 1.47 times.  fp32 (256, 32, 498, 81, 3, 1 x 1) 118 -> 41
+// us, (128, 512, 64, 15, 15, 1 x 1, s 2) 49 -> 24, bf16 (256, 32, 16, 36, 43, 1 x 1) 27.9 -> 14.1, (8, 88, 96, 77, 77, 1 x 1, s 2) 28.6 -> 9.3.
+// Not for what was not drawn: larger problems, bf16 Images of 100 MB and more with overlapping windows, and the stem's own kernel.
+bool flat_beats_fixed(const cacnn_problem& p, int dtype, const VariantInfo& v, double flat_est, double tiled_est) {
+    const Bytes b = compulsory_bytes(p, dtype);
+    const double total = b.image + b.filter + b.out, depth = (double)p.C * p.R * p.S;
+    const double flops = 2.0 * depth * (double)p.K * (double)p.W * (double)p.H * (double)p.B;
+    const double overlap = std::max(1.0, (double)p.R / (double)p.sigma_w) * std::max(1.0, (double)p.S / (double)p.sigma_h);
+    if (total > 250e6 || flops > (dtype == CACNN_F32 ? 7.6e9 : 59.2e9) || v.fx_whole || (dtype != CACNN_F32 && b.image >= 100e6 && overlap > 1.0)) return false;
+    auto over = [](double x, double unit) { return std::max(0.0, std::log(x / unit)); };
+    const double one = p.R * p.S == 1 ? 1.0 : 0.0, taps = v.fx_br == 1 && v.fx_bs == 1 && !one ? 1.0 : 0.0, copy = total / 4.6e6, out = b.out / total;
+    const double log_tiled = std::log(tiled_est), log_flat = std::log(flat_est), deep = over(depth, 128.0), wide = over((double)p.K, 64.0);
+    const double narrow = over(32.0, (double)p.C), batch = std::min(1.0, (double)p.B / 64.0), large = over(b.image, 16e6), lap = std::log(overlap);
+    const double tc = copy / tiled_est, fc = copy / flat_est;
+    const bool f32 = dtype == CACNN_F32;
+    const double tiled_fix = f32 ? 0.218 + 0.084 * one + (0.112 + 0.138 * one) * tc + 0.141 * out - 0.071 * log_tiled + 0.020 * taps + 0.012 * narrow - 0.067 * deep + 0.035 * batch
+                                 : 0.480 + 0.060 * one + (0.016 - 0.133 * one) * tc - 0.108 * out - 0.107 * log_tiled - 0.092 * taps + 0.092 * narrow + 0.012 * deep - 0.025 * batch;
+    const double flat_fix = f32 ? 0.112 - 0.010 * lap - 0.088 * fc - 0.042 * log_flat + (0.009 + 0.061 * lap) * large - 0.008 * one + 0.218 * out + (0.026 + 0.014 * one) * deep - 0.016 * wide
+                                : 0.052 - 0.012 * lap - 0.211 * fc - 0.018 * log_flat + (0.035 + 0.042 * lap) * large - 0.144 * one + 0.166 * out + (0.040 + 0.065 * one) * deep + 0.024 * wide;
+    return flat_est * std::exp(flat_fix) < (f32 ? 0.8 : 0.75) * tiled_est * std::exp(tiled_fix);
+}
+
 // Workgroups share a tile's contraction where the estimate of that is below the other kernel's by this factor: with 1.0 15 of 400 layers
 // take up to 1.22 times as long as undivided, with 1.2 one (1.05 times), and the time over all 400 is 0.888 of the undivided one, against 0.882.
 // fp32 (1, 784, 64, 3, 12, 3 x 3) 42.2 -> 8.8 us, (4, 464, 156, 10, 7, 3 x 3) 30.6 -> 12.6, bf16 (3, 859, 480, 42, 5, 3 x 3, s 2) 41.5 ->
@@ -1520,8 +1559,10 @@ int plan_route(const cacnn_problem& p, int dtype, bool aligned_img, bool aligned
         const int fi = choose_flat(p, dtype, &flat_est);
         // (a call whose plan cannot be launched is refused, as it would be without the flattened kernels)
         const VariantInfo& v = variant(plan.variant).info;
+        const double tiled_est = with_copy_time(tiled_us - 2.1, p, dtype) + 2.1;
         if (fi >= 0 && tile_list_in_range(p, v, plan.xcd_walk, plan.xcd_split_k) &&
-            (v.fx_ct == 0 ? !boxes_for_short_rows(p, dtype) : flat_est < flat_margin(p, dtype) * (with_copy_time(tiled_us - 2.1, p, dtype) + 2.1))) {
+            (v.fx_ct == 0 ? !boxes_for_short_rows(p, dtype)
+                          : flat_est < flat_margin(p, dtype) * tiled_est || flat_beats_fixed(p, dtype, v, flat_est, tiled_est))) {
             WindowTile tile;
             const int wi = dtype != CACNN_F32 && aligned_img ? choose_window(p, flat_est, &tile) : -1;
             if (wi >= 0 && prepare_window(p, wi, tile, out) == CACNN_OK) return CACNN_OK;

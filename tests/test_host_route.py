@@ -171,3 +171,13 @@ def test_first_layers_keep_their_window_in_lds():
         assert " flat window " not in routed(dims, F32)
     for dims in ((8, 3, 64, 56, 56, 7, 7, 2, 2), (40, 3, 64, 112, 112, 7, 7, 2, 2), (16, 2, 64, 112, 112, 7, 3, 2, 2), (64, 3, 59, 33, 72, 5, 5, 1, 1)):
         assert " flat window " not in routed(dims, BF16) and " flat " in routed(dims, BF16)
+
+
+# Layers whose plan is a fixed-geometry variant and that measurements give to the flattened kernels, and some that they leave where they are
+def test_short_launches_of_fixed_geometry_variants_run_flattened():
+    for dtype, dims in ((F32, (256, 32, 498, 81, 3, 1, 1, 1, 1)), (F32, (128, 512, 64, 15, 15, 1, 1, 2, 2)), (BF16, (256, 32, 16, 36, 43, 1, 1, 1, 1)),
+                        (BF16, (8, 88, 96, 77, 77, 1, 1, 2, 2))):
+        assert " fx" in cc.cacnn_variant_name(cc.cacnn_tile_plan(dims, dtype).variant) and " flat " in routed(dims, dtype)
+    for dtype, dims in ((F32, (8, 64, 64, 56, 56, 3, 3, 1, 1)), (BF16, (64, 64, 256, 56, 56, 1, 1, 1, 1)), (BF16, (32, 128, 256, 28, 28, 3, 3, 2, 2)),
+                        (BF16, (128, 400, 224, 26, 5, 3, 3, 1, 1)), (BF16, (32, 96, 206, 42, 42, 3, 3, 1, 1)), (F32, (8, 320, 496, 37, 7, 3, 3, 1, 1))):
+        assert routed(dims, dtype) == cc.cacnn_variant_name(cc.cacnn_tile_plan(dims, dtype).variant)
