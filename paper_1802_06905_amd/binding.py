@@ -262,6 +262,26 @@ def _stream_handle(stream) -> int:
     return int(stream.cuda_stream)
 
 
+def _load_native():
+    """The module that takes the usual call; set up for this library's Problem and its two calls with element counts."""
+    if not os.path.exists(os.path.join(_HERE, "_cacnn_torch.so")):
+        raise ImportError(f"{_HERE}/_cacnn_torch.so is missing: build it with `python paper_1802_06905_amd/build.py`")
+    from . import _cacnn_torch
+    address = lambda f: ctypes.cast(f, ctypes.c_void_p).value  # noqa: E731
+    _cacnn_torch.setup(Problem, address(_lib.cacnn_internal_conv_forward_sized), address(_lib.cacnn_internal_pool_forward_sized))
+    return _cacnn_torch
+
+
+def _in_forked_child() -> None:
+    # (torch refuses its streams in a forked child of a process that has used the GPU; without the module a call asks it and says so)
+    global _native
+    _native = None
+
+
+_native = _load_native()
+os.register_at_fork(after_in_child=_in_forked_child)
+
+
 def cacnn_conv_forward(problem, dtype: int, image, filt, out, stream=None) -> None:
     """Enqueue Out = conv(Image, Filter) on `stream` (torch stream, raw handle, or None = torch's current stream).
     image/filt/out are device tensors laid out Image[IW,IH,C,B], Filter[K,R,S,C], Out[K,H,W,B] (fp32)."""
@@ -269,6 +289,13 @@ def cacnn_conv_forward(problem, dtype: int, image, filt, out, stream=None) -> No
     # enqueues nothing if it finds fault with an argument; then, and for every other kind of operand, the checks below
     # tell what is wrong (17 comparisons and products in the interpreter took as long as the launch).  An error of the runtime or a
     # missing device is final: the work may have been enqueued.
+    # First in native code (-1: nothing tried), which saves 1.2 us of a call; then the same here, for a forked child and dtypes that are not int.
+    if _native is not None:
+        rc = _native.conv(problem, dtype, image, filt, out, stream if stream is None or type(stream) is int else _stream_handle(stream))
+        if rc == 0:
+            return
+        if rc > 0 and rc not in _ARGUMENT_ERRORS:
+            raise CacnnError(rc, "cacnn_conv_forward")
     if type(dtype) is not int:
         dtype = int(dtype)
     if type(problem) is Problem and type(image) is type(filt) is type(out) is _Tensor and image.is_cuda and filt.is_cuda and out.is_cuda \
@@ -403,6 +430,12 @@ def cacnn_pool_lower_bound(problem, M_words: float) -> PoolBound:
 def cacnn_pool_forward(problem, dtype: int, mode: int, image, out, stream=None) -> None:
     """Enqueue per-channel average (mode 0) or max (mode 1) pooling of Image[IW,IH,C,B] into Out[K=C,H,W,B] (fp32)."""
     # (as in cacnn_conv_forward)
+    if _native is not None:
+        rc = _native.pool(problem, dtype, mode, image, out, stream if stream is None or type(stream) is int else _stream_handle(stream))
+        if rc == 0:
+            return
+        if rc > 0 and rc not in _ARGUMENT_ERRORS:
+            raise CacnnError(rc, "cacnn_pool_forward")
     if type(dtype) is not int:
         dtype = int(dtype)
     if type(problem) is Problem and type(image) is type(out) is _Tensor and image.is_cuda and out.is_cuda and out.dtype is _float32 \

@@ -1,7 +1,9 @@
-"""Build libcacnn.so (host planner + gfx950 kernels) in-tree with hipcc.  Usage: python paper_1802_06905_amd/build.py"""
+"""Build libcacnn.so (host planner + gfx950 kernels) with hipcc and _cacnn_torch.so (the binding's calls on torch tensors) with the host
+compiler, in-tree.  Usage: python paper_1802_06905_amd/build.py"""
 import os
 import subprocess
 import sys
+import sysconfig
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
@@ -11,13 +13,32 @@ HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared", "-Wall", "-Wno-unused-function",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops"]
 
+TORCH_LIB = os.path.join(HERE, "_cacnn_torch.so")
+
+
+def torch_command() -> list:
+    """How _cacnn_torch.so is compiled: torch's own headers and libraries, which are in the process before it is imported."""
+    import torch
+    root = os.path.dirname(torch.__file__)
+    rocm = os.path.dirname(os.path.dirname(HIPCC))
+    return [os.environ.get("CXX", "g++"), "-std=c++17", "-O2", "-fPIC", "-shared", "-Wall", "-DUSE_ROCM=1", "-D__HIP_PLATFORM_AMD__=1",
+            f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}", "-isystem", os.path.join(root, "include"),
+            "-isystem", sysconfig.get_paths()["include"], "-isystem", os.path.join(rocm, "include"), "-o", TORCH_LIB,
+            os.path.join(CSRC, "cacnn_torch.cpp"), "-L" + os.path.join(root, "lib"), "-ltorch_python", "-ltorch_cpu", "-lc10_hip", "-lc10"]
+
 
 def build(verbose: bool = False) -> str:
-    """Compile every source for gfx950 and link the shared library.  Always recompiles."""
+    """Compile every source for gfx950 and link the shared library, and the module beside it.  Always recompiles."""
     cmd = [HIPCC] + FLAGS + ["-o", LIB] + [os.path.join(CSRC, s) for s in SOURCES]
+    torch_cmd = torch_command()
     if verbose:
         print(" ".join(cmd))
+        print(" ".join(torch_cmd))
+    beside = subprocess.Popen(torch_cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
     res = subprocess.run(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
+    torch_out = beside.communicate()[0]
+    if beside.returncode != 0:
+        raise RuntimeError("the host compiler failed:\n" + torch_out)
     # the host pass does not know the packed-fp32 feature and says so once per file: not an error
     out = "\n".join(l for l in res.stdout.splitlines() if "packed-fp32-ops" not in l)
     if res.returncode != 0:
