@@ -90,3 +90,14 @@ def test_an_argument_that_the_library_refuses_is_its_error(library, call, status
     with pytest.raises(cc.CacnnError) as error:
         call(0)
     assert error.value.status == status
+
+
+def test_the_native_call_leaves_what_it_does_not_take_alone():
+    """-1, nothing tried: operands that are not device tensors, a problem that is no Problem, other kinds of numbers and streams."""
+    assert binding._native is not None
+    t = torch.zeros(4)
+    for args in ((PROBLEM, 0, t, t, t, None), (PROBLEM, 0, 1, 2, 3, 0), (tuple(range(9)), 0, t, t, t, 0), (PROBLEM, True, t, t, t, 0),
+                 (PROBLEM, 2 ** 70, t, t, t, 0), (PROBLEM, 0, t, t, t, "0"), (PROBLEM, 0, Tensor(4, torch.float32), t, t, 0)):
+        assert binding._native.conv(*args) == -1
+        assert binding._native.pool(args[0], args[1], 1, *args[3:]) == -1
+    assert binding._native.conv() == -1 and binding._native.pool(PROBLEM) == -1
