@@ -1427,10 +1427,26 @@ int prepare_window(const cacnn_problem& p, int wi, const WindowTile& t, Launch* 
     return CACNN_OK;
 }
 
+// The tile of a window kernel with `bufs` boxes whose position tiles stage the fewest words, of those that leave room for a second workgroup on the
+// compute unit, and its launch; false where none does
+bool pick_window_tile(const cacnn_problem& p, int wi, int bufs, WindowTile* pick, Launch* out) {
+    const WindowInfo& v = window_variant(wi).info;
+    WindowTile t;
+    double words = 0.0;
+    *pick = t;
+    t.bufs = bufs;
+    for (t.TW = v.cols() / v.TB; t.TW >= 1; t.TW /= 2) {
+        t.TH = v.cols() / v.TB / t.TW;
+        if (prepare_window(p, wi, t, out) != CACNN_OK || out->lds > 80 * 1024) continue;
+        const double w = (double)out->w.tiles_n * (double)out->w.rows;
+        if (!pick->TW || w < words) *pick = t, words = w;
+    }
+    return pick->TW && prepare_window(p, wi, *pick, out) == CACNN_OK;
+}
+
 // The window kernel of a first layer: few channels, and a batch of which every tile is whole rows of images (others, whose stores are pieces of
-// cache lines, took up to 1.36 times as long as the flattened kernels).  The box with the fewest staged words that leaves room for
-// a second workgroup on the compute unit; one box per workgroup or two, whichever fills its last round of tiles better.  -1 where the
-// flattened kernel's estimate is below 10 us (1.7 us are spent before the first product: 5.6 -> 7.3 us at (8, 3, 64, 56, 56, 7 x 7, s 2)), and, up to 22
+// cache lines, took up to 1.36 times as long as the flattened kernels).  One box per workgroup or two, whichever fills its last round of tiles
+// better.  -1 where the flattened kernel's estimate is below 10 us (1.7 us are spent before the first product: 5.6 -> 7.3 us at (8, 3, 64, 56, 56, 7 x 7, s 2)), and, up to 22
 // us, where less than 0.64 of the last round and of the tiles along k is filled ((128, 3, 48, 56, 24, 3 x 3) 10.6 -> 12.3 us).  Over 113 first layers of
 // 8 us and more the time is 0.89 of the flattened kernels' in the geometric mean, 0.51 at best and 1.03 at worst.
 int choose_window(const cacnn_problem& p, double flat_est, WindowTile* tile) {
@@ -1443,16 +1459,8 @@ int choose_window(const cacnn_problem& p, double flat_est, WindowTile* tile) {
         if (v.TB != TB) continue;
         for (int bufs = 2; bufs >= 1; --bufs) {
             Launch l;
-            WindowTile t, pick;
-            double words = 0.0;
-            t.bufs = bufs;
-            for (t.TW = v.cols() / TB; t.TW >= 1; t.TW /= 2) {
-                t.TH = v.cols() / TB / t.TW;
-                if (prepare_window(p, i, t, &l) != CACNN_OK || l.lds > 80 * 1024) continue;
-                const double w = (double)l.w.tiles_n * (double)l.w.rows;
-                if (!pick.TW || w < words) pick = t, words = w;
-            }
-            if (!pick.TW || prepare_window(p, i, pick, &l) != CACNN_OK) continue;
+            WindowTile pick;
+            if (!pick_window_tile(p, i, bufs, &pick, &l)) continue;
             // tiles per round of the workgroups that are resident together (launch_bounds: four waves a SIMD)
             const double resident = (double)kDefaultMachine.num_cu * (double)std::min<int64_t>(160 * 1024 / (int64_t)l.lds, 16 / (v.threads() / 64));
             const double rounds = bufs == 2 ? (double)l.w.tiles_n / l.w.t_step : (double)l.grid / resident;
@@ -1759,6 +1767,20 @@ int cacnn_tune(const cacnn_problem* problem, int dtype, const void* image, const
             best_ms = ms;
         }
     }
+    // ... and every window kernel with one box and with two, each on the tile that stages the fewest words
+    int window = -1;
+    WindowTile window_tile;
+    for (int i = 0; i < 2 * num_window() && best.variant >= 0 && dtype != CACNN_F32 && aligned16(image); ++i) {
+        WindowTile t;
+        Launch l;
+        if (!pick_window_tile(*problem, i / 2, 2 - i % 2, &t, &l)) continue;
+        const float ms = time_ms([&] { return fire(l, image, filter, out, hip_stream); });
+        if (ms >= 0.f && ms < best_ms) {
+            window = i / 2;
+            window_tile = t;
+            best_ms = ms;
+        }
+    }
     // ... and those whose workgroups share the contraction, each with the number of parts that the estimate likes best
     int split = -1, split_parts = 0;
     for (int i = 0; i < num_flat() && best.variant >= 0 && !hip_stream; ++i) {
@@ -1780,9 +1802,10 @@ int cacnn_tune(const cacnn_problem* problem, int dtype, const void* image, const
     const int rc = fill_plan(*problem, dtype, kDefaultMachine, best, &plan);
     if (rc != CACNN_OK) return rc;
     Launch launch;
-    const int lrc = flat >= 0 ? prepare_flat(*problem, dtype, flat, &launch)
-                              : prepare_tiled(*problem, dtype, plan.variant, plan.b_c, plan.b_r, plan.b_s, plan.xcd_split_k, plan.xcd_walk,
-                                              aligned16(image), aligned16(filter), &launch);
+    const int lrc = window >= 0 ? prepare_window(*problem, window, window_tile, &launch)
+                    : flat >= 0 ? prepare_flat(*problem, dtype, flat, &launch)
+                                : prepare_tiled(*problem, dtype, plan.variant, plan.b_c, plan.b_r, plan.b_s, plan.xcd_split_k, plan.xcd_walk,
+                                                aligned16(image), aligned16(filter), &launch);
     if (lrc != CACNN_OK) return lrc;
     if (split >= 0) (void)prepare_split(*problem, dtype, split, split_parts, &launch);
     store_plan(*problem, key, launch);

@@ -1,0 +1,71 @@
+"""What the library hands to the runtime, with a stand-in for the runtime (tests/hip_stand_in.cpp): nothing runs, no GPU is needed."""
+import os
+import subprocess
+import sys
+
+import pytest
+
+import paper_1802_06905_amd as cc
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+
+# (in a process of its own: the stand-in has to be there before the library looks for the runtime)
+PRELUDE = r'''
+import ctypes, sys
+hip = ctypes.CDLL(sys.argv[1], mode=ctypes.RTLD_GLOBAL)
+lib = ctypes.CDLL(sys.argv[2])
+hip.stand_in_launches.restype = ctypes.c_char_p
+hip.stand_in_cost.argtypes = [ctypes.c_char_p, ctypes.c_double]
+lib.cacnn_variant_name.restype = ctypes.c_char_p
+V, I = ctypes.c_void_p, ctypes.c_int
+IMAGE, FILTER, OUT = 1 << 20, 2 << 20, 3 << 20       # addresses that nothing reads
+def problem(*dims): return ctypes.byref((ctypes.c_int64 * 9)(*dims))
+def kernels(): return hip.stand_in_launches().decode().split()
+def forward(dims, dtype, stream=0, image=IMAGE):
+    assert lib.cacnn_conv_forward(problem(*dims), I(dtype), V(image), V(FILTER), V(OUT), V(stream)) == 0
+    return kernels()
+def tune(dims, dtype, stream=0, image=IMAGE):
+    assert lib.cacnn_tune(problem(*dims), I(dtype), V(image), V(FILTER), V(OUT), V(stream), V(0)) == 0
+    return kernels()
+'''
+
+
+@pytest.fixture(scope="module")
+def run(tmp_path_factory):
+    stand_in = str(tmp_path_factory.mktemp("stand_in") / "hip_stand_in.so")
+    subprocess.run(["g++", "-std=c++17", "-O1", "-fPIC", "-shared", "-o", stand_in, os.path.join(ROOT, "tests", "hip_stand_in.cpp"), "-ldl"], check=True)
+
+    def program(body):
+        p = subprocess.run([sys.executable, "-c", PRELUDE + body, stand_in, cc.library_path()], capture_output=True, text=True, timeout=120)
+        assert p.returncode == 0, p.stdout + p.stderr
+        return p.stdout
+    return program
+
+
+def test_tuning_times_the_window_kernels(run):
+    """A first bf16 layer that runs on a window kernel untuned stays on one when it is tuned and they are the fastest, on every stream; an Image that
+    16-byte loads cannot read is not tried on them."""
+    run(r'''
+stem = (16, 3, 64, 112, 112, 7, 7, 2, 2)
+hip.stand_in_cost(b"conv_window", 1.0)
+hip.stand_in_cost(b"conv_", 2.0)
+assert "conv_window" in forward(stem, 1)[0]
+untuned = forward(stem, 1)
+for stream in (0, 4096):
+    timed = tune(stem, 1, stream)
+    assert set(untuned) <= set(timed) and any("conv_flat" in k for k in timed)
+    for where in (0, 4096):
+        assert "conv_window" in forward(stem, 1, where)[0]
+assert not any("conv_window" in k for k in tune(stem, 1, 0, IMAGE + 8)) and "conv_window" not in forward(stem, 1, 0, IMAGE + 8)[0]
+assert not any("conv_window" in k for k in tune(stem, 0))
+''')
+
+
+def test_tuning_leaves_a_window_kernel_for_a_faster_one(run):
+    run(r'''
+stem = (16, 3, 64, 112, 112, 7, 7, 2, 2)
+hip.stand_in_cost(b"conv_flat_lds", 1.0)
+hip.stand_in_cost(b"conv_", 2.0)
+assert any("conv_window" in k for k in tune(stem, 1, 4096))
+assert "conv_flat_lds" in forward(stem, 1, 4096)[0]
+''')
