@@ -1520,23 +1520,26 @@ double flat_margin(const cacnn_problem& p, int dtype) {
 
 // The two estimates compared as measurements correct them: whether the flattened kernel is expected to take less than a share of the
 // fixed-geometry one's time.  The factors on either estimate are least-squares fits of the logarithm of time over estimate, on 1850
-// layers whose plan is a fixed-geometry variant and whose flattened estimate is not below the margin above, drawn over sizes up to 250 MB and
-// 60 (fp32 7.6) GFLOP, all run on both: the planner's price is low by up to half where a launch is short, and by the more the larger
+// layers of up to 250 MB whose plan is a fixed-geometry variant and whose flattened estimate is not below the margin above, all
+// run on both: the planner's price is low by up to half where a launch is short, and by the more the larger
 // Out's part of the words is; the flattened kernel's is low for large Images with overlapping windows.  At these shares (fp32 0.8, bf16 0.75) the
 // time over all of them is 0.867 and 0.863 of the fixed-geometry kernels' in the geometric mean (the faster of the two each time:
 // 0.829 and 0.795), and three take longer, by up to 1.19; at 0.83 and 0.8 it is 0.854 and 0.836, nine take up to 1.2 times as long and
 // one of 4 us 1.45, at 0.9 44 do, up to 1.47 times.  fp32 (256, 32, 498, 81, 3, 1 x 1) 118 -> 41
 // us, (128, 512, 64, 15, 15, 1 x 1, s 2) 49 -> 24, bf16 (256, 32, 16, 36, 43, 1 x 1) 27.9 -> 14.1, (8, 88, 96, 77, 77, 1 x 1, s 2) 28.6 -> 9.3.
-// Not for what was not drawn: larger problems, bf16 Images of 100 MB and more with overlapping windows, and the stem's own kernel.
+// No size ends it; what is there for short launches levels off at 60 us, which 123 of those 1850 exceed.  So it holds beyond the layers it was
+// fitted on: of 5700 others of 150 MB to 5 GB and up to 200 GFLOP (bf16 2 TFLOP), 800 of them large bf16 Images with overlapping windows, 469 fp32
+// and 17 bf16 layers beyond 250 MB or 7.6 (59.2) GFLOP are given to the flattened kernel by this comparison alone, and take 0.58 and 0.61 of the
+// fixed-geometry kernels' time in the geometric mean, 1.03 at worst: fp32 (256, 32, 498, W, 3, 1 x 1) at W = 155, 170 224 and 242 -> 74 and 88 us, (40, 88,
+// 1860, 44, 17, 1 x 1, s 2) 211 -> 125, bf16 (16, 192, 80, 251, 251, 1 x 1) 276 -> 180.  Not for the stem's own kernel, which none of these has.
 bool flat_beats_fixed(const cacnn_problem& p, int dtype, const VariantInfo& v, double flat_est, double tiled_est) {
+    if (v.fx_whole) return false;
     const Bytes b = compulsory_bytes(p, dtype);
     const double total = b.image + b.filter + b.out, depth = (double)p.C * p.R * p.S;
-    const double flops = 2.0 * depth * (double)p.K * (double)p.W * (double)p.H * (double)p.B;
     const double overlap = std::max(1.0, (double)p.R / (double)p.sigma_w) * std::max(1.0, (double)p.S / (double)p.sigma_h);
-    if (total > 250e6 || flops > (dtype == CACNN_F32 ? 7.6e9 : 59.2e9) || v.fx_whole || (dtype != CACNN_F32 && b.image >= 100e6 && overlap > 1.0)) return false;
     auto over = [](double x, double unit) { return std::max(0.0, std::log(x / unit)); };
     const double one = p.R * p.S == 1 ? 1.0 : 0.0, taps = v.fx_br == 1 && v.fx_bs == 1 && !one ? 1.0 : 0.0, copy = total / 4.6e6, out = b.out / total;
-    const double log_tiled = std::log(tiled_est), log_flat = std::log(flat_est), deep = over(depth, 128.0), wide = over((double)p.K, 64.0);
+    const double log_tiled = std::log(std::min(tiled_est, 60.0)), log_flat = std::log(std::min(flat_est, 60.0)), deep = over(depth, 128.0), wide = over((double)p.K, 64.0);
     const double narrow = over(32.0, (double)p.C), batch = std::min(1.0, (double)p.B / 64.0), large = over(b.image, 16e6), lap = std::log(overlap);
     const double tc = copy / tiled_est, fc = copy / flat_est;
     const bool f32 = dtype == CACNN_F32;

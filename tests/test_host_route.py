@@ -181,3 +181,16 @@ def test_short_launches_of_fixed_geometry_variants_run_flattened():
     for dtype, dims in ((F32, (8, 64, 64, 56, 56, 3, 3, 1, 1)), (BF16, (64, 64, 256, 56, 56, 1, 1, 1, 1)), (BF16, (32, 128, 256, 28, 28, 3, 3, 2, 2)),
                         (BF16, (128, 400, 224, 26, 5, 3, 3, 1, 1)), (BF16, (32, 96, 206, 42, 42, 3, 3, 1, 1)), (F32, (8, 320, 496, 37, 7, 3, 3, 1, 1))):
         assert routed(dims, dtype) == cc.cacnn_variant_name(cc.cacnn_tile_plan(dims, dtype).variant)
+
+
+# The corrected comparison of the two estimates knows no largest size: what a layer of 240 MB or 7 GFLOP is given to, a larger one is as well
+@pytest.mark.parametrize("dtype,dims,sizes", [(F32, (256, 32, 498, 0, 3, 1, 1, 1, 1), (81, 155, 170)),
+                                              (F32, (256, 32, 498, 81, 0, 1, 1, 1, 1), (3, 5, 6, 7, 9)),
+                                              (F32, (128, 512, 64, 0, 0, 1, 1, 2, 2), (26, 30, 32, 38, 44)),
+                                              (F32, (128, 512, 64, 0, 15, 1, 1, 2, 2), (40, 60, 70, 80)),
+                                              (F32, (64, 52, 0, 5, 54, 7, 1, 1, 1), (400, 1216, 1600)),
+                                              (BF16, (256, 24, 2, 0, 0, 1, 1, 1, 1), (90, 120, 145, 200)), (BF16, (56, 56, 7, 0, 0, 1, 1, 1, 1), (100, 179, 250))])
+def test_a_larger_layer_stays_on_the_kernel_of_the_smaller_one(dtype, dims, sizes):
+    for n in sizes:
+        grown = tuple(n if d == 0 else d for d in dims)
+        assert " fx" in cc.cacnn_variant_name(cc.cacnn_tile_plan(grown, dtype).variant) and " flat " in routed(grown, dtype), grown
