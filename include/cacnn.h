@@ -192,7 +192,8 @@ int cacnn_plan_variant(const cacnn_problem* problem, int dtype, int variant_inde
  * HIP events; it allocates no device memory.  `out` is overwritten by every candidate and ends up holding a valid
  * result.  Arguments as for cacnn_conv_forward; out_plan (host, may be NULL) receives the plan of the fastest variant.  (The
  * kernels with flattened positions and those that keep a tile's window in LDS are timed as well, and remembered where one is
- * faster still; they have no plan.)
+ * faster still; they have no plan.  Those whose workgroups share a contraction run on the default stream alone: they are timed
+ * when that is hip_stream, and after a call with another one the default stream keeps the one that it ran before.)
  * Errors: as cacnn_conv_forward; CACNN_ERR_UNSUPPORTED if no variant accepts the problem.
  */
 int cacnn_tune(const cacnn_problem* problem, int dtype, const void* image, const void* filter, void* out,

@@ -1811,6 +1811,13 @@ int cacnn_tune(const cacnn_problem* problem, int dtype, const void* image, const
                                                 aligned16(image), aligned16(filter), &launch);
     if (lrc != CACNN_OK) return lrc;
     if (split >= 0) (void)prepare_split(*problem, dtype, split, split_parts, &launch);
+    // (the entry is one for all streams: tuned on another one, where they cannot be timed, the null stream keeps those that it had)
+    LaunchPtr before;
+    if (hip_stream && route(*problem, dtype, image, filter, &before) == CACNN_OK && before->split) {
+        launch.split = before->split;
+        launch.split_grid = before->split_grid;
+        launch.fs = before->fs;
+    }
     store_plan(*problem, key, launch);
     if (out_plan) *out_plan = plan;
     return CACNN_OK;

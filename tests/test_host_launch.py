@@ -69,3 +69,25 @@ hip.stand_in_cost(b"conv_", 2.0)
 assert any("conv_window" in k for k in tune(stem, 1, 4096))
 assert "conv_flat_lds" in forward(stem, 1, 4096)[0]
 ''')
+
+
+def test_tuning_on_another_stream_leaves_the_null_stream_its_divided_kernel(run):
+    """Workgroups share a contraction on the null stream alone, and a problem has one entry for all streams: what that stream ran, by estimate or by
+    its own tuning, is what it runs after a tuning elsewhere, which cannot time it."""
+    run(r'''
+deep = (1, 784, 64, 3, 12, 3, 3, 1, 1)
+hip.stand_in_cost(b"conv_", 1.0)
+divided = forward(deep, 0)
+assert "FlatSplitArgs" in divided[0] and "FlatSplitArgs" not in forward(deep, 0, 4096)[0]
+assert not any("FlatSplitArgs" in k for k in tune(deep, 0, 4096))
+assert forward(deep, 0) == divided and "FlatSplitArgs" not in forward(deep, 0, 4096)[0]
+''')
+    run(r'''
+deep = (1, 784, 64, 3, 12, 3, 3, 1, 1)
+hip.stand_in_cost(b"FlatSplitArgs", 2.0)
+hip.stand_in_cost(b"conv_", 1.0)
+assert any("FlatSplitArgs" in k for k in tune(deep, 0))
+for stream in (0, 4096):
+    assert "FlatSplitArgs" not in forward(deep, 0)[0]
+    tune(deep, 0, 4096)
+''')
