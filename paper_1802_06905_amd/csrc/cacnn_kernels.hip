@@ -3273,16 +3273,15 @@ __global__ void __launch_bounds__(512) conv_f32_stem_pair_kernel(const KernelArg
 // launch table
 
 template <typename KernelT>
-static int launch_kernel(KernelT kernel, bool& attr_done, int threads, const KernelArgs& a, int grid, size_t lds_bytes,
+static int launch_kernel(KernelT kernel, OncePerDevice& attr_done, int threads, const KernelArgs& a, int grid, size_t lds_bytes,
                          void* stream) {
-    if (!attr_done) {
-        // raise the dynamic-LDS ceiling of this kernel to the CU's full 160 KiB once
-        if (hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024) !=
-            hipSuccess) {
-            (void)hipGetLastError();
-            return 1;
-        }
-        attr_done = true;
+    // raise the dynamic-LDS ceiling of this kernel to the CU's full 160 KiB once for each device
+    int device = -1;
+    if (hipGetDevice(&device) != hipSuccess || !attr_done(device, [&] {
+            return hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024) == hipSuccess;
+        })) {
+        (void)hipGetLastError();
+        return 1;
     }
     hipLaunchKernelGGL(kernel, dim3(grid), dim3(threads), lds_bytes, (hipStream_t)stream, a);
     return hipGetLastError() == hipSuccess ? 0 : 1;
@@ -3294,7 +3293,7 @@ static int launch_kernel(KernelT kernel, bool& attr_done, int threads, const Ker
     {                                                                                                    \
         {NAME, DT, WM, WN, MBLK, NBLK, TB, TW, TH, 0, 0, 0, 2, 0, TUNE},                                             \
             [](const KernelArgs& a, int grid, size_t lds, void* stream) -> int {                         \
-                static bool attr_done = false;                                                           \
+                static OncePerDevice attr_done;                                                          \
                 return launch_kernel(KERNEL<WM, WN, MBLK, NBLK, TB, TW, TH>, attr_done, WM * WN * 64, a, \
                                      grid, lds, stream);                                                 \
             }                                                                                            \
@@ -3304,7 +3303,7 @@ static int launch_kernel(KernelT kernel, bool& attr_done, int threads, const Ker
     {                                                                                                          \
         {NAME, DT, WM, WN, MBLK, NBLK, TB, TW, TH, 1, MAXI, MAXF, OCC, 0, 1.0f},                               \
             [](const KernelArgs& a, int grid, size_t lds, void* stream) -> int {                               \
-                static bool attr_done = false;                                                                 \
+                static OncePerDevice attr_done;                                                                \
                 return launch_kernel(KERNEL<WM, WN, MBLK, NBLK, TB, TW, TH, MAXI, MAXF>, attr_done,            \
                                      WM * WN * 64, a, grid, lds, stream);                                      \
             }                                                                                                  \
@@ -3314,7 +3313,7 @@ static int launch_kernel(KernelT kernel, bool& attr_done, int threads, const Ker
     {                                                                                                          \
         {NAME, 1, WM, WN, MBLK, NBLK, TB, TW, TH, 1, MAXI, MAXF, OCC, BR, 1.0f},                               \
             [](const KernelArgs& a, int grid, size_t lds, void* stream) -> int {                               \
-                static bool attr_done = false;                                                                 \
+                static OncePerDevice attr_done;                                                                \
                 return launch_kernel(conv_bf16_pipe_kernel<WM, WN, MBLK, NBLK, TB, TW, TH, MAXI, MAXF, BR>,    \
                                      attr_done, WM * WN * 64, a, grid, lds, stream);                           \
             }                                                                                                  \
@@ -3324,7 +3323,7 @@ static int launch_kernel(KernelT kernel, bool& attr_done, int threads, const Ker
     {                                                                                                          \
         {NAME, DT, WM, WN, MBLK, NBLK, TB, TW, TH, 2, MAXI, MAXF, 1, BR, TUNE},                                \
             [](const KernelArgs& a, int grid, size_t lds, void* stream) -> int {                               \
-                static bool attr_done = false;                                                                 \
+                static OncePerDevice attr_done;                                                                \
                 return launch_kernel(__VA_ARGS__, attr_done, WM * WN * 128, a, grid, lds, stream);             \
             }                                                                                                  \
     }
@@ -3335,7 +3334,7 @@ static int launch_kernel(KernelT kernel, bool& attr_done, int threads, const Ker
         {NAME, 1, 2, 2, 1, Bf16DirectFixed<TW, TH>::NBLK, 64, TW, TH, 2, 1, Bf16DirectFixed<TW, TH>::MAXF, 1, 3, 1.0f, 32, 3,  \
          1, Bf16DirectFixed<TW, TH>::YS, 1, 1, Bf16DirectFixed<TW, TH>::LDS_BYTES, UNIT_US, FIXED_US, 0, 2, CALIB},       \
             [](const KernelArgs& a, int grid, size_t lds, void* stream) -> int {                               \
-                static bool attr_done = false;                                                                 \
+                static OncePerDevice attr_done;                                                                \
                 if (!Bf16DirectFixed<TW, TH>::matches_host(a) || lds != (size_t)Bf16DirectFixed<TW, TH>::LDS_BYTES) return 1; \
                 return launch_kernel(conv_bf16_direct_kernel<TW, TH>, attr_done, 512, a, grid, lds, stream);    \
             }                                                                                                  \
@@ -3347,7 +3346,7 @@ static int launch_kernel(KernelT kernel, bool& attr_done, int threads, const Ker
         {NAME, 1, 2, 2, 1, Bf16DirectFixed<TW, TH, 1, 64, 1, 64>::NBLK, 64, TW, TH, 2, 1, Bf16DirectFixed<TW, TH, 1, 64, 1, 64>::MAXF, 1, 1, 1.0f, 64, 1,  \
          1, Bf16DirectFixed<TW, TH, 1, 64, 1, 64>::YS, 1, 1, Bf16DirectFixed<TW, TH, 1, 64, 1, 64>::LDS_BYTES, UNIT_US, FIXED_US, 0, 2, 256, 1},  \
             [](const KernelArgs& a, int grid, size_t lds, void* stream) -> int {                               \
-                static bool attr_done = false;                                                                 \
+                static OncePerDevice attr_done;                                                                \
                 if (!Bf16DirectFixed<TW, TH, 1, 64, 1, 64>::matches_host(a) || lds != (size_t)Bf16DirectFixed<TW, TH, 1, 64, 1, 64>::LDS_BYTES) return 1; \
                 return launch_kernel(conv_bf16_direct_kernel<TW, TH, 1, 64, 1, false, 64>, attr_done, 512, a, grid, lds, stream); \
             }                                                                                                  \
@@ -3359,7 +3358,7 @@ static int launch_kernel(KernelT kernel, bool& attr_done, int threads, const Ker
         {NAME, 1, 2, 2, 1, Bf16DirectFixed<TW, TH, 1, 64, 1, 64>::NBLK, 64, TW, TH, 2, 1, Bf16DirectFixed<TW, TH, 1, 64, 1, 64>::MAXF, 1, 1, 1.0f, 64, 1,  \
          1, Bf16DirectFixed<TW, TH, 1, 64, 1, 64>::YS, 1, 1, Bf16DirectFixed<TW, TH, 1, 64, 1, 64>::LDS_BYTES, UNIT_US, FIXED_US, 0, 2, 256, 1, 1},  \
             [](const KernelArgs& a, int grid, size_t lds, void* stream) -> int {                               \
-                static bool attr_done = false;                                                                 \
+                static OncePerDevice attr_done;                                                                \
                 if (!Bf16DirectFixed<TW, TH, 1, 64, 1, 64>::matches_host(a, true) || lds != (size_t)Bf16DirectFixed<TW, TH, 1, 64, 1, 64>::LDS_BYTES) return 1; \
                 return launch_kernel(conv_bf16_direct_kernel<TW, TH, 1, 64, 1, true, 64>, attr_done, 512, a, grid, lds, stream); \
             }                                                                                                  \
@@ -3371,7 +3370,7 @@ static int launch_kernel(KernelT kernel, bool& attr_done, int threads, const Ker
         {NAME, 1, 2, 2, 1, Bf16DirectFixed<TW, TH, BR>::NBLK, 64, TW, TH, 2, 1, Bf16DirectFixed<TW, TH, BR>::MAXF, 1, BR, 1.0f, 32, BR,  \
          1, Bf16DirectFixed<TW, TH, BR>::YS, 1, 1, Bf16DirectFixed<TW, TH, BR>::LDS_BYTES, UNIT_US, FIXED_US, 0, 2, CALIB, BR == 1, 1},  \
             [](const KernelArgs& a, int grid, size_t lds, void* stream) -> int {                               \
-                static bool attr_done = false;                                                                 \
+                static OncePerDevice attr_done;                                                                \
                 if (!Bf16DirectFixed<TW, TH, BR>::matches_host(a, true) || lds != (size_t)Bf16DirectFixed<TW, TH, BR>::LDS_BYTES) return 1; \
                 return launch_kernel(conv_bf16_direct_kernel<TW, TH, BR, 64, 1, true>, attr_done, 512, a, grid, lds, stream); \
             }                                                                                                  \
@@ -3383,7 +3382,7 @@ static int launch_kernel(KernelT kernel, bool& attr_done, int threads, const Ker
         {NAME, 1, 2, 2, 1, Bf16DirectFixed<TW, TH, 3, 64, 2>::NBLK, 64, TW, TH, 2, 1, Bf16DirectFixed<TW, TH, 3, 64, 2>::MAXF, 1, 3, 1.0f, 32, 3,  \
          1, Bf16DirectFixed<TW, TH, 3, 64, 2>::YS_HOST, 2, 2, Bf16DirectFixed<TW, TH, 3, 64, 2>::LDS_BYTES, UNIT_US, FIXED_US, 0, 2, CALIB},  \
             [](const KernelArgs& a, int grid, size_t lds, void* stream) -> int {                               \
-                static bool attr_done = false;                                                                 \
+                static OncePerDevice attr_done;                                                                \
                 if (!Bf16DirectFixed<TW, TH, 3, 64, 2>::matches_host(a) || lds != (size_t)Bf16DirectFixed<TW, TH, 3, 64, 2>::LDS_BYTES) return 1; \
                 return launch_kernel(conv_bf16_direct_kernel<TW, TH, 3, 64, 2>, attr_done, 512, a, grid, lds, stream); \
             }                                                                                                  \
@@ -3395,7 +3394,7 @@ static int launch_kernel(KernelT kernel, bool& attr_done, int threads, const Ker
         {NAME, 1, 2, 2, 1, Bf16DirectFixed<TW, 2, BR, 32>::NBLK, 32, TW, 2, 2, 1, Bf16DirectFixed<TW, 2, BR, 32>::MAXF, 1, BR, 1.0f, 32, BR,  \
          1, Bf16DirectFixed<TW, 2, BR, 32>::YS, 1, 1, Bf16DirectFixed<TW, 2, BR, 32>::LDS_BYTES, UNIT_US, FIXED_US, 0, 2, 256, BR == 1},  \
             [](const KernelArgs& a, int grid, size_t lds, void* stream) -> int {                               \
-                static bool attr_done = false;                                                                 \
+                static OncePerDevice attr_done;                                                                \
                 if (!Bf16DirectFixed<TW, 2, BR, 32>::matches_host(a) || lds != (size_t)Bf16DirectFixed<TW, 2, BR, 32>::LDS_BYTES) return 1; \
                 return launch_kernel(conv_bf16_direct_kernel<TW, 2, BR, 32>, attr_done, 512, a, grid, lds, stream); \
             }                                                                                                  \
@@ -3407,7 +3406,7 @@ static int launch_kernel(KernelT kernel, bool& attr_done, int threads, const Ker
         {NAME, 1, 2, 2, 1, Bf16DirectFixed<TW, 2, BR, 32>::NBLK, 32, TW, 2, 2, 1, Bf16DirectFixed<TW, 2, BR, 32>::MAXF, 1, BR, 1.0f, 32, BR,  \
          1, Bf16DirectFixed<TW, 2, BR, 32>::YS, 1, 1, Bf16DirectFixed<TW, 2, BR, 32>::LDS_BYTES, UNIT_US, FIXED_US, 0, 2, 256, BR == 1, 1},  \
             [](const KernelArgs& a, int grid, size_t lds, void* stream) -> int {                               \
-                static bool attr_done = false;                                                                 \
+                static OncePerDevice attr_done;                                                                \
                 if (!Bf16DirectFixed<TW, 2, BR, 32>::matches_host(a, true) || lds != (size_t)Bf16DirectFixed<TW, 2, BR, 32>::LDS_BYTES) return 1; \
                 return launch_kernel(conv_bf16_direct_kernel<TW, 2, BR, 32, 1, true>, attr_done, 512, a, grid, lds, stream); \
             }                                                                                                  \
@@ -3419,7 +3418,7 @@ static int launch_kernel(KernelT kernel, bool& attr_done, int threads, const Ker
         {NAME, 1, 2, 2, 1, Bf16DirectFixed<TW, TH, 1>::NBLK, 64, TW, TH, 2, 1, Bf16DirectFixed<TW, TH, 1>::MAXF, 1, 1, 1.0f, 32, 1,  \
          1, Bf16DirectFixed<TW, TH, 1>::YS, 1, 1, Bf16DirectFixed<TW, TH, 1>::LDS_BYTES, UNIT_US, FIXED_US, 0, 2, 256, 1}, \
             [](const KernelArgs& a, int grid, size_t lds, void* stream) -> int {                               \
-                static bool attr_done = false;                                                                 \
+                static OncePerDevice attr_done;                                                                \
                 if (!Bf16DirectFixed<TW, TH, 1>::matches_host(a) || lds != (size_t)Bf16DirectFixed<TW, TH, 1>::LDS_BYTES) return 1; \
                 return launch_kernel(conv_bf16_direct_kernel<TW, TH, 1>, attr_done, 512, a, grid, lds, stream); \
             }                                                                                                  \
@@ -3431,7 +3430,7 @@ static int launch_kernel(KernelT kernel, bool& attr_done, int threads, const Ker
         {NAME, 1, 2, 2, 1, Bf16StagedFixed<TW, TH, BSI>::NBLK, 64, TW, TH, 2, 1, Bf16StagedFixed<TW, TH, BSI>::MAXF, 1, 3, 1.0f, 32, 3,  \
          BSI, Bf16StagedFixed<TW, TH, BSI>::YSI, 1, 1, Bf16StagedFixed<TW, TH, BSI>::LDS_BYTES, UNIT_US, FIXED_US, 0, 0, CALIB},  \
             [](const KernelArgs& a, int grid, size_t lds, void* stream) -> int {                               \
-                static bool attr_done = false;                                                                 \
+                static OncePerDevice attr_done;                                                                \
                 if (!Bf16StagedFixed<TW, TH, BSI>::matches_host(a) || lds != (size_t)Bf16StagedFixed<TW, TH, BSI>::LDS_BYTES) return 1; \
                 return launch_kernel(conv_bf16_staged_kernel<TW, TH, BSI>, attr_done, 512, a, grid, lds, stream); \
             }                                                                                                  \
@@ -3443,7 +3442,7 @@ static int launch_kernel(KernelT kernel, bool& attr_done, int threads, const Ker
         {NAME, 0, 2, 2, 1, F32DirectFixed<TW, TH>::NBLK, 8, TW, TH, 2, 1, F32DirectFixed<TW, TH>::MAXF, 1, -4, 1.0f, 16, 3,    \
          3, F32DirectFixed<TW, TH>::YS, 1, 1, F32DirectFixed<TW, TH>::LDS_BYTES, UNIT_US, FIXED_US, 0},         \
             [](const KernelArgs& a, int grid, size_t lds, void* stream) -> int {                               \
-                static bool attr_done = false;                                                                 \
+                static OncePerDevice attr_done;                                                                \
                 if (!F32DirectFixed<TW, TH>::matches_host(a) || lds != (size_t)F32DirectFixed<TW, TH>::LDS_BYTES) return 1; \
                 return launch_kernel(conv_f32_direct_kernel<TW, TH>, attr_done, 512, a, grid, lds, stream);     \
             }                                                                                                  \
@@ -3455,7 +3454,7 @@ static int launch_kernel(KernelT kernel, bool& attr_done, int threads, const Ker
         {NAME, 0, 2, 2, 1, F32Direct16<TW, TH>::NBLK, 8, TW, TH, 2, 1, F32Direct16<TW, TH>::MAXF, 1, -4, 1.0f, 16, 3,    \
          3, F32Direct16<TW, TH>::YS, 1, 1, F32Direct16<TW, TH>::LDS_BYTES, UNIT_US, FIXED_US, 0, 1, 0, 0, 2},               \
             [](const KernelArgs& a, int grid, size_t lds, void* stream) -> int {                               \
-                static bool attr_done = false;                                                                 \
+                static OncePerDevice attr_done;                                                                \
                 if (!F32Direct16<TW, TH>::matches_host(a) || lds != (size_t)F32Direct16<TW, TH>::LDS_BYTES) return 1; \
                 return launch_kernel(conv_f32_direct16_kernel<TW, TH>, attr_done, 512, a, grid, lds, stream);   \
             }                                                                                                  \
@@ -3467,7 +3466,7 @@ static int launch_kernel(KernelT kernel, bool& attr_done, int threads, const Ker
         {NAME, 0, 2, 2, 1, F32Direct16<TW, TH, 1>::NBLK, 8, TW, TH, 2, 1, F32Direct16<TW, TH, 1>::MAXF, 1, -4, 1.0f, 16, 1,    \
          1, F32Direct16<TW, TH, 1>::YS, 1, 1, F32Direct16<TW, TH, 1>::LDS_BYTES, UNIT_US, FIXED_US, 0, 1, 0, 1, 2},         \
             [](const KernelArgs& a, int grid, size_t lds, void* stream) -> int {                               \
-                static bool attr_done = false;                                                                 \
+                static OncePerDevice attr_done;                                                                \
                 if (!F32Direct16<TW, TH, 1>::matches_host(a) || lds != (size_t)F32Direct16<TW, TH, 1>::LDS_BYTES) return 1; \
                 return launch_kernel(conv_f32_direct16_kernel<TW, TH, 1>, attr_done, 512, a, grid, lds, stream); \
             }                                                                                                  \
@@ -3553,9 +3552,9 @@ static const Variant g_variants[] = {
     {{"f32 fxsd k64 b32w2h2 w2x2 m1n2 c3r7s7 s2", 0, 2, 2, 1, F32StemDirect<2, 2>::NBLK, 32, 2, 2, 2, 1, 1, 1, 0, 1.0f, 3, 7, 7,
       F32StemDirect<2, 2>::YS, 2, 2, F32StemDirect<2, 2>::LDS_BYTES, 5.15f, 4.5f, 1, 2},
      [](const KernelArgs& a, int grid, size_t lds, void* stream) -> int {
-         static bool attr_done = false;
+         static OncePerDevice attr_done;
          if (!F32StemDirect<2, 2>::matches_host(a) || lds != (size_t)F32StemDirect<2, 2>::LDS_BYTES) return 1;
-         static bool attr_done_ragged = false, pair_done = false, pair_done_ragged = false;
+         static OncePerDevice attr_done_ragged, pair_done, pair_done_ragged;
          // (the offsets of a box's nine planes have to fit 31 bits)
          if (a.tiles_k == 1 && (int64_t)a.IH * a.C * a.B * 4 * (F32StemDirect<2, 2>::XS + 1) < (int64_t)1 << 31) {
              if (a.B % 32 == 0 && a.W % 2 == 0 && a.H % 2 == 0 && a.K % 64 == 0)

@@ -221,14 +221,13 @@ static int launch_mfma_and_fill(const void* operands, const void* src, uint32_t 
                                 int barrier, float* sink, int grid, void* stream) {
     // 46 KiB of unused dynamic LDS on top of the kernel's own 50 KiB: no second workgroup fits the compute unit, so a
     // grid below the CU count leaves exactly that many compute units idle
-    static bool attr_done = false;
-    if (!attr_done) {
-        if (hipFuncSetAttribute((const void*)mfma_and_fill_kernel<TW, THW>, hipFuncAttributeMaxDynamicSharedMemorySize, 46 * 1024) !=
-            hipSuccess) {
-            (void)hipGetLastError();
-            return 1;
-        }
-        attr_done = true;
+    static OncePerDevice attr_done;
+    int device = -1;
+    if (hipGetDevice(&device) != hipSuccess || !attr_done(device, [] {
+            return hipFuncSetAttribute((const void*)mfma_and_fill_kernel<TW, THW>, hipFuncAttributeMaxDynamicSharedMemorySize, 46 * 1024) == hipSuccess;
+        })) {
+        (void)hipGetLastError();
+        return 1;
     }
     hipLaunchKernelGGL((mfma_and_fill_kernel<TW, THW>), dim3(grid), dim3(512), 46 * 1024, (hipStream_t)stream,
                        (const uint32_t*)operands, (const char*)src, window, mfma_iters, fill_iters, lds_reads, barrier, sink);

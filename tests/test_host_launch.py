@@ -91,3 +91,29 @@ for stream in (0, 4096):
     assert "FlatSplitArgs" not in forward(deep, 0)[0]
     tune(deep, 0, 4096)
 ''')
+
+
+def test_every_device_gets_the_lds_that_a_kernel_needs(run):
+    """A kernel's LDS limit is a setting of one device: each variant, and the divided, flattened and window kernels, launch on a second one as well."""
+    out = run(r'''
+shapes = [(32, 3, 64, 112, 112, 7, 7, 2, 2), (32, 3, 65, 9, 8, 7, 7, 2, 2), (36, 3, 64, 41, 43, 7, 7, 2, 2), (64, 64, 64, 14, 14, 3, 3, 1, 1), (64, 40, 70, 13, 9, 3, 3, 1, 1),
+          (64, 64, 64, 14, 14, 1, 1, 1, 1), (64, 64, 64, 14, 14, 1, 1, 2, 2), (64, 64, 64, 14, 14, 3, 3, 2, 2), (32, 72, 64, 14, 14, 5, 5, 1, 1), (8, 5, 9, 6, 7, 3, 3, 1, 1)]
+plan = (ctypes.c_char * 4096)()
+ran = set()
+for i in range(lib.cacnn_variant_count()):
+    dtype = int(lib.cacnn_variant_name(i).startswith(b"bf16"))
+    for dims in shapes:
+        if lib.cacnn_plan_variant(problem(*dims), I(dtype), I(i), plan, V(0), V(0)) == 0:
+            for device in (0, 1):
+                hip.stand_in_device(device)
+                assert lib.cacnn_conv_forward_with_plan(problem(*dims), I(dtype), plan, V(IMAGE), V(FILTER), V(OUT), V(0)) == 0, (device, lib.cacnn_variant_name(i), dims)
+                ran.update(kernels())
+for dims, dtype in (((1, 784, 64, 3, 12, 3, 3, 1, 1), 0), ((72, 976, 16, 5, 5, 3, 3, 2, 2), 1), ((16, 3, 64, 112, 112, 7, 7, 2, 2), 1), ((128, 3, 32, 89, 89, 5, 5, 2, 2), 1)):
+    for device in (2, 3):
+        hip.stand_in_device(device)
+        for stream in (0, 4096):
+            ran.update(forward(dims, dtype, stream))
+print("\n".join(ran))
+''')
+    for part in ("conv_f32_stem_pair", "conv_f32_stem_direct", "conv_f32_direct16", "conv_bf16_direct", "FlatSplitArgs", "conv_window"):
+        assert part in out
