@@ -161,6 +161,8 @@ _lib.cacnn_internal_conv_forward_sized.argtypes = [ctypes.POINTER(Problem), ctyp
 _lib.cacnn_internal_pool_forward_sized.restype = ctypes.c_int
 _lib.cacnn_internal_pool_forward_sized.argtypes = [ctypes.POINTER(Problem), ctypes.c_int, ctypes.c_int] + \
     [ctypes.c_void_p, ctypes.c_int64] * 2 + [ctypes.c_void_p]
+_lib.cacnn_internal_sized_interface.restype = ctypes.c_int
+_lib.cacnn_internal_sized_interface.argtypes = []
 _lib.cacnn_internal_route.restype = ctypes.c_int
 _lib.cacnn_internal_route.argtypes = [ctypes.POINTER(Problem), ctypes.c_int, ctypes.c_void_p, ctypes.c_void_p, ctypes.POINTER(ctypes.c_int32)]
 _lib.cacnn_internal_route_split.restype = ctypes.c_int
@@ -263,16 +265,22 @@ def _stream_handle(stream) -> int:
     return int(stream.cuda_stream)
 
 
+def _native_interface():
+    """What the module is told of the library: the interface it must have been compiled for, and where its calls are."""
+    address = lambda f: ctypes.cast(f, ctypes.c_void_p).value  # noqa: E731
+    return (_lib.cacnn_internal_sized_interface(), ctypes.sizeof(Problem), Problem,
+            address(_lib.cacnn_internal_conv_forward_sized), address(_lib.cacnn_internal_pool_forward_sized))
+
+
 def _load_native():
     """The module that takes the usual call, set up for this library's Problem and its two calls with element counts.  None, with a
-    warning, where it was not built or for another torch: the calls below launch the same kernels and take 5.2 us instead of 4.1."""
+    warning, where it was not built, or for another torch or library: the calls below launch the same kernels and take 5.2 us instead of 4.1."""
     try:
         from . import _cacnn_torch
+        _cacnn_torch.setup(*_native_interface())
     except ImportError as error:
         warnings.warn(f"calls take the longer way, build the module with `python paper_1802_06905_amd/build.py`: {error}", RuntimeWarning)
         return None
-    address = lambda f: ctypes.cast(f, ctypes.c_void_p).value  # noqa: E731
-    _cacnn_torch.setup(Problem, address(_lib.cacnn_internal_conv_forward_sized), address(_lib.cacnn_internal_pool_forward_sized))
     return _cacnn_torch
 
 

@@ -2149,6 +2149,7 @@ int cacnn_internal_pool_forward_sized(const cacnn_problem* problem, int dtype, i
     if (!problem || problem->K != problem->C || !holds(*problem, image_elems, INT64_MAX, out_elems)) return CACNN_ERR_INVALID_ARG;
     return cacnn_pool_forward(problem, dtype, mode, image, out, hip_stream);
 }
+int cacnn_internal_sized_interface(void) { return kSizedInterface; }
 // Which kernel cacnn_conv_forward launches for a problem and operands at these addresses (of which the alignment alone matters):
 // {0: a variant with box tiles, 1: a flattened kernel, 2: a window kernel; its index; workgroups; threads of one}.  Nothing is enqueued.
 int cacnn_internal_route(const cacnn_problem* problem, int dtype, const void* image, const void* filter, int32_t* four) {

@@ -10,6 +10,10 @@
 
 namespace cacnn {
 
+// What cacnn_torch.cpp takes on trust of the library: the problem's layout and the signatures of cacnn_internal_conv_forward_sized and
+// cacnn_internal_pool_forward_sized.  To be raised with any of them; a module and a library that differ are not used together.
+constexpr int kSizedInterface = 1;
+
 // Set-up that a process needs once for each device: done(device, set_up) calls set_up() until it has succeeded there.  A failure is not
 // remembered; threads that come at the same time may both set up.
 struct OncePerDevice {

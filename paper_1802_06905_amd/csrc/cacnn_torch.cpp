@@ -8,12 +8,15 @@
 #include <torch/csrc/Exceptions.h>
 #include <torch/csrc/autograd/python_variable.h>
 
+#include "cacnn_internal.h"
+
 namespace {
 
 using ConvFn = int (*)(const void* problem, int dtype, const void* image, int64_t image_elems, const void* filter, int64_t filter_elems,
                        void* out, int64_t out_elems, void* stream);
 using PoolFn = int (*)(const void* problem, int dtype, int mode, const void* image, int64_t image_elems, void* out, int64_t out_elems, void* stream);
 
+constexpr Py_ssize_t kProblemBytes = 9 * 8;
 PyTypeObject* g_problem = nullptr;   // the binding's Problem, a ctypes structure
 ConvFn g_conv = nullptr;
 PoolFn g_pool = nullptr;
@@ -56,7 +59,7 @@ const void* problem_of(PyObject* o) {
         PyErr_Clear();
         return nullptr;
     }
-    const void* p = view.len == 9 * 8 ? view.buf : nullptr;
+    const void* p = view.len == kProblemBytes ? view.buf : nullptr;
     PyBuffer_Release(&view);
     return p;
 }
@@ -105,10 +108,17 @@ PyObject* pool(PyObject*, PyObject* const* args, Py_ssize_t n) {
     END_HANDLE_TH_ERRORS
 }
 
-// setup(Problem, address of cacnn_internal_conv_forward_sized, address of cacnn_internal_pool_forward_sized)
+// setup(cacnn_internal_sized_interface(), size of Problem, Problem, address of cacnn_internal_conv_forward_sized, of cacnn_internal_pool_forward_sized);
+// ImportError where the first two are not what this module was compiled for
 PyObject* setup(PyObject*, PyObject* args) {
     PyObject *problem, *conv_at, *pool_at;
-    if (!PyArg_ParseTuple(args, "O!OO", &PyType_Type, &problem, &conv_at, &pool_at)) return nullptr;
+    int interface = 0;
+    Py_ssize_t size = 0;
+    if (!PyArg_ParseTuple(args, "inO!OO", &interface, &size, &PyType_Type, &problem, &conv_at, &pool_at)) return nullptr;
+    if (interface != cacnn::kSizedInterface || size != kProblemBytes) {
+        PyErr_SetString(PyExc_ImportError, "_cacnn_torch was compiled for another version of the library");
+        return nullptr;
+    }
     void* const c = PyLong_AsVoidPtr(conv_at);
     void* const p = PyLong_AsVoidPtr(pool_at);
     if (PyErr_Occurred()) return nullptr;
