@@ -1,6 +1,7 @@
 """Build libcacnn.so (host planner + gfx950 kernels) with hipcc and _cacnn_torch.so (the binding's calls on torch tensors) with the host
 compiler, in-tree.  Usage: python paper_1802_06905_amd/build.py"""
 import os
+import shutil
 import subprocess
 import sys
 import sysconfig
@@ -21,7 +22,7 @@ def torch_command() -> list:
     """How _cacnn_torch.so is compiled: torch's own headers and libraries, which are in the process before it is imported."""
     import torch
     root = os.path.dirname(torch.__file__)
-    rocm = os.path.dirname(os.path.dirname(HIPCC))
+    rocm = os.path.dirname(os.path.dirname(shutil.which(HIPCC) or HIPCC))        # (HIPCC may be a name that PATH finds)
     return [os.environ.get("CXX", "g++"), "-std=c++17", "-O2", "-fPIC", "-shared", "-Wall", "-DUSE_ROCM=1", "-D__HIP_PLATFORM_AMD__=1",
             f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}", "-isystem", os.path.join(root, "include"),
             "-isystem", sysconfig.get_paths()["include"], "-isystem", os.path.join(rocm, "include"), "-o", TORCH_LIB,

@@ -48,6 +48,17 @@ def test_a_failure_of_hipcc_is_what_is_reported(build, module):
         build(1, module)
 
 
+def test_the_compiler_may_be_named_without_its_folder(build, tmp_path, monkeypatch):
+    """HIPCC=hipcc: the runtime's headers lie beside the compiler that PATH finds."""
+    build(0, 0)
+    import paper_1802_06905_amd.build as script
+    (tmp_path / "bin").mkdir()
+    (tmp_path / "hipcc").rename(tmp_path / "bin" / "hipcc")
+    monkeypatch.setenv("PATH", str(tmp_path / "bin"), prepend=os.pathsep)
+    monkeypatch.setattr(script, "HIPCC", "hipcc")
+    assert str(tmp_path / "include") in script.torch_command()
+
+
 def test_the_module_refuses_another_library_interface():
     from paper_1802_06905_amd import binding
     good = binding._native_interface()
