@@ -147,7 +147,10 @@ int cacnn_tile_plan(const cacnn_problem* problem, int dtype, const cacnn_machine
  * positions and needs no plan (same sums, same inputs and outputs, fp32 accumulation).  On the default stream (hip_stream NULL), where
  * launches follow one another, few tiles with a long contraction are shared by several workgroups each, which exchange partial sums in
  * 8 MiB of device memory that the library's code object holds; on every other stream, and so in a graph, the same call runs a kernel that needs
- * none.  Either adds up in a fixed order, the two in different ones: the last bits of a call's result may depend on the stream, on nothing else.
+ * none.  Every kernel adds up in a fixed order, different ones in different orders, so the last bits of a call's result are the same for the
+ * same problem, dtype, 16-byte alignment (or not) of image and of filter, kind of stream (default or other) and tuning (cacnn_tune keeps
+ * what measured fastest, which may differ from one run to the next).  Who needs the same bits in a graph and outside calls on other streams than
+ * the default one.
  * The call enqueues work on the stream and returns; it never synchronises, allocates no device memory and
  * keeps no reference to the buffers.  The caller owns all three buffers.  Pointers must be aligned to their
  * element size; 16-byte alignment enables the vector paths.
