@@ -3555,8 +3555,8 @@ static const Variant g_variants[] = {
          static OncePerDevice attr_done;
          if (!F32StemDirect<2, 2>::matches_host(a) || lds != (size_t)F32StemDirect<2, 2>::LDS_BYTES) return 1;
          static OncePerDevice attr_done_ragged, pair_done, pair_done_ragged;
-         // (the offsets of a box's nine planes have to fit 31 bits)
-         if (a.tiles_k == 1 && (int64_t)a.IH * a.C * a.B * 4 * (F32StemDirect<2, 2>::XS + 1) < (int64_t)1 << 31) {
+         // (the pair's 32-bit offsets into a box's nine planes: the planner gives this variant no Image of which ten planes reach 2^31 bytes)
+         if (a.tiles_k == 1) {
              if (a.B % 32 == 0 && a.W % 2 == 0 && a.H % 2 == 0 && a.K % 64 == 0)
                  return launch_kernel(conv_f32_stem_pair_kernel<2, 2, false>, pair_done, 512, a, grid, lds, stream);
              return launch_kernel(conv_f32_stem_pair_kernel<2, 2, true>, pair_done_ragged, 512, a, grid, lds, stream);

@@ -117,3 +117,21 @@ print("\n".join(ran))
 ''')
     for part in ("conv_f32_stem_pair", "conv_f32_stem_direct", "conv_f32_direct16", "conv_bf16_direct", "FlatSplitArgs", "conv_window"):
         assert part in out
+
+
+def test_the_stem_kernel_takes_no_planes_beyond_31_bits_of_offset(run):
+    """One k-tile (K <= 64) runs on the pair of sets, more on the kernel with staging waves; an Image of which ten planes reach 2^31 bytes is given to neither."""
+    run(r'''
+plan = (ctypes.c_char * 4096)()
+variant = [i for i in range(lib.cacnn_variant_count()) if lib.cacnn_variant_name(i).startswith(b"f32 fxsd ")][0]
+for B, K, H in ((8192, 8, 1089), (8192, 65, 1089), (8192, 8, 1090), (8192, 64, 100), (32, 65, 9), (32, 64, 9), (8180, 7, 1092), (8180, 70, 1091)):
+    dims = problem(B, 3, K, 2, H, 7, 7, 2, 2)
+    status = lib.cacnn_plan_variant(dims, I(0), I(variant), plan, V(0), V(0))
+    assert status == (0 if 10 * 4 * 3 * B * (2 * H + 5) < 2 ** 31 else 3), (B, K, H)
+    if status == 0:
+        assert lib.cacnn_conv_forward_with_plan(dims, I(0), plan, V(IMAGE), V(FILTER), V(OUT), V(0)) == 0
+        assert [("stem_pair" if K <= 64 else "stem_direct") in k for k in kernels()] == [True], (B, K, H)
+    assert lib.cacnn_plan_variant(problem(32, 3, K, 2, 9, 7, 7, 2, 2), I(0), I(variant), plan, V(0), V(0)) == 0
+    if status:
+        assert lib.cacnn_conv_forward_with_plan(dims, I(0), plan, V(IMAGE), V(FILTER), V(OUT), V(0)) == 3 and not kernels()
+''')
