@@ -122,3 +122,33 @@ def test_non_finite_values_stay_where_they_belong(env):  # noqa: F811
     torch.cuda.synchronize()
     got = out.cpu().numpy().reshape(cfg.out_shape)
     assert not np.isfinite(got[7]).any() and np.isfinite(np.delete(got, 7, axis=0)).all()
+
+
+def test_different_problems_one_behind_the_other(env):  # noqa: F811
+    """Launches of different problems without a wait between them use the same scratch memory and counters, with other numbers of tiles, of parts and
+    of sums: each gives the bits that it gives alone."""
+    cc, torch, _ = env
+    from paper_1802_06905_amd import binding
+    problems = [("f32", (4, 200, 40, 6, 5, 3, 3, 1, 1)), ("bf16", (24, 700, 19, 5, 5, 3, 3, 1, 1)), ("bf16", (3, 400, 70, 9, 5, 3, 3, 2, 2)), ("f32", (1, 784, 64, 3, 12, 3, 3, 1, 1)),
+                ("bf16", (72, 976, 16, 5, 5, 3, 3, 2, 2)), ("bf16", (3, 859, 480, 42, 5, 3, 3, 2, 2))]
+    calls, kinds = [], set()
+    for dtype, dims in problems:
+        cfg = ci.custom("split", *dims, dtype=dtype, dist="normal", seed=12)
+        img, flt = ci.make_inputs(cfg)
+        _, parts, workgroups = binding.routed_split(dims, gu.dtype_code(cfg))
+        kinds.add((parts, workgroups // parts))
+        alone = torch.full((int(np.prod(cfg.out_shape)),), float("nan"), dtype=torch.float32, device="cuda:0")
+        calls.append((cfg, *gu.upload(cfg, img, flt, torch), alone))
+        cc.cacnn_conv_forward(dims, gu.dtype_code(cfg), *calls[-1][1:], stream=0)
+        torch.cuda.synchronize()
+        check(cfg, alone.cpu().numpy().reshape(cfg.out_shape), *gu.oracle_full(cfg, img, flt), "alone")
+    assert len(kinds) == len(problems)
+    order = np.random.default_rng(2).integers(0, len(calls), 120)
+    outs = [torch.full_like(calls[i][3], float("nan")) for i in order]
+    torch.cuda.synchronize()
+    for i, out in zip(order, outs):
+        cfg, d_img, d_flt, _ = calls[i]
+        cc.cacnn_conv_forward(cfg.dims, gu.dtype_code(cfg), d_img, d_flt, out, stream=0)
+    torch.cuda.synchronize()
+    for n, (i, out) in enumerate(zip(order, outs)):
+        assert torch.equal(out, calls[i][3]), (n, calls[i][0].dims)
