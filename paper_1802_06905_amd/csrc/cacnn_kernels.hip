@@ -24,6 +24,7 @@
 #include <utility>
 
 #include "cacnn_internal.h"
+#include "cacnn_lds_load.h"
 
 namespace cacnn {
 
@@ -3104,19 +3105,9 @@ __global__ void __launch_bounds__(512) conv_f32_stem_direct_kernel(const KernelA
 // which the other set has its second half of products.  A half-step is 7 of the 14 groups of products for either set, and
 // there is one barrier at its end: half-step k is the first half of tile k for set k % 2 and the second half of tile k - 1 for the other, which
 // also fetches tile k + 1, as nobody reads the third buffer then.
-// No staging waves, so the loads to LDS are issued by waves that read LDS: as assembly, because the compiler makes every LDS access it
-// knows of wait for all outstanding loads into LDS.  A set waits for its loads at the end of a half-step in which it stores nothing.
+// No staging waves, so the loads to LDS are issued by waves that read LDS (load_to_lds_unseen).  A set waits for its loads at the end of a half-step in which it stores nothing.
 // Measured, four multiplying waves and four staging ones before (us): (32, 3, 64, 112, 112) 74.3 -> 70.2, (128, 3, 64, 54, 21) 34.9 -> 31.6, (256, 3, 37, 22,
 // 22) 32.6 -> 29.3.  The products alone are 54 us of the first: 13 rounds of 154 MFMAs of 64 cycles on tiles for 12.25.
-typedef int i32x4 __attribute__((ext_vector_type(4)));
-#pragma clang diagnostic push
-#pragma clang diagnostic ignored "-Winline-asm"
-// 64 lanes x 16 bytes, lane L's from byte off of the descriptor to LDS byte dst + 16 L (m0 belongs to no one for longer than the instruction it is set for)
-__device__ __forceinline__ void load_to_lds_unseen(i32x4 d, uint32_t off, uint32_t dst) {
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds" ::"s"(dst), "v"(off), "s"(d) : "memory", "m0");
-}
-#pragma clang diagnostic pop
-
 template <int TW, int TH, bool RAGGED>
 __global__ void __launch_bounds__(512) conv_f32_stem_pair_kernel(const KernelArgs a) {
     using GEO = F32StemDirect<TW, TH>;

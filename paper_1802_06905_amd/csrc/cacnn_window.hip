@@ -11,8 +11,7 @@
 // transposing LDS reads of four rows each at a lane's own position: nothing is decoded in the loop, any filter and strides will do.
 // A workgroup keeps its Filter tile in LDS and walks position tiles, one box ahead (bufs = 2), or takes one tile (bufs = 1).
 //
-// Data goes to LDS by buffer loads with LDS destination, 64 lanes x 16 bytes each.  They are written as assembly: the compiler makes
-// every LDS access it knows of wait for all outstanding loads into LDS, and these are meant to be in flight under the products.
+// Data goes to LDS by buffer loads with LDS destination, 64 lanes x 16 bytes each, which are in flight under the products (cacnn_lds_load.h).
 //
 // Measured (us, flattened kernel before): (16, 3, 64, 112, 112, 7 x 7, s 2) 22.0 -> 16.4, 32 images 37.1 -> 28.0, (16, 1, 48, 100, 100, 11 x 11, s 4)
 // 16.8 -> 13.6.  What is left is Out, 51 MB of the first one's 59, the 1.7 us before the first product (the Filter tile, the lanes' places in
@@ -21,12 +20,12 @@
 #include <stdint.h>
 
 #include "cacnn_internal.h"
+#include "cacnn_lds_load.h"
 
 namespace cacnn {
 
 typedef float wf32x16 __attribute__((ext_vector_type(16)));
 typedef unsigned int wu32x4 __attribute__((ext_vector_type(4)));
-typedef int wi32x4 __attribute__((ext_vector_type(4)));
 typedef short ws16x4 __attribute__((ext_vector_type(4)));
 typedef __bf16 wbf16x8 __attribute__((ext_vector_type(8)));
 #define WIN_LDS(T) __attribute__((address_space(3))) T
@@ -35,20 +34,14 @@ struct __attribute__((packed, aligned(2))) WinBytes16 {
 };
 
 // a descriptor of the `left` bytes from p on: loads beyond them return zeros
-__device__ __forceinline__ wi32x4 window_rsrc(const char* p, uint32_t left) {
+__device__ __forceinline__ i32x4 window_rsrc(const char* p, uint32_t left) {
     const uint64_t a = (uint64_t)p;
-    wi32x4 d;
+    i32x4 d;
     d[0] = __builtin_amdgcn_readfirstlane((int)(uint32_t)a);
     d[1] = __builtin_amdgcn_readfirstlane((int)(uint32_t)(a >> 32) & 0xffff);
     d[2] = __builtin_amdgcn_readfirstlane((int)left);
     d[3] = 0x00020000;
     return d;
-}
-// (m0 belongs to no one for longer than the instruction that it is set for)
-#pragma clang diagnostic ignored "-Winline-asm"
-// 64 lanes x 16 bytes, lane L's from descriptor offset off to LDS byte dst + 16 L (dst wave-uniform).  No register is written.
-__device__ __forceinline__ void window_load(wi32x4 d, uint32_t off, uint32_t dst) {
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds" ::"s"(dst), "v"(off), "s"(d) : "memory", "m0");
 }
 __device__ __forceinline__ void window_loads_done() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
 
@@ -95,10 +88,10 @@ __global__ void __launch_bounds__(WM* WN * 64) conv_window_kernel(const WindowAr
     }
     auto fetch = [&](Tile t, uint32_t dst) {
         const uint32_t org = t.w0 * a.img_w + t.h0 * a.img_h + t.b0 * 2;
-        const wi32x4 d = window_rsrc((const char*)a.image + org, a.img_bytes - org);
+        const i32x4 d = window_rsrc((const char*)a.image + org, a.img_bytes - org);
 #pragma unroll
         for (int i = 0; i < kWindowItems; ++i)
-            if (i < (int)a.img_items) window_load(d, ioff[i], dst + (wave + i * WAVES) * 1024);
+            if (i < (int)a.img_items) load_to_lds_unseen(d, ioff[i], dst + (wave + i * WAVES) * 1024);
     };
 
     // ---- multiplication
