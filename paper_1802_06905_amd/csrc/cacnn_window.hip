@@ -13,9 +13,9 @@
 //
 // Data goes to LDS by buffer loads with LDS destination, 64 lanes x 16 bytes each, which are in flight under the products (cacnn_lds_load.h).
 //
-// Measured (us, flattened kernel before): (16, 3, 64, 112, 112, 7 x 7, s 2) 22.0 -> 16.4, 32 images 37.1 -> 28.0, (16, 1, 48, 100, 100, 11 x 11, s 4)
-// 16.8 -> 13.6.  What is left is Out, 51 MB of the first one's 59, the 1.7 us before the first product (the Filter tile, the lanes' places in
-// the box), and a last round of tiles that is not full.
+// Measured (us, flattened kernel before): (16, 3, 64, 112, 112, 7 x 7, s 2) 19.6 -> 15.8, 32 images 33.4 -> 29.5, (128, 3, 32, 89, 89, 5 x 5, s 2)
+// 56.7 -> 30.9, (256, 3, 16, 98, 98, 5 x 5) 81.2 -> 42.2.  What is left is Out, 51 MB of the first one's 56, the 1.7 us before the first product (the
+// Filter tile, the lanes' places in the box), and a last round of tiles that is not full.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
